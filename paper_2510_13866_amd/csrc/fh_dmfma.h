@@ -71,6 +71,85 @@ __device__ inline double wave_sum_f64(double v) {
 __device__ inline int t64_x(int q, int lane) { return 16 * (q & 1) + (lane & 15); }
 __device__ inline int t64_y(int q, int r, int lane) { return 16 * (q >> 1) + 4 * r + (lane >> 4); }
 
+// C F C of a lattice with L <= 16, which fills tile (0, 0) only: every product with another tile
+// is an exact zero, so the two multiplications take ceil(L / 4) instructions each instead of 32
+// and leave the bits of circ64(circ64(F)). Cb[r]: the B operands Cb[2 r] of the 32 x 32 layout.
+__device__ inline f64x4 circ16(const f64x4& F, const double (&Cb)[4], int L) {
+    f64x4 X = {0.0, 0.0, 0.0, 0.0}, H = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (4 * r < L) X = __builtin_amdgcn_mfma_f64_16x16x4f64(F[r], Cb[r], X, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (4 * r < L) H = __builtin_amdgcn_mfma_f64_16x16x4f64(X[r], Cb[r], H, 0, 0, 0);
+    return H;
+}
+
+// dmfma_block_forward_end for L <= 16 (wtab(l, w) fills w[r] at the lane's element (0, r)), with
+// the next slice's W~ loaded a step ahead: at 2 ceil(L / 4) products a step the load latency
+// would show. A step of a lone 4 x 4 recursion takes 0.6 us (3.0 us on the full tiling, whose
+// 64 products bound it).
+template <typename WTab, typename Put, typename PutEnd>
+__device__ inline double dmfma16_block_forward_end(const double (&Cb)[4], int L, int L_tau,
+                                                   int start, int len, int a, int e, double la,
+                                                   const double* __restrict__ shift, WTab wtab,
+                                                   Put put, PutEnd put_end, double* la_end,
+                                                   bool* ok) {
+#pragma clang fp contract(off)  // the same bits from every form of the recursion
+    const int lane = threadIdx.x & 63;
+    auto inside = [&](int r) { return t64_x(0, lane) < L && t64_y(0, r, lane) < L; };
+    const int ax = a % L, ay = a / L;
+    f64x4 F;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        F[r] = (t64_x(0, lane) == ax && t64_y(0, r, lane) == ay) ? 1.0 : 0.0;
+    bool good = true;
+    double wa[4], wb[4];
+    int l = (start + 1) % L_tau;
+    wtab(l, wa);
+    auto step = [&](int j, const double (&w)[4], double (&wf)[4]) {
+        const double sh = shift[l];
+        l = l + 1 == L_tau ? 0 : l + 1;
+        wtab(l, wf);  // the last step fetches a slice it does not use
+        const f64x4 H = circ16(F, Cb, L);
+        double sum = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            F[r] = H[r] * w[r];
+            sum += F[r];
+        }
+        const double tot = wave_sum_f64(sum);
+        good = good && tot > 0.0 && isfinite(tot);
+        const double inv = 1.0 / tot;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            F[r] *= inv;
+            if (inside(r)) put(j, 0, r, F[r]);
+        }
+        la += log(tot) + sh;
+    };
+    int j = 1;
+    for (; j + 1 < len; j += 2) {
+        step(j, wa, wb);
+        step(j + 1, wb, wa);
+    }
+    if (j < len) step(j, wa, wb);
+    const f64x4 H = circ16(F, Cb, L);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (inside(r)) put_end(0, r, H[r]);
+    *la_end = la;
+    const int ex = e % L, ey = e / L, re = ey >> 2;
+    double hv = 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (r == re) hv = H[r];
+    hv = __shfl(hv, ex + 16 * (ey & 3), 64);
+    good = good && hv > 0.0;
+    *ok = good;
+    return la + log(hv);
+}
+
 // The forward recursion of one block on the FP64 circulant, one wavefront (Sec. 3.5.2, site
 // basis, with the per-step sum normaliser and the log-shifted potentials W~ = W exp(-m_l)):
 //   f~_0 = delta_a; h_j = W~_{start+j} . (C f~_{j-1} C); c_j = sum h_j; f~_j = h_j / c_j
@@ -79,7 +158,8 @@ __device__ inline int t64_y(int q, int r, int lane) { return 16 * (q >> 1) + 4 *
 // slice l at the lane's element (q, r) (any finite value at padded positions, where C f C is an
 // exact zero); put(j, q, r, v) receives element (q, r) of row f~_j, j = 1 .. len - 1, at the
 // lane's positions inside the L x L lattice only; put_end(q, r, v) the same elements of the end
-// tile C f~_{len-1} C, and *la_end log Z without the end weight (for worldlines that share these
+// tile C f~_{len-1} C (L <= 16: w holds the four elements of tile 0 only, and only those are
+// put), and *la_end log Z without the end weight (for worldlines that share these
 // rows but end elsewhere). Returns log Z; *ok becomes false when a normaliser or the end weight
 // is not a positive finite number.
 template <typename WTab, typename Put, typename PutEnd>
@@ -88,7 +168,13 @@ __device__ inline double dmfma_block_forward_end(const double (&Cb)[16], int L, 
                                                  const double* __restrict__ shift, WTab wtab,
                                                  Put put, PutEnd put_end, double* la_end,
                                                  bool* ok) {
+#pragma clang fp contract(off)  // the same bits from every form of the recursion
     const int lane = threadIdx.x & 63;
+    if (L <= 16) {
+        const double C4[4] = {Cb[0], Cb[2], Cb[4], Cb[6]};
+        return dmfma16_block_forward_end(C4, L, L_tau, start, len, a, e, la, shift, wtab, put,
+                                         put_end, la_end, ok);
+    }
     auto inside = [&](int q, int r) { return t64_x(q, lane) < L && t64_y(q, r, lane) < L; };
     const int ax = a % L, ay = a / L;
     Tile64 F;
@@ -156,6 +242,181 @@ __device__ inline double dmfma_block_forward(const double (&Cb)[16], int L, int 
                                    [](int, int, double) {}, &la_end, ok);
 }
 
+// The recursion of dmfma_block_forward_end by one workgroup of four wavefronts, for passes with
+// too few recursions to fill the chip with one wavefront each. Wavefront wq owns the 16 x 16 tile
+// wq = 2 I + J of the padded 32 x 32 filter: every wavefront holds the whole filter F, forms the
+// two tiles X(0, I), X(1, I) of X = F^T C that its tile of H = X^T C needs, then that tile: 24
+// products per step where one wavefront takes 64. The four W-weighted tiles meet in LDS (xch,
+// double-buffered; *buf is kept between calls), and every wavefront sums all of them in the order
+// of dmfma_block_forward_end, so the normaliser, the rows, the end tile and log Z are bit for bit
+// those of the one-wavefront recursion. cm: the chain's B operands [16][64]; Wl0: W~ of slice 0;
+// row f~_j goes to rows + (j - 1) N, the end tile C f~_{len-1} C to end (nullable). *la enters
+// as log W_start(a) and leaves as log Z without the end weight. Returns true on the wavefront
+// that holds the end weight, *hv (every lane).
+__device__ inline bool dmfma4_block_forward(const double* __restrict__ cm, int L, int L_tau,
+                                            int start, int len, int a, int e,
+                                            const double* __restrict__ Wl0,
+                                            const double* __restrict__ shift,
+                                            double* __restrict__ rows, double* __restrict__ end,
+                                            f64x4 (*xch)[4][64], int wq, int lane, int* buf,
+                                            double* la, double* hv, bool* ok) {
+#pragma clang fp contract(off)  // the same bits from every form of the recursion
+    const int N = L * L, I = wq >> 1, J = wq & 1;
+    // the B operands this wavefront's products take: column block I of C for X(K, I), column
+    // block J for its tile of H (loaded by index, not picked from registers at a run-time index,
+    // which would put them in scratch)
+    double CbI[8], CbJ[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        CbI[k] = cm[(k * 2 + I) * 64 + lane];
+        CbJ[k] = cm[(k * 2 + J) * 64 + lane];
+    }
+    // this wavefront's elements: site of register r of tile wq (-1 where padded; W is read at
+    // site 0 there and multiplies an exact zero)
+    int site[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int x = t64_x(wq, lane), y = t64_y(wq, r, lane);
+        site[r] = (x < L && y < L) ? y * L + x : -1;
+    }
+    auto load_w = [&](int l, double (&w)[4]) {
+        const double* Wl = Wl0 + (int64_t)l * N;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[r] = Wl[max(site[r], 0)];
+    };
+    // this wavefront's tile of H = (F^T C)^T C = C F C
+    auto own_tile = [&](const Tile64& F) {
+        f64x4 X[2];
+#pragma unroll
+        for (int K = 0; K < 2; ++K) {
+            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int K2 = 0; K2 < 2; ++K2)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(F.t[2 * K2 + K][r], CbI[4 * K2 + r],
+                                                               acc, 0, 0, 0);
+            X[K] = acc;
+        }
+        f64x4 H = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int K = 0; K < 2; ++K)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                H = __builtin_amdgcn_mfma_f64_16x16x4f64(X[K][r], CbJ[4 * K + r], H, 0, 0, 0);
+        return H;
+    };
+    Tile64 F;
+    const int ax = a % L, ay = a / L;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            F.t[q][r] = (t64_x(q, lane) == ax && t64_y(q, r, lane) == ay) ? 1.0 : 0.0;
+    bool good = true;
+    double lz = *la;
+    int bf = *buf;
+    // W of the next slice loaded one step ahead, in two buffers that swap roles
+    double wa[4], wb[4];
+    load_w((start + 1) % L_tau, wa);
+    auto step = [&](int j, const double (&w)[4], double (&wf)[4]) {
+        const int l = (start + j) % L_tau;
+        const f64x4 H = own_tile(F);
+        load_w((l + 1) % L_tau, wf);  // the last step fetches a slice it does not use
+        f64x4 P;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) P[r] = H[r] * w[r];
+        xch[bf][wq][lane] = P;
+        __syncthreads();
+        double sum = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f64x4 v = xch[bf][q][lane];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                F.t[q][r] = v[r];
+                sum += v[r];
+            }
+        }
+        bf ^= 1;
+        const double tot = wave_sum_f64(sum);
+        good = good && tot > 0.0 && isfinite(tot);
+        const double inv = 1.0 / tot;
+        lz += log(tot) + shift[l];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) F.t[q][r] *= inv;
+        // this wavefront's tile of the row: its own products scaled as F.t[wq] (read from the
+        // products it holds, as F.t[wq] at a run-time index would live in scratch)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (site[r] >= 0) rows[(int64_t)(j - 1) * N + site[r]] = P[r] * inv;
+    };
+    int j = 1;
+    for (; j + 1 < len; j += 2) {
+        step(j, wa, wb);
+        step(j + 1, wb, wa);
+    }
+    if (j < len) step(j, wa, wb);
+    // end weight (C f~ C)(e): the end tile, and the element at e from its tile's wavefront
+    const f64x4 H = own_tile(F);
+    if (end) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (site[r] >= 0) end[site[r]] = H[r];
+    }
+    *buf = bf;
+    *la = lz;
+    *ok = good;
+    const int ex = e % L, ey = e / L, re = (ey & 15) >> 2;
+    double h = 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (r == re) h = H[r];
+    *hv = __shfl(h, (ex & 15) + 16 * (ey & 3), 64);
+    return wq == 2 * (ey >> 4) + (ex >> 4);
+}
+
+// One recursion by one workgroup: four wavefronts for L > 16, the first one alone for L <= 16
+// (one tile). Arguments as dmfma4_block_forward; *lz receives log Z (valid, with *ok, on the
+// wavefront that gets true).
+__device__ inline bool dmfma_wg_forward(const double* __restrict__ cm, int L, int L_tau, int start,
+                                        int len, int a, int e, const double* __restrict__ Wl0,
+                                        const double* __restrict__ shift,
+                                        double* __restrict__ rows, double* __restrict__ end,
+                                        f64x4 (*xch)[4][64], int wq, int lane, int* buf,
+                                        double* la, double* lz, bool* ok) {
+    if (L <= 16) {
+        if (wq != 0) return false;
+        const int N = L * L;
+        double Cb[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Cb[r] = cm[2 * r * 64 + lane];
+        auto site = [&](int r) { return t64_y(0, r, lane) * L + t64_x(0, lane); };
+        auto wtab = [&](int l, double (&w)[4]) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool in = t64_x(0, lane) < L && t64_y(0, r, lane) < L;
+                w[r] = Wl0[(int64_t)l * N + (in ? site(r) : 0)];
+            }
+        };
+        auto put = [&](int j, int, int r, double v) { rows[(int64_t)(j - 1) * N + site(r)] = v; };
+        auto put_end = [&](int, int r, double v) {
+            if (end) end[site(r)] = v;
+        };
+        *lz = dmfma16_block_forward_end(Cb, L, L_tau, start, len, a, e, *la, shift, wtab, put,
+                                        put_end, la, ok);
+        return true;
+    }
+    double hv;
+    const bool mine = dmfma4_block_forward(cm, L, L_tau, start, len, a, e, Wl0, shift, rows, end,
+                                           xch, wq, lane, buf, la, &hv, ok);
+    *ok = *ok && hv > 0.0;
+    *lz = *la + log(hv);
+    return mine;
+}
+
 // Lattices of side L = 16 NT with NT = 3 or 4 (L = 48, 64) on the same instruction. The filter
 // is NT x NT tiles of 16 x 16, tile q = NT I + J holding rows 16 I .. and columns 16 J .., its
 // element (16 I + 4 r + lane / 16, 16 J + lane % 16) in register r, as above. C[k][j] =
@@ -201,6 +462,7 @@ __device__ inline double dmfma_big_block_forward_end(const double (&Cb)[16], int
                                                      const double* __restrict__ shift, WTab wtab,
                                                      Put put, PutEnd put_end, double* la_end,
                                                      bool* ok) {
+#pragma clang fp contract(off)  // the same bits from every form of the recursion
     constexpr int L = 16 * NT, NQ = NT * NT;
     const int lane = threadIdx.x & 63;
     const int ax = a % L, ay = a / L;

@@ -51,7 +51,8 @@ struct ChainInfo {
     // start site, so worldlines of one (spin, block) with the same start site share the rows of
     // the lowest-numbered of them, their representative. dedup = 1: every chain with L <= 32 of
     // the split-bf16 plan (32 x 32, padded and packed tiles), in the FP32 passes and the FP64
-    // re-filter's phase A; end_off locates their per-(particle, block) end tiles [N].
+    // re-filter's phase A; end_off locates their per-(particle, block) end tiles [N]; and every
+    // chain of an FP64 plan on the FP64 circulant (end tiles in the filter workspace).
     // dedup = 2: 48 x 48 and 64 x 64 chains of FP32 plans,
     // in phase A only (their FP32 passes keep one recursion per worldline, and their map is the
     // identity while the chain is not held).
@@ -67,6 +68,10 @@ FH_HD inline int64_t tab_g(const ChainInfo& c) { return c.tab_off + 2 * c.N; }
 FH_HD inline int64_t tab_tw(const ChainInfo& c) { return c.tab_off + 2 * c.N + c.L; }
 inline int64_t tab_size(int L) { return 2 * (int64_t)L * L + L + 2 * L; }
 constexpr int kBwCounts = 4;  // offset of the per-chain counts in Device::bw_state
+// Counts of the dense lists k_dedup fills on FP64 plans: representatives with L <= 32, L = 64 and
+// L = 48.
+constexpr int kListFwd = 0, kListFwd64 = 1, kListFwd48 = 2;
+constexpr int kListWords = 16;
 constexpr int kCmatPerChain = 3 * 2 * 64 * 8;
 constexpr int kCmat64PerChain = 16 * 64;
 // Lattices above 32 that the FP64 circulant takes (fh_dmfma.h): L = 16 NT with NT = 3 or 4; 0
@@ -259,6 +264,8 @@ struct Device {
     double* blk_la = nullptr;
     float* endrow = nullptr;
     DrawTask* dedup_tasks = nullptr;
+    int32_t* lists = nullptr;  // counts of the pass's dense lists (kList*), zeroed by k_potentials
+    DrawTask* fwddc_tasks = nullptr;  // FP64 plans: the representatives k_dedup lists, as fwdd_tasks
     double* dt = nullptr;     // per particle d log Z / d t
     PairTask* fwd_tasks = nullptr;
     DrawTask* draw_tasks = nullptr;

@@ -278,9 +278,11 @@ __global__ __launch_bounds__(kThreads) void k_potentials(const ChainInfo* __rest
                                                          int n_chains, const T* __restrict__ aux,
                                                          T* __restrict__ W, double* __restrict__ wshift,
                                                          int64_t aux_elems, int64_t total_slices,
-                                                         int32_t* status) {
+                                                         int32_t* status, int32_t* lists) {
     __shared__ double red[2 * kWaves];
     const int gs = blockIdx.x;
+    // the pass's dense lists start empty (k_dedup fills them after this kernel)
+    if (lists && gs == 0 && threadIdx.x < kListWords) lists[threadIdx.x] = 0;
     const int ci = find_chain(n_chains, gs, [&](int i) { return chains[i].slice_off; });
     const ChainInfo& c = chains[ci];
     const int64_t base = c.aux_off + (int64_t)(gs - c.slice_off) * c.N;
@@ -1425,7 +1427,7 @@ __global__ __launch_bounds__(kThreads, NT == 2 ? 2 : 1) void k_rescue(
         auto wtab = [&](int l, auto& w) {
             const double* Wl = Wl0 + (int64_t)l * N;
 #pragma unroll
-            for (int q = 0; q < (NT == 2 ? 4 : NT * NT); ++q)
+            for (int q = 0; q < (int)(sizeof(w) / (4 * sizeof(double))); ++q)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) w[4 * q + r] = Wl[max(site(q, r), 0)];
         };
@@ -1467,13 +1469,8 @@ __global__ __launch_bounds__(kThreads, NT == 2 ? 2 : 1) void k_rescue(
 // goes to blk_logz, log Z without the end weight to blk_la (shared-filter chains), and the slot
 // to rep_slot.
 //
-// Lattices with L <= 32: one workgroup of four wavefronts per representative. Wavefront q owns
-// the 16 x 16 tile q = 2 I + J of the padded 32 x 32 filter (fh_dmfma.h): every wavefront holds
-// the whole filter F, forms the two tiles X(0, I), X(1, I) of X = F^T C that its tile of
-// H = X^T C needs, then that tile: 24 products per step where one wavefront takes 64. The four
-// W-weighted tiles meet in LDS, and every wavefront sums all of them in the order of
-// dmfma_block_forward_end, so the normaliser, the rows, the end tile and log Z are bit for bit
-// those of the one-wavefront recursion (k_rescue).
+// Lattices with L <= 32: one workgroup per representative (dmfma_wg_forward), bit for bit the
+// one-wavefront recursion of k_rescue.
 __global__ __launch_bounds__(kThreads, 1) void k_rescue_share_fwd4(
     const ChainInfo* __restrict__ chains, const double* __restrict__ cmat64,
     const float* __restrict__ aux, const double* __restrict__ wshift, int64_t total_slices,
@@ -1487,7 +1484,6 @@ __global__ __launch_bounds__(kThreads, 1) void k_rescue_share_fwd4(
     __shared__ int32_t slot_sh;
     const int lane = threadIdx.x & 63;
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // this wavefront's tile
-    const int I = wq >> 1, J = wq & 1;
     const int n = __builtin_amdgcn_readfirstlane(rsc.words[6]);
     const uint64_t sweep = *sweep_ptr;
     int buf = 0;
@@ -1510,124 +1506,18 @@ __global__ __launch_bounds__(kThreads, 1) void k_rescue_share_fwd4(
         const int a = checked_site(pc[(int64_t)start * c.np + t.p], N, status, t.chain);
         const int e = checked_site(pc[(int64_t)((start + len) % L_tau) * c.np +
                                       (start + len >= L_tau ? qn : t.p)], N, status, t.chain);
-        // the B operands this wavefront's products take: column block I of C for X(K, I),
-        // column block J for its tile of H (loaded by index, not picked from registers at a
-        // run-time index, which would put them in scratch)
-        double CbI[8], CbJ[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            CbI[k] = cmat64[((int64_t)t.chain * 16 + k * 2 + I) * 64 + lane];
-            CbJ[k] = cmat64[((int64_t)t.chain * 16 + k * 2 + J) * 64 + lane];
-        }
-        const double* Wl0 = W64 + spin * aux_elems + c.aux_off;
-        // this wavefront's elements: site of register r of tile wq (-1 where padded; W is read
-        // at site 0 there and multiplies an exact zero)
-        int site[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int x = t64_x(wq, lane), y = t64_y(wq, r, lane);
-            site[r] = (x < L && y < L) ? y * L + x : -1;
-        }
-        auto load_w = [&](int l, double (&w)[4]) {
-            const double* Wl = Wl0 + (int64_t)l * N;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) w[r] = Wl[max(site[r], 0)];
-        };
-        // this wavefront's tile of H = (F^T C)^T C = C F C
-        auto own_tile = [&](const Tile64& F) {
-            f64x4 X[2];
-#pragma unroll
-            for (int K = 0; K < 2; ++K) {
-                f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int K2 = 0; K2 < 2; ++K2)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(F.t[2 * K2 + K][r],
-                                                                   CbI[4 * K2 + r], acc, 0, 0, 0);
-                X[K] = acc;
-            }
-            f64x4 H = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int K = 0; K < 2; ++K)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    H = __builtin_amdgcn_mfma_f64_16x16x4f64(X[K][r], CbJ[4 * K + r], H, 0, 0, 0);
-            return H;
-        };
-        Tile64 F;
-        const int ax = a % L, ay = a / L;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                F.t[q][r] = (t64_x(q, lane) == ax && t64_y(q, r, lane) == ay) ? 1.0 : 0.0;
-        double la = coef * (double)aux[c.aux_off + (int64_t)start * N + a];
-        bool good = true;
-        // W of the next slice loaded one step ahead, in two buffers that swap roles
-        double wa[4], wb[4];
-        load_w((start + 1) % L_tau, wa);
-        auto step = [&](int j, const double (&w)[4], double (&wf)[4]) {
-            const int l = (start + j) % L_tau;
-            const f64x4 H = own_tile(F);
-            load_w((l + 1) % L_tau, wf);  // the last step fetches a slice it does not use
-            f64x4 P;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) P[r] = H[r] * w[r];
-            xch[buf][wq][lane] = P;
-            __syncthreads();
-            double sum = 0.0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f64x4 v = xch[buf][q][lane];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    F.t[q][r] = v[r];
-                    sum += v[r];
-                }
-            }
-            buf ^= 1;
-            const double tot = wave_sum_f64(sum);
-            good = good && tot > 0.0 && isfinite(tot);
-            const double inv = 1.0 / tot;
-            la += log(tot) + shift[l];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) F.t[q][r] *= inv;
-            // this wavefront's tile of the row: its own products scaled as F.t[wq] (read from
-            // the products it holds, as F.t[wq] at a run-time index would live in scratch)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (site[r] >= 0) slot[(int64_t)(j - 1) * N + site[r]] = P[r] * inv;
-        };
-        int j = 1;
-        for (; j + 1 < len; j += 2) {
-            step(j, wa, wb);
-            step(j + 1, wb, wa);
-        }
-        if (j < len) step(j, wa, wb);
-        // end weight (C f~ C)(e): the end tile, and the element at e from its tile's wavefront
-        const f64x4 H = own_tile(F);
-        double* end = slot + (int64_t)(c.B - 1) * N;  // after the longest block's rows
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (site[r] >= 0) end[site[r]] = H[r];
-        const int ex = e % L, ey = e / L;
-        if (wq == 2 * (ey >> 4) + (ex >> 4)) {
-            const int re = (ey & 15) >> 2;
-            double hv = 0.0;
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (r == re) hv = H[r];
-            hv = __shfl(hv, (ex & 15) + 16 * (ey & 3), 64);
-            if (lane == 0) {
-                const int64_t bi = c.blk_off + (int64_t)t.p * c.nb + t.block;
-                if (!(good && hv > 0.0)) set_status(status, FH_ERR_NONFINITE, t.chain);
-                blk_logz[bi] = la + log(hv);
-                if (c.dedup) blk_la[bi] = la;
-                rep_slot[bi] = slot_id;
-            }
+        const double* cm = cmat64 + (int64_t)t.chain * kCmat64PerChain;
+        double la = coef * (double)aux[c.aux_off + (int64_t)start * N + a], lz;
+        bool good;
+        if (dmfma_wg_forward(cm, L, L_tau, start, len, a, e, W64 + spin * aux_elems + c.aux_off,
+                             shift, slot, slot + (int64_t)(c.B - 1) * N, xch, wq, lane, &buf, &la,
+                             &lz, &good) &&
+            lane == 0) {
+            const int64_t bi = c.blk_off + (int64_t)t.p * c.nb + t.block;
+            if (!good) set_status(status, FH_ERR_NONFINITE, t.chain);
+            blk_logz[bi] = lz;
+            if (c.dedup) blk_la[bi] = la;
+            rep_slot[bi] = slot_id;
         }
         __syncthreads();  // slot_sh and the exchange buffers are free for the next representative
     }
@@ -1751,7 +1641,9 @@ __global__ __launch_bounds__(kThreads, kShareDrawWaves) void k_rescue_share_draw
 // dispatched, spread over the XCDs, instead of sitting at fixed grid positions that map a whole
 // settled batch onto a few compute units. Packed lattices (pack = P) list their representatives
 // in prep (count in words[10]) and P^2 of them to a tile in cpack (P = 2: from the front, count
-// in words[8]; P = 4: from n_p2 on, count in words[9]).
+// in words[8]; P = 4: from n_p2 on, count in words[9]). FP64 plans list every representative in
+// csingles, by tiling: L <= 32 from the front, 64 x 64 from off64 on, 48 x 48 from off48 on
+// (counts in lists[kListFwd..]).
 __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict__ chains,
                                                     const DrawTask* __restrict__ tasks,
                                                     const int32_t* __restrict__ paths,
@@ -1760,7 +1652,9 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
                                                     PairTask* __restrict__ cpairs,
                                                     DrawTask* __restrict__ csingles,
                                                     PackTask* __restrict__ cpack, int n_p2,
-                                                    int32_t* __restrict__ prep) {
+                                                    int32_t* __restrict__ prep,
+                                                    int32_t* __restrict__ lists, int off64,
+                                                    int off48) {
     __shared__ int32_t first[kDedupMaxN];
     __shared__ int32_t rlist[kDedupMaxN];
     __shared__ int32_t n_rep, c_base, p_base;
@@ -1791,11 +1685,13 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
     }
     __syncthreads();
     // the chain's forward recursions in this pass (the FP64 re-filter's phase A sizes by them)
-    if (threadIdx.x == 0) atomicAdd(&rsc.words[kRescueChain + 3 * rsc.n_chains + t.chain], n_rep);
+    if (rsc.words && threadIdx.x == 0)
+        atomicAdd(&rsc.words[kRescueChain + 3 * rsc.n_chains + t.chain], n_rep);
     // the 32 x 32 chains' representatives go to cpairs, two to a task; the padded lattices'
     // (16 < L < 32, one worldline to a wavefront) to csingles (count in words[7]); the packed
     // ones to cpack
-    const bool pairs = c.L == 32;
+    const bool fp64 = rsc.words == nullptr;  // FP64 plans: csingles, whatever the lattice
+    const bool pairs = c.L == 32 && !fp64;
     const int PP = c.pack * c.pack;  // worldlines per packed tile
     if (c.dedup != 1 || (pairs ? !cpairs : c.pack ? !cpack : !csingles) ||
         rescue_held(rsc, t.chain))
@@ -1822,6 +1718,10 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
                 p_base = atomicAdd(&rsc.words[10], cnt);
                 c_base = atomicAdd(&rsc.words[c.pack == 2 ? 8 : 9], (cnt + PP - 1) / PP) +
                          (c.pack == 2 ? 0 : n_p2);
+            } else if (fp64) {  // one list per tiling (launch_forward_dmfma)
+                c_base = c.L <= 32 ? atomicAdd(&lists[kListFwd], cnt)
+                         : c.L == 64 ? off64 + atomicAdd(&lists[kListFwd64], cnt)
+                                     : off48 + atomicAdd(&lists[kListFwd48], cnt);
             } else {
                 c_base = atomicAdd(&rsc.words[7], cnt);
             }
@@ -1848,10 +1748,13 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
 // the end weight and reads its own end weight from the representative's end tile
 // (C f~ C)(e), exactly what its own recursion would have computed; an end weight below
 // kRangeFloor queues the block like the forward kernel's own check.
+// FP64 plans keep the end tiles in the filter workspace's free rows (after the L_tau - nb rows of
+// the blocks), and an end weight that is not positive latches FH_ERR_NONFINITE.
+template <typename T>
 __global__ void k_member_logz(const ChainInfo* __restrict__ chains, int n_chains,
                               const int32_t* __restrict__ paths, const int32_t* __restrict__ perm,
                               const uint64_t* __restrict__ sweep_ptr,
-                              const double* __restrict__ blk_la, const float* __restrict__ endrow,
+                              const double* __restrict__ blk_la, const T* __restrict__ endrow,
                               double* __restrict__ blk_logz, int64_t blk_elems, int32_t* status,
                               const Rescue rsc) {
     const uint64_t sweep = *sweep_ptr;
@@ -1871,8 +1774,14 @@ __global__ void k_member_logz(const ChainInfo* __restrict__ chains, int n_chains
         const int e = checked_site(
             paths[c.path_off + (int64_t)((start + len) % L_tau) * c.np + qe], c.N, status, ci);
         const int64_t ri = c.blk_off + (int64_t)rp * c.nb + b;
-        const float hv = endrow[c.end_off + ((int64_t)rp * c.nb + b) * c.N + e];
-        if (!(hv >= kRangeFloor)) rescue_push(rsc, c, ci, p, b, kCauseEnd);
+        T hv;
+        if constexpr (sizeof(T) == 8) {
+            hv = endrow[c.filt_off + ((int64_t)rp * L_tau + L_tau - c.nb + b) * c.N + e];
+            if (!(hv > 0.0)) set_status(status, FH_ERR_NONFINITE, ci);
+        } else {
+            hv = endrow[c.end_off + ((int64_t)rp * c.nb + b) * c.N + e];
+            if (!(hv >= kRangeFloor)) rescue_push(rsc, c, ci, p, b, kCauseEnd);
+        }
         blk_logz[i] = blk_la[ri] + log((double)hv);
     }
 }
@@ -2758,11 +2667,11 @@ hipError_t launch_potentials(fh_plan p, const void* aux, hipStream_t s) {
     if (p->precision == FH_FP64)
         hipLaunchKernelGGL(k_potentials<double>, dim3(g), dim3(kThreads), 0, s, p->d.chains,
                            p->n_chains, (const double*)aux, (double*)p->d.W, p->d.wshift,
-                           p->aux_elems, p->total_slices, p->d.status);
+                           p->aux_elems, p->total_slices, p->d.status, p->d.lists);
     else
         hipLaunchKernelGGL(k_potentials<float>, dim3(g), dim3(kThreads), 0, s, p->d.chains,
                            p->n_chains, (const float*)aux, (float*)p->d.W, p->d.wshift,
-                           p->aux_elems, p->total_slices, p->d.status);
+                           p->aux_elems, p->total_slices, p->d.status, p->d.lists);
     return hipGetLastError();
 }
 
@@ -2870,16 +2779,24 @@ hipError_t launch_dedup(fh_plan p, const int32_t* paths, hipStream_t s) {
     if (p->n_dedup_tasks == 0 || p->share_off) return hipSuccess;
     hipLaunchKernelGGL(k_dedup, dim3((unsigned)p->n_dedup_tasks), dim3(kThreads), 0, s,
                        p->d.chains, p->d.dedup_tasks, paths, p->d.sweep, p->d.rep, rescue_args(p),
-                       p->d.fwd32c_tasks, p->d.fwdxc_tasks, p->d.fwdpc_tasks, p->n_fwdp2_tasks,
-                       p->d.prep);
+                       p->d.fwd32c_tasks,
+                       p->precision == FH_FP64 ? p->d.fwddc_tasks : p->d.fwdxc_tasks,
+                       p->d.fwdpc_tasks, p->n_fwdp2_tasks, p->d.prep, p->d.lists,
+                       p->n_fwdd_tasks, p->n_fwdd_tasks + p->n_fwdd4_tasks);
     return hipGetLastError();
 }
 
 hipError_t launch_member_logz(fh_plan p, const int32_t* paths, hipStream_t s) {
     if (p->n_dedup_tasks == 0 || p->share_off) return hipSuccess;
-    hipLaunchKernelGGL(k_member_logz, dim3(grid_for(p->blk_elems)), dim3(kThreads), 0, s,
-                       p->d.chains, p->n_chains, paths, p->d.perm, p->d.sweep, p->d.blk_la,
-                       p->d.endrow, p->d.blk_logz, p->blk_elems, p->d.status, rescue_args(p));
+    if (p->precision == FH_FP64)
+        hipLaunchKernelGGL(k_member_logz<double>, dim3(grid_for(p->blk_elems)), dim3(kThreads), 0,
+                           s, p->d.chains, p->n_chains, paths, p->d.perm, p->d.sweep, p->d.blk_la,
+                           (const double*)p->d.filt, p->d.blk_logz, p->blk_elems, p->d.status,
+                           rescue_args(p));
+    else
+        hipLaunchKernelGGL(k_member_logz<float>, dim3(grid_for(p->blk_elems)), dim3(kThreads), 0,
+                           s, p->d.chains, p->n_chains, paths, p->d.perm, p->d.sweep, p->d.blk_la,
+                           p->d.endrow, p->d.blk_logz, p->blk_elems, p->d.status, rescue_args(p));
     return hipGetLastError();
 }
 

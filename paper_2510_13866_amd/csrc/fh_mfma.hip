@@ -19,6 +19,8 @@
 // bias of the kernel's mass (log Z drifts ~1e-4 over 160 slices) or a filter drift ~4e-5.
 // The per-step normaliser is a DPP wavefront sum in FP32; log Z is accumulated in FP64.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 #include <math.h>
 
 #include <type_traits>
@@ -318,63 +320,111 @@ __global__ __launch_bounds__(kThreads, LFIX ? 4 : 2) void k_forward_mfma(
 
 // ---- FP64 circulant on the FP64 matrix cores (fh_dmfma.h) ----------------------------------
 
-// One wavefront per (chain, worldline, block) of an FP64 plan with L <= 32: the forward
-// recursion of one block with the FP64 circulant,
-//   f~_0 = delta_a; h_j = W~_{start+j} . (C f~_{j-1} C); c_j = sum h_j; f~_j = h_j / c_j
-//   log Z = coef aux_start(a) + sum_j (log c_j + m_{start+j}) + log (C f~_{len-1} C)(e),
-// rows f~_j (j >= 1) stored as FP64 rows of N values, exactly where the FFT path stores them.
-// Padded positions (x or y >= L) stay exact zeros: C is zero outside the lattice.
+// FP64 circulant forward of the FP64 plans (L <= 32). With shared filters (ccount given) the tasks
+// are the dense list of representatives ctasks (k_dedup), whose end tiles and log Z before the
+// end weight k_member_logz completes for the worldlines that share their rows.
+// A pass with at most kDmfmaWgTasks recursions gives each a workgroup (dmfma_wg_forward), more
+// take one wavefront each: a step of a 32 x 32 recursion takes 1.4 us against 2.7 us, but 96
+// instead of 64 products, so past one workgroup per compute unit the split only adds matrix work.
+// The bits are the same either way. Bound: the 159 dependent steps of a recursion. Settled chains
+// need one or two recursions per spin and block: 8 chains of 32 x 32, L_tau = 160, 3463 us with
+// one recursion per worldline, 227 us shared; one 4 x 4 chain, L_tau = 16, 45 -> 13 us (one tile).
+constexpr int kDmfmaWgTasks = 256;
+
+// The slot of block b's end tile of worldline p: the filter workspace holds L_tau rows per
+// worldline and a sweep's blocks L_tau - nb of them, so the last nb rows are free.
+__device__ inline double* end_row64(double* filt, const ChainInfo& c, int p, int b) {
+    return filt + c.filt_off + ((int64_t)p * c.L_tau + c.L_tau - c.nb + b) * c.N;
+}
+
+struct Fwd64Ctx {  // what a forward task of the FP64 plans reads
+    int start, len, a, e;
+    const double* W;
+    const double* shift;
+    double la;
+    double* rows;
+};
+__device__ inline Fwd64Ctx fwd64_ctx(const DrawTask& t, const ChainInfo& c, const double* aux,
+                                     const double* W, const double* wshift, int64_t aux_elems,
+                                     int64_t total_slices, const int32_t* paths,
+                                     const int32_t* perm, double* filt, uint64_t sweep,
+                                     int32_t* status) {
+    Fwd64Ctx x;
+    block_of(c, sweep, t.block, &x.start, &x.len);
+    const int N = c.N, spin = t.p >= c.n_up ? 1 : 0;
+    x.W = W + spin * aux_elems + c.aux_off;
+    x.shift = wshift + spin * total_slices + c.slice_off;
+    const int32_t* pc = paths + c.path_off;
+    x.a = pc[(int64_t)x.start * c.np + t.p];
+    // a block that runs past slice L_tau - 1 ends on the worldline its owner reconnects to
+    const int qe = x.start + x.len >= c.L_tau ? perm[c.part_off + t.p] : t.p;
+    x.e = pc[(int64_t)((x.start + x.len) % c.L_tau) * c.np + qe];
+    if (x.a < 0 || x.a >= N || x.e < 0 || x.e >= N) {
+        if ((threadIdx.x & 63) == 0) set_status(status, FH_ERR_BAD_PATH, t.chain);
+        x.a = (x.a < 0 || x.a >= N) ? 0 : x.a;
+        x.e = (x.e < 0 || x.e >= N) ? 0 : x.e;
+    }
+    x.la = (spin ? c.coef_dn : c.coef_up) * aux[c.aux_off + (int64_t)x.start * N + x.a];
+    x.rows = filt + c.filt_off + ((int64_t)t.p * c.L_tau + (int64_t)t.block * (c.B - 1)) * N;
+    return x;
+}
+
 __global__ __launch_bounds__(kThreads) void k_forward_dmfma(
     const ChainInfo* __restrict__ chains, const DrawTask* __restrict__ tasks, int n_tasks,
     const double* __restrict__ cmat64, const double* __restrict__ aux, const double* __restrict__ W,
     const double* __restrict__ wshift, int64_t aux_elems, int64_t total_slices,
     const int32_t* __restrict__ paths, const int32_t* __restrict__ perm, double* __restrict__ filt,
-    double* __restrict__ blk_logz, const uint64_t* __restrict__ sweep_ptr, int32_t* status) {
+    double* __restrict__ blk_logz, const uint64_t* __restrict__ sweep_ptr, int32_t* status,
+    const DrawTask* __restrict__ ctasks, const int32_t* __restrict__ ccount,
+    double* __restrict__ blk_la) {
+    __shared__ f64x4 xch[2][4][64];
     const int lane = threadIdx.x & 63;
-    const int task = __builtin_amdgcn_readfirstlane(blockIdx.x * kWaves + (threadIdx.x >> 6));
-    if (task >= n_tasks) return;  // whole wavefront; no barriers in this kernel
-    const DrawTask t = tasks[task];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = __builtin_amdgcn_readfirstlane(ccount ? *ccount : n_tasks);
+    const bool wg = n <= kDmfmaWgTasks;  // uniform over the grid
+    const int task = wg ? (int)blockIdx.x : (int)blockIdx.x * kWaves + wv;
+    if (task >= n) return;  // the whole workgroup where the workgroup has barriers
+    const DrawTask t = ccount ? ctasks[task] : tasks[task];
     const ChainInfo& c = chains[t.chain];
-    int start, len;
-    block_of(c, *sweep_ptr, t.block, &start, &len);
-    const int L = c.L, N = c.N, L_tau = c.L_tau;
-    const int spin = t.p >= c.n_up ? 1 : 0;
-    const double* Wsp = W + spin * aux_elems + c.aux_off;
-    const double* shift = wshift + spin * total_slices + c.slice_off;
-    const double coef = spin ? c.coef_dn : c.coef_up;
-    const int32_t* pc = paths + c.path_off;
-    int a = pc[(int64_t)start * c.np + t.p];
-    // a block that runs past slice L_tau - 1 ends on the worldline its owner reconnects to
-    const int qe = start + len >= L_tau ? perm[c.part_off + t.p] : t.p;
-    int e = pc[(int64_t)((start + len) % L_tau) * c.np + qe];
-    if (a < 0 || a >= N || e < 0 || e >= N) {
-        if (lane == 0) set_status(status, FH_ERR_BAD_PATH, t.chain);
-        a = (a < 0 || a >= N) ? 0 : a;
-        e = (e < 0 || e >= N) ? 0 : e;
+    const Fwd64Ctx x = fwd64_ctx(t, c, aux, W, wshift, aux_elems, total_slices, paths, perm, filt,
+                                 *sweep_ptr, status);
+    const int L = c.L, N = c.N;
+    double* end = ccount ? end_row64(filt, c, t.p, t.block) : nullptr;
+    const int64_t bi = c.blk_off + (int64_t)t.p * c.nb + t.block;
+    bool ok = true, mine = true;
+    double lz, la_end = x.la;
+    if (wg) {
+        int buf = 0;
+        mine = dmfma_wg_forward(cmat64 + (int64_t)t.chain * kCmat64PerChain, L, c.L_tau, x.start,
+                                x.len, x.a, x.e, x.W, x.shift, x.rows, end, xch, wv, lane, &buf,
+                                &la_end, &lz, &ok);
+    } else {
+        double Cb[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) Cb[q] = cmat64[((int64_t)t.chain * 16 + q) * 64 + lane];
+        auto wtab = [&](int l, auto& w) {
+            const double* Wl = x.W + (int64_t)l * N;
+#pragma unroll
+            for (int q = 0; q < (int)(sizeof(w) / (4 * sizeof(double))); ++q)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {  // a padded position reads site 0 (in bounds), times 0
+                    const int xx = t64_x(q, lane), yy = t64_y(q, r, lane);
+                    w[4 * q + r] = Wl[(xx < L && yy < L) ? yy * L + xx : 0];
+                }
+        };
+        auto put = [&](int j, int q, int r, double v) {
+            x.rows[(int64_t)(j - 1) * N + t64_y(q, r, lane) * L + t64_x(q, lane)] = v;
+        };
+        auto put_end = [&](int q, int r, double v) {
+            if (end) end[t64_y(q, r, lane) * L + t64_x(q, lane)] = v;
+        };
+        lz = dmfma_block_forward_end(Cb, L, c.L_tau, x.start, x.len, x.a, x.e, x.la, x.shift, wtab,
+                                     put, put_end, &la_end, &ok);
     }
-    double Cb[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) Cb[q] = cmat64[((int64_t)t.chain * 16 + q) * 64 + lane];
-    const double la = coef * aux[c.aux_off + (int64_t)start * N + a];
-    double* rows = filt + c.filt_off + ((int64_t)t.p * L_tau + (int64_t)t.block * (c.B - 1)) * N;
-    auto wtab = [&](int l, double (&w)[16]) {
-        const double* Wl = Wsp + (int64_t)l * N;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {  // a padded position reads site 0 (in bounds), times 0
-                const int x = t64_x(q, lane), y = t64_y(q, r, lane);
-                w[4 * q + r] = Wl[(x < L && y < L) ? y * L + x : 0];
-            }
-    };
-    auto put = [&](int j, int q, int r, double v) {
-        rows[(int64_t)(j - 1) * N + t64_y(q, r, lane) * L + t64_x(q, lane)] = v;
-    };
-    bool ok = true;
-    const double lz = dmfma_block_forward(Cb, L, L_tau, start, len, a, e, la, shift, wtab, put, &ok);
-    if (lane == 0) {
+    if (mine && lane == 0) {
         if (!ok) set_status(status, FH_ERR_NONFINITE, t.chain);
-        blk_logz[c.blk_off + (int64_t)t.p * c.nb + t.block] = lz;
+        blk_logz[bi] = lz;
+        if (ccount) blk_la[bi] = la_end;
     }
 }
 
@@ -388,51 +438,44 @@ __global__ __launch_bounds__(kThreads, 1) void k_forward_dmfma_big(
     const double* __restrict__ cmat64, const double* __restrict__ aux, const double* __restrict__ W,
     const double* __restrict__ wshift, int64_t aux_elems, int64_t total_slices,
     const int32_t* __restrict__ paths, const int32_t* __restrict__ perm, double* __restrict__ filt,
-    double* __restrict__ blk_logz, const uint64_t* __restrict__ sweep_ptr, int32_t* status) {
+    double* __restrict__ blk_logz, const uint64_t* __restrict__ sweep_ptr, int32_t* status,
+    const DrawTask* __restrict__ ctasks, const int32_t* __restrict__ ccount,
+    double* __restrict__ blk_la) {
     constexpr int L = 16 * NT, N = L * L, NQ = NT * NT;
     const int lane = threadIdx.x & 63;
     const int task = __builtin_amdgcn_readfirstlane(blockIdx.x * kWaves + (threadIdx.x >> 6));
-    if (task >= n_tasks) return;  // whole wavefront; no barriers in this kernel
-    const DrawTask t = tasks[task];
+    if (task >= (ccount ? *ccount : n_tasks)) return;  // whole wavefront; no barriers here
+    const DrawTask t = ccount ? ctasks[task] : tasks[task];
     const ChainInfo& c = chains[t.chain];
-    int start, len;
-    block_of(c, *sweep_ptr, t.block, &start, &len);
-    const int L_tau = c.L_tau;
-    const int spin = t.p >= c.n_up ? 1 : 0;
-    const double* Wsp = W + spin * aux_elems + c.aux_off;
-    const double* shift = wshift + spin * total_slices + c.slice_off;
-    const double coef = spin ? c.coef_dn : c.coef_up;
-    const int32_t* pc = paths + c.path_off;
-    int a = pc[(int64_t)start * c.np + t.p];
-    const int qe = start + len >= L_tau ? perm[c.part_off + t.p] : t.p;  // reconnection
-    int e = pc[(int64_t)((start + len) % L_tau) * c.np + qe];
-    if (a < 0 || a >= N || e < 0 || e >= N) {
-        if (lane == 0) set_status(status, FH_ERR_BAD_PATH, t.chain);
-        a = (a < 0 || a >= N) ? 0 : a;
-        e = (e < 0 || e >= N) ? 0 : e;
-    }
+    const Fwd64Ctx x = fwd64_ctx(t, c, aux, W, wshift, aux_elems, total_slices, paths, perm, filt,
+                                 *sweep_ptr, status);
+    double* end = ccount ? end_row64(filt, c, t.p, t.block) : nullptr;
     double Cb[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) Cb[q] = cmat64[((int64_t)t.chain * 16 + q) * 64 + lane];
-    const double la = coef * aux[c.aux_off + (int64_t)start * N + a];
-    double* rows = filt + c.filt_off + ((int64_t)t.p * L_tau + (int64_t)t.block * (c.B - 1)) * N;
+    auto site = [&](int q, int r) { return tb_y<NT>(q, r, lane) * L + tb_x<NT>(q, lane); };
     auto wtab = [&](int l, double (&w)[4 * NQ]) {
-        const double* Wl = Wsp + (int64_t)l * N;
+        const double* Wl = x.W + (int64_t)l * N;
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) w[4 * q + r] = Wl[tb_y<NT>(q, r, lane) * L + tb_x<NT>(q, lane)];
+            for (int r = 0; r < 4; ++r) w[4 * q + r] = Wl[site(q, r)];
     };
     auto put = [&](int j, int q, int r, double v) {
-        rows[(int64_t)(j - 1) * N + tb_y<NT>(q, r, lane) * L + tb_x<NT>(q, lane)] = v;
+        x.rows[(int64_t)(j - 1) * N + site(q, r)] = v;
+    };
+    auto put_end = [&](int q, int r, double v) {
+        if (end) end[site(q, r)] = v;
     };
     bool ok = true;
     double la_end;
-    const double lz = dmfma_big_block_forward_end<NT>(
-        Cb, L_tau, start, len, a, e, la, shift, wtab, put, [](int, int, double) {}, &la_end, &ok);
+    const double lz = dmfma_big_block_forward_end<NT>(Cb, c.L_tau, x.start, x.len, x.a, x.e, x.la,
+                                                      x.shift, wtab, put, put_end, &la_end, &ok);
     if (lane == 0) {
+        const int64_t bi = c.blk_off + (int64_t)t.p * c.nb + t.block;
         if (!ok) set_status(status, FH_ERR_NONFINITE, t.chain);
-        blk_logz[c.blk_off + (int64_t)t.p * c.nb + t.block] = lz;
+        blk_logz[bi] = lz;
+        if (ccount) blk_la[bi] = la_end;
     }
 }
 
@@ -1779,27 +1822,23 @@ __global__ __launch_bounds__(kThreads, 2) void k_forward_classes(
 }  // namespace
 
 hipError_t launch_forward_dmfma(fh_plan p, const void* aux, const int32_t* paths, hipStream_t s) {
-    // fwdd_tasks: the L <= 32 tasks, then those of the 64 x 64 chains, then of the 48 x 48 ones
+    // fwdd_tasks: the L <= 32 tasks, then those of the 64 x 64 chains, then of the 48 x 48 ones;
+    // the representatives k_dedup lists take the same places in fwddc_tasks
     const int32_t n2 = p->n_fwdd_tasks, n4 = p->n_fwdd4_tasks, n3 = p->n_fwdd3_tasks;
+    const bool shared = p->d.fwddc_tasks && !p->share_off;
     auto blocks = [](int32_t n) { return (unsigned)((n + kWaves - 1) / kWaves); };
-    if (n2 > 0)
-        hipLaunchKernelGGL(k_forward_dmfma, dim3(blocks(n2)), dim3(kThreads), 0, s, p->d.chains,
-                           p->d.fwdd_tasks, n2, p->d.cmat64, (const double*)aux,
+    auto run = [&](auto kern, int32_t off, int32_t n, int list, unsigned grid) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), 0, s, p->d.chains,
+                           p->d.fwdd_tasks + off, n, p->d.cmat64, (const double*)aux,
                            (const double*)p->d.W, p->d.wshift, p->aux_elems, p->total_slices,
                            paths, p->d.perm, (double*)p->d.filt, p->d.blk_logz, p->d.sweep,
-                           p->d.status);
-    if (n4 > 0)
-        hipLaunchKernelGGL(k_forward_dmfma_big<4>, dim3(blocks(n4)), dim3(kThreads), 0, s,
-                           p->d.chains, p->d.fwdd_tasks + n2, n4, p->d.cmat64,
-                           (const double*)aux, (const double*)p->d.W, p->d.wshift, p->aux_elems,
-                           p->total_slices, paths, p->d.perm, (double*)p->d.filt, p->d.blk_logz,
-                           p->d.sweep, p->d.status);
-    if (n3 > 0)
-        hipLaunchKernelGGL(k_forward_dmfma_big<3>, dim3(blocks(n3)), dim3(kThreads), 0, s,
-                           p->d.chains, p->d.fwdd_tasks + n2 + n4, n3, p->d.cmat64,
-                           (const double*)aux, (const double*)p->d.W, p->d.wshift, p->aux_elems,
-                           p->total_slices, paths, p->d.perm, (double*)p->d.filt, p->d.blk_logz,
-                           p->d.sweep, p->d.status);
+                           p->d.status, shared ? p->d.fwddc_tasks + off : nullptr,
+                           shared ? p->d.lists + list : nullptr, p->d.blk_la);
+    };
+    if (n2 > 0)
+        run(k_forward_dmfma, 0, n2, kListFwd, std::max(blocks(n2), (unsigned)std::min(n2, kDmfmaWgTasks)));
+    if (n4 > 0) run(k_forward_dmfma_big<4>, n2, n4, kListFwd64, blocks(n4));
+    if (n3 > 0) run(k_forward_dmfma_big<3>, n2 + n4, n3, kListFwd48, blocks(n3));
     return hipGetLastError();
 }
 
