@@ -2032,10 +2032,11 @@ template <typename T>
 __device__ inline int local_move(const ChainInfo& c, const double* g, const T* ax, int l, int cur,
                                  int prev, int next, double coef, int p, uint64_t sweep, int ps) {
     const int L = c.L;
-    auto G = [&](int a, int b) {  // G(a - b) on the periodic lattice
-        int dx = a % L - b % L;
+    const float rL = 1.0f / (float)L;  // (r + 1/2) / L in FP32 floors exactly for r < 2^12
+    auto row = [&](int r) { return (int)(((float)r + 0.5f) * rL); };
+    const int py = row(prev), px = prev - py * L, qy = row(next), qx = next - qy * L;
+    auto G = [&](int dx, int dy) {  // G on the periodic lattice, dx and dy in (-L, L)
         dx += dx < 0 ? L : 0;
-        int dy = a / L - b / L;
         dy += dy < 0 ? L : 0;
         return g[dx] * g[dy];
     };
@@ -2043,23 +2044,33 @@ __device__ inline int local_move(const ChainInfo& c, const double* g, const T* a
                                   kTagLocal + 256ull * (uint64_t)ps, c.seed, 0);
     const int e = (int)(w.x1 >> 62);
     const double u = u01_from(w.x0);
-    const int x = cur % L, y = cur / L;
+    const int y = row(cur), x = cur - y * L;
     const int nx = e == 0 ? (x + 1 == L ? 0 : x + 1) : e == 1 ? (x == 0 ? L - 1 : x - 1) : x;
     const int ny = e == 2 ? (y + 1 == L ? 0 : y + 1) : e == 3 ? (y == 0 ? L - 1 : y - 1) : y;
     const int cand = nx + L * ny;
     const double dA = (double)ax[(int64_t)l * c.N + cand] - (double)ax[(int64_t)l * c.N + cur];
     const double R =
-        exp(coef * dA) * ((G(cand, prev) * G(next, cand)) / (G(cur, prev) * G(next, cur)));
+        exp(coef * dA) * ((G(nx - px, ny - py) * G(qx - nx, qy - ny)) /
+                          (G(x - px, y - py) * G(qx - x, qy - y)));
     return u < R ? cand : cur;
 }
 
-// One pass of local updates: a checkerboard in tau, four launches. PHASE 0 moves the odd
+// One pass of local updates: a checkerboard in tau, three launches. PHASE 0 moves the odd
 // interior slices 1, 3, ... <= L_tau-2 of every worldline, PHASE 1 the even interior slices
-// 2, 4, ... <= L_tau-2, PHASE 2 slice 0 (whose previous slice is slice L_tau-1 of perm_inv[p]),
-// PHASE 3 slice L_tau-1 (whose next slice is slice 0 of perm[p]). A move sees only the two
-// adjacent slices, which belong to other phases, so the moves of a launch are independent: one
-// thread per (worldline, slice). Interior phases take k0 plus the grid's y index as the slice
-// pair k (slice 2k + 1 or 2k + 2); threads past a chain's last slice of the phase leave.
+// 2, 4, ... <= L_tau-2, PHASE 2 the end slices: slice 0 of every worldline, then slice L_tau-1 of
+// every worldline. A move sees only the two adjacent slices, which belong to other phases, so the
+// moves of a phase are independent: one thread per (worldline, slice). Slice 0 of worldline q
+// links to slice L_tau-1 of p = perm_inv[q] and to its own slice 1; slice L_tau-1 of p links to
+// its own slice L_tau-2 and to slice 0 of q. So the thread of p takes both ends of the link: it
+// moves slice 0 of q = perm[p], then slice L_tau-1 of p, which sees the site just taken; no other
+// thread reads or writes either. Two-slice chains, whose slice 1 is both, move it in a launch of
+// its own (PHASE 3). Interior phases take k0 plus the grid's y index as the group k of kLocalSlices
+// slices (from 2 kLocalSlices k + 1 or + 2 on); threads past a chain's last slice of the phase
+// leave. A thread's slices share its chain lookup, and the sites between them are read once. Bound:
+// the generator's 64-bit multiplications and the FP64 ratio of each proposal. A pass over 16
+// chains of 512 + 512 worldlines, L_tau = 160, 2.6e6 proposals: 55 us as four launches of one
+// proposal per thread, 39 us as three.
+constexpr int kLocalSlices = 4;
 template <typename T, int PHASE>
 __global__ __launch_bounds__(kThreads) void k_local(const ChainInfo* __restrict__ chains,
                                                     int n_chains, int64_t particles,
@@ -2067,7 +2078,6 @@ __global__ __launch_bounds__(kThreads) void k_local(const ChainInfo* __restrict_
                                                     const T* __restrict__ aux,
                                                     int32_t* __restrict__ paths,
                                                     const int32_t* __restrict__ perm,
-                                                    const int32_t* __restrict__ perm_inv,
                                                     const uint64_t* __restrict__ sweep_ptr,
                                                     int ps, int k0, int32_t* status) {
     const int64_t gp = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -2077,55 +2087,52 @@ __global__ __launch_bounds__(kThreads) void k_local(const ChainInfo* __restrict_
     const int p = (int)(gp - c.part_off);
     const int N = c.N, L_tau = c.L_tau;
     const int64_t np = c.np;
-    int l, qprev = p, qnext = p;  // slice, and the worldlines holding its neighbours
-    if (PHASE < 2) {
-        l = 2 * (k0 + (int)blockIdx.y) + 1 + PHASE;
-        if (l > L_tau - 2) return;
-    } else if (PHASE == 2) {
-        l = 0;
-        qprev = perm_inv[c.part_off + p];
-    } else {
-        l = L_tau - 1;
-        qnext = perm[c.part_off + p];
-    }
     const double* g = tables + tab_g(c);
-    const double coef = p >= c.n_up ? c.coef_dn : c.coef_up;
     const T* ax = aux + c.aux_off;
     int32_t* col = paths + c.path_off;  // slice l of worldline q at col[l * np + q]
     const uint64_t sweep = *sweep_ptr;
-    const int lp = l == 0 ? L_tau - 1 : l - 1, ln = l == L_tau - 1 ? 0 : l + 1;
-    const int prev = col[(int64_t)lp * np + qprev];
-    const int next = col[(int64_t)ln * np + qnext];
-    const int cur = col[(int64_t)l * np + p];
-    if (prev < 0 || prev >= N || next < 0 || next >= N || cur < 0 || cur >= N) {
-        set_status(status, FH_ERR_BAD_PATH, ci);
-        return;
+    // moves slice l of worldline w between the sites prev and next
+    auto move = [&](int l, int w, int prev, int next, int cur) {
+        if (prev < 0 || prev >= N || next < 0 || next >= N || cur < 0 || cur >= N) {
+            set_status(status, FH_ERR_BAD_PATH, ci);
+            return cur;
+        }
+        const double coef = w >= c.n_up ? c.coef_dn : c.coef_up;
+        const int taken = local_move(c, g, ax, l, cur, prev, next, coef, w, sweep, ps);
+        if (taken != cur) col[(int64_t)l * np + w] = taken;
+        return taken;
+    };
+    if (PHASE < 2) {
+        // kLocalSlices slices of the phase: the 2 kLocalSlices + 1 sites first, all in flight
+        const int l0 = 2 * kLocalSlices * (k0 + (int)blockIdx.y) + 1 + PHASE;
+        if (l0 > L_tau - 2) return;
+        int site[2 * kLocalSlices + 1];
+#pragma unroll
+        for (int i = 0; i <= 2 * kLocalSlices; ++i)
+            site[i] = col[(int64_t)min(l0 - 1 + i, L_tau - 1) * np + p];
+#pragma unroll
+        for (int i = 0; i < kLocalSlices; ++i)
+            if (l0 + 2 * i <= L_tau - 2)
+                move(l0 + 2 * i, p, site[2 * i], site[2 * i + 2], site[2 * i + 1]);
+    } else {
+        const bool two = L_tau == 2;  // slice 1 of q, next to slice 0, is then another thread's
+        if (PHASE == 3 && !two) return;
+        const int q = perm[c.part_off + p];
+        const int64_t last = (int64_t)(L_tau - 1) * np;
+        int first = col[q];
+        const int end = col[last + p];
+        if (PHASE == 2) first = move(0, q, end, col[np + q], first);
+        if (PHASE == 3 || !two) move(L_tau - 1, p, col[last - np + p], first, end);
     }
-    const int taken = local_move(c, g, ax, l, cur, prev, next, coef, p, sweep, ps);
-    if (taken != cur) col[(int64_t)l * np + p] = taken;
 }
 
-// Pair swaps of the reconnections at tau = beta (Sec. 3.5.6), one thread per worldline; the
-// first worldline p of each candidate pair of pass ps, (p0 + o + 2i, p0 + o + 2i + 1) within its
-// spin, o = ps mod 2, trades perm[p] and perm[q = p + 1] iff u < R,
-//   R = G(r^{P(q)}_0 - r^p_{L-1}) G(r^{P(p)}_0 - r^q_{L-1}) / [G(r^{P(p)}_0 - r^p_{L-1}) G(r^{P(q)}_0 - r^q_{L-1})]
-// (only the two boundary hops change), u from Philox (p, 0, sweep, kTagPerm + 256 ps). An accepted
-// swap flips the chain's sign (+1 <-> -1 by one atomic xor). The pairs of a pass are disjoint.
-__global__ __launch_bounds__(kThreads) void k_perm_update(
-    const ChainInfo* __restrict__ chains, int n_chains, int64_t particles,
-    const double* __restrict__ tables, const int32_t* __restrict__ paths, int32_t* perm,
-    int32_t* perm_inv, int32_t* sign, const uint64_t* __restrict__ sweep_ptr, int ps,
-    int32_t* status) {
-    const int64_t gp = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (gp >= particles) return;
-    const int ci = find_chain(n_chains, gp, [&](int i) { return chains[i].part_off; });
-    const ChainInfo& c = chains[ci];
-    const int p = (int)(gp - c.part_off);
-    const int p0 = p < c.n_up ? 0 : c.n_up, n = p < c.n_up ? c.n_up : c.n_dn;
-    const int k = p - p0 - (ps & 1);
-    if (k < 0 || (k & 1) || p + 1 >= p0 + n) return;
+// One candidate pair (p, p + 1) of k_perm_update: trades perm[p] and perm[p + 1] and returns true
+// iff the swap is accepted.
+__device__ inline bool perm_swap(const ChainInfo& c, int ci, int p, int ps,
+                                 const double* __restrict__ g, const int32_t* __restrict__ paths,
+                                 int32_t* perm, int32_t* perm_inv, uint64_t sweep,
+                                 int32_t* status) {
     const int q = p + 1, L = c.L, N = c.N;
-    const double* g = tables + tab_g(c);
     auto G = [&](int a, int b) {
         int dx = a % L - b % L;
         dx += dx < 0 ? L : 0;
@@ -2139,17 +2146,51 @@ __global__ __launch_bounds__(kThreads) void k_perm_update(
     const int lp = col[last + p], lq = col[last + q], fp = col[Pp], fq = col[Pq];
     if (lp < 0 || lp >= N || lq < 0 || lq >= N || fp < 0 || fp >= N || fq < 0 || fq >= N) {
         set_status(status, FH_ERR_BAD_PATH, ci);
-        return;
+        return false;
     }
     const double R = (G(fq, lp) * G(fp, lq)) / (G(fp, lp) * G(fq, lq));
-    const u64x4 w = philox4x64_10((uint64_t)p, 0, *sweep_ptr, kTagPerm + 256ull * (uint64_t)ps,
+    const u64x4 w = philox4x64_10((uint64_t)p, 0, sweep, kTagPerm + 256ull * (uint64_t)ps,
                                   c.seed, 0);
-    if (u01_from(w.x0) < R) {
-        perm[c.part_off + p] = Pq;
-        perm[c.part_off + q] = Pp;
-        perm_inv[c.part_off + Pq] = p;
-        perm_inv[c.part_off + Pp] = q;
-        atomicXor(&sign[ci], (int32_t)0xFFFFFFFE);
+    if (!(u01_from(w.x0) < R)) return false;
+    perm[c.part_off + p] = Pq;
+    perm[c.part_off + q] = Pp;
+    perm_inv[c.part_off + Pq] = p;
+    perm_inv[c.part_off + Pp] = q;
+    return true;
+}
+
+// Pair swaps of the reconnections at tau = beta (Sec. 3.5.6), one thread per worldline; the
+// first worldline p of each candidate pair of pass ps, (p0 + o + 2i, p0 + o + 2i + 1) within its
+// spin, o = ps mod 2, trades perm[p] and perm[q = p + 1] iff u < R,
+//   R = G(r^{P(q)}_0 - r^p_{L-1}) G(r^{P(p)}_0 - r^q_{L-1}) / [G(r^{P(p)}_0 - r^p_{L-1}) G(r^{P(q)}_0 - r^q_{L-1})]
+// (only the two boundary hops change), u from Philox (p, 0, sweep, kTagPerm + 256 ps). An accepted
+// swap flips the chain's sign (+1 <-> -1); a wavefront counts its swaps per chain and flips an odd
+// count by one atomic xor (an atomic per swap queued thousands on the few words of a batch's
+// signs: 16 chains of 512 + 512 worldlines on one site each, 96 us a pass against 4.5 us).
+// The pairs of a pass are disjoint.
+__global__ __launch_bounds__(kThreads) void k_perm_update(
+    const ChainInfo* __restrict__ chains, int n_chains, int64_t particles,
+    const double* __restrict__ tables, const int32_t* __restrict__ paths, int32_t* perm,
+    int32_t* perm_inv, int32_t* sign, const uint64_t* __restrict__ sweep_ptr, int ps,
+    int32_t* status) {
+    const int64_t gp = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const bool valid = gp < particles;
+    const int ci = find_chain(n_chains, valid ? gp : 0, [&](int i) { return chains[i].part_off; });
+    const ChainInfo& c = chains[ci];
+    const int p = valid ? (int)(gp - c.part_off) : 0;
+    const int p0 = p < c.n_up ? 0 : c.n_up, n = p < c.n_up ? c.n_up : c.n_dn;
+    const int k = p - p0 - (ps & 1);
+    const bool pair = valid && k >= 0 && !(k & 1) && p + 1 < p0 + n;
+    const bool took = pair && perm_swap(c, ci, p, ps, tables + tab_g(c), paths, perm, perm_inv,
+                                        *sweep_ptr, status);
+    uint64_t left = __ballot(took);
+    while (left) {  // the wavefront's accepted swaps, one chain at a time
+        const int lane0 = __ffsll((unsigned long long)left) - 1;
+        const int c0 = __builtin_amdgcn_readlane(ci, lane0);
+        const uint64_t of = __ballot(took && ci == c0);
+        left &= ~of;
+        if ((int)(threadIdx.x & 63) == lane0 && (__popcll(of) & 1))
+            atomicXor(&sign[c0], (int32_t)0xFFFFFFFE);
     }
 }
 
@@ -2899,28 +2940,26 @@ template <typename T>
 hipError_t launch_local_t(fh_plan p, const T* aux, int32_t* paths, int n_passes, hipStream_t s) {
     const unsigned blocks = (unsigned)((p->particles + kThreads - 1) / kThreads);
     int max_tau = 2;
-    for (const ChainInfo& c : p->chains) max_tau = std::max(max_tau, c.L_tau);
-    const int pairs = std::max(1, (max_tau - 1) / 2);  // slice pairs of the interior phases
+    bool two_slices = false;
+    for (const ChainInfo& c : p->chains) {
+        max_tau = std::max(max_tau, c.L_tau);
+        two_slices = two_slices || c.L_tau == 2;
+    }
+    // slice groups of the interior phases
+    const int pairs = std::max(1, ((max_tau - 1) / 2 + kLocalSlices - 1) / kLocalSlices);
     constexpr int kMaxGridY = 65535;
     for (int ps = 0; ps < n_passes; ++ps) {
-        for (int ph = 0; ph < 2; ++ph)
-            for (int k0 = 0; k0 < pairs; k0 += kMaxGridY) {
-                const dim3 grid(blocks, (unsigned)std::min(kMaxGridY, pairs - k0));
-                if (ph == 0)
-                    hipLaunchKernelGGL((k_local<T, 0>), grid, dim3(kThreads), 0, s, p->d.chains,
-                                       p->n_chains, p->particles, p->d.tables, aux, paths,
-                                       p->d.perm, p->d.perm_inv, p->d.sweep, ps, k0, p->d.status);
-                else
-                    hipLaunchKernelGGL((k_local<T, 1>), grid, dim3(kThreads), 0, s, p->d.chains,
-                                       p->n_chains, p->particles, p->d.tables, aux, paths,
-                                       p->d.perm, p->d.perm_inv, p->d.sweep, ps, k0, p->d.status);
-            }
-        hipLaunchKernelGGL((k_local<T, 2>), dim3(blocks), dim3(kThreads), 0, s, p->d.chains,
-                           p->n_chains, p->particles, p->d.tables, aux, paths, p->d.perm,
-                           p->d.perm_inv, p->d.sweep, ps, 0, p->d.status);
-        hipLaunchKernelGGL((k_local<T, 3>), dim3(blocks), dim3(kThreads), 0, s, p->d.chains,
-                           p->n_chains, p->particles, p->d.tables, aux, paths, p->d.perm,
-                           p->d.perm_inv, p->d.sweep, ps, 0, p->d.status);
+        auto run = [&](auto kern, dim3 grid, int k0) {
+            hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, p->d.chains, p->n_chains,
+                               p->particles, p->d.tables, aux, paths, p->d.perm, p->d.sweep, ps,
+                               k0, p->d.status);
+        };
+        for (int k0 = 0; k0 < pairs; k0 += kMaxGridY)
+            run(k_local<T, 0>, dim3(blocks, (unsigned)std::min(kMaxGridY, pairs - k0)), k0);
+        for (int k0 = 0; k0 < pairs; k0 += kMaxGridY)
+            run(k_local<T, 1>, dim3(blocks, (unsigned)std::min(kMaxGridY, pairs - k0)), k0);
+        run(k_local<T, 2>, dim3(blocks), 0);
+        if (two_slices) run(k_local<T, 3>, dim3(blocks), 0);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
