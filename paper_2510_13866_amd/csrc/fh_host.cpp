@@ -203,7 +203,7 @@ hipError_t dalloc(T** p, size_t bytes) {
 
 void free_device(fh::Device& d) {
     void* ptrs[] = {d.chains, d.tables, d.cmat, d.cmat64, d.fwdd_tasks, d.W, d.wshift, d.filt, d.blk_logz, d.dt, d.fwd_tasks,
-                    d.draw_tasks, d.group_tasks, d.gpart, d.ckpt, d.rep, d.blk_la, d.endrow, d.dedup_tasks, d.lists, d.fwddc_tasks, d.fwd32_tasks, d.fwd32c_tasks, d.fwdxc_tasks, d.fwdpc_tasks, d.prep, d.fwdx_tasks, d.fwdp_tasks, d.cmatp, d.cmatb, d.fwd64_tasks, d.draw32_tasks, d.draww_tasks, d.drawx_tasks, d.meas, d.mala, d.perm, d.perm_inv, d.sign, d.bw_state,
+                    d.draw_tasks, d.group_tasks, d.gpart, d.ckpt, d.rep, d.blk_la, d.endrow, d.dedup_tasks, d.lists, d.staged, d.members, d.stage_tasks, d.stage_tasks_a, d.fwddc_tasks, d.fwd32_tasks, d.fwd32c_tasks, d.fwdxc_tasks, d.fwdpc_tasks, d.prep, d.fwdx_tasks, d.fwdp_tasks, d.cmatp, d.cmatb, d.fwd64_tasks, d.draw32_tasks, d.draww_tasks, d.drawx_tasks, d.meas, d.mala, d.perm, d.perm_inv, d.sign, d.bw_state,
                     d.rescue, d.rescue_list, d.rep_slot, d.arep, d.rescue_ws, d.rescue_w, d.status, d.sweep};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -279,7 +279,7 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
     p->real_size = precision == FH_FP64 ? 8 : 4;
     p->descs.assign(descs, descs + n_chains);
 
-    int64_t aux = 0, path = 0, part = 0, tab = 0, filt = 0, blk = 0, slices = 0;
+    int64_t aux = 0, path = 0, part = 0, tab = 0, filt = 0, blk = 0, slices = 0, sb = 0;
     for (int c = 0; c < n_chains; ++c) {
         const fh_chain_desc& d = descs[c];
         ChainInfo ci;
@@ -308,6 +308,8 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
         ci.filt_off = filt;
         ci.blk_off = blk;
         ci.slice_off = slices;
+        ci.sb_off = sb;
+        sb += 2 * ci.nb;
         ci.site_off = p->total_sites;
         p->total_sites += ci.N;
         slices += d.L_tau;
@@ -435,9 +437,26 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
             ci.end_off = p->end_elems;
             p->end_elems += (int64_t)ci.np * ci.nb * ci.N;
         }
-        for (int spin = 0; spin < 2; ++spin)
-            if ((spin ? ci.n_dn : ci.n_up) > 0)
-                for (int b = 0; b < ci.nb; ++b) dedup.push_back({c, spin, b, 0});
+    }
+    // heaviest chains first, so that the tasks k_dedup lists start in that order; the most tasks
+    // of k_backward_stage are one per kStageMembers worldlines and one per group of start sites
+    for (int c : order) {
+        const ChainInfo& ci = p->chains[c];
+        if (!ci.dedup) continue;
+        for (int spin = 0; spin < 2; ++spin) {
+            const int n = spin ? ci.n_dn : ci.n_up;
+            if (n == 0) continue;
+            auto most = [&](int64_t value_size) {
+                const int64_t R = std::min<int64_t>(kStageMembers,
+                                                    kStageBytes / (ci.N * value_size));
+                return R < 1 ? 0 : n / kStageMembers + (std::min(n, ci.N) + R - 1) / R;
+            };
+            if (ci.win_on && ci.L >= kStageMinL && ci.N % 4 == 0) {
+                if (ci.dedup == 1) p->n_stage_tasks += (int32_t)(ci.nb * most(p->real_size));
+                if (precision != FH_FP64) p->n_stage_tasks_a += (int32_t)(ci.nb * most(8));
+            }
+            for (int b = 0; b < ci.nb; ++b) dedup.push_back({c, spin, b, 0});
+        }
     }
     p->n_dedup_tasks = (int32_t)dedup.size();
     std::vector<DrawTask> fwdd;
@@ -520,7 +539,8 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
         p->rescuable_blocks = rescuable;
         const int64_t waves = std::min<int64_t>(kRescueMaxSlots, std::max<int64_t>(rescuable, 1));
         p->n_rescue_slots = (int32_t)((waves + 3) / 4 * 4);
-        p->rescue_slot_elems = std::max<int64_t>(p->rescue_slot_elems, 1);
+        // whole 16-byte units: k_backward_stage copies the rows by them
+        p->rescue_slot_elems = (std::max<int64_t>(p->rescue_slot_elems, 1) + 1) & ~(int64_t)1;
     }
 
     hipError_t e = hipSuccess;
@@ -539,6 +559,13 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
         if (e == hipSuccess) e = dalloc(&dv.blk_la, sizeof(double) * (size_t)blk);
         if (e == hipSuccess && p->end_elems > 0)
             e = dalloc(&dv.endrow, sizeof(float) * (size_t)p->end_elems);
+        if (e == hipSuccess) e = dalloc(&dv.staged, sizeof(int32_t) * (size_t)sb);
+        if (e == hipSuccess) e = hipMemset(dv.staged, 0, sizeof(int32_t) * (size_t)sb);
+        if (e == hipSuccess) e = dalloc(&dv.members, sizeof(int32_t) * (size_t)blk);
+        if (e == hipSuccess)
+            e = dalloc(&dv.stage_tasks, sizeof(DrawTask) * (size_t)p->n_stage_tasks);
+        if (e == hipSuccess)
+            e = dalloc(&dv.stage_tasks_a, sizeof(DrawTask) * (size_t)p->n_stage_tasks_a);
         if (e == hipSuccess) e = dalloc(&dv.dedup_tasks, sizeof(DrawTask) * dedup.size());
         if (e == hipSuccess)
             e = hipMemcpy(dv.dedup_tasks, dedup.data(), sizeof(DrawTask) * dedup.size(),

@@ -29,6 +29,7 @@ struct ChainInfo {
     int64_t filt_off;  // filter workspace: filt[filt_off + (p*L_tau + row)*N + r]
     int64_t blk_off;   // per-(particle, block) log Z: blk[blk_off + p*nb + block]
     int64_t slice_off; // index of this chain's slice 0 among all chains' slices
+    int64_t sb_off;    // per-(spin, block) flags: [sb_off + spin nb + block]
     int64_t site_off;  // per-site outputs (S(k), C(r)) packed by chain: [site_off + r]
     int32_t g0, g1;    // gradient worldline groups of this chain: [g0, g1)
     int32_t win_w;     // windowed backward draws: half-width w of the window around s
@@ -68,9 +69,19 @@ FH_HD inline int64_t tab_g(const ChainInfo& c) { return c.tab_off + 2 * c.N; }
 FH_HD inline int64_t tab_tw(const ChainInfo& c) { return c.tab_off + 2 * c.N + c.L; }
 inline int64_t tab_size(int L) { return 2 * (int64_t)L * L + L + 2 * L; }
 constexpr int kBwCounts = 4;  // offset of the per-chain counts in Device::bw_state
-// Counts of the dense lists k_dedup fills on FP64 plans: representatives with L <= 32, L = 64 and
+// k_backward_stage: worldlines per workgroup, bytes of rows per slice in LDS (two slices are held),
+// workgroups per launch, and the row bytes per worldline up to which k_dedup stages a (chain,
+// spin, block).
+constexpr int kStageMembers = 64;
+constexpr int kStageBytes = 32768;
+constexpr int kStageGrid = 1024;
+constexpr int kStageCost = 2048;
+constexpr int kStageMinL = 8;
+// Counts of the dense lists k_dedup fills. On FP64 plans: representatives with L <= 32, L = 64 and
 // L = 48.
 constexpr int kListFwd = 0, kListFwd64 = 1, kListFwd48 = 2;
+// Tasks of k_backward_stage, and of its phase A launch (the held chains).
+constexpr int kListStage = 3, kListStageA = 4;
 constexpr int kListWords = 16;
 constexpr int kCmatPerChain = 3 * 2 * 64 * 8;
 constexpr int kCmat64PerChain = 16 * 64;
@@ -203,6 +214,7 @@ struct Rescue {
     DrawTask* list;
     int32_t n_chains;
     const int32_t* rep;
+    const int32_t* staged;  // per (chain, spin, block): 1 if k_backward_stage draws it; nullable
 };
 // The worldline whose stored rows block `block` of worldline p reads.
 __device__ inline int row_owner(const Rescue& r, const ChainInfo& c, int p, int block) {
@@ -265,6 +277,11 @@ struct Device {
     float* endrow = nullptr;
     DrawTask* dedup_tasks = nullptr;
     int32_t* lists = nullptr;  // counts of the pass's dense lists (kList*), zeroed by k_potentials
+    // staged backward draws (k_backward_stage): flags, sorted worldlines, tasks of the pass
+    int32_t* staged = nullptr;
+    int32_t* members = nullptr;
+    DrawTask* stage_tasks = nullptr;
+    DrawTask* stage_tasks_a = nullptr;
     DrawTask* fwddc_tasks = nullptr;  // FP64 plans: the representatives k_dedup lists, as fwdd_tasks
     double* dt = nullptr;     // per particle d log Z / d t
     PairTask* fwd_tasks = nullptr;
@@ -345,6 +362,7 @@ struct fh_plan_s {
     int64_t ckpt_elems = 0;     // FH_FLAG_GRAD_CHECKPOINT: checkpoint + segment rows (elements)
     int32_t n_rescue_slots = 0;     // FP32 plans: wavefronts of k_rescue
     int64_t rescuable_blocks = 0;   // FP32 plans: blocks of the chains the FP64 re-filter takes
+    int32_t n_stage_tasks = 0, n_stage_tasks_a = 0;  // most tasks of k_backward_stage in a pass
     int32_t n_dedup_tasks = 0;      // (chain, spin, block) tasks of k_dedup (chains with dedup)
     bool share_off = false;         // fh_debug_share_filters(plan, 0): every worldline its own rows
     int64_t end_elems = 0;          // end tiles of the chains with dedup (f32 elements)
@@ -386,6 +404,7 @@ inline Rescue rescue_args(fh_plan p) {
     r.flags = p->d.rescue ? p->d.rescue + kRescueChain + kRescuePerChain * p->n_chains : nullptr;
     r.list = p->d.rescue_list;
     r.rep = p->d.rep;
+    r.staged = p->share_off ? nullptr : p->d.staged;
     r.n_chains = p->n_chains;
     return r;
 }

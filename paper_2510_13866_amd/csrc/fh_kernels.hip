@@ -390,6 +390,11 @@ __global__ void k_logz_reduce(const ChainInfo* __restrict__ chains, int n_chains
     logZ[gp] = s;
 }
 
+// The (chain, spin, block) is drawn by k_backward_stage in this pass (k_dedup's decision).
+__device__ inline bool staged(const Rescue& r, const ChainInfo& c, int p, int block) {
+    return r.staged && r.staged[c.sb_off + (p >= c.n_up ? c.nb : 0) + block] != 0;
+}
+
 // A windowed chain's backward tasks sit in the windowed kernel's list and in a full-row
 // kernel's list; the windowed kernel draws them unless k_bw_adapt has moved the plan to the
 // full-row kernels for this pass (bw_state[0] > 0).
@@ -413,6 +418,7 @@ __global__ __launch_bounds__(kThreads) void k_backward(
     if (on_window(chains, tasks[task].chain, bw_state)) return;  // k_backward_win draws it
     const DrawTask t = tasks[task];
     const ChainInfo& c = chains[t.chain];
+    if (staged(rsc, c, t.p, t.block)) return;
     if (rescue_queued(rsc, c, t.p, t.block)) return;  // k_rescue redraws it in FP64
     const uint64_t sweep = *sweep_ptr;
     int start, len;
@@ -721,7 +727,8 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 4 ? 4 : 3) void k_backward_l
     if (active) {
         t = tasks[task];
         g2sh[wv][lane] = tables[tab_g(chains[t.chain]) + (lane & 31)];
-        active = !rescue_queued(rsc, chains[t.chain], t.p, t.block);  // k_rescue draws it
+        active = !staged(rsc, chains[t.chain], t.p, t.block) &&
+                 !rescue_queued(rsc, chains[t.chain], t.p, t.block);  // k_rescue draws it
     }
     __syncthreads();  // the only barrier; every wave reaches it
     if (!active) return;
@@ -1060,7 +1067,8 @@ __global__ __launch_bounds__(kThreads) void k_backward_win(
     const ChainInfo& c = chains[t.chain];
     // a block queued for the FP64 re-filter is drawn by k_rescue (SLOT: by this kernel when its
     // chain is windowed)
-    const bool active = SLOT ? listed && c.win_on : listed && !rescue_queued(rsc, c, t.p, t.block);
+    const bool active = listed && (SLOT ? c.win_on != 0 : !rescue_queued(rsc, c, t.p, t.block)) &&
+                        !staged(rsc, c, t.p, t.block);
     // an inactive group draws nothing; on a one-site lattice its table fill and loads stay minimal
     const int L = active ? c.L : 1, N = active ? c.N : 1, L_tau = c.L_tau, w = c.win_w;
     double* g = gsh[grp] + kWinMaxL;  // g[d] = g(d mod L) for -L < d < L
@@ -1281,6 +1289,476 @@ __global__ __launch_bounds__(kThreads) void k_backward_win(
             if (!(hv > 0.0)) set_status(status, FH_ERR_NONFINITE, t.chain);
             sr.blk_logz[c.blk_off + (int64_t)t.p * c.nb + t.block] = sr.blk_la[ri] + log(hv);
         }
+    }
+}
+
+// Backward sampling of worldlines that share rows, staged through LDS. Most worldlines of a
+// settled chain read the same rows (shared forward filters), and which rows a draw chain needs is
+// known before its sites are: only the window's place in the row depends on the previous draw. So
+// one workgroup takes up to kStageMembers worldlines of one (chain, spin, block), sorted by
+// representative (k_dedup), and walks the slices together: four producer wavefronts bring the
+// next slices' whole rows into LDS, the worldlines' uniforms too, and store the drawn sites; four
+// consumer wavefronts draw, four lanes per worldline, and never wait for global memory. One
+// barrier per slice.
+//
+// Per draw, lane li of a worldline holds the window rows 2 li and 2 li + 1 of the (at most 7 x 7)
+// first window in site order: the prefix sums of max(f, 0) g(dx) along each row, times g(dy), scanned
+// over the four lanes. Of the lane's two rows only the one that holds tau = u T is searched: with
+// bound B, n1 and n2 its cumulative sums at or below tau - B and tau + B; the draw is certified
+// (fh_window.h) by the one lane whose row starts at or below tau - B and has n1 = n2 sums left of
+// a sum above tau + B. Uncertified draws take the wider window, then the row, as in
+// k_backward_win, by the whole wavefront; worldlines of the wavefront at the same site of the
+// same row share the sums. The draws are the full-row rule's either way.
+//
+// Bound: a slice's chain of LDS reads, FP64 sums and cross-lane steps, 0.9 us a draw plus about
+// 2 us where a workgroup falls back to the row; k_backward_win spends 16 lanes a worldline and
+// waits for L2 each draw (2.5 us). Launch times, settled chains, windowed kernel against this:
+// 16 x 32 x 32, L_tau = 160: 500 -> 168 us; 8 of them in FP64: 325 -> 176 us; 4 x 32 x 32,
+// L_tau = 1024, blocks of 64: 458 -> 178 us; 64 x 16 x 16 Ising (20 start sites a spin): 130 -> 90
+// us; the uneven batch of 256 chains: 1130 -> 725 us; held 64 x 64 chains' FP64 rows: 977 -> 431
+// us.
+//
+// Uniforms: producer lane (worldline, t) runs the ten Philox rounds of draw 4 c + t spread over
+// the four slices before chunk c. SLOT: phase A of the FP64 re-filter, rows in the representatives'
+// slots (see k_backward_win).
+constexpr int kStageThreads = 512;
+constexpr int kStageLoads = (int)(kStageBytes / (16 * kThreads));  // 16-B loads per producer lane
+template <int CTRL>
+__device__ inline double quad_f64(double v) {  // quad_perm lane exchange
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+
+// The fallback draws of k_backward_stage, whose row is in LDS: the whole wavefront forms the sums
+// of one (row, site) and leaves the lanes' inclusive sums and own sums in sum_sh[0 .. 63] and
+// [64 .. 127]; then every worldline (four lanes, its own u) searches them, four ways split, side
+// by side. Lanes of other worldlines search along and drop the result.
+__device__ inline int quad_min(int v) {
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true));
+    return min(v, __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true));
+}
+__device__ inline int quad_sum(int v) {
+    v += __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
+    return v + __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);
+}
+__device__ inline void stage_sums(double own, double incl, int lane, double* sum_sh) {
+    __builtin_amdgcn_wave_barrier();  // the last search's reads precede these writes
+    sum_sh[lane] = incl;
+    sum_sh[64 + lane] = own;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// The 15 x 15 window around (cx, cy): lane k holds the ranks 4k .. 4k + 3 in site order. Returns
+// (1 << 16 | y << 8 | x) for a certified draw, else 0: with B the bound, n1 and n2 of the lanes'
+// inclusive sums lie at or below tau - B and tau + B; certified if n1 = n2 and within lane n1 the
+// same holds of its four cumulative sums.
+template <typename T>
+__device__ __forceinline__ int stage_window(const T* row, int L, int cx, int cy, const double* g,
+                                            double u, double bound, int lane, double* sum_sh) {
+    const int WW = win_width(kWin2W, L), nwin = WW * WW;
+    const float rw = 1.0f / (float)WW;  // (q + 1/2) / WW in FP32 floors exactly for q < 2^12
+    int tx, bx, ty, by;
+    win_axis(cx, kWin2W, L, WW, &tx, &bx);
+    win_axis(cy, kWin2W, L, WW, &ty, &by);
+    auto weight = [&](int q, int* xy) {  // of rank q, 0 past the window
+        const int qq = q < nwin ? q : 0;
+        const int qy = (int)(((float)qq + 0.5f) * rw);
+        const int x = win_at(qq - qy * WW, tx, bx), y = win_at(qy, ty, by);
+        *xy = (y << 8) | x;
+        const T f = row[y * L + x];
+        return q < nwin && f > T(0) ? (double)f * (g[cy - y] * g[cx - x]) : 0.0;
+    };
+    double own = 0.0;
+    int xy;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) own += weight(4 * lane + k, &xy);
+    double total;
+    const double incl = wave_incl_scan_f64(own, lane, &total);
+    stage_sums(own, incl, lane, sum_sh);
+    const double B = bound + kWinSlack * total, tau = u * total;
+    const double lo = tau - B, hi = tau + B;
+    int n1 = 0, n2 = 0;
+    const int l0 = 16 * (lane & 3);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const double v = sum_sh[l0 + i];
+        n1 += v <= lo ? 1 : 0;
+        n2 += v <= hi ? 1 : 0;
+    }
+    n1 = quad_sum(n1);
+    n2 = quad_sum(n2);
+    const int src = min(n1, 63);
+    double run = sum_sh[src] - sum_sh[64 + src];
+    bool ok = n1 == n2 && n1 < 64 && total > 0.0 && isfinite(total) && run <= lo;
+    int picked = -1;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        run += weight(4 * src + k, &xy);
+        if (picked < 0) {
+            if (run > hi)
+                picked = xy;
+            else if (!(run <= lo))
+                ok = false;
+        }
+    }
+    return ok && picked >= 0 ? (1 << 16) | picked : 0;
+}
+// The whole row, with k_backward's rule in wave_row_draw's arithmetic (lane k sums the ceil(N / 64)
+// sites from k ceil(N / 64) on): the drawn site, or *bad as wave_row_draw.
+template <typename T>
+__device__ __forceinline__ int stage_row(const T* row, int N, int L, int cur, const double* g,
+                                         double u, int lane, double* sum_sh, int* bad,
+                                         bool range) {
+    const int cy = cur / L, cx = cur - cy * L, per = (N + 63) >> 6;
+    auto walk = [&](int who, auto visit) {  // visit(site, weight) over the sites of lane `who`
+        const int i0 = who * per, i1 = min(i0 + per, N);
+        int x = i0 % L, y = i0 / L;
+        for (int i = i0; i < i1; ++i) {
+            const T f = row[i];
+            visit(i, f > T(0) ? (double)f * (g[cy - y] * g[cx - x]) : 0.0);
+            if (++x == L) {
+                x = 0;
+                ++y;
+            }
+        }
+    };
+    double own = 0.0, total;
+    int lastpos = -1;
+    walk(lane, [&](int i, double w) {
+        own += w;
+        if (w > 0.0) lastpos = i;
+    });
+    const double incl = wave_incl_scan_f64(own, lane, &total);
+    if (!(total > 0.0) || !isfinite(total)) {  // uniform
+        *bad = range ? kBadRange : isfinite(total) ? FH_ERR_ZERO_WEIGHT : FH_ERR_NONFINITE;
+        return cur;
+    }
+    stage_sums(own, incl, lane, sum_sh);
+    const double Tq = u * total;
+    // the first lane with a positive sum whose inclusive sum exceeds Tq
+    int src = 64;
+    const int l0 = 16 * (lane & 3);
+#pragma unroll
+    for (int i = 15; i >= 0; --i)
+        if (sum_sh[l0 + i] > Tq && sum_sh[64 + l0 + i] > 0.0) src = l0 + i;
+    src = quad_min(src);
+    // without one, the row's last site with a positive weight
+    const uint64_t lm = __ballot(lastpos >= 0);
+    int chosen = lm ? __builtin_amdgcn_readlane(lastpos, 63 - __clzll((long long)lm)) : cur;
+    const int lane_last = __shfl(lastpos, src & 63, 64);
+    if (src < 64) {
+        double run = sum_sh[src] - sum_sh[64 + src];
+        int pick = -1, last_in = -1;
+        walk(src, [&](int i, double w) {
+            run += w;
+            if (pick < 0) {
+                if (w > 0.0) last_in = i;
+                if (run > Tq) pick = i;
+            }
+        });
+        chosen = pick >= 0 ? pick : last_in >= 0 ? last_in : lane_last;
+    }
+    if (range && !((double)row[chosen] >= kRangeFloorD)) *bad = kBadRange;
+    return chosen;
+}
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <typename T, bool SLOT>
+__global__ __launch_bounds__(kStageThreads, 4) void k_backward_stage(
+    const ChainInfo* __restrict__ chains, const DrawTask* __restrict__ tasks,
+    const int32_t* __restrict__ lists, const int32_t* __restrict__ members,
+    const double* __restrict__ tables, const T* __restrict__ filt, int32_t* __restrict__ paths,
+    const int32_t* __restrict__ perm, const uint64_t* __restrict__ sweep_ptr, int32_t* status,
+    int32_t* __restrict__ bw_state, int count_uncertified, const Rescue rsc, const SlotRows sr) {
+    static_assert(!SLOT || sizeof(T) == 8, "phase A's rows are FP64");
+    constexpr int K = 2 * kWinMaxW + 1;
+    __shared__ u32x4 rowbuf[2][kStageBytes / 16];
+    __shared__ double gsh[2 * kWinMaxL];
+    __shared__ double ubuf[2][4 * kStageMembers];
+    __shared__ int32_t sites[2][kStageMembers];
+    __shared__ int32_t src_sh[kStageMembers];  // per slot: its row of j = 1, in 16-B units from src
+    __shared__ double sum_sh[4][128];  // per consumer wavefront: the fallbacks' lane sums
+    __shared__ int32_t mem_sh[kStageMembers], slot_sh[kStageMembers], act_sh[kStageMembers];
+    __shared__ int32_t nslot_sh;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint64_t sweep = *sweep_ptr;
+    const int n_tasks = __builtin_amdgcn_readfirstlane(lists[SLOT ? kListStageA : kListStage]);
+    for (int ti = blockIdx.x; ti < n_tasks; ti += gridDim.x) {
+        const DrawTask t = tasks[ti];  // p: first member, pad: member count
+        const ChainInfo& c = chains[t.chain];
+        // phase A: only chains admitted to it (the others wait for phase 2)
+        const bool live = !SLOT || rsc.words[kRescueChain + 2 * rsc.n_chains + t.chain] != 0;
+        int start, len;
+        block_of(c, sweep, t.block, &start, &len);
+        const int nd = len - 1;  // draw s sets slice start + (nd - s), s = 0 .. nd - 1
+        const int L = c.L, N = c.N, L_tau = c.L_tau, np = c.np;
+        int32_t* pc = paths + c.path_off;
+        const T* src = SLOT ? (const T*)sr.ws : filt + c.filt_off;
+        // members, their representatives' slots (members are sorted by representative)
+        if (wv == 0) {
+            const int p = lane < t.pad ? members[t.p + lane] : 0;
+            const int64_t bi = c.blk_off + (int64_t)p * c.nb + t.block;
+            const int ro = lane < t.pad ? rsc.rep[bi] : -1;
+            const int before = __shfl_up(ro, 1, 64);
+            const bool fresh = lane < t.pad && (lane == 0 || ro != before);
+            const uint64_t fm = __ballot(fresh);
+            const int slot = lane < t.pad ? __popcll(fm & ((2ull << lane) - 1)) - 1 : 0;
+            if (fresh) {
+                const int64_t ri = c.blk_off + (int64_t)ro * c.nb + t.block;
+                const int64_t row1 = SLOT ? (live ? (int64_t)sr.rep_slot[ri] * sr.slot_elems : 0)
+                                          : ((int64_t)ro * L_tau + (int64_t)t.block * (c.B - 1)) * N;
+                src_sh[slot] = (int32_t)(row1 / (16 / (int)sizeof(T)));
+            }
+            mem_sh[lane] = p;
+            slot_sh[lane] = slot;
+            act_sh[lane] = live && lane < t.pad && (SLOT || !rescue_queued(rsc, c, p, t.block));
+            if (lane == 0) nslot_sh = __popcll(fm);
+        }
+        for (int d = tid; d < L; d += kStageThreads) {
+            const double gd = tables[tab_g(c) + d];
+            gsh[kWinMaxL + d] = gd;
+            if (d > 0) gsh[kWinMaxL + d - L] = gd;
+        }
+        __syncthreads();
+        const bool any = __ballot(act_sh[lane] != 0) != 0 && nd >= 1;  // uniform over the workgroup
+        if (any && wv >= 4) {  // ---- producers
+            const int pt = tid - 256, pw = wv - 4;
+            const int upr = N * (int)sizeof(T) / 16;  // 16-B units per row
+            const int units = nslot_sh * upr;
+            const int nl = __builtin_amdgcn_readfirstlane((units + 255) / 256);
+            uint32_t base[kStageLoads];  // past the last unit: the first one again
+#pragma unroll
+            for (int i = 0; i < kStageLoads; ++i) {
+                const int u = pt + 256 * i < units ? pt + 256 * i : 0;
+                base[i] = (uint32_t)src_sh[u / upr] + (uint32_t)(u % upr);
+            }
+            u32x4 ra[kStageLoads];
+            auto fetch = [&](int s, u32x4 (&r)[kStageLoads]) __attribute__((always_inline)) {  // the rows of draw s (row nd - s)
+                const u32x4* o = (const u32x4*)src + (int64_t)max(nd - s - 1, 0) * upr;
+#pragma unroll
+                for (int i = 0; i < kStageLoads; ++i)
+                    if (i < nl) r[i] = o[base[i]];
+            };
+            auto put = [&](int b, const u32x4 (&r)[kStageLoads]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < kStageLoads; ++i)
+                    if (pt + 256 * i < units) rowbuf[b][pt + 256 * i] = r[i];
+            };
+            // uniforms: this lane's worldline and draw of a chunk of four
+            const int um = pw * 16 + (lane >> 2), up = mem_sh[um];
+            u64x4 px;
+            uint64_t k0, k1;
+            auto u_init = [&](int chunk) __attribute__((always_inline)) {
+                const int j = max(nd - (4 * chunk + (lane & 3)), 0);
+                int l = start + j;
+                l -= l >= L_tau ? L_tau : 0;
+                px = {(uint64_t)up, (uint64_t)l, sweep, kTagPath};
+                k0 = c.seed;
+                k1 = 0;
+            };
+            auto u_put = [&](int chunk) __attribute__((always_inline)) { ubuf[chunk & 1][pw * 64 + lane] = u01_from(px.x0); };
+            // sites of draw s: one producer wavefront, lane = worldline
+            const int sp = mem_sh[lane], sq = perm[c.part_off + sp];
+            const bool sact = act_sh[lane] != 0;
+            auto store = [&](int s) __attribute__((always_inline)) {
+                const int jd = nd - s;
+                int l = start + jd;
+                const bool wrap = l >= L_tau;
+                l -= wrap ? L_tau : 0;
+                if (sact) pc[(int64_t)l * np + (wrap ? sq : sp)] = sites[s & 1][lane];
+            };
+            fetch(0, ra);
+            u_init(0);
+            philox_rounds<10>(px, k0, k1);
+            u_put(0);
+            put(0, ra);
+            fetch(1, ra);
+            __syncthreads();
+            // slice s: rows of s + 1 to LDS, those of s + 2 requested; a part of the next
+            // chunk's uniforms; the sites of s - 1 stored
+            auto slice = [&](int s, int phase) __attribute__((always_inline)) {
+                put((s + 1) & 1, ra);
+                fetch(s + 2, ra);
+                if (phase == 0) u_init((s >> 2) + 1);
+                if (phase < 3) {
+                    philox_rounds<3>(px, k0, k1);
+                } else {
+                    philox_rounds<1>(px, k0, k1);
+                    u_put((s >> 2) + 1);
+                }
+                if (s > 0 && pw == ((s - 1) & 3)) store(s - 1);
+                __syncthreads();
+            };
+            int s = 0;
+            for (; s + 4 <= nd; s += 4) {
+                slice(s, 0);
+                slice(s + 1, 1);
+                slice(s + 2, 2);
+                slice(s + 3, 3);
+            }
+            if (s < nd) slice(s, 0);
+            if (s + 1 < nd) slice(s + 1, 1);
+            if (s + 2 < nd) slice(s + 2, 2);
+            if (pw == ((nd - 1) & 3)) store(nd - 1);
+        } else if (any) {  // ---- consumers: four lanes per worldline
+            const int m = wv * 16 + (lane >> 2), li = lane & 3;
+            const int p = mem_sh[m], slot = slot_sh[m];
+            const bool act = act_sh[m] != 0;
+            const int qn = perm[c.part_off + p];
+            int cur = act ? checked_site(pc[(int64_t)((start + len) % L_tau) * np +
+                                            (start + len >= L_tau ? qn : p)], N, status, t.chain)
+                          : 0;
+            int cx = cur % L, cy = cur / L;
+            const double* g = gsh + kWinMaxL;
+            const double mass = SLOT ? 1.0 : c.row_mass;
+            // the window is 7 x 7 here, whatever the chain's win_w <= 3: the outside bound of a
+            // narrower window bounds it too
+            const double gout = c.win_gout * mass * kWinMassBound;
+            const double gout2 = c.win_gout2 * mass * kWinMassBound;
+            const bool range = !SLOT && rsc.words != nullptr;
+            const int q0 = 2 * li, q1 = min(2 * li + 1, K - 1);  // lane 3 holds one row
+            bool halt = false;  // the block left FP32's range: k_rescue redraws it
+            int err = 0, n_unc = 0;
+            __syncthreads();
+            for (int s = 0; s < nd; ++s) {
+                const T* row = (const T*)rowbuf[s & 1] + slot * N;
+                const double u = ubuf[(s >> 2) & 1][4 * m + (s & 3)];
+                int tx, bx, ty, by;
+                win_axis(cx, kWinMaxW, L, K, &tx, &bx);
+                win_axis(cy, kWinMaxW, L, K, &ty, &by);
+                const int y0 = win_at(q0, ty, by), y1 = win_at(q1, ty, by);
+                const T* R0 = row + y0 * L;
+                const T* R1 = row + y1 * L;
+                const double gy0 = g[cy - y0], gyb = g[cy - y1];
+                const double gy1 = li < 3 ? gyb : 0.0;
+                T f0[K], f1[K];
+                double gx[K];
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int x = win_at(k, tx, bx);
+                    f0[k] = R0[x];
+                    f1[k] = R1[x];
+                    gx[k] = g[cx - x];
+                }
+                double P0[K], P1[K];
+                double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    a0 += fmax((double)f0[k], 0.0) * gx[k];
+                    a1 += fmax((double)f1[k], 0.0) * gx[k];
+                    P0[k] = a0;
+                    P1[k] = a1;
+                }
+                const double S0 = a0 * gy0, S = S0 + a1 * gy1;
+                double incl = S;
+                const double t1 = quad_f64<0x90>(incl);  // lanes 0, 0, 1, 2
+                incl += li >= 1 ? t1 : 0.0;
+                const double t2 = quad_f64<0x40>(incl);  // lanes 0, 0, 0, 1
+                incl += li >= 2 ? t2 : 0.0;
+                const double te = quad_f64<0x90>(incl);
+                const double excl = li >= 1 ? te : 0.0;
+                const double T_in = quad_f64<0xFF>(incl);  // lane 3's, the window's total
+                const double tau = u * T_in;
+                const double B = gout + kWinSlack * T_in;
+                const double lo = tau - B, hi = tau + B;
+                const bool second = tau >= excl + S0;
+                const double c0 = second ? excl + S0 : excl, gyr = second ? gy1 : gy0;
+                int n1 = 0, n2 = 0;
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const double ck = c0 + (second ? P1[k] : P0[k]) * gyr;
+                    n1 += ck <= lo ? 1 : 0;
+                    n2 += ck <= hi ? 1 : 0;
+                }
+                const bool cert_l = c0 <= lo && n1 == n2 && n1 < K;
+                const int dxs = win_at(n1, tx, bx), dys = second ? y1 : y0;
+                int mine = cert_l ? (1 << 16) | (dys << 8) | dxs : 0;
+                mine |= __builtin_amdgcn_mov_dpp(mine, 0xB1, 0xF, 0xF, true);
+                mine |= __builtin_amdgcn_mov_dpp(mine, 0x4E, 0xF, 0xF, true);
+                const bool real = act && !halt;
+                const bool need = real && !(mine >> 16);
+                int nx = mine & 255, ny = (mine >> 8) & 255;
+                uint64_t todo = __ballot(li == 0 && need);
+                if (todo) {
+                    // the wider window, then the row, for one (row, site) of the wavefront at a
+                    // time: the sums by all 64 lanes, the picks of its worldlines side by side
+                    n_unc += need ? 1 : 0;
+                    int fl = lane;  // opaque, so that nothing of this branch is hoisted from it
+                    asm volatile("" : "+v"(fl));
+                    const int key = (slot << 16) | cur;
+                    bool need_row = need;
+                    while (todo) {
+                        const int kg = __builtin_amdgcn_readlane(key, __ffsll((unsigned long long)todo) - 1);
+                        const bool mine_k = need && key == kg;
+                        todo &= ~__ballot(mine_k);
+                        const int pk = stage_window(
+                            (const T*)rowbuf[s & 1] + (kg >> 16) * N, L, (kg & 0xFFFF) % L,
+                            (kg & 0xFFFF) / L, g, u, gout2, fl, sum_sh[wv]);
+                        if (mine_k && (pk >> 16)) {
+                            nx = pk & 255;
+                            ny = (pk >> 8) & 255;
+                            need_row = false;
+                        }
+                    }
+                    todo = __ballot(li == 0 && need_row);
+                    while (todo) {
+                        const int kg = __builtin_amdgcn_readlane(key, __ffsll((unsigned long long)todo) - 1);
+                        const bool mine_k = need_row && key == kg;
+                        todo &= ~__ballot(mine_k);
+                        int bad = 0;
+                        const int chosen =
+                            stage_row((const T*)rowbuf[s & 1] + (kg >> 16) * N, N, L, kg & 0xFFFF, g, u,
+                                      fl, sum_sh[wv], &bad, range);
+                        if (mine_k) {
+                            ny = chosen / L;
+                            nx = chosen - ny * L;
+                            if (bad == kBadRange)
+                                halt = true;
+                            else if (bad != 0 && err == 0)
+                                err = bad;
+                        }
+                    }
+                }
+                // the drawn site's filter value, FP32 plans (the row draw checks its own)
+                if (range && real && !((double)row[ny * L + nx] >= kRangeFloorD)) halt = true;
+                if (real) {
+                    cx = nx;
+                    cy = ny;
+                    cur = cx + L * cy;
+                }
+                if (li == 0) sites[s & 1][m] = cur;
+                __syncthreads();
+            }
+            if (halt && li == 0) rescue_push(rsc, c, t.chain, p, t.block, kCauseDraw);
+            if (err != 0 && li == 0) set_status(status, err, t.chain);
+            if (count_uncertified) {  // one atomic per wavefront
+                int nu = li == 0 ? n_unc : 0;
+#pragma unroll
+                for (int o = 4; o < 64; o <<= 1) nu += __shfl_xor(nu, o, 64);
+                if (lane == 0 && nu > 0) atomicAdd(&bw_state[kBwCounts + t.chain], nu);
+            }
+        }
+        if constexpr (SLOT) {  // a worldline sharing its representative's rows: its own end weight
+            if (wv == 0 && act_sh[lane] != 0) {
+                const int p = mem_sh[lane];
+                const int64_t bi = c.blk_off + (int64_t)p * c.nb + t.block;
+                const int ro = rsc.rep[bi];
+                if (ro != p) {
+                    const int qe = start + len >= L_tau ? perm[c.part_off + p] : p;
+                    const int e = checked_site(pc[(int64_t)((start + len) % L_tau) * np + qe], N,
+                                               status, t.chain);
+                    const double hv = (double)src[(int64_t)src_sh[slot_sh[lane]] * 2 +
+                                                  (int64_t)(c.B - 1) * N + e];
+                    if (!(hv > 0.0)) set_status(status, FH_ERR_NONFINITE, t.chain);
+                    sr.blk_logz[bi] = sr.blk_la[c.blk_off + (int64_t)ro * c.nb + t.block] + log(hv);
+                }
+            }
+        }
+        __syncthreads();  // the shared tables are free for the next task
     }
 }
 
@@ -1630,6 +2108,77 @@ __global__ __launch_bounds__(kThreads, kShareDrawWaves) void k_rescue_share_draw
     }
 }
 
+// The worldlines p0 .. p1 - 1 of one (chain, spin, block), sorted by start site, and the tasks of
+// k_backward_stage over them: groups of as many representatives as its row buffer holds, each
+// group in runs of up to kStageMembers worldlines. The whole workgroup; scratch: kDedupMaxN ints.
+struct StageLists {
+    int32_t* staged;   // [chain's sb_off + spin nb + block] 1 if k_backward_stage draws it
+    int32_t* members;  // [chain's blk_off ..]: per (spin, block) its worldlines, sorted
+    DrawTask* tasks;   // p: first member's index, pad: member count (counts in lists)
+    DrawTask* tasks_a; // the same for the held chains (phase A)
+    int32_t row_size;  // bytes of a stored row's value
+};
+__device__ inline void stage_members(const ChainInfo& c, const DrawTask& t, const int32_t* row,
+                                     int p0, int p1, int rowb, bool held, int32_t* scratch_lds,
+                                     int32_t* lists, const StageLists& st) {
+    __shared__ int32_t place[kDedupMaxN];  // counts, then the next free position, per site
+    __shared__ int2 part[kWaves];
+    const int R = min(kStageMembers, kStageBytes / rowb);
+    const int per = (c.N + kThreads - 1) / kThreads, tid = threadIdx.x, lane = tid & 63;
+    for (int i = tid; i < c.N; i += kThreads) place[i] = 0;
+    __syncthreads();
+    for (int q = p0 + tid; q < p1; q += kThreads) atomicAdd(&place[row[q]], 1);
+    __syncthreads();
+    // exclusive scan over the sites of (worldlines, occupied sites)
+    int2 own = {0, 0};
+    for (int i = tid * per; i < min((tid + 1) * per, c.N); ++i) {
+        own.x += place[i];
+        own.y += place[i] > 0;
+    }
+    int2 incl = own;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int ux = __shfl_up(incl.x, o, 64), uy = __shfl_up(incl.y, o, 64);
+        if (lane >= o) {
+            incl.x += ux;
+            incl.y += uy;
+        }
+    }
+    if (lane == 63) part[tid >> 6] = incl;
+    __syncthreads();
+    int2 at = {incl.x - own.x, incl.y - own.y};
+    int n_occ = 0;
+    for (int w = 0; w < kWaves; ++w) {
+        if (w < (tid >> 6)) {
+            at.x += part[w].x;
+            at.y += part[w].y;
+        }
+        n_occ += part[w].y;
+    }
+    for (int i = tid * per; i < min((tid + 1) * per, c.N); ++i) {
+        const int n = place[i];
+        if (n > 0) {
+            if (at.y % R == 0) scratch_lds[at.y / R] = at.x;  // a group's first worldline
+            ++at.y;
+        }
+        place[i] = at.x;
+        at.x += n;
+    }
+    __syncthreads();
+    const int64_t m0 = c.blk_off + (t.p ? (int64_t)c.n_up * c.nb : 0) + (int64_t)t.block * (p1 - p0);
+    for (int q = p0 + tid; q < p1; q += kThreads)
+        st.members[m0 + atomicAdd(&place[row[q]], 1)] = q;
+    const int groups = (n_occ + R - 1) / R;
+    for (int gi = tid; gi < groups; gi += kThreads) {
+        const int a = scratch_lds[gi], e = gi + 1 < groups ? scratch_lds[gi + 1] : p1 - p0;
+        const int nt = (e - a + kStageMembers - 1) / kStageMembers;
+        const int base = atomicAdd(&lists[held ? kListStageA : kListStage], nt);
+        DrawTask* out = held ? st.tasks_a : st.tasks;
+        for (int k = 0; k < nt; ++k)
+            out[base + k] = DrawTask{t.chain, (int32_t)(m0 + a + k * kStageMembers), t.block,
+                                     min(kStageMembers, e - a - k * kStageMembers)};
+    }
+}
+
 // Shared forward filters, before an FP32 forward pass: one workgroup per (chain, spin, block)
 // of the chains with dedup. The rows of a block depend only on the spin's W tables, the block's
 // slices and its start site, so every worldline of the (spin, block) is mapped to the lowest
@@ -1654,27 +2203,31 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
                                                     PackTask* __restrict__ cpack, int n_p2,
                                                     int32_t* __restrict__ prep,
                                                     int32_t* __restrict__ lists, int off64,
-                                                    int off48) {
+                                                    int off48, const StageLists st) {
     __shared__ int32_t first[kDedupMaxN];
     __shared__ int32_t rlist[kDedupMaxN];
-    __shared__ int32_t n_rep, c_base, p_base;
+    __shared__ int32_t n_rep, n_bad, c_base, p_base;
     const DrawTask t = tasks[blockIdx.x];  // t.p holds the spin
     const ChainInfo& c = chains[t.chain];
     int start, len;
     block_of(c, *sweep_ptr, t.block, &start, &len);
     const int p0 = t.p ? c.n_up : 0, p1 = t.p ? c.np : c.n_up;
     if (c.dedup == 2 && !rescue_held(rsc, t.chain)) {  // shares only in phase A: identity
+        if (threadIdx.x == 0) st.staged[c.sb_off + t.p * c.nb + t.block] = 0;
         for (int q = p0 + threadIdx.x; q < p1; q += blockDim.x)
             rep[c.blk_off + (int64_t)q * c.nb + t.block] = q;
         return;
     }
     for (int i = threadIdx.x; i < c.N; i += blockDim.x) first[i] = 0x7fffffff;
-    if (threadIdx.x == 0) n_rep = 0;
+    if (threadIdx.x == 0) n_rep = n_bad = 0;
     __syncthreads();
     const int32_t* row = paths + c.path_off + (int64_t)start * c.np;
     for (int q = p0 + threadIdx.x; q < p1; q += blockDim.x) {
         const int a = row[q];
-        if (a >= 0 && a < c.N) atomicMin(&first[a], q);
+        if (a >= 0 && a < c.N)
+            atomicMin(&first[a], q);
+        else
+            n_bad = 1;
     }
     __syncthreads();
     for (int q = p0 + threadIdx.x; q < p1; q += blockDim.x) {
@@ -1687,6 +2240,24 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
     // the chain's forward recursions in this pass (the FP64 re-filter's phase A sizes by them)
     if (rsc.words && threadIdx.x == 0)
         atomicAdd(&rsc.words[kRescueChain + 3 * rsc.n_chains + t.chain], n_rep);
+    // worldlines that share rows enough are drawn by k_backward_stage
+    {
+        const bool held = rescue_held(rsc, t.chain);
+        const int rowb = c.N * (held ? 8 : st.row_size), n_mem = p1 - p0;
+        // Where the line lies: a staged workgroup reads its representatives' whole rows once per
+        // slice, the windowed kernel about seven 128-byte lines per worldline and slice (more
+        // than half of them misses). 16 x 32 x 32, two sweeps from the start (every worldline its own
+        // row), took 17.4 ms with the line at 1 KB or 2 KB a worldline and 21.4 ms at 4 KB; the
+        // settled batches are the same at all three. Rows of odd lattices (N not a multiple of 4) are not
+        // 16-byte aligned, and invalid sites are left to the kernels that report them. Below 8 x 8
+        // the window is the lattice, and one wavefront per four worldlines has less to set up.
+        const bool on = c.win_on && c.L >= kStageMinL && c.N % 4 == 0 && !n_bad &&
+                        rowb <= kStageBytes &&
+                        (int64_t)n_rep * rowb <= (int64_t)n_mem * kStageCost;
+        if (threadIdx.x == 0) st.staged[c.sb_off + t.p * c.nb + t.block] = on ? 1 : 0;
+        if (on) stage_members(c, t, row, p0, p1, rowb, held, rlist, lists, st);
+        __syncthreads();  // rlist is free again
+    }
     // the 32 x 32 chains' representatives go to cpairs, two to a task; the padded lattices'
     // (16 < L < 32, one worldline to a wavefront) to csingles (count in words[7]); the packed
     // ones to cpack
@@ -2011,6 +2582,7 @@ __global__ __launch_bounds__(kThreads) void k_backward_fast(
     __syncthreads();  // the only barrier; every wave reaches it
     if (!active) return;
     const ChainInfo& c = chains[t.chain];
+    if (staged(rsc, c, t.p, t.block)) return;
     const uint64_t sweep = *sweep_ptr;
     if (c.N <= 256)
         backward_task<T, false, 0, 4>(t, c, gsh[wv], filt, paths, perm, sweep, status, lane,
@@ -2746,6 +3318,19 @@ hipError_t launch_logz_reduce(fh_plan p, double* logZ, hipStream_t s) {
 
 namespace {
 hipError_t launch_backward_kernels(fh_plan p, int32_t* paths, hipStream_t s) {
+    if (p->n_stage_tasks > 0 && !p->share_off) {
+        auto run = [&](auto kern, auto* filt) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)std::min(p->n_stage_tasks, kStageGrid)),
+                               dim3(kStageThreads), 0, s, p->d.chains, p->d.stage_tasks,
+                               p->d.lists, p->d.members, p->d.tables, filt, paths, p->d.perm,
+                               p->d.sweep, p->d.status, p->d.bw_state, p->bw_adapt ? 1 : 0,
+                               rescue_args(p), SlotRows{});
+        };
+        if (p->precision == FH_FP64)
+            run(k_backward_stage<double, false>, (const double*)p->d.filt);
+        else
+            run(k_backward_stage<float, false>, (const float*)p->d.filt);
+    }
     if (p->n_draww_tasks > 0) {
         const unsigned blocks = (unsigned)((p->n_draww_tasks + kThreads / kWinLanes - 1) /
                                            (kThreads / kWinLanes));
@@ -2823,7 +3408,9 @@ hipError_t launch_dedup(fh_plan p, const int32_t* paths, hipStream_t s) {
                        p->d.fwd32c_tasks,
                        p->precision == FH_FP64 ? p->d.fwddc_tasks : p->d.fwdxc_tasks,
                        p->d.fwdpc_tasks, p->n_fwdp2_tasks, p->d.prep, p->d.lists,
-                       p->n_fwdd_tasks, p->n_fwdd_tasks + p->n_fwdd4_tasks);
+                       p->n_fwdd_tasks, p->n_fwdd_tasks + p->n_fwdd4_tasks,
+                       StageLists{p->d.staged, p->d.members, p->d.stage_tasks,
+                                  p->d.stage_tasks_a, (int32_t)p->real_size});
     return hipGetLastError();
 }
 
@@ -2887,8 +3474,17 @@ hipError_t launch_rescue(fh_plan p, const void* aux, int32_t* paths, bool draw, 
         };
         if (p->rescue_l64) fwd(k_rescue_share_fwd<4>);
         if (p->rescue_l48) fwd(k_rescue_share_fwd<3>);
-        // the draws: windowed chains four blocks to a wavefront from the slots' FP64 rows, the
-        // others one block to a wavefront (they take no slot: twice the slot count of them)
+        // the draws: windowed chains from the slots' FP64 rows, staged or four blocks to a
+        // wavefront, the others one block to a wavefront (they take no slot: twice the slot count of them)
+        if (p->n_stage_tasks_a > 0 && !p->share_off)
+            hipLaunchKernelGGL((k_backward_stage<double, true>),
+                               dim3((unsigned)std::min(p->n_stage_tasks_a, kStageGrid)),
+                               dim3(kStageThreads), 0, s, p->d.chains, p->d.stage_tasks_a,
+                               p->d.lists, p->d.members, p->d.tables, (const double*)nullptr,
+                               paths, p->d.perm, p->d.sweep, p->d.status, p->d.bw_state, 0,
+                               rescue_args(p),
+                               SlotRows{p->d.rep_slot, p->d.rescue_ws, p->rescue_slot_elems,
+                                        p->d.blk_logz, p->d.blk_la});
         const unsigned wblocks = (unsigned)((p->rescuable_blocks + kThreads / kWinLanes - 1) /
                                             (kThreads / kWinLanes));
         hipLaunchKernelGGL((k_backward_win<double, true>), dim3(wblocks), dim3(kThreads), 0, s,

@@ -40,21 +40,25 @@ struct u64x4 {
     uint64_t x0, x1, x2, x3;
 };
 
-FH_HD inline u64x4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3, uint64_t k0,
-                                  uint64_t k1) {
+// R rounds of the generator on counter x with keys k0, k1 (both advanced).
+template <int R>
+FH_HD inline void philox_rounds(u64x4& x, uint64_t& k0, uint64_t& k1) {
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
+    for (int r = 0; r < R; ++r) {
         uint64_t hi0, lo0, hi1, lo1;
-        mul128(kPhiloxM0, c0, &hi0, &lo0);
-        mul128(kPhiloxM1, c2, &hi1, &lo1);
-        c0 = hi1 ^ c1 ^ k0;
-        c1 = lo1;
-        c2 = hi0 ^ c3 ^ k1;
-        c3 = lo0;
+        mul128(kPhiloxM0, x.x0, &hi0, &lo0);
+        mul128(kPhiloxM1, x.x2, &hi1, &lo1);
+        x = {hi1 ^ x.x1 ^ k0, lo1, hi0 ^ x.x3 ^ k1, lo0};
         k0 += kPhiloxW0;
         k1 += kPhiloxW1;
     }
-    return {c0, c1, c2, c3};
+}
+
+FH_HD inline u64x4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3, uint64_t k0,
+                                  uint64_t k1) {
+    u64x4 x = {c0, c1, c2, c3};
+    philox_rounds<10>(x, k0, k1);
+    return x;
 }
 
 // 53-bit uniform in [0, 1).
