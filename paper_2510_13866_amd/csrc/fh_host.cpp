@@ -203,7 +203,7 @@ hipError_t dalloc(T** p, size_t bytes) {
 
 void free_device(fh::Device& d) {
     void* ptrs[] = {d.chains, d.tables, d.cmat, d.cmat64, d.fwdd_tasks, d.W, d.wshift, d.filt, d.blk_logz, d.dt, d.fwd_tasks,
-                    d.draw_tasks, d.group_tasks, d.gpart, d.ckpt, d.rep, d.blk_la, d.endrow, d.dedup_tasks, d.lists, d.staged, d.members, d.stage_tasks, d.stage_tasks_a, d.fwddc_tasks, d.fwd32_tasks, d.fwd32c_tasks, d.fwdxc_tasks, d.fwdpc_tasks, d.prep, d.fwdx_tasks, d.fwdp_tasks, d.cmatp, d.cmatb, d.fwd64_tasks, d.draw32_tasks, d.draww_tasks, d.drawx_tasks, d.meas, d.mala, d.perm, d.perm_inv, d.sign, d.bw_state,
+                    d.draw_tasks, d.group_tasks, d.gpart, d.ckpt, d.rep, d.blk_la, d.endrow, d.dedup_tasks, d.lists, d.staged, d.members, d.stage_tasks, d.stage_tasks_a, d.grad.list, d.grad.count, d.grad.n, d.grad.of, d.grad.per, d.grad.groups, d.fwddc_tasks, d.fwd32_tasks, d.fwd32c_tasks, d.fwdxc_tasks, d.fwdpc_tasks, d.prep, d.fwdx_tasks, d.fwdp_tasks, d.cmatp, d.cmatb, d.fwd64_tasks, d.draw32_tasks, d.draww_tasks, d.drawx_tasks, d.meas, d.mala, d.perm, d.perm_inv, d.sign, d.bw_state,
                     d.rescue, d.rescue_list, d.rep_slot, d.arep, d.rescue_ws, d.rescue_w, d.status, d.sweep};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -579,12 +579,19 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
                           hipMemcpyHostToDevice);
         }
     }
+    if (e == hipSuccess) e = dalloc(&dv.grad.list, sizeof(int32_t) * (size_t)part);
+    if (e == hipSuccess) e = dalloc(&dv.grad.count, sizeof(int32_t) * (size_t)part);
+    if (e == hipSuccess) e = dalloc(&dv.grad.of, sizeof(int32_t) * (size_t)part);
+    if (e == hipSuccess) e = dalloc(&dv.grad.n, sizeof(int32_t) * 2 * (size_t)n_chains);
+    if (e == hipSuccess) e = dalloc(&dv.grad.per, sizeof(int32_t) * 2 * (size_t)n_chains);
+    if (e == hipSuccess) e = dalloc(&dv.grad.groups, sizeof(int32_t) * groups.size());
     if (e == hipSuccess) e = dalloc(&dv.dt, sizeof(double) * (size_t)part);
     if (e == hipSuccess) e = dalloc(&dv.fwd_tasks, sizeof(PairTask) * fwdf.size());
     if (e == hipSuccess) e = dalloc(&dv.fwdd_tasks, sizeof(DrawTask) * fwdd.size());
     if (e == hipSuccess && !fwdd.empty())  // the representatives among them (shared filters)
         e = dalloc(&dv.fwddc_tasks, sizeof(DrawTask) * fwdd.size());
     if (e == hipSuccess) e = dalloc(&dv.lists, sizeof(int32_t) * kListWords);
+    dv.grad.n_groups = dv.lists + kListGrad;
     if (e == hipSuccess) e = dalloc(&dv.cmat64, sizeof(double) * p->cmat64.size());
     if (e == hipSuccess) e = dalloc(&dv.draw_tasks, sizeof(DrawTask) * draw.size());
     if (e == hipSuccess) e = dalloc(&dv.group_tasks, sizeof(GroupTask) * groups.size());
@@ -1001,6 +1008,7 @@ static hipError_t enqueue_logz_grad(fh_plan p, const void* aux, const int32_t* p
                                     int32_t anchor_slice, double* logZ, void* grad_aux,
                                     double* grad_t, hipStream_t s) {
     hipError_t e = launch_potentials(p, aux, s);
+    if (e == hipSuccess) e = launch_grad_dedup(p, paths, anchor_slice, s);
     if (e != hipSuccess) return e;
     if (p->precision == FH_FP32_MFMA3) {
         e = launch_grad_mfma(p, aux, paths, anchor_slice, grad_aux, s);
@@ -1009,7 +1017,7 @@ static hipError_t enqueue_logz_grad(fh_plan p, const void* aux, const int32_t* p
     } else {
         e = launch_grad(p, aux, paths, anchor_slice, grad_aux, s);
     }
-    if (e == hipSuccess) e = launch_grad_reduce(p, logZ, grad_t, s);
+    if (e == hipSuccess) e = launch_grad_reduce(p, grad_aux, logZ, grad_t, s);
     return e;
 }
 
@@ -1140,6 +1148,11 @@ int fh_get_filters(fh_plan p, int32_t chain, int32_t particle, void* dst, int64_
         FH_TRY(hipStreamSynchronize(s));
         FH_TRY(hipMemcpy(owner.data(), p->d.rep + c.blk_off + (int64_t)particle * c.nb,
                          sizeof(int32_t) * c.nb, hipMemcpyDeviceToHost));
+    }
+    if (p->filters_are_ring) {  // the worldline whose ring it shares
+        FH_TRY(hipStreamSynchronize(s));
+        FH_TRY(hipMemcpy(owner.data(), p->d.grad.of + c.part_off + particle, sizeof(int32_t),
+                         hipMemcpyDeviceToHost));
     }
     // ring rows: one block of L_tau rows; sweep rows: B - 1 (the last block: its length - 1)
     const int nseg = p->filters_are_ring ? 1 : c.nb;

@@ -82,6 +82,8 @@ constexpr int kStageMinL = 8;
 constexpr int kListFwd = 0, kListFwd64 = 1, kListFwd48 = 2;
 // Tasks of k_backward_stage, and of its phase A launch (the held chains).
 constexpr int kListStage = 3, kListStageA = 4;
+// Worldline groups of the adjoint that hold rings (k_grad_dedup).
+constexpr int kListGrad = 5;
 constexpr int kListWords = 16;
 constexpr int kCmatPerChain = 3 * 2 * 64 * 8;
 constexpr int kCmat64PerChain = 16 * 64;
@@ -120,7 +122,7 @@ FH_HD inline int pack_blocks(int L) { return L <= 8 ? 4 : 2; }
 constexpr int kPackTiles = 1;
 // Up to kGroup worldlines of one (chain, spin) processed by one workgroup in the matrix-core
 // adjoints (two, one complex FFT signal, in the FFT adjoint); part_off locates the group's
-// partial field-gradient slab [L_tau][N], which k_gpart_reduce adds per chain in a fixed order.
+// partial field-gradient slab [L_tau][N], which k_grad_reduce adds per chain in a fixed order.
 constexpr int kGroup = 4;
 struct GroupTask {
     int32_t chain, p0, count, spin;
@@ -257,6 +259,41 @@ struct TuneRecord {
     float ms;
 };
 
+// Shared adjoints: the ring of a worldline depends only on its spin's W tables and on the sites it
+// starts from and closes on, so one adjoint serves every worldline of the spin with the same two
+// sites, its results taken as often. Per (chain, spin), the lowest-numbered worldline of each such
+// set in increasing order at the spin's place in `list` (counts at the same place in `count`), their
+// number in n[2 chain + spin]; of[particle]: the worldline whose ring a worldline shares.
+// Written by k_grad_dedup before every adjoint.
+struct GradShare {
+    int32_t* list;
+    int32_t* count;
+    int32_t* n;
+    int32_t* of;
+    int32_t* per;      // [2 chain + spin] rings per group: the plan's group size, or 1 (alone)
+    int32_t* groups;   // the groups that hold rings, densely: workgroup b takes groups[b]
+    int32_t* n_groups; // their number
+};
+// The rings a group takes from its (chain, spin)'s list: entries i0 .. i0 + count - 1 at `base`;
+// alone: the spin has so few rings that each has a group, and a workgroup, of its own.
+struct GradGroup {
+    int32_t base, i0, count;
+    bool alone;
+};
+__device__ inline GradGroup grad_group(const GradShare& gs, const GroupTask& g, const ChainInfo& c,
+                                       int gsize) {
+    const int s0 = g.spin ? c.n_up : 0, per = gs.per[2 * g.chain + g.spin];
+    GradGroup r;
+    r.i0 = (g.p0 - s0) / gsize * per;
+    r.base = (int)c.part_off + s0;
+    r.count = min(per, gs.n[2 * g.chain + g.spin] - r.i0);
+    r.alone = per == 1;
+    return r;
+}
+// Rings of a whole batch up to which a matrix-core adjoint in FP64 gives each a workgroup
+// (k_grad_dmfma): two per compute unit.
+constexpr int kGradAlone = 512;
+
 struct Device {
     ChainInfo* chains = nullptr;
     double* tables = nullptr;
@@ -282,6 +319,7 @@ struct Device {
     int32_t* members = nullptr;
     DrawTask* stage_tasks = nullptr;
     DrawTask* stage_tasks_a = nullptr;
+    GradShare grad = {};              // shared adjoints
     DrawTask* fwddc_tasks = nullptr;  // FP64 plans: the representatives k_dedup lists, as fwdd_tasks
     double* dt = nullptr;     // per particle d log Z / d t
     PairTask* fwd_tasks = nullptr;
@@ -397,6 +435,11 @@ struct fh_plan_s {
 
 namespace fh {
 
+// Rings per group of the plan's adjoint.
+inline int grad_group_size(fh_plan p) {
+    return p->precision == FH_FP32_MFMA3 || p->grad_dmfma ? kGroup : 2;
+}
+
 // The rescue state of a plan as passed to the kernels (all null for FP64 plans).
 inline Rescue rescue_args(fh_plan p) {
     Rescue r;
@@ -454,9 +497,12 @@ hipError_t launch_mala_accept(fh_plan p, void* aux, const void* prop, const void
                               double eps, int32_t* accepted, hipStream_t s);
 hipError_t launch_grad(fh_plan p, const void* aux, const int32_t* paths, int32_t anchor,
                        void* grad_aux, hipStream_t s);
-hipError_t launch_grad_reduce(fh_plan p, double* logZ, double* grad_t, hipStream_t s);
-// grad_aux = per chain, the sum of its groups' partial slabs in group order (every adjoint).
-hipError_t launch_gpart_reduce(fh_plan p, void* grad_aux, hipStream_t s);
+// Before every adjoint: the rings the worldlines share.
+hipError_t launch_grad_dedup(fh_plan p, const int32_t* paths, int32_t anchor, hipStream_t s);
+// logZ, grad_t (nullable): per chain, the sums over its worldlines; grad_aux (nullable) = per chain,
+// the sum of its groups' partial slabs in group order (every adjoint).
+hipError_t launch_grad_reduce(fh_plan p, void* grad_aux, double* logZ, double* grad_t,
+                              hipStream_t s);
 // energy[c] <- -(t_c / beta_c) energy[c]: d log Z_path / d t into the kinetic-energy estimate.
 hipError_t launch_kinetic_scale(fh_plan p, double* energy, hipStream_t s);
 hipError_t launch_grad_mfma(fh_plan p, const void* aux, const int32_t* paths, int32_t anchor,

@@ -2992,6 +2992,101 @@ __global__ __launch_bounds__(kThreads) void k_measure_reduce(
     }
 }
 
+// The rings that worldlines share (GradShare), one workgroup per (chain, spin): an LDS hash table
+// over (anchor site, closing site) keeps the lowest worldline and the number of each pair, and a
+// scan in worldline order lists the lowest ones, so the list is the same on every call. A spin
+// with more than kGradKeys different pairs shares nothing; an invalid site keeps its own ring (the
+// adjoint reports it). Settled Gaussian chains have one ring per spin. The groups with rings are
+// listed densely: left at their places in the grid (every 128th one of a settled batch), the
+// dispatcher put them on a few compute units, one after another (64 settled 32 x 32 chains in
+// FP64, 128 of 16384 groups: 17.1 ms, sixteen groups deep).
+constexpr int kGradKeys = 4096;
+__global__ __launch_bounds__(kThreads) void k_grad_dedup(const ChainInfo* __restrict__ chains,
+                                                         const int32_t* __restrict__ paths,
+                                                         const int32_t* __restrict__ perm,
+                                                         int anchor, int gsize, int alone,
+                                                         const GradShare gs) {
+    __shared__ int32_t keys[kGradKeys], low[kGradKeys], cnt[kGradKeys];
+    __shared__ int32_t full, part[kWaves];
+    const int ci = blockIdx.x >> 1, spin = blockIdx.x & 1, tid = threadIdx.x, lane = tid & 63;
+    const ChainInfo& c = chains[ci];
+    const int p0 = spin ? c.n_up : 0, p1 = spin ? c.np : c.n_up;
+    for (int i = tid; i < kGradKeys; i += kThreads) {
+        keys[i] = -1;
+        low[i] = 0x7fffffff;
+        cnt[i] = 0;
+    }
+    if (tid == 0) full = 0;
+    __syncthreads();
+    const int32_t* row = paths + c.path_off + (int64_t)anchor * c.np;
+    auto key_of = [&](int p) {
+        const int a = row[p], e = row[perm[c.part_off + p]];
+        return (a < 0 || a >= c.N || e < 0 || e >= c.N) ? -1 : a * c.N + e;
+    };
+    auto first = [&](int key) { return (int)(((uint32_t)key * 2654435761u) >> 20); };
+    static_assert(kGradKeys == 1 << 12, "the hash keeps the top 12 bits");
+    for (int p = p0 + tid; p < p1; p += kThreads) {
+        const int key = key_of(p);
+        if (key < 0) continue;
+        int h = first(key), probes = 0;
+        for (; probes < kGradKeys; ++probes, h = (h + 1) & (kGradKeys - 1)) {
+            const int was = atomicCAS(&keys[h], -1, key);
+            if (was == -1 || was == key) break;
+        }
+        if (probes == kGradKeys) {
+            full = 1;
+        } else {
+            atomicMin(&low[h], p);
+            atomicAdd(&cnt[h], 1);
+        }
+    }
+    __syncthreads();
+    const bool own = full != 0;
+    int at = 0;  // listed so far
+    for (int q = p0; q < p1; q += kThreads) {
+        const int p = q + tid;
+        int rep = p, times = 1;
+        if (p < p1 && !own) {
+            const int key = key_of(p);
+            if (key >= 0) {
+                int h = first(key);
+                while (keys[h] != key) h = (h + 1) & (kGradKeys - 1);  // it is in the table
+                rep = low[h];
+                times = cnt[h];
+            }
+        }
+        const bool is_rep = p < p1 && rep == p;
+        const uint64_t mask = __ballot(is_rep);
+        if (lane == 0) part[tid >> 6] = __popcll(mask);
+        __syncthreads();
+        int pos = at + __popcll(mask & ((1ull << lane) - 1));
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < (tid >> 6)) pos += part[w];
+            at += part[w];
+        }
+        if (p < p1) gs.of[c.part_off + p] = rep;
+        if (is_rep) {
+            gs.list[c.part_off + p0 + pos] = p;
+            gs.count[c.part_off + p0 + pos] = times;
+        }
+        __syncthreads();  // part is free
+    }
+    __shared__ int32_t base;
+    // a group of its own for each ring where they are few (alone: the most a spin may have) and
+    // the spin's group slabs suffice
+    const int n_up_groups = (c.n_up + gsize - 1) / gsize;
+    const int per = at <= alone && at <= (p1 - p0 + gsize - 1) / gsize ? 1 : gsize;
+    const int n_groups = (at + per - 1) / per;
+    if (tid == 0) {
+        gs.n[2 * ci + spin] = at;
+        gs.per[2 * ci + spin] = per;
+        base = atomicAdd(gs.n_groups, n_groups);
+    }
+    __syncthreads();
+    for (int i = tid; i < n_groups; i += kThreads)
+        gs.groups[base + i] = c.g0 + (spin ? n_up_groups : 0) + i;
+}
+
 // Adjoint of the forward filter over the ring anchored at `anchor` (one block of length L_tau,
 // closing on the anchor site e of the reconnected worldline, e = a without reconnection):
 // forward pass storing f~_j (j = 0..L_tau-1), then backward messages
@@ -3005,14 +3100,19 @@ __global__ __launch_bounds__(kThreads) void k_grad(
     const double* __restrict__ wshift, int64_t aux_elems, int64_t total_slices,
     const int32_t* __restrict__ paths, T* __restrict__ filt, double* __restrict__ blk_logz,
     double* __restrict__ dt_out, T* __restrict__ gpart, int anchor,
-    const int32_t* __restrict__ perm, int32_t* status, int maxN, int maxL) {
+    const int32_t* __restrict__ perm, int32_t* status, int maxN, int maxL, const GradShare gs) {
     extern __shared__ __align__(16) unsigned char smem[];
     FftLds<T> l = carve<T>(smem, maxN, maxL, true);
-    const GroupTask g = groups[blockIdx.x];  // one or two worldlines of one (chain, spin)
-    const PairTask t = {g.chain, g.p0, g.count > 1 ? g.p0 + 1 : -1, 0};
-    const ChainInfo& c = chains[t.chain];
+    if ((int)blockIdx.x >= *gs.n_groups) return;  // the whole workgroup
+    const GroupTask g = groups[gs.groups[blockIdx.x]];  // one or two rings of one (chain, spin)
+    const ChainInfo& c = chains[g.chain];
+    const GradGroup gg = grad_group(gs, g, c, 2);
+    const bool has_b = gg.count > 1;
+    const PairTask t = {g.chain, gs.list[gg.base + gg.i0], has_b ? gs.list[gg.base + gg.i0 + 1] : -1,
+                        0};
+    const double times_a = gs.count[gg.base + gg.i0];
+    const double times_b = has_b ? gs.count[gg.base + gg.i0 + 1] : 0.0;
     const int N = c.N, L = c.L, L_tau = c.L_tau;
-    const bool has_b = t.p_b >= 0;
     const int spin = t.p_a >= c.n_up ? 1 : 0;
     const double coef = spin ? c.coef_dn : c.coef_up;
     const T* Wsp = W + spin * aux_elems + c.aux_off;
@@ -3037,7 +3137,7 @@ __global__ __launch_bounds__(kThreads) void k_grad(
     for (int r = threadIdx.x; r < N; r += blockDim.x)
         l.U[r] = {r == e_a ? T(1) : T(0), (has_b && r == e_b) ? T(1) : T(0)};
     double dta = 0.0, dtb = 0.0;
-    // the pair's own partial field-gradient slab [L_tau][N]; k_gpart_reduce adds a chain's slabs
+    // the pair's own partial field-gradient slab [L_tau][N]; k_grad_reduce adds a chain's slabs
     // in group order, so the field gradient is the same on every call
     T* gl = gpart ? gpart + g.part_off : nullptr;
     for (int j = L_tau - 1; j >= 0; --j) {
@@ -3070,7 +3170,7 @@ __global__ __launch_bounds__(kThreads) void k_grad(
         dta += s[0] / s[1];
         if (has_b) dtb += s[2] / s[3];
         if (gl) {
-            const double ka = coef / s[1], kb = has_b ? coef / s[3] : 0.0;
+            const double ka = times_a * coef / s[1], kb = has_b ? times_b * coef / s[3] : 0.0;
             for (int r = threadIdx.x; r < N; r += blockDim.x) {
                 double v = ka * (double)fa[r] * (double)l.A[r].re;
                 if (has_b) v += kb * (double)fb[r] * (double)l.A[r].im;
@@ -3104,32 +3204,6 @@ __global__ __launch_bounds__(kThreads) void k_grad(
             blk_logz[c.blk_off + (int64_t)t.p_b * c.nb] = lzb;
             dt_out[c.part_off + t.p_b] = dtb;
         }
-    }
-}
-
-// Per chain, in particle order: logZ = sum of ring log Z_p, grad_t = sum of d log Z_p / dt.
-// Per chain: log Z_path = sum of the ring log Z of its worldlines, d/dt = sum of theirs. One
-// wavefront per chain; lane k sums worldlines k, k + 64, ... in order, then a fixed butterfly adds
-// the lanes, so the result is the same on every call.
-__global__ void k_grad_reduce(const ChainInfo* __restrict__ chains, int n_chains,
-                              const double* __restrict__ blk_logz, const double* __restrict__ dt,
-                              double* logZ, double* grad_t) {
-    const int c = blockIdx.x;
-    const int lane = threadIdx.x;
-    if (c >= n_chains) return;
-    const ChainInfo& ci = chains[c];
-    double a = 0.0, b = 0.0;
-    for (int p = lane; p < ci.np; p += 64) {
-        a += blk_logz[ci.blk_off + (int64_t)p * ci.nb];
-        b += dt[ci.part_off + p];
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        a += __shfl_xor(a, o, 64);
-        b += __shfl_xor(b, o, 64);
-    }
-    if (lane == 0) {
-        if (logZ) logZ[c] = a;
-        if (grad_t) grad_t[c] = b;
     }
 }
 
@@ -3670,17 +3744,16 @@ hipError_t launch_grad(fh_plan p, const void* aux, const int32_t* paths, int32_t
                            p->d.chains, p->d.group_tasks, p->d.tables, (const double*)aux,
                            (const double*)p->d.W, p->d.wshift, p->aux_elems, p->total_slices,
                            paths, (double*)p->d.filt, p->d.blk_logz, p->d.dt, (double*)slabs,
-                           anchor, p->d.perm, p->d.status, p->max_N, p->max_L);
+                           anchor, p->d.perm, p->d.status, p->max_N, p->max_L, p->d.grad);
     } else {
         if ((e = allow_lds(k_grad<float>, lds)) != hipSuccess) return e;
         hipLaunchKernelGGL(k_grad<float>, dim3(p->n_groups), dim3(kThreads), lds, s,
                            p->d.chains, p->d.group_tasks, p->d.tables, (const float*)aux,
                            (const float*)p->d.W, p->d.wshift, p->aux_elems, p->total_slices,
                            paths, (float*)p->d.filt, p->d.blk_logz, p->d.dt, (float*)slabs,
-                           anchor, p->d.perm, p->d.status, p->max_N, p->max_L);
+                           anchor, p->d.perm, p->d.status, p->max_N, p->max_L, p->d.grad);
     }
-    if ((e = hipGetLastError()) != hipSuccess || !grad_aux) return e;
-    return launch_gpart_reduce(p, grad_aux, s);
+    return hipGetLastError();
 }
 
 __global__ void k_kinetic_scale(const ChainInfo* __restrict__ chains, int n_chains,
@@ -3698,10 +3771,11 @@ hipError_t launch_kinetic_scale(fh_plan p, double* energy, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_grad_reduce(fh_plan p, double* logZ, double* grad_t, hipStream_t s) {
-    if (!logZ && !grad_t) return hipSuccess;
-    hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)p->n_chains), dim3(64), 0, s,
-                       p->d.chains, p->n_chains, p->d.blk_logz, p->d.dt, logZ, grad_t);
+hipError_t launch_grad_dedup(fh_plan p, const int32_t* paths, int32_t anchor, hipStream_t s) {
+    hipLaunchKernelGGL(k_grad_dedup, dim3((unsigned)(2 * p->n_chains)), dim3(kThreads), 0, s,
+                       p->d.chains, paths, p->d.perm, anchor, grad_group_size(p),
+                       p->grad_dmfma && !p->d.ckpt ? std::max(1, kGradAlone / (2 * p->n_chains)) : 0,
+                       p->d.grad);
     return hipGetLastError();
 }
 

@@ -1274,8 +1274,9 @@ __device__ __forceinline__ void ring_store(float* row, const f32x16& F, int lane
 
 // Adjoint of the forward filter over the ring anchored at `anchor` (one block of length L_tau,
 // closing on the anchor site e of the reconnected worldline, e = a without reconnection), on
-// the matrix cores. A workgroup takes up to kGroup worldlines of one (chain, spin), one per
-// wavefront, in lockstep over the slices:
+// the matrix cores. A workgroup takes up to kGroup of the rings that the worldlines of one (chain,
+// spin) share (GradShare; each counts as often as it is shared), one per wavefront, in lockstep
+// over the slices:
 //   forward:  f~_j as in k_forward_mfma, every row j = 0..L_tau-1 stored (row 0 = delta_a)
 //   backward: u_{L_tau} = delta_e; beta_j = C u_{j+1} C; u_j = W~_j . beta_j / sum
 //   d log Z / d log W_j(r) = f~_j(r) beta_j(r) / <f~_j, beta_j>   (the smoothing marginal)
@@ -1283,7 +1284,7 @@ __device__ __forceinline__ void ring_store(float* row, const f32x16& F, int lane
 //                    matrix: G = exp(t dtau A), so dG/dt = dtau A G and <u, (dG/dt) f> =
 //                    dtau <A G u, f>; A beta is a four-neighbour stencil read from LDS.
 // The marginals of the group are summed in LDS and written (times the spin's coefficient) to
-// the group's partial slab; k_gpart_reduce adds the slabs of a chain in a fixed order, so the
+// the group's partial slab; k_grad_reduce adds the slabs of a chain in a fixed order, so the
 // field gradient is the same on every call.
 // With ckpt (FH_FLAG_GRAD_CHECKPOINT) the forward pass keeps only rows j = 0, K, 2K, .. (K =
 // ceil(sqrt(L_tau))); when the backward messages enter a segment sK .. sK + K - 1 from above,
@@ -1299,18 +1300,22 @@ __global__ __launch_bounds__(kThreads, LFIX || !CK ? 3 : 2) void k_grad_mfma(
     const int32_t* __restrict__ paths, float* __restrict__ filt, float* __restrict__ gpart,
     double* __restrict__ blk_logz, double* __restrict__ dt_out, int anchor,
     const int32_t* __restrict__ perm, int32_t* status, const NegPairs neg,
-    float* __restrict__ ckpt) {
+    float* __restrict__ ckpt, const GradShare gs) {
     // beta tile of each wavefront with a halo row on each side: row y at (y + 1) * 32, row -1
     // repeats row L - 1 and row L repeats row 0, so the four-neighbour stencil reads at fixed
     // offsets from three per-lane bases
     __shared__ float bt[kWaves][34 * 32];
     __shared__ float mg[2][kWaves][1024];  // marginal tiles, double-buffered over the slices
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const GroupTask g = groups[blockIdx.x];
+    if ((int)blockIdx.x >= *gs.n_groups) return;  // the whole workgroup
+    const GroupTask g = groups[gs.groups[blockIdx.x]];
     const ChainInfo& c = chains[g.chain];
     const int L = LFIX ? LFIX : c.L, N = LFIX ? LFIX * LFIX : c.N, L_tau = c.L_tau;
-    const bool real = wv < g.count;            // extra wavefronts shadow worldline p0
-    const int p = g.p0 + (real ? wv : 0);
+    const GradGroup gg = grad_group(gs, g, c, kGroup);
+    const bool real = wv < gg.count;           // extra wavefronts shadow the group's first ring
+    const int at = gg.base + gg.i0 + (real ? wv : 0);
+    const int p = __builtin_amdgcn_readfirstlane(gs.list[at]);
+    const int times = __builtin_amdgcn_readfirstlane(gs.count[at]);  // worldlines on this ring
     const float* Wsp = W + g.spin * aux_elems + c.aux_off;
     const double* shift = wshift + g.spin * total_slices + c.slice_off;
     const double coef = g.spin ? c.coef_dn : c.coef_up;
@@ -1365,9 +1370,9 @@ __global__ __launch_bounds__(kThreads, LFIX || !CK ? 3 : 2) void k_grad_mfma(
             la -= log(prod);
             prod = 1.0;
         }
-        la += shift[l];
         if (real && j % K == 0) ring_store<LFIX>(ring_row(j), F, lane, L);
     }
+    la += block_shift_sum(shift, anchor, L_tau, L_tau, 0.0, lane);
     {
         const f32x16 X = circ_step(F, C, neg);
         const f32x16 H = circ_step(X, C, neg);
@@ -1389,7 +1394,7 @@ __global__ __launch_bounds__(kThreads, LFIX || !CK ? 3 : 2) void k_grad_mfma(
 #pragma unroll
     for (int v = 0; v < 16; ++v) U[v] = (x == ex && tile_row(lane, v) == ey) ? 1.0f : 0.0f;
     double dt = 0.0;
-    float* slab = gpart + g.part_off;
+    float* slab = gpart ? gpart + g.part_off : nullptr;  // the field gradient only when asked for
     const int xp = x + 1 == L ? 0 : x + 1, xm = x == 0 ? L - 1 : x - 1;
     float* btw = bt[wv] + 4 * (lane >> 5) * 32;  // row 4 (lane / 32) - 1 of the halo layout
     for (int j = L_tau - 1; j >= 0; --j) {
@@ -1456,21 +1461,24 @@ __global__ __launch_bounds__(kThreads, LFIX || !CK ? 3 : 2) void k_grad_mfma(
         }
         const double dden = (double)wave_sum_f32(den);
         const double dnum = (double)wave_sum_f32(num);
-        dt += dtau * dnum / dden;
-        const float k = real ? (float)(coef / dden) : 0.0f;
-        float* mgb = mg[j & 1][wv];
+        const double rden = 1.0 / dden;  // one FP64 division a slice
+        dt += dtau * dnum * rden;
+        const float k = real ? (float)((double)times * coef * rden) : 0.0f;
+        if (slab) {
+            float* mgb = mg[j & 1][wv];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) mgb[tile_row(lane, v) * 32 + x] = k * fj[v] * B[v];
-        __syncthreads();  // one barrier per slice: the tiles of slice j + 2 reuse these buffers
-        {
-            const float* m0 = mg[j & 1][0];
-            const float* m1 = mg[j & 1][1];
-            const float* m2 = mg[j & 1][2];
-            const float* m3 = mg[j & 1][3];
-            float* srow = slab + (int64_t)l * N;
-            for (int i = threadIdx.x; i < 1024; i += kThreads) {
-                const int yy = i >> 5, xx = i & 31;
-                if (LFIX || (xx < L && yy < L)) srow[yy * L + xx] = (m0[i] + m1[i]) + (m2[i] + m3[i]);
+            for (int v = 0; v < 16; ++v) mgb[tile_row(lane, v) * 32 + x] = k * fj[v] * B[v];
+            __syncthreads();  // one barrier per slice: the tiles of slice j + 2 reuse these buffers
+            {
+                const float* m0 = mg[j & 1][0];
+                const float* m1 = mg[j & 1][1];
+                const float* m2 = mg[j & 1][2];
+                const float* m3 = mg[j & 1][3];
+                float* srow = slab + (int64_t)l * N;
+                for (int i = threadIdx.x; i < 1024; i += kThreads) {
+                    const int yy = i >> 5, xx = i & 31;
+                    if (LFIX || (xx < L && yy < L)) srow[yy * L + xx] = (m0[i] + m1[i]) + (m2[i] + m3[i]);
+                }
             }
         }
         if (j > 0) {
@@ -1493,6 +1501,161 @@ __global__ __launch_bounds__(kThreads, LFIX || !CK ? 3 : 2) void k_grad_mfma(
     if (real && lane == 0) dt_out[c.part_off + p] = dt;
 }
 
+// The FP64 adjoint of one ring by a whole workgroup, for batches with few rings (settled chains):
+// the forward recursion of dmfma_wg_forward, then the backward messages split the same way.
+// Wavefront wq owns tile wq of the 32 x 32 messages (L <= 16: the first wavefront alone, one tile):
+// it holds all of u_{j+1}, forms its tile of beta_j = C u C (24 products of the 128 a slice takes
+// on one wavefront), and puts beta and W~ beta into LDS. One barrier per slice later every
+// wavefront reads the four W~ beta tiles (the next u, scaled by the sum all of them form in the
+// same order) and its tile's neighbours for the d/dt stencil. rows: the ring rows; slab: the
+// field gradient's [L_tau][N], scaled by kcoef. Returns false if a normaliser or the end weight is
+// not a positive finite number (first wavefront).
+// Bound: the 2 L_tau dependent steps. 8 settled 32 x 32 chains, L_tau = 128 (16 rings): 483 us
+// against 1084 us with one wavefront to a ring, and 9035 us with one ring per worldline.
+__device__ inline bool grad_wg64(const double* __restrict__ cm, int L, int L_tau, int anchor, int a,
+                                 int e, double la, const double* __restrict__ Wsp,
+                                 const double* __restrict__ shift, double* __restrict__ rows,
+                                 double* __restrict__ slab, double kcoef, double dtau, double* lds,
+                                 int wq, int lane, double* lz, double* dt_out) {
+#pragma clang fp contract(off)
+    const int N = L * L, I = wq >> 1, J = wq & 1;
+    const bool works = L > 16 || wq == 0;  // wavefronts without a tile only meet the barriers
+    const int nw = L > 16 ? kWaves : 1;
+    f64x4(*xch)[4][64] = (f64x4(*)[4][64])lds;                 // [2][4][64]
+    double(*bh)[34 * 32] = (double(*)[34 * 32])(lds + 2 * 4 * 64 * 4);  // [2] beta with halo rows
+    double(*part)[kWaves] = (double(*)[kWaves])(lds + 2 * 4 * 64 * 4 + 2 * 34 * 32);  // [2][kWaves]
+    double* dts = lds + 2 * 4 * 64 * 4 + 2 * 34 * 32 + 2 * kWaves;
+    int site[4], x = t64_x(wq, lane), y[4];
+    bool in[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        y[r] = t64_y(wq, r, lane);
+        in[r] = works && x < L && y[r] < L;
+        site[r] = in[r] ? y[r] * L + x : 0;
+        if (in[r]) rows[site[r]] = site[r] == a ? 1.0 : 0.0;
+    }
+    int buf = 0;
+    bool ok = true;
+    double lzv = 0.0;
+    // the end weight's wavefront tells the first one through LDS
+    const bool mine = dmfma_wg_forward(cm, L, L_tau, anchor, L_tau, a, e, Wsp, shift, rows + N,
+                                       nullptr, xch, wq, lane, &buf, &la, &lzv, &ok);
+    if (mine && lane == 0) {
+        dts[0] = lzv;
+        dts[1] = ok ? 1.0 : 0.0;
+    }
+    __syncthreads();  // also: the ring rows are stored, the exchange buffers are free
+    *lz = dts[0];
+    ok = dts[1] != 0.0;
+    double CbI[8], CbJ[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        CbI[k] = cm[(k * 2 + I) * 64 + lane];
+        CbJ[k] = cm[(k * 2 + J) * 64 + lane];
+    }
+    const int ex = e % L, ey = e / L;
+    Tile64 U;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            U.t[q][r] = (t64_x(q, lane) == ex && t64_y(q, r, lane) == ey) ? 1.0 : 0.0;
+    const int xp = x + 1 == L ? 0 : x + 1, xm = x == 0 ? L - 1 : x - 1;
+    double fj[4], wl[4], fn[4], wn[4];
+    auto load = [&](int j, double (&f)[4], double (&w)[4]) {
+        const int l = (anchor + j) % L_tau;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            f[r] = rows[(int64_t)j * N + site[r]];
+            w[r] = Wsp[(int64_t)l * N + site[r]];
+        }
+    };
+    double dt = 0.0;
+    load(L_tau - 1, fn, wn);
+    for (int j = L_tau - 1; j >= 0; --j) {
+        const int l = (anchor + j) % L_tau, b = j & 1;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            fj[r] = in[r] ? fn[r] : 0.0;
+            wl[r] = wn[r];
+        }
+        if (works) load(j > 0 ? j - 1 : 0, fn, wn);  // a slice ahead of its use
+        f64x4 B = {0.0, 0.0, 0.0, 0.0};
+        if (L > 16) {  // this wavefront's tile of C U C
+            f64x4 X[2];
+#pragma unroll
+            for (int K = 0; K < 2; ++K) {
+                f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int K2 = 0; K2 < 2; ++K2)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(U.t[2 * K2 + K][r],
+                                                                   CbI[4 * K2 + r], acc, 0, 0, 0);
+                X[K] = acc;
+            }
+#pragma unroll
+            for (int K = 0; K < 2; ++K)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    B = __builtin_amdgcn_mfma_f64_16x16x4f64(X[K][r], CbJ[4 * K + r], B, 0, 0, 0);
+        } else if (works) {
+            const double C4[4] = {CbI[0], CbI[1], CbI[2], CbI[3]};
+            B = circ16(U.t[0], C4, L);
+        }
+        double den = 0.0;
+        f64x4 V;
+        if (works) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                den += fj[r] * B[r];
+                V[r] = in[r] ? wl[r] * B[r] : 0.0;
+                if (in[r]) {
+                    bh[b][(y[r] + 1) * 32 + x] = B[r];
+                    if (y[r] == L - 1) bh[b][x] = B[r];            // halo row -1
+                    if (y[r] == 0) bh[b][(L + 1) * 32 + x] = B[r];  // halo row L
+                }
+            }
+            xch[b][wq][lane] = V;
+            den = wave_sum_f64(den);
+            if (lane == 0) part[b][wq] = den;
+        }
+        __syncthreads();  // slice j + 2's buffers are this slice's
+        if (!works) continue;
+        den = 0.0;
+        for (int w = 0; w < nw; ++w) den += part[b][w];
+        double sum = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q >= nw) break;
+            U.t[q] = xch[b][q][lane];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum += U.t[q][r];
+        }
+        const double tot = wave_sum_f64(sum);
+        if (j > 0) ok = ok && tot > 0.0 && isfinite(tot);
+        const double inv = 1.0 / tot;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) U.t[q][r] *= inv;
+        const double kd = kcoef / den;
+        double num = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const double* up = bh[b] + y[r] * 32;  // the row above, in the halo layout
+            const double nbr = in[r] ? up[32 + xp] + up[32 + xm] + up[64 + x] + up[x] : 0.0;
+            num += fj[r] * nbr;
+            if (slab && in[r]) slab[(int64_t)l * N + site[r]] = kd * fj[r] * B[r];
+        }
+        dt += dtau * wave_sum_f64(num) / den;
+    }
+    if (lane == 0) dts[2 + wq] = works ? dt : 0.0;
+    __syncthreads();
+    *dt_out = (dts[2] + dts[3]) + (dts[4] + dts[5]);
+    return ok;
+}
+
 // The adjoint of k_grad_mfma on the FP64 matrix cores (FP64 plans, every chain L <= 32): the
 // same ring, recursion, marginals and d/dt stencil, every product and sum in FP64 with the
 // circulant of k_forward_dmfma; ring rows stored as FP64 rows, group partial slabs in FP64;
@@ -1504,17 +1667,22 @@ __global__ __launch_bounds__(kThreads) void k_grad_dmfma(
     const double* __restrict__ W, const double* __restrict__ wshift, int64_t aux_elems,
     int64_t total_slices, const int32_t* __restrict__ paths, double* __restrict__ filt,
     double* __restrict__ gpart, double* __restrict__ blk_logz, double* __restrict__ dt_out,
-    int anchor, const int32_t* __restrict__ perm, int32_t* status, double* __restrict__ ckpt) {
+    int anchor, const int32_t* __restrict__ perm, int32_t* status, double* __restrict__ ckpt,
+    const GradShare gs) {
     // beta tile of each wavefront with halo rows (row y at (y + 1) * 32; row -1 repeats row L - 1,
     // row L repeats row 0), and double-buffered marginal tiles, as in k_grad_mfma
-    __shared__ double bt[kWaves][34 * 32];
-    __shared__ double mg[2][kWaves][1024];
+    __shared__ double lds[kWaves * 34 * 32 + 2 * kWaves * 1024];
+    double(*bt)[34 * 32] = (double(*)[34 * 32])lds;
+    double(*mg)[kWaves][1024] = (double(*)[kWaves][1024])(lds + kWaves * 34 * 32);
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const GroupTask g = groups[blockIdx.x];
+    if ((int)blockIdx.x >= *gs.n_groups) return;  // the whole workgroup
+    const GroupTask g = groups[gs.groups[blockIdx.x]];
     const ChainInfo& c = chains[g.chain];
     const int L = c.L, N = c.N, L_tau = c.L_tau;
-    const bool real = wv < g.count;  // extra wavefronts shadow worldline p0
-    const int p = g.p0 + (real ? wv : 0);
+    const GradGroup gg = grad_group(gs, g, c, kGroup);
+    const bool real = wv < gg.count;  // extra wavefronts shadow the group's first ring
+    const int p = gs.list[gg.base + gg.i0 + (real ? wv : 0)];
+    const double times = gs.count[gg.base + gg.i0 + (real ? wv : 0)];  // worldlines on this ring
     const double* Wsp = W + g.spin * aux_elems + c.aux_off;
     const double* shift = wshift + g.spin * total_slices + c.slice_off;
     const double coef = g.spin ? c.coef_dn : c.coef_up;
@@ -1527,9 +1695,31 @@ __global__ __launch_bounds__(kThreads) void k_grad_dmfma(
         a = a < 0 || a >= N ? 0 : a;
         e = e < 0 || e >= N ? 0 : e;
     }
+    if (!CK && gg.alone) {  // one ring, the whole workgroup
+        const int wq = __builtin_amdgcn_readfirstlane(wv);
+        double lz, dt;
+        const bool ok = grad_wg64(cmat64 + (int64_t)g.chain * kCmat64PerChain, L, L_tau, anchor, a,
+                                  e, coef * aux[c.aux_off + (int64_t)anchor * N + a], Wsp, shift,
+                                  filt + c.filt_off + (int64_t)p * L_tau * N,
+                                  gpart ? gpart + g.part_off : nullptr,
+                                  times * coef, dtau, lds, wq, lane, &lz, &dt);
+        if (threadIdx.x == 0) {
+            if (!ok) set_status(status, FH_ERR_NONFINITE, g.chain);
+            blk_logz[c.blk_off + (int64_t)p * c.nb] = lz;
+            dt_out[c.part_off + p] = dt;
+        }
+        return;
+    }
     double Cb[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) Cb[q] = cmat64[((int64_t)g.chain * 16 + q) * 64 + lane];
+    const double C4[4] = {Cb[0], Cb[2], Cb[4], Cb[6]};
+    auto conv = [&](const Tile64& X) {  // C X C; a lattice with L <= 16 has one tile
+        if (L > 16) return circ64(circ64(X, Cb), Cb);
+        Tile64 Y = {};
+        Y.t[0] = circ16(X.t[0], C4, L);
+        return Y;
+    };
     const int xl = lane & 15, yl = lane >> 4;
     auto xo = [&](int q) { return 16 * (q & 1) + xl; };
     auto yo = [&](int q, int r) { return 16 * (q >> 1) + 4 * r + yl; };
@@ -1561,7 +1751,7 @@ __global__ __launch_bounds__(kThreads) void k_grad_dmfma(
 #pragma unroll
             for (int r = 0; r < 4; ++r) w[4 * q + r] = Wl[inside(q, r) ? yo(q, r) * L + xo(q) : 0];
         __builtin_amdgcn_sched_barrier(0);  // W in flight during the matrix work
-        const Tile64 H = circ64(circ64(F, Cb), Cb);
+        const Tile64 H = conv(F);
         double sum = 0.0;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -1595,7 +1785,7 @@ __global__ __launch_bounds__(kThreads) void k_grad_dmfma(
         if (real && j % K == 0) store_row(ring_row(j), F);
     }
     {
-        const Tile64 H = circ64(circ64(F, Cb), Cb);
+        const Tile64 H = conv(F);
         const int qe = 2 * (ey >> 4) + (ex >> 4), re = (ey & 15) >> 2;
         double hv = 0.0;
 #pragma unroll
@@ -1617,7 +1807,7 @@ __global__ __launch_bounds__(kThreads) void k_grad_dmfma(
 #pragma unroll
         for (int r = 0; r < 4; ++r) U.t[q][r] = (xo(q) == ex && yo(q, r) == ey) ? 1.0 : 0.0;
     double dt = 0.0;
-    double* slab = gpart + g.part_off;
+    double* slab = gpart ? gpart + g.part_off : nullptr;
     for (int j = L_tau - 1; j >= 0; --j) {
         const int l = (anchor + j) % L_tau;
         if (ck && j % K != 0 && (j == L_tau - 1 || (j + 1) % K == 0)) {
@@ -1649,7 +1839,7 @@ __global__ __launch_bounds__(kThreads) void k_grad_dmfma(
                 wl[4 * q + r] = Wl[o];
             }
         __builtin_amdgcn_sched_barrier(0);
-        const Tile64 B = circ64(circ64(U, Cb), Cb);  // beta_j = C u_{j+1} C
+        const Tile64 B = conv(U);  // beta_j = C u_{j+1} C
         double den = 0.0;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -1687,22 +1877,24 @@ __global__ __launch_bounds__(kThreads) void k_grad_dmfma(
         const double dden = wave_sum_f64(den);
         const double dnum = wave_sum_f64(num);
         dt += dtau * dnum / dden;
-        const double k = real ? coef / dden : 0.0;
-        double* mgb = mg[j & 1][wv];
+        const double k = real ? times * coef / dden : 0.0;
+        if (slab) {
+            double* mgb = mg[j & 1][wv];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) mgb[yo(q, r) * 32 + xo(q)] = k * fj[4 * q + r] * B.t[q][r];
-        __syncthreads();  // one barrier per slice: the tiles of slice j + 2 reuse these buffers
-        {
-            const double* m0 = mg[j & 1][0];
-            const double* m1 = mg[j & 1][1];
-            const double* m2 = mg[j & 1][2];
-            const double* m3 = mg[j & 1][3];
-            double* srow = slab + (int64_t)l * N;
-            for (int i = threadIdx.x; i < 1024; i += kThreads) {
-                const int yy = i >> 5, xx = i & 31;
-                if (xx < L && yy < L) srow[yy * L + xx] = (m0[i] + m1[i]) + (m2[i] + m3[i]);
+                for (int r = 0; r < 4; ++r) mgb[yo(q, r) * 32 + xo(q)] = k * fj[4 * q + r] * B.t[q][r];
+            __syncthreads();  // one barrier per slice: the tiles of slice j + 2 reuse these buffers
+            {
+                const double* m0 = mg[j & 1][0];
+                const double* m1 = mg[j & 1][1];
+                const double* m2 = mg[j & 1][2];
+                const double* m3 = mg[j & 1][3];
+                double* srow = slab + (int64_t)l * N;
+                for (int i = threadIdx.x; i < 1024; i += kThreads) {
+                    const int yy = i >> 5, xx = i & 31;
+                    if (xx < L && yy < L) srow[yy * L + xx] = (m0[i] + m1[i]) + (m2[i] + m3[i]);
+                }
             }
         }
         if (j > 0) {
@@ -1728,16 +1920,45 @@ __global__ __launch_bounds__(kThreads) void k_grad_dmfma(
     if (real && lane == 0) dt_out[c.part_off + p] = dt;
 }
 
-// grad_aux[chain][l][r] = sum over the chain's groups, in group order, of the partial slabs.
+// After an adjoint. Workgroups [0, n_chains): log Z_path = sum of the ring log Z of the chain's
+// worldlines, d/dt = sum of theirs, a shared ring's values taken as often as it is shared; thread
+// k sums the rings k, k + kThreads, ... of each spin's list in order, then the threads are added
+// in a fixed order. The other workgroups (with grad): grad[chain][l][r] = sum over the chain's
+// groups with rings, in group order, of the partial slabs. The results are the same on every call.
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_gpart_reduce(const ChainInfo* __restrict__ chains,
-                                                           int n_chains,
-                                                           const GroupTask* __restrict__ groups,
-                                                           const T* __restrict__ gpart,
-                                                           T* __restrict__ grad,
-                                                           int64_t aux_elems) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < aux_elems;
-         e += (int64_t)gridDim.x * blockDim.x) {
+__global__ __launch_bounds__(kThreads) void k_grad_reduce(
+    const ChainInfo* __restrict__ chains, int n_chains, const GroupTask* __restrict__ groups,
+    const T* __restrict__ gpart, T* __restrict__ grad, int64_t aux_elems, int gsize,
+    const double* __restrict__ blk_logz, const double* __restrict__ dt, double* logZ,
+    double* grad_t, const GradShare gs) {
+    if ((int)blockIdx.x < n_chains) {
+        __shared__ double red[2][kWaves];
+        const ChainInfo& c = chains[blockIdx.x];
+        double z = 0.0, t = 0.0;
+        for (int spin = 0; spin < 2; ++spin) {
+            const int64_t base = c.part_off + (spin ? c.n_up : 0);
+            for (int i = threadIdx.x; i < gs.n[2 * blockIdx.x + spin]; i += kThreads) {
+                const int p = gs.list[base + i];
+                const double times = gs.count[base + i];
+                z += times * blk_logz[c.blk_off + (int64_t)p * c.nb];
+                t += times * dt[c.part_off + p];
+            }
+        }
+        z = wave_sum_f64(z);
+        t = wave_sum_f64(t);
+        if ((threadIdx.x & 63) == 0) {
+            red[0][threadIdx.x >> 6] = z;
+            red[1][threadIdx.x >> 6] = t;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            if (logZ) logZ[blockIdx.x] = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+            if (grad_t) grad_t[blockIdx.x] = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+        }
+        return;
+    }
+    for (int64_t e = (int64_t)(blockIdx.x - n_chains) * kThreads + threadIdx.x; e < aux_elems;
+         e += (int64_t)(gridDim.x - n_chains) * kThreads) {
         int lo = 0, hi = n_chains - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -1747,21 +1968,24 @@ __global__ __launch_bounds__(kThreads) void k_gpart_reduce(const ChainInfo* __re
                 hi = mid - 1;
         }
         const ChainInfo& c = chains[lo];
-        // a chain's group slabs are consecutive, [L_tau][N] apart: eight loads in flight, the
-        // sum still taken in group order
+        // a chain's group slabs are consecutive, [L_tau][N] apart, and each spin's first groups
+        // hold its rings: eight loads in flight, the sum still taken in group order
         const int64_t stride = (int64_t)c.L_tau * c.N;
         const T* src = gpart + groups[c.g0].part_off + (e - c.aux_off);
-        const int n = c.g1 - c.g0;
         T s = T(0);
-        int q = 0;
-        for (; q + 8 <= n; q += 8) {
-            T v[8];
+        for (int spin = 0; spin < 2; ++spin) {
+            const int per = gs.per[2 * lo + spin], n = (gs.n[2 * lo + spin] + per - 1) / per;
+            int q = 0;
+            for (; q + 8 <= n; q += 8) {
+                T v[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = src[(int64_t)(q + k) * stride];
+                for (int k = 0; k < 8; ++k) v[k] = src[(int64_t)(q + k) * stride];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) s += v[k];
+                for (int k = 0; k < 8; ++k) s += v[k];
+            }
+            for (; q < n; ++q) s += src[(int64_t)q * stride];
+            src += (int64_t)((c.n_up + gsize - 1) / gsize) * stride;
         }
-        for (; q < n; ++q) s += src[(int64_t)q * stride];
         grad[e] = s;
     }
 }
@@ -1961,24 +2185,28 @@ hipError_t launch_grad_mfma(fh_plan p, const void* aux, const int32_t* paths, in
     hipLaunchKernelGGL(kern, dim3(p->n_groups), dim3(kThreads), 0, s, p->d.chains,
                        p->d.group_tasks, p->d.cmat, (const float*)aux, (const float*)p->d.W,
                        p->d.wshift, p->aux_elems, p->total_slices, paths, (float*)p->d.filt,
-                       (float*)p->d.gpart, p->d.blk_logz, p->d.dt, anchor, p->d.perm,
-                       p->d.status, kNegPairs, (float*)p->d.ckpt);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !grad_aux) return e;
-    return launch_gpart_reduce(p, grad_aux, s);
+                       grad_aux ? (float*)p->d.gpart : nullptr, p->d.blk_logz, p->d.dt, anchor,
+                       p->d.perm,
+                       p->d.status, kNegPairs, (float*)p->d.ckpt, p->d.grad);
+    return hipGetLastError();
 }
 
-hipError_t launch_gpart_reduce(fh_plan p, void* grad_aux, hipStream_t s) {
-    int64_t b = (p->aux_elems + kThreads - 1) / kThreads;
-    if (b > 65536) b = 65536;
+hipError_t launch_grad_reduce(fh_plan p, void* grad_aux, double* logZ, double* grad_t,
+                              hipStream_t s) {
+    const int64_t slab_blocks =
+        grad_aux ? std::min<int64_t>((p->aux_elems + kThreads - 1) / kThreads, 65536) : 0;
+    const int gsize = grad_group_size(p);
+    auto run = [&](auto kern, auto* zero) {
+        using T = std::remove_pointer_t<decltype(zero)>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(p->n_chains + slab_blocks)), dim3(kThreads), 0, s,
+                           p->d.chains, p->n_chains, p->d.group_tasks, (const T*)p->d.gpart,
+                           (T*)grad_aux, p->aux_elems, gsize, p->d.blk_logz, p->d.dt, logZ, grad_t,
+                           p->d.grad);
+    };
     if (p->precision == FH_FP64)
-        hipLaunchKernelGGL(k_gpart_reduce<double>, dim3((unsigned)b), dim3(kThreads), 0, s,
-                           p->d.chains, p->n_chains, p->d.group_tasks, (const double*)p->d.gpart,
-                           (double*)grad_aux, p->aux_elems);
+        run(k_grad_reduce<double>, (double*)nullptr);
     else
-        hipLaunchKernelGGL(k_gpart_reduce<float>, dim3((unsigned)b), dim3(kThreads), 0, s,
-                           p->d.chains, p->n_chains, p->d.group_tasks, (const float*)p->d.gpart,
-                           (float*)grad_aux, p->aux_elems);
+        run(k_grad_reduce<float>, (float*)nullptr);
     return hipGetLastError();
 }
 
@@ -1988,11 +2216,10 @@ hipError_t launch_grad_dmfma(fh_plan p, const void* aux, const int32_t* paths, i
                        dim3(kThreads), 0, s, p->d.chains,
                        p->d.group_tasks, p->d.cmat64, (const double*)aux, (const double*)p->d.W,
                        p->d.wshift, p->aux_elems, p->total_slices, paths, (double*)p->d.filt,
-                       (double*)p->d.gpart, p->d.blk_logz, p->d.dt, anchor, p->d.perm,
-                       p->d.status, (double*)p->d.ckpt);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !grad_aux) return e;
-    return launch_gpart_reduce(p, grad_aux, s);
+                       grad_aux ? (double*)p->d.gpart : nullptr, p->d.blk_logz, p->d.dt, anchor,
+                       p->d.perm,
+                       p->d.status, (double*)p->d.ckpt, p->d.grad);
+    return hipGetLastError();
 }
 
 }  // namespace fh
