@@ -522,4 +522,138 @@ __device__ inline double dmfma_big_block_forward_end(const double (&Cb)[16], int
     return la + log(hv);
 }
 
+// dmfma_big_block_forward_end by one workgroup, for passes with few recursions: wavefront w < NT
+// owns row block w of the NT x NT tiles. It forms column block w of X = F^T C and, from exactly
+// those tiles, row block w of H = X^T C: 8 NT^2 products, the whole step's 8 NT^3 split without
+// repeats. The W-weighted tiles meet in LDS (xch, [2][NT^2][64], double-buffered; *buf is kept
+// between calls), and every wavefront sums all of them in the one-wavefront order, so every bit is
+// the same. Wl0: W~ of slice 0; rows f~_j go to rows + (j - 1) N, the end tile to end (nullable).
+// *la enters as log W_start(a) and leaves as log Z without the end weight; *lz receives log Z on
+// the wavefront that gets true. Wavefronts past NT only meet the barriers.
+// Bound: FP64 products, 2 NT^2 (NT = 4: 128) of 64 cycles a wavefront and step; a 64 x 64 step took
+// 18.6 us on one wavefront, @BIG@ us here.
+template <int NT>
+__device__ inline bool dmfma_big_wg_forward(const double (&Cb)[16], int L_tau, int start, int len,
+                                            int a, int e, const double* __restrict__ Wl0,
+                                            const double* __restrict__ shift,
+                                            double* __restrict__ rows, double* __restrict__ end,
+                                            f64x4 (*xch)[NT * NT][64], int w, int lane, int* buf,
+                                            double* la, double* lz, bool* ok) {
+#pragma clang fp contract(off)
+    constexpr int L = 16 * NT, N = L * L, NQ = NT * NT;
+    const bool works = w < NT;
+    const int row = works ? w : 0;  // this wavefront's row block
+    // its elements: tile (row, J), register r; every position is a lattice site
+    const int y0 = 16 * row + (lane >> 4), x0 = lane & 15;
+    auto site = [&](int J, int r) { return (y0 + 4 * r) * L + 16 * J + x0; };
+    TileBig<NT> F;
+    const int ax = a % L, ay = a / L;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            F.t[q][r] = (tb_x<NT>(q, lane) == ax && tb_y<NT>(q, r, lane) == ay) ? 1.0 : 0.0;
+    // column block `row` of C is Cb rotated by it: the operands of the X tiles, picked once (a
+    // run-time index into registers would put them in scratch)
+    double Cr[16];
+#pragma unroll
+    for (int D = 0; D < NT; ++D)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            double v = 0.0;
+#pragma unroll
+            for (int s = 0; s < NT; ++s)
+                if (s == row) v = Cb[4 * ((D - s + NT) % NT) + r];
+            Cr[4 * D + r] = v;  // block (D, row)
+        }
+    auto own_tiles = [&](f64x4 (&H)[NT]) {
+        f64x4 X[NT];  // X(K, row)
+#pragma unroll
+        for (int K = 0; K < NT; ++K) {
+            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int K2 = 0; K2 < NT; ++K2)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(F.t[NT * K2 + K][r], Cr[4 * K2 + r],
+                                                               acc, 0, 0, 0);
+            X[K] = acc;
+        }
+#pragma unroll
+        for (int J = 0; J < NT; ++J) {
+            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int K = 0; K < NT; ++K)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                        X[K][r], Cb[4 * ((K - J + NT) % NT) + r], acc, 0, 0, 0);
+            H[J] = acc;
+        }
+    };
+    bool good = true;
+    double lzv = *la;
+    int bf = *buf;
+    for (int j = 1; j < len; ++j) {
+        const int l = (start + j) % L_tau;
+        f64x4 P[NT];
+        if (works) {
+            double wv[NT][4];
+#pragma unroll
+            for (int J = 0; J < NT; ++J)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) wv[J][r] = Wl0[(int64_t)l * N + site(J, r)];
+            __builtin_amdgcn_sched_barrier(0);  // W in flight during the matrix work
+            own_tiles(P);
+#pragma unroll
+            for (int J = 0; J < NT; ++J) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) P[J][r] *= wv[J][r];
+                xch[bf][NT * row + J][lane] = P[J];
+            }
+        }
+        __syncthreads();
+        if (works) {
+            double sum = 0.0;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                F.t[q] = xch[bf][q][lane];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sum += F.t[q][r];
+            }
+            const double tot = wave_sum_f64(sum);
+            good = good && tot > 0.0 && isfinite(tot);
+            const double inv = 1.0 / tot;
+            lzv += log(tot) + shift[l];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) F.t[q][r] *= inv;
+#pragma unroll
+            for (int J = 0; J < NT; ++J)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) rows[(int64_t)(j - 1) * N + site(J, r)] = P[J][r] * inv;
+        }
+        bf ^= 1;
+    }
+    *buf = bf;
+    if (!works) return false;
+    f64x4 H[NT];  // end weight (C f~ C)(e)
+    own_tiles(H);
+    const int ex = e % L, ey = e / L, re = (ey & 15) >> 2;
+    double hv = 0.0;
+#pragma unroll
+    for (int J = 0; J < NT; ++J)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (end) end[site(J, r)] = H[J][r];
+            if (J == (ex >> 4) && r == re) hv = H[J][r];
+        }
+    hv = __shfl(hv, (ex & 15) + 16 * (ey & 3), 64);
+    *la = lzv;
+    *ok = good && hv > 0.0;
+    *lz = lzv + log(hv);
+    return row == (ey >> 4);
+}
+
 }  // namespace fh

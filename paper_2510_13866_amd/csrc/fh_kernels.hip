@@ -2001,8 +2001,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_rescue_share_fwd4(
     }
 }
 
-// The 48 x 48 and 64 x 64 chains' representatives (NT = 3, 4, fh_dmfma.h), one wavefront each,
-// wavefront w taking entries w, w + n_waves, ... of arep.
+// The 48 x 48 and 64 x 64 chains' representatives (NT = 3, 4), one workgroup each
+// (dmfma_big_wg_forward).
 template <int NT>
 __global__ __launch_bounds__(kThreads, 1) void k_rescue_share_fwd(
     const ChainInfo* __restrict__ chains, const double* __restrict__ cmat64,
@@ -2011,20 +2011,23 @@ __global__ __launch_bounds__(kThreads, 1) void k_rescue_share_fwd(
     double* __restrict__ blk_logz, double* __restrict__ blk_la,
     const uint64_t* __restrict__ sweep_ptr, int32_t* status, const Rescue rsc,
     const DrawTask* __restrict__ arep, int32_t* __restrict__ rep_slot, double* __restrict__ ws,
-    int64_t slot_elems, int n_waves, const double* __restrict__ W64, int64_t aux_elems) {
+    int64_t slot_elems, const double* __restrict__ W64, int64_t aux_elems) {
     static_assert(NT == 3 || NT == 4, "the 16 x 16 tilings");
     constexpr int L = 16 * NT, N = L * L;
+    __shared__ f64x4 xch[2][NT * NT][64];
+    __shared__ int32_t slot_sh;
     const int lane = threadIdx.x & 63;
-    const int wid = __builtin_amdgcn_readfirstlane(blockIdx.x * kWaves + (threadIdx.x >> 6));
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = __builtin_amdgcn_readfirstlane(rsc.words[6]);
     const uint64_t sweep = *sweep_ptr;
-    for (int i = wid; i < n; i += n_waves) {
+    int buf = 0;
+    for (int i = blockIdx.x; i < n; i += gridDim.x) {
         const DrawTask t = arep[i];
         const ChainInfo& c = chains[t.chain];
-        if (c.L != L) continue;  // another launch's chain
-        int slot_id = 0;
-        if (lane == 0) slot_id = atomicAdd(&rsc.words[4], 1);
-        slot_id = __builtin_amdgcn_readfirstlane(__shfl(slot_id, 0, 64));
+        if (c.L != L) continue;  // another launch's chain (the whole workgroup)
+        if (threadIdx.x == 0) slot_sh = atomicAdd(&rsc.words[4], 1);
+        __syncthreads();
+        const int slot_id = slot_sh;
         double* slot = ws + (int64_t)slot_id * slot_elems;
         int start, len;
         block_of(c, sweep, t.block, &start, &len);
@@ -2040,32 +2043,20 @@ __global__ __launch_bounds__(kThreads, 1) void k_rescue_share_fwd(
         double Cb[16];
 #pragma unroll
         for (int q = 0; q < 16; ++q) Cb[q] = cmat64[((int64_t)t.chain * 16 + q) * 64 + lane];
-        const double* Wl0 = W64 + spin * aux_elems + c.aux_off;
-        auto site = [&](int q, int r) { return tb_y<NT>(q, r, lane) * L + tb_x<NT>(q, lane); };
-        auto wtab = [&](int l, double (&w)[4 * NT * NT]) {
-            const double* Wl = Wl0 + (int64_t)l * N;
-#pragma unroll
-            for (int q = 0; q < NT * NT; ++q)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) w[4 * q + r] = Wl[site(q, r)];
-        };
-        auto put = [&](int j, int q, int r, double v) {
-            slot[(int64_t)(j - 1) * N + site(q, r)] = v;
-        };
-        double* end = slot + (int64_t)(c.B - 1) * N;  // after the longest block's rows
-        auto put_end = [&](int q, int r, double v) { end[site(q, r)] = v; };
-        bool ok = true;
-        double la_end = 0.0;
-        const double la0 = coef * (double)aux[c.aux_off + (int64_t)start * N + a];
-        const double lz = dmfma_big_block_forward_end<NT>(Cb, L_tau, start, len, a, e, la0, shift,
-                                                          wtab, put, put_end, &la_end, &ok);
-        if (lane == 0) {
+        double la = coef * (double)aux[c.aux_off + (int64_t)start * N + a], lz;
+        bool ok;
+        if (dmfma_big_wg_forward<NT>(Cb, L_tau, start, len, a, e,
+                                     W64 + spin * aux_elems + c.aux_off, shift, slot,
+                                     slot + (int64_t)(c.B - 1) * N, xch, wv, lane, &buf, &la, &lz,
+                                     &ok) &&
+            lane == 0) {
             const int64_t bi = c.blk_off + (int64_t)t.p * c.nb + t.block;
             if (!ok) set_status(status, FH_ERR_NONFINITE, t.chain);
             blk_logz[bi] = lz;
-            if (c.dedup) blk_la[bi] = la_end;
+            if (c.dedup) blk_la[bi] = la;
             rep_slot[bi] = slot_id;
         }
+        __syncthreads();  // slot_sh and the exchange buffers are free for the next representative
     }
 }
 
@@ -3532,7 +3523,7 @@ hipError_t launch_rescue(fh_plan p, const void* aux, int32_t* paths, bool draw, 
                        p->aux_elems, p->total_slices, rescue_args(p), phase);
     const unsigned blocks = (unsigned)(p->n_rescue_slots / kWaves);
     if (draw && phase == 1) {  // representatives into their slots, then every block's draws
-        // L <= 32: a workgroup per representative; 48 x 48, 64 x 64: a wavefront each
+        // a workgroup per representative, one launch per tiling
         hipLaunchKernelGGL(k_rescue_share_fwd4, dim3(blocks), dim3(kThreads), 0, s, p->d.chains,
                            p->d.cmat64, (const float*)aux, p->d.wshift, p->total_slices, paths,
                            p->d.perm, p->d.blk_logz, p->d.blk_la, p->d.sweep, p->d.status,
@@ -3543,8 +3534,8 @@ hipError_t launch_rescue(fh_plan p, const void* aux, int32_t* paths, bool draw, 
                                p->d.cmat64, (const float*)aux, p->d.wshift, p->total_slices,
                                paths, p->d.perm, p->d.blk_logz, p->d.blk_la, p->d.sweep,
                                p->d.status, rescue_args(p), p->d.arep, p->d.rep_slot,
-                               p->d.rescue_ws, p->rescue_slot_elems, p->n_rescue_slots,
-                               p->d.rescue_w, p->aux_elems);
+                               p->d.rescue_ws, p->rescue_slot_elems, p->d.rescue_w,
+                               p->aux_elems);
         };
         if (p->rescue_l64) fwd(k_rescue_share_fwd<4>);
         if (p->rescue_l48) fwd(k_rescue_share_fwd<3>);

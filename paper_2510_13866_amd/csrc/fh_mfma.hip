@@ -431,7 +431,8 @@ __global__ __launch_bounds__(kThreads) void k_forward_dmfma(
 // k_forward_dmfma for the chains with L = 16 NT, NT = 3 or 4 (48 x 48, 64 x 64): the same
 // recursion on NT x NT tiles of 16 x 16 with the block-circulant operands (fh_dmfma.h). The
 // filter and its product take 2 NT^2 accumulator tiles (256 registers at NT = 4), so one
-// wavefront runs per SIMD.
+// wavefront runs per SIMD. A pass with at most kDmfmaWgTasks recursions gives each a workgroup
+// (dmfma_big_wg_forward).
 template <int NT>
 __global__ __launch_bounds__(kThreads, 1) void k_forward_dmfma_big(
     const ChainInfo* __restrict__ chains, const DrawTask* __restrict__ tasks, int n_tasks,
@@ -442,9 +443,13 @@ __global__ __launch_bounds__(kThreads, 1) void k_forward_dmfma_big(
     const DrawTask* __restrict__ ctasks, const int32_t* __restrict__ ccount,
     double* __restrict__ blk_la) {
     constexpr int L = 16 * NT, N = L * L, NQ = NT * NT;
+    __shared__ f64x4 xch[2][NT * NT][64];
     const int lane = threadIdx.x & 63;
-    const int task = __builtin_amdgcn_readfirstlane(blockIdx.x * kWaves + (threadIdx.x >> 6));
-    if (task >= (ccount ? *ccount : n_tasks)) return;  // whole wavefront; no barriers here
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = __builtin_amdgcn_readfirstlane(ccount ? *ccount : n_tasks);
+    const bool wg = n <= kDmfmaWgTasks;  // uniform over the grid
+    const int task = wg ? (int)blockIdx.x : (int)blockIdx.x * kWaves + wv;
+    if (task >= n) return;  // the whole workgroup where the workgroup has barriers
     const DrawTask t = ccount ? ctasks[task] : tasks[task];
     const ChainInfo& c = chains[t.chain];
     const Fwd64Ctx x = fwd64_ctx(t, c, aux, W, wshift, aux_elems, total_slices, paths, perm, filt,
@@ -467,11 +472,17 @@ __global__ __launch_bounds__(kThreads, 1) void k_forward_dmfma_big(
     auto put_end = [&](int q, int r, double v) {
         if (end) end[site(q, r)] = v;
     };
-    bool ok = true;
-    double la_end;
-    const double lz = dmfma_big_block_forward_end<NT>(Cb, c.L_tau, x.start, x.len, x.a, x.e, x.la,
-                                                      x.shift, wtab, put, put_end, &la_end, &ok);
-    if (lane == 0) {
+    bool ok = true, mine = true;
+    double la_end = x.la, lz;
+    if (wg) {
+        int buf = 0;
+        mine = dmfma_big_wg_forward<NT>(Cb, c.L_tau, x.start, x.len, x.a, x.e, x.W, x.shift, x.rows,
+                                        end, xch, wv, lane, &buf, &la_end, &lz, &ok);
+    } else {
+        lz = dmfma_big_block_forward_end<NT>(Cb, c.L_tau, x.start, x.len, x.a, x.e, x.la, x.shift,
+                                             wtab, put, put_end, &la_end, &ok);
+    }
+    if (mine && lane == 0) {
         const int64_t bi = c.blk_off + (int64_t)t.p * c.nb + t.block;
         if (!ok) set_status(status, FH_ERR_NONFINITE, t.chain);
         blk_logz[bi] = lz;
@@ -2059,10 +2070,12 @@ hipError_t launch_forward_dmfma(fh_plan p, const void* aux, const int32_t* paths
                            p->d.status, shared ? p->d.fwddc_tasks + off : nullptr,
                            shared ? p->d.lists + list : nullptr, p->d.blk_la);
     };
-    if (n2 > 0)
-        run(k_forward_dmfma, 0, n2, kListFwd, std::max(blocks(n2), (unsigned)std::min(n2, kDmfmaWgTasks)));
-    if (n4 > 0) run(k_forward_dmfma_big<4>, n2, n4, kListFwd64, blocks(n4));
-    if (n3 > 0) run(k_forward_dmfma_big<3>, n2 + n4, n3, kListFwd48, blocks(n3));
+    auto grid = [&](int32_t n) {  // a workgroup per recursion, or one per four
+        return std::max(blocks(n), (unsigned)std::min(n, kDmfmaWgTasks));
+    };
+    if (n2 > 0) run(k_forward_dmfma, 0, n2, kListFwd, grid(n2));
+    if (n4 > 0) run(k_forward_dmfma_big<4>, n2, n4, kListFwd64, grid(n4));
+    if (n3 > 0) run(k_forward_dmfma_big<3>, n2 + n4, n3, kListFwd48, grid(n3));
     return hipGetLastError();
 }
 

@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("L,L_tau,n_up,n_dn,block,chains", [
     (2, 6, 3, 2, 0, 1), (4, 16, 8, 8, 0, 1), (8, 13, 20, 9, 4, 3), (9, 10, 11, 12, 0, 2),
     (16, 17, 128, 100, 8, 2), (18, 12, 60, 61, 0, 2), (27, 9, 40, 33, 4, 1),
-    (32, 24, 300, 200, 11, 2), (48, 8, 40, 30, 0, 1), (64, 7, 30, 20, 3, 1)])
+    (32, 24, 300, 200, 11, 2), (48, 8, 40, 30, 0, 1), (64, 7, 30, 20, 3, 1),
+    (48, 5, 150, 120, 0, 1), (64, 6, 200, 90, 3, 1)])
 def test_fp64_shared_forward_filters_change_nothing(L, L_tau, n_up, n_dn, block, chains):
     from paper_2510_13866_amd import fhmc
     from paper_2510_13866_amd.sampler import Sampler
