@@ -203,7 +203,7 @@ hipError_t dalloc(T** p, size_t bytes) {
 
 void free_device(fh::Device& d) {
     void* ptrs[] = {d.chains, d.tables, d.cmat, d.cmat64, d.fwdd_tasks, d.W, d.wshift, d.filt, d.blk_logz, d.dt, d.fwd_tasks,
-                    d.draw_tasks, d.group_tasks, d.gpart, d.ckpt, d.rep, d.blk_la, d.endrow, d.dedup_tasks, d.lists, d.staged, d.members, d.stage_tasks, d.stage_tasks_a, d.grad.list, d.grad.count, d.grad.n, d.grad.of, d.grad.per, d.grad.groups, d.fwddc_tasks, d.fwd32_tasks, d.fwd32c_tasks, d.fwdxc_tasks, d.fwdpc_tasks, d.prep, d.fwdx_tasks, d.fwdp_tasks, d.cmatp, d.cmatb, d.fwd64_tasks, d.draw32_tasks, d.draww_tasks, d.drawx_tasks, d.meas, d.mala, d.perm, d.perm_inv, d.sign, d.bw_state,
+                    d.draw_tasks, d.group_tasks, d.gpart, d.ckpt, d.rep, d.blk_la, d.endrow, d.dedup_tasks, d.lists, d.staged, d.members, d.stage_tasks, d.stage_tasks_a, d.grad.list, d.grad.count, d.grad.n, d.grad.of, d.grad.per, d.grad.groups, d.fwddc_tasks, d.fwd64c_tasks, d.fwd32_tasks, d.fwd32c_tasks, d.fwdxc_tasks, d.fwdpc_tasks, d.prep, d.fwdx_tasks, d.fwdp_tasks, d.cmatp, d.cmatb, d.fwd64_tasks, d.draw32_tasks, d.draww_tasks, d.drawx_tasks, d.meas, d.mala, d.perm, d.perm_inv, d.sign, d.bw_state,
                     d.rescue, d.rescue_list, d.rep_slot, d.arep, d.rescue_ws, d.rescue_w, d.status, d.sweep};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -417,11 +417,9 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
                fp64_circulant(p->chains[c].L);
     };
     std::vector<PairTask> fwdf;
-    // shared forward filters: the 32 x 32 chains of the matrix-core plan (one tile per worldline
-    // pair) and its padded lattices (dedup = 1), and, in the FP64 re-filter of held chains only,
-    // the 48 x 48 and 64 x 64 chains of FP32 plans (dedup = 2); every FP64-circulant chain of an
-    // FP64 plan (dedup = 1, end tiles in the filter workspace); k_dedup runs one workgroup per
-    // (chain, spin, block)
+    // shared forward filters: every chain of the split-bf16 plan and every FP64-circulant chain of
+    // an FP64 plan (dedup = 1); in the FP64 re-filter of held chains only, the 48 x 48 and 64 x 64
+    // chains of FP32 FFT plans (dedup = 2); k_dedup runs one workgroup per (chain, spin, block)
     std::vector<DrawTask> dedup;
     for (int c = 0; c < n_chains; ++c) {
         ChainInfo& ci = p->chains[c];
@@ -430,10 +428,10 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
         const bool packs = ci.L <= kPackMaxL &&
                            (int64_t)ci.np * ci.L_tau * ci.N * 4 < ((int64_t)1 << 31);
         ci.pack = (precision == FH_FP32_MFMA3 && packs) ? pack_blocks(ci.L) : 0;
-        ci.dedup = ((precision == FH_FP32_MFMA3 && ci.L <= 32) || dmfma(c)) ? 1
+        ci.dedup = precision == FH_FP32_MFMA3 || dmfma(c) ? 1
                    : (precision != FH_FP64 && big_nt(ci.L) != 0) ? 2 : 0;
         if (!ci.dedup) continue;
-        if (ci.dedup == 1 && precision != FH_FP64) {
+        if (precision == FH_FP32_MFMA3 && ci.L <= 32) {
             ci.end_off = p->end_elems;
             p->end_elems += (int64_t)ci.np * ci.nb * ci.N;
         }
@@ -612,6 +610,8 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
     if (e == hipSuccess) e = dalloc(&dv.cmatp, sizeof(uint16_t) * p->cmatp.size());
     if (e == hipSuccess) e = dalloc(&dv.cmatb, sizeof(uint16_t) * p->cmatb.size());
     if (e == hipSuccess) e = dalloc(&dv.fwd64_tasks, sizeof(DrawTask) * fwd64.size());
+    if (e == hipSuccess && precision == FH_FP32_MFMA3 && !fwd64.empty())
+        e = dalloc(&dv.fwd64c_tasks, sizeof(DrawTask) * fwd64.size());
     if (e == hipSuccess && !fwd64.empty()) e = hipMemcpy(dv.fwd64_tasks, fwd64.data(), sizeof(DrawTask) * fwd64.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = dalloc(&dv.draw32_tasks, sizeof(DrawTask) * draw32.size());
     if (e == hipSuccess) e = dalloc(&dv.draww_tasks, sizeof(DrawTask) * draww.size());

@@ -50,13 +50,13 @@ struct ChainInfo {
     int32_t ck_k, ck_n;
     // Shared forward filters: the rows of a block depend only on the spin's W and the block's
     // start site, so worldlines of one (spin, block) with the same start site share the rows of
-    // the lowest-numbered of them, their representative. dedup = 1: every chain with L <= 32 of
-    // the split-bf16 plan (32 x 32, padded and packed tiles), in the FP32 passes and the FP64
-    // re-filter's phase A; end_off locates their per-(particle, block) end tiles [N]; and every
-    // chain of an FP64 plan on the FP64 circulant (end tiles in the filter workspace).
-    // dedup = 2: 48 x 48 and 64 x 64 chains of FP32 plans,
-    // in phase A only (their FP32 passes keep one recursion per worldline, and their map is the
-    // identity while the chain is not held).
+    // the lowest-numbered of them, their representative. dedup = 1: every chain of the split-bf16
+    // plan, in the FP32 passes and the FP64 re-filter's phase A (end_off locates the end tiles [N]
+    // per (particle, block) of L <= 32, larger lattices keep them in the filter workspace), and
+    // every chain of an FP64 plan on the FP64 circulant (end tiles in the filter workspace).
+    // dedup = 2: 48 x 48 and 64 x 64 chains of FP32 FFT plans, in phase A only (their FP32 passes
+    // keep one recursion per worldline, and their map is the identity while the chain is not
+    // held).
     int32_t dedup;
     int32_t pack;  // the packed forward's P (4: L <= 8, 2: L <= 16) on the split-bf16 plan, else 0
     int64_t end_off;
@@ -80,6 +80,8 @@ constexpr int kStageMinL = 8;
 // Counts of the dense lists k_dedup fills. On FP64 plans: representatives with L <= 32, L = 64 and
 // L = 48.
 constexpr int kListFwd = 0, kListFwd64 = 1, kListFwd48 = 2;
+// Split-bf16 plans: representatives with L = 64 (kListFwd64) and 32 < L < 64.
+constexpr int kListFwdPad = 2;
 // Tasks of k_backward_stage, and of its phase A launch (the held chains).
 constexpr int kListStage = 3, kListStageA = 4;
 // Worldline groups of the adjoint that hold rings (k_grad_dedup).
@@ -218,6 +220,13 @@ struct Rescue {
     const int32_t* rep;
     const int32_t* staged;  // per (chain, spin, block): 1 if k_backward_stage draws it; nullable
 };
+// The place of block b's end tile of worldline p where it is kept in the filter workspace (FP64
+// plans, and L > 32): the workspace holds L_tau rows per worldline and a sweep's blocks L_tau - nb of
+// them, so the last nb rows are free.
+template <typename T>
+__device__ inline T* end_row_big(T* filt, const ChainInfo& c, int p, int b) {
+    return filt + c.filt_off + ((int64_t)p * c.L_tau + c.L_tau - c.nb + b) * c.N;
+}
 // The worldline whose stored rows block `block` of worldline p reads.
 __device__ inline int row_owner(const Rescue& r, const ChainInfo& c, int p, int block) {
     return r.rep ? r.rep[c.blk_off + (int64_t)p * c.nb + block] : p;
@@ -320,6 +329,7 @@ struct Device {
     DrawTask* stage_tasks = nullptr;
     DrawTask* stage_tasks_a = nullptr;
     GradShare grad = {};              // shared adjoints
+    DrawTask* fwd64c_tasks = nullptr;  // split-bf16: the same, as fwd64_tasks
     DrawTask* fwddc_tasks = nullptr;  // FP64 plans: the representatives k_dedup lists, as fwdd_tasks
     double* dt = nullptr;     // per particle d log Z / d t
     PairTask* fwd_tasks = nullptr;

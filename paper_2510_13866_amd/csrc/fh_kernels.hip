@@ -2181,9 +2181,9 @@ __device__ inline void stage_members(const ChainInfo& c, const DrawTask& t, cons
 // dispatched, spread over the XCDs, instead of sitting at fixed grid positions that map a whole
 // settled batch onto a few compute units. Packed lattices (pack = P) list their representatives
 // in prep (count in words[10]) and P^2 of them to a tile in cpack (P = 2: from the front, count
-// in words[8]; P = 4: from n_p2 on, count in words[9]). FP64 plans list every representative in
-// csingles, by tiling: L <= 32 from the front, 64 x 64 from off64 on, 48 x 48 from off48 on
-// (counts in lists[kListFwd..]).
+// in words[8]; P = 4: from n_p2 on, count in words[9]). Lattices above 32 go to cbig, 64 x 64
+// from off64 on, the others from off48 on; FP64 plans list every representative in csingles,
+// L <= 32 from the front, the larger ones likewise (counts in lists[kListFwd..]).
 __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict__ chains,
                                                     const DrawTask* __restrict__ tasks,
                                                     const int32_t* __restrict__ paths,
@@ -2191,6 +2191,7 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
                                                     int32_t* __restrict__ rep, const Rescue rsc,
                                                     PairTask* __restrict__ cpairs,
                                                     DrawTask* __restrict__ csingles,
+                                                    DrawTask* __restrict__ cbig,
                                                     PackTask* __restrict__ cpack, int n_p2,
                                                     int32_t* __restrict__ prep,
                                                     int32_t* __restrict__ lists, int off64,
@@ -2252,10 +2253,12 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
     // the 32 x 32 chains' representatives go to cpairs, two to a task; the padded lattices'
     // (16 < L < 32, one worldline to a wavefront) to csingles (count in words[7]); the packed
     // ones to cpack
-    const bool fp64 = rsc.words == nullptr;  // FP64 plans: csingles, whatever the lattice
+    // one list per tiling: FP64 plans, whatever the lattice, and the lattices above 32
+    const bool fp64 = rsc.words == nullptr, big = c.L > 32;
     const bool pairs = c.L == 32 && !fp64;
     const int PP = c.pack * c.pack;  // worldlines per packed tile
-    if (c.dedup != 1 || (pairs ? !cpairs : c.pack ? !cpack : !csingles) ||
+    DrawTask* singles = fp64 || !big ? csingles : cbig;
+    if (c.dedup != 1 || (pairs ? !cpairs : c.pack ? !cpack : !singles) ||
         rescue_held(rsc, t.chain))
         return;
     // the representatives in worldline order (first wavefront), then their pairs
@@ -2280,7 +2283,8 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
                 p_base = atomicAdd(&rsc.words[10], cnt);
                 c_base = atomicAdd(&rsc.words[c.pack == 2 ? 8 : 9], (cnt + PP - 1) / PP) +
                          (c.pack == 2 ? 0 : n_p2);
-            } else if (fp64) {  // one list per tiling (launch_forward_dmfma)
+            } else if (fp64 || big) {
+                static_assert(kListFwd48 == kListFwdPad, "the third list of either plan");
                 c_base = c.L <= 32 ? atomicAdd(&lists[kListFwd], cnt)
                          : c.L == 64 ? off64 + atomicAdd(&lists[kListFwd64], cnt)
                                      : off48 + atomicAdd(&lists[kListFwd48], cnt);
@@ -2301,7 +2305,7 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
                                           2 * i + 1 < n_rep ? rlist[2 * i + 1] : -1, t.block};
     } else {
         for (int i = threadIdx.x; i < n_rep; i += blockDim.x)
-            csingles[c_base + i] = DrawTask{t.chain, rlist[i], t.block, 0};
+            singles[c_base + i] = DrawTask{t.chain, rlist[i], t.block, 0};
     }
 }
 
@@ -2310,13 +2314,14 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
 // the end weight and reads its own end weight from the representative's end tile
 // (C f~ C)(e), exactly what its own recursion would have computed; an end weight below
 // kRangeFloor queues the block like the forward kernel's own check.
-// FP64 plans keep the end tiles in the filter workspace's free rows (after the L_tau - nb rows of
-// the blocks), and an end weight that is not positive latches FH_ERR_NONFINITE.
+// FP64 plans and lattices above 32 keep the end tiles in the filter workspace (end_row_big); on
+// FP64 plans an end weight that is not positive latches FH_ERR_NONFINITE.
 template <typename T>
 __global__ void k_member_logz(const ChainInfo* __restrict__ chains, int n_chains,
                               const int32_t* __restrict__ paths, const int32_t* __restrict__ perm,
                               const uint64_t* __restrict__ sweep_ptr,
                               const double* __restrict__ blk_la, const T* __restrict__ endrow,
+                              const T* __restrict__ filt,
                               double* __restrict__ blk_logz, int64_t blk_elems, int32_t* status,
                               const Rescue rsc) {
     const uint64_t sweep = *sweep_ptr;
@@ -2338,10 +2343,11 @@ __global__ void k_member_logz(const ChainInfo* __restrict__ chains, int n_chains
         const int64_t ri = c.blk_off + (int64_t)rp * c.nb + b;
         T hv;
         if constexpr (sizeof(T) == 8) {
-            hv = endrow[c.filt_off + ((int64_t)rp * L_tau + L_tau - c.nb + b) * c.N + e];
+            hv = end_row_big(filt, c, rp, b)[e];
             if (!(hv > 0.0)) set_status(status, FH_ERR_NONFINITE, ci);
         } else {
-            hv = endrow[c.end_off + ((int64_t)rp * c.nb + b) * c.N + e];
+            hv = c.L > 32 ? end_row_big(filt, c, rp, b)[e]
+                          : endrow[c.end_off + ((int64_t)rp * c.nb + b) * c.N + e];
             if (!(hv >= kRangeFloor)) rescue_push(rsc, c, ci, p, b, kCauseEnd);
         }
         blk_logz[i] = blk_la[ri] + log((double)hv);
@@ -3468,12 +3474,14 @@ hipError_t launch_scale_copy(float* dst, const float* src, int64_t n, float fact
 
 hipError_t launch_dedup(fh_plan p, const int32_t* paths, hipStream_t s) {
     if (p->n_dedup_tasks == 0 || p->share_off) return hipSuccess;
+    const bool fp64 = p->precision == FH_FP64;
     hipLaunchKernelGGL(k_dedup, dim3((unsigned)p->n_dedup_tasks), dim3(kThreads), 0, s,
                        p->d.chains, p->d.dedup_tasks, paths, p->d.sweep, p->d.rep, rescue_args(p),
                        p->d.fwd32c_tasks,
-                       p->precision == FH_FP64 ? p->d.fwddc_tasks : p->d.fwdxc_tasks,
+                       fp64 ? p->d.fwddc_tasks : p->d.fwdxc_tasks, p->d.fwd64c_tasks,
                        p->d.fwdpc_tasks, p->n_fwdp2_tasks, p->d.prep, p->d.lists,
-                       p->n_fwdd_tasks, p->n_fwdd_tasks + p->n_fwdd4_tasks,
+                       fp64 ? p->n_fwdd_tasks : 0,
+                       fp64 ? p->n_fwdd_tasks + p->n_fwdd4_tasks : p->n_fwd64_tasks,
                        StageLists{p->d.staged, p->d.members, p->d.stage_tasks,
                                   p->d.stage_tasks_a, (int32_t)p->real_size});
     return hipGetLastError();
@@ -3484,12 +3492,14 @@ hipError_t launch_member_logz(fh_plan p, const int32_t* paths, hipStream_t s) {
     if (p->precision == FH_FP64)
         hipLaunchKernelGGL(k_member_logz<double>, dim3(grid_for(p->blk_elems)), dim3(kThreads), 0,
                            s, p->d.chains, p->n_chains, paths, p->d.perm, p->d.sweep, p->d.blk_la,
-                           (const double*)p->d.filt, p->d.blk_logz, p->blk_elems, p->d.status,
+                           nullptr, (const double*)p->d.filt, p->d.blk_logz, p->blk_elems,
+                           p->d.status,
                            rescue_args(p));
     else
         hipLaunchKernelGGL(k_member_logz<float>, dim3(grid_for(p->blk_elems)), dim3(kThreads), 0,
                            s, p->d.chains, p->n_chains, paths, p->d.perm, p->d.sweep, p->d.blk_la,
-                           p->d.endrow, p->d.blk_logz, p->blk_elems, p->d.status, rescue_args(p));
+                           p->d.endrow, (const float*)p->d.filt, p->d.blk_logz, p->blk_elems,
+                           p->d.status, rescue_args(p));
     return hipGetLastError();
 }
 

@@ -331,11 +331,6 @@ __global__ __launch_bounds__(kThreads, LFIX ? 4 : 2) void k_forward_mfma(
 // one recursion per worldline, 227 us shared; one 4 x 4 chain, L_tau = 16, 45 -> 13 us (one tile).
 constexpr int kDmfmaWgTasks = 256;
 
-// The slot of block b's end tile of worldline p: the filter workspace holds L_tau rows per
-// worldline and a sweep's blocks L_tau - nb of them, so the last nb rows are free.
-__device__ inline double* end_row64(double* filt, const ChainInfo& c, int p, int b) {
-    return filt + c.filt_off + ((int64_t)p * c.L_tau + c.L_tau - c.nb + b) * c.N;
-}
 
 struct Fwd64Ctx {  // what a forward task of the FP64 plans reads
     int start, len, a, e;
@@ -389,7 +384,7 @@ __global__ __launch_bounds__(kThreads) void k_forward_dmfma(
     const Fwd64Ctx x = fwd64_ctx(t, c, aux, W, wshift, aux_elems, total_slices, paths, perm, filt,
                                  *sweep_ptr, status);
     const int L = c.L, N = c.N;
-    double* end = ccount ? end_row64(filt, c, t.p, t.block) : nullptr;
+    double* end = ccount ? end_row_big(filt, c, t.p, t.block) : nullptr;
     const int64_t bi = c.blk_off + (int64_t)t.p * c.nb + t.block;
     bool ok = true, mine = true;
     double lz, la_end = x.la;
@@ -454,7 +449,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_forward_dmfma_big(
     const ChainInfo& c = chains[t.chain];
     const Fwd64Ctx x = fwd64_ctx(t, c, aux, W, wshift, aux_elems, total_slices, paths, perm, filt,
                                  *sweep_ptr, status);
-    double* end = ccount ? end_row64(filt, c, t.p, t.block) : nullptr;
+    double* end = ccount ? end_row_big(filt, c, t.p, t.block) : nullptr;
     double Cb[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) Cb[q] = cmat64[((int64_t)t.chain * 16 + q) * 64 + lane];
@@ -814,13 +809,18 @@ __global__ __launch_bounds__(kThreads) void k_forward_mfma64(
     const double* __restrict__ wshift, int64_t aux_elems, int64_t total_slices,
     const int32_t* __restrict__ paths, const int32_t* __restrict__ perm, float* __restrict__ filt,
     double* __restrict__ blk_logz, const uint64_t* __restrict__ sweep_ptr, int32_t* status,
-    const Rescue rsc, const NegPairs neg) {
+    const Rescue rsc, const NegPairs neg, double* __restrict__ blk_la,
+    const DrawTask* __restrict__ ctasks, const int32_t* __restrict__ ccount) {
     constexpr int NB = PAD ? 4 : 2;  // operand blocks
     const int lane = threadIdx.x & 63;
     const int task = __builtin_amdgcn_readfirstlane(blockIdx.x * kWaves + (threadIdx.x >> 6));
-    if (task >= n_tasks) return;  // whole wavefront; no barriers in this kernel
-    const DrawTask t = tasks[task];
+    // shared forward filters: wavefront i takes representative i of k_dedup's dense list
+    if (task >= (ccount ? *ccount : n_tasks)) return;  // whole wavefront; no barriers here
+    const DrawTask t = ccount ? ctasks[task] : tasks[task];
     const ChainInfo& c = chains[t.chain];
+    // few representatives keep their rows in the cache for the worldlines that read them next
+    const bool cached = ccount && (int64_t)rsc.words[kRescueChain + 3 * rsc.n_chains + t.chain] *
+                                          (c.B - 1) * c.N * 4 <= kCachedRowBytes;
     // re-filtered whole in FP64 this pass (lattices with the FP64 circulant)
     if ((!PAD || fp64_circulant(c.L)) && rescue_held(rsc, t.chain)) return;
     const int L = PAD ? c.L : 64, N = PAD ? c.N : 4096;
@@ -931,8 +931,13 @@ __global__ __launch_bounds__(kThreads) void k_forward_mfma64(
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     F[R][S][v] *= k;
-                    if (inside(R, S, v))
-                        __builtin_nontemporal_store(F[R][S][v], row + 32 * (R * L + S) + vrow(v) * L);
+                    float* at = row + 32 * (R * L + S) + vrow(v) * L;
+                    if (inside(R, S, v)) {
+                        if (cached)
+                            *at = F[R][S][v];
+                        else
+                            __builtin_nontemporal_store(F[R][S][v], at);
+                    }
                 }
     }
     la += block_shift_sum(shift, start, len, L_tau, lsc, lane);
@@ -940,6 +945,16 @@ __global__ __launch_bounds__(kThreads) void k_forward_mfma64(
     f32x16 X[2][2], H[2][2];
     circ64_step<PAD>(F, X, T, neg);
     circ64_step<PAD>(X, H, T, neg);
+    if (ccount) {  // the end tile, for the worldlines that share these rows (k_member_logz)
+        float* end = end_row_big(filt, c, t.p, t.block) + lane_off;
+#pragma unroll
+        for (int R = 0; R < 2; ++R)
+#pragma unroll
+            for (int S = 0; S < 2; ++S)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (inside(R, S, v)) end[32 * (R * L + S) + vrow(v) * L] = H[R][S][v];
+    }
     const int ex = e % L, ey = e / L;
     const int Re = ey >> 5, Se = ex >> 5, ty = ey & 31, tx = ex & 31;
     const int ve = (ty >> 3) * 4 + (ty & 3);
@@ -957,6 +972,7 @@ __global__ __launch_bounds__(kThreads) void k_forward_mfma64(
         if (low || !(hv >= kRangeFloor))
             rescue_push(rsc, c, t.chain, t.p, t.block, low ? kCauseStep : kCauseEnd);
         blk_logz[c.blk_off + (int64_t)t.p * c.nb + t.block] = la + log((double)hv);
+        if (ccount) blk_la[c.blk_off + (int64_t)t.p * c.nb + t.block] = la;
     }
 }
 
@@ -2081,6 +2097,7 @@ hipError_t launch_forward_dmfma(fh_plan p, const void* aux, const int32_t* paths
 
 hipError_t launch_forward_mfma(fh_plan p, const void* aux, const int32_t* paths, hipStream_t s) {
     const bool shared_packs = p->d.fwdpc_tasks && !p->share_off;
+    const bool shared64 = p->d.fwd64c_tasks && !p->share_off;  // L > 32
     auto blocks_for = [](int32_t n) { return (int32_t)((n + kWaves - 1) / kWaves); };
     const int classes = (p->n_fwd32_tasks > 0) + (p->n_fwdx_tasks > 0) + (p->n_fwdp2_tasks > 0) +
                         (p->n_fwdp4_tasks > 0);
@@ -2141,13 +2158,14 @@ hipError_t launch_forward_mfma(fh_plan p, const void* aux, const int32_t* paths,
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (p->n_fwd64_tasks > 0) {  // L = 64: four sub-tiles per worldline
+    if (p->n_fwd64_tasks > 0) {  // L = 64: four sub-tiles per worldline (representative)
         const unsigned blocks = (unsigned)((p->n_fwd64_tasks + kWaves - 1) / kWaves);
         hipLaunchKernelGGL(k_forward_mfma64<false>, dim3(blocks), dim3(kThreads), 0, s, p->d.chains,
                            p->d.fwd64_tasks, p->n_fwd64_tasks, p->d.cmatb, (const float*)aux,
                            (const float*)p->d.W, p->d.wshift, p->aux_elems, p->total_slices,
                            paths, p->d.perm, (float*)p->d.filt, p->d.blk_logz, p->d.sweep, p->d.status,
-                           rescue_args(p), kNegPairs);
+                           rescue_args(p), kNegPairs, p->d.blk_la, p->d.fwd64c_tasks,
+                           shared64 ? p->d.lists + kListFwd64 : nullptr);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -2158,7 +2176,9 @@ hipError_t launch_forward_mfma(fh_plan p, const void* aux, const int32_t* paths,
                            p->d.fwd64_tasks + p->n_fwd64_tasks, p->n_fwd64p_tasks, p->d.cmatb,
                            (const float*)aux, (const float*)p->d.W, p->d.wshift, p->aux_elems,
                            p->total_slices, paths, p->d.perm, (float*)p->d.filt, p->d.blk_logz,
-                           p->d.sweep, p->d.status, rescue_args(p), kNegPairs);
+                           p->d.sweep, p->d.status, rescue_args(p), kNegPairs, p->d.blk_la,
+                           p->d.fwd64c_tasks ? p->d.fwd64c_tasks + p->n_fwd64_tasks : nullptr,
+                           shared64 ? p->d.lists + kListFwdPad : nullptr);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
