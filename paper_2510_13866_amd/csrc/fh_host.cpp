@@ -203,8 +203,8 @@ hipError_t dalloc(T** p, size_t bytes) {
 
 void free_device(fh::Device& d) {
     void* ptrs[] = {d.chains, d.tables, d.cmat, d.cmat64, d.fwdd_tasks, d.W, d.wshift, d.filt, d.blk_logz, d.dt, d.fwd_tasks,
-                    d.draw_tasks, d.group_tasks, d.gpart, d.ckpt, d.rep, d.blk_la, d.endrow, d.dedup_tasks, d.lists, d.staged, d.members, d.stage_tasks, d.stage_tasks_a, d.grad.list, d.grad.count, d.grad.n, d.grad.of, d.grad.per, d.grad.groups, d.fwddc_tasks, d.fwd64c_tasks, d.fwd32_tasks, d.fwd32c_tasks, d.fwdxc_tasks, d.fwdpc_tasks, d.prep, d.fwdx_tasks, d.fwdp_tasks, d.cmatp, d.cmatb, d.fwd64_tasks, d.draw32_tasks, d.draww_tasks, d.drawx_tasks, d.meas, d.mala, d.perm, d.perm_inv, d.sign, d.bw_state,
-                    d.rescue, d.rescue_list, d.rep_slot, d.arep, d.rescue_ws, d.rescue_w, d.status, d.sweep};
+                    d.draw_tasks, d.group_tasks, d.gpart, d.ckpt, d.rep, d.blk_la, d.endrow, d.dedup_tasks, d.lists, d.staged, d.members, d.stage_tasks, d.stage_tasks_s, d.grad.list, d.grad.count, d.grad.n, d.grad.of, d.grad.per, d.grad.groups, d.fwddc_tasks, d.fwd64c_tasks, d.fwd32_tasks, d.fwd32c_tasks, d.fwdxc_tasks, d.fwdpc_tasks, d.prep, d.fwdx_tasks, d.fwdp_tasks, d.cmatp, d.cmatb, d.fwd64_tasks, d.draw32_tasks, d.draww_tasks, d.drawx_tasks, d.meas, d.mala, d.perm, d.perm_inv, d.sign, d.bw_state,
+                    d.rescue, d.rescue_list, d.rep_slot, d.arep, d.arep_b, d.rescue_ws, d.rescue_w, d.status, d.sweep};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     d = fh::Device();
@@ -451,7 +451,7 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
             };
             if (ci.win_on && ci.L >= kStageMinL && ci.N % 4 == 0) {
                 if (ci.dedup == 1) p->n_stage_tasks += (int32_t)(ci.nb * most(p->real_size));
-                if (precision != FH_FP64) p->n_stage_tasks_a += (int32_t)(ci.nb * most(8));
+                if (precision != FH_FP64) p->n_stage_tasks_s += (int32_t)(ci.nb * most(8));
             }
             for (int b = 0; b < ci.nb; ++b) dedup.push_back({c, spin, b, 0});
         }
@@ -563,7 +563,7 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
         if (e == hipSuccess)
             e = dalloc(&dv.stage_tasks, sizeof(DrawTask) * (size_t)p->n_stage_tasks);
         if (e == hipSuccess)
-            e = dalloc(&dv.stage_tasks_a, sizeof(DrawTask) * (size_t)p->n_stage_tasks_a);
+            e = dalloc(&dv.stage_tasks_s, sizeof(DrawTask) * (size_t)p->n_stage_tasks_s);
         if (e == hipSuccess) e = dalloc(&dv.dedup_tasks, sizeof(DrawTask) * dedup.size());
         if (e == hipSuccess)
             e = hipMemcpy(dv.dedup_tasks, dedup.data(), sizeof(DrawTask) * dedup.size(),
@@ -627,6 +627,9 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
         if (e == hipSuccess) e = dalloc(&dv.rescue_list, sizeof(DrawTask) * draw.size());
         if (e == hipSuccess) e = dalloc(&dv.rep_slot, sizeof(int32_t) * (size_t)blk);
         if (e == hipSuccess) e = dalloc(&dv.arep, sizeof(DrawTask) * (size_t)p->n_rescue_slots);
+        p->phase_b = precision == FH_FP32_MFMA3 && (p->rescue_l48 || p->rescue_l64);
+        if (e == hipSuccess && p->phase_b)
+            e = dalloc(&dv.arep_b, sizeof(DrawTask) * (size_t)p->n_rescue_slots);
         if (e == hipSuccess && !ckpt)
             e = dalloc(&dv.rescue_ws, sizeof(double) * (size_t)p->n_rescue_slots * p->rescue_slot_elems);
         if (e == hipSuccess) e = dalloc(&dv.rescue_w, sizeof(double) * 2 * (size_t)aux);

@@ -77,13 +77,16 @@ constexpr int kStageBytes = 32768;
 constexpr int kStageGrid = 1024;
 constexpr int kStageCost = 2048;
 constexpr int kStageMinL = 8;
+// What k_backward_stage draws of a (chain, spin, block): its draws from the plan's rows, and from the
+// FP64 re-filter's slots.
+constexpr int kStagedRows = 1, kStagedSlots = 2;
 // Counts of the dense lists k_dedup fills. On FP64 plans: representatives with L <= 32, L = 64 and
 // L = 48.
 constexpr int kListFwd = 0, kListFwd64 = 1, kListFwd48 = 2;
 // Split-bf16 plans: representatives with L = 64 (kListFwd64) and 32 < L < 64.
 constexpr int kListFwdPad = 2;
-// Tasks of k_backward_stage, and of its phase A launch (the held chains).
-constexpr int kListStage = 3, kListStageA = 4;
+// Tasks of k_backward_stage, and of its launches on the FP64 re-filter's slots.
+constexpr int kListStage = 3, kListStageS = 4;
 // Worldline groups of the adjoint that hold rings (k_grad_dedup).
 constexpr int kListGrad = 5;
 constexpr int kListWords = 16;
@@ -168,16 +171,17 @@ constexpr int64_t kScratchDoubles = (int64_t)1 << 22;
 // of the dense list of the padded lattices' representatives (k_dedup), [8] and [9] entries of
 // the dense lists of packed tiles of representatives (P = 2 and P = 4, k_dedup), [10]
 // representatives listed for those tiles, [11 + k] the blocks queued for floor k since the
-// plan was made (kCause*: never cleared, read by fh_debug_rescue_causes), [15] unused, then per
-// chain: blocks queued by the kernels in this pass
+// plan was made (kCause*: never cleared, read by fh_debug_rescue_causes), [15] and [16] entries of
+// phase B's list of representatives and slots it has taken, [17] chains k_rescue_expand has done,
+// [18] and [19] unused, then per chain: blocks queued by the kernels in this pass
 // (kRescueChain + c), forward passes left on FP64 (kRescueChain + n_chains + c), 1 if the chain
-// is in phase A (kRescueChain + 2 n_chains + c), the forward recursions its blocks need in this
+// is in phase A, 2 in phase B (kRescueChain + 2 n_chains + c), the forward recursions its blocks need in this
 // pass (kRescueChain + 3 n_chains + c: the representatives of the shared filters), the hold at
 // the start of the previous pass (kRescueChain + 4 n_chains + c) and the length of the next
 // hold (kRescueChain + 5 n_chains + c), then one flag per (chain, particle, block) at
 // kRescueChain + kRescuePerChain n_chains + blk_off + p nb + b (the `flags` pointer passed to
 // the kernels).
-constexpr int kRescueChain = 16;
+constexpr int kRescueChain = 20;
 // Why a kernel queued a block (rescue words 11 + cause): a forward step's W-weighted mass below
 // step_floor (or not finite), an end weight below kRangeFloor, a backward draw at a site whose
 // filter value is below kRangeFloor (or with no positive weight), an FFT forward (either floor).
@@ -218,7 +222,7 @@ struct Rescue {
     DrawTask* list;
     int32_t n_chains;
     const int32_t* rep;
-    const int32_t* staged;  // per (chain, spin, block): 1 if k_backward_stage draws it; nullable
+    const int32_t* staged;  // per (chain, spin, block): kStaged* bits; nullable
 };
 // The place of block b's end tile of worldline p where it is kept in the filter workspace (FP64
 // plans, and L > 32): the workspace holds L_tau rows per worldline and a sweep's blocks L_tau - nb of
@@ -327,7 +331,7 @@ struct Device {
     int32_t* staged = nullptr;
     int32_t* members = nullptr;
     DrawTask* stage_tasks = nullptr;
-    DrawTask* stage_tasks_a = nullptr;
+    DrawTask* stage_tasks_s = nullptr;
     GradShare grad = {};              // shared adjoints
     DrawTask* fwd64c_tasks = nullptr;  // split-bf16: the same, as fwd64_tasks
     DrawTask* fwddc_tasks = nullptr;  // FP64 plans: the representatives k_dedup lists, as fwdd_tasks
@@ -369,6 +373,7 @@ struct Device {
     DrawTask* rescue_list = nullptr;  // blocks queued for the FP64 re-filter, [n_draw_tasks]
     int32_t* rep_slot = nullptr;      // phase A: the slot of each representative's block [blk]
     DrawTask* arep = nullptr;         // phase A: its representatives, densely [n_rescue_slots]
+    DrawTask* arep_b = nullptr;       // phase B: the same
     double* rescue_ws = nullptr;      // [n_rescue_slots][rescue_slot_elems] FP64 filter rows
     double* rescue_w = nullptr;       // [2][aux_elems] FP64 W~ of the chains with queued blocks
     int32_t* status = nullptr;   // [0] first error code, [1] its chain
@@ -401,6 +406,7 @@ struct fh_plan_s {
     int32_t n_fwdd_tasks = 0;  // FP64 circulant forward tasks (the FFT takes n_fwd_tasks pairs)
     // after them in fwdd_tasks: the tasks of the 64 x 64, then of the 48 x 48 chains
     int32_t n_fwdd4_tasks = 0, n_fwdd3_tasks = 0;
+    bool phase_b = false;  // a sweep re-filters chains that just left FP32's range in phase B
     bool rescue_l48 = false, rescue_l64 = false;  // FP32 plans: chains the big FP64 re-filter takes
     bool grad_dmfma = false;   // FP64 plan whose chains all have L <= 32: adjoint on the matrix cores
     double win_bound_scale = 1.0;  // test hook: >= 1 inflates every window bound
@@ -410,7 +416,7 @@ struct fh_plan_s {
     int64_t ckpt_elems = 0;     // FH_FLAG_GRAD_CHECKPOINT: checkpoint + segment rows (elements)
     int32_t n_rescue_slots = 0;     // FP32 plans: wavefronts of k_rescue
     int64_t rescuable_blocks = 0;   // FP32 plans: blocks of the chains the FP64 re-filter takes
-    int32_t n_stage_tasks = 0, n_stage_tasks_a = 0;  // most tasks of k_backward_stage in a pass
+    int32_t n_stage_tasks = 0, n_stage_tasks_s = 0;  // most tasks of k_backward_stage in a pass
     int32_t n_dedup_tasks = 0;      // (chain, spin, block) tasks of k_dedup (chains with dedup)
     bool share_off = false;         // fh_debug_share_filters(plan, 0): every worldline its own rows
     int64_t end_elems = 0;          // end tiles of the chains with dedup (f32 elements)

@@ -390,9 +390,11 @@ __global__ void k_logz_reduce(const ChainInfo* __restrict__ chains, int n_chains
     logZ[gp] = s;
 }
 
-// The (chain, spin, block) is drawn by k_backward_stage in this pass (k_dedup's decision).
-__device__ inline bool staged(const Rescue& r, const ChainInfo& c, int p, int block) {
-    return r.staged && r.staged[c.sb_off + (p >= c.n_up ? c.nb : 0) + block] != 0;
+// The (chain, spin, block) is drawn by k_backward_stage in this pass, from the plan's rows or from
+// the FP64 re-filter's slots (k_dedup's decision).
+__device__ inline bool staged(const Rescue& r, const ChainInfo& c, int p, int block,
+                              int what = kStagedRows) {
+    return r.staged && (r.staged[c.sb_off + (p >= c.n_up ? c.nb : 0) + block] & what) != 0;
 }
 
 // A windowed chain's backward tasks sit in the windowed kernel's list and in a full-row
@@ -1068,7 +1070,7 @@ __global__ __launch_bounds__(kThreads) void k_backward_win(
     // a block queued for the FP64 re-filter is drawn by k_rescue (SLOT: by this kernel when its
     // chain is windowed)
     const bool active = listed && (SLOT ? c.win_on != 0 : !rescue_queued(rsc, c, t.p, t.block)) &&
-                        !staged(rsc, c, t.p, t.block);
+                        !staged(rsc, c, t.p, t.block, SLOT ? kStagedSlots : kStagedRows);
     // an inactive group draws nothing; on a one-site lattice its table fill and loads stay minimal
     const int L = active ? c.L : 1, N = active ? c.N : 1, L_tau = c.L_tau, w = c.win_w;
     double* g = gsh[grp] + kWinMaxL;  // g[d] = g(d mod L) for -L < d < L
@@ -1319,8 +1321,8 @@ __global__ __launch_bounds__(kThreads) void k_backward_win(
 // us.
 //
 // Uniforms: producer lane (worldline, t) runs the ten Philox rounds of draw 4 c + t spread over
-// the four slices before chunk c. SLOT: phase A of the FP64 re-filter, rows in the representatives'
-// slots (see k_backward_win).
+// the four slices before chunk c. SLOT: the FP64 re-filter's phases A (see k_backward_win) and B,
+// rows in the representatives' slots.
 constexpr int kStageThreads = 512;
 constexpr int kStageLoads = (int)(kStageBytes / (16 * kThreads));  // 16-B loads per producer lane
 template <int CTRL>
@@ -1472,8 +1474,9 @@ __global__ __launch_bounds__(kStageThreads, 4) void k_backward_stage(
     const int32_t* __restrict__ lists, const int32_t* __restrict__ members,
     const double* __restrict__ tables, const T* __restrict__ filt, int32_t* __restrict__ paths,
     const int32_t* __restrict__ perm, const uint64_t* __restrict__ sweep_ptr, int32_t* status,
-    int32_t* __restrict__ bw_state, int count_uncertified, const Rescue rsc, const SlotRows sr) {
-    static_assert(!SLOT || sizeof(T) == 8, "phase A's rows are FP64");
+    int32_t* __restrict__ bw_state, int count_uncertified, const Rescue rsc, const SlotRows sr,
+    int phase) {
+    static_assert(!SLOT || sizeof(T) == 8, "the re-filter's rows are FP64");
     constexpr int K = 2 * kWinMaxW + 1;
     __shared__ u32x4 rowbuf[2][kStageBytes / 16];
     __shared__ double gsh[2 * kWinMaxL];
@@ -1486,12 +1489,12 @@ __global__ __launch_bounds__(kStageThreads, 4) void k_backward_stage(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint64_t sweep = *sweep_ptr;
-    const int n_tasks = __builtin_amdgcn_readfirstlane(lists[SLOT ? kListStageA : kListStage]);
+    const int n_tasks = __builtin_amdgcn_readfirstlane(lists[SLOT ? kListStageS : kListStage]);
     for (int ti = blockIdx.x; ti < n_tasks; ti += gridDim.x) {
         const DrawTask t = tasks[ti];  // p: first member, pad: member count
         const ChainInfo& c = chains[t.chain];
-        // phase A: only chains admitted to it (the others wait for phase 2)
-        const bool live = !SLOT || rsc.words[kRescueChain + 2 * rsc.n_chains + t.chain] != 0;
+        // the re-filter's launches: only the chains of their phase (the whole workgroup)
+        if (SLOT && rsc.words[kRescueChain + 2 * rsc.n_chains + t.chain] != phase) continue;
         int start, len;
         block_of(c, sweep, t.block, &start, &len);
         const int nd = len - 1;  // draw s sets slice start + (nd - s), s = 0 .. nd - 1
@@ -1509,13 +1512,13 @@ __global__ __launch_bounds__(kStageThreads, 4) void k_backward_stage(
             const int slot = lane < t.pad ? __popcll(fm & ((2ull << lane) - 1)) - 1 : 0;
             if (fresh) {
                 const int64_t ri = c.blk_off + (int64_t)ro * c.nb + t.block;
-                const int64_t row1 = SLOT ? (live ? (int64_t)sr.rep_slot[ri] * sr.slot_elems : 0)
+                const int64_t row1 = SLOT ? (int64_t)sr.rep_slot[ri] * sr.slot_elems
                                           : ((int64_t)ro * L_tau + (int64_t)t.block * (c.B - 1)) * N;
                 src_sh[slot] = (int32_t)(row1 / (16 / (int)sizeof(T)));
             }
             mem_sh[lane] = p;
             slot_sh[lane] = slot;
-            act_sh[lane] = live && lane < t.pad && (SLOT || !rescue_queued(rsc, c, p, t.block));
+            act_sh[lane] = lane < t.pad && (SLOT || !rescue_queued(rsc, c, p, t.block));
             if (lane == 0) nslot_sh = __popcll(fm);
         }
         for (int d = tid; d < L; d += kStageThreads) {
@@ -1835,7 +1838,7 @@ __device__ __attribute__((noinline)) void rescue_draws(const DrawTask& t, const 
 // FP32's range (kRangeFloor). The FP32 pass's rows for such a block hold values at FP32's floor
 // that decide its draws and log Z; FP64 holds them to ~2^-1022. Phase 0 takes the whole queue,
 // phase 1 its phase A [0, words[3]) (a sweep's held chains, beside the FP32 passes), phase 2 the
-// rest (after phase 1 has ended). One wavefront takes queued blocks i = lo + wid,
+// rest (after phase 1 has ended) but for the chains of phase B (k_rescue_expand). One wavefront takes queued blocks i = lo + wid,
 // lo + wid + n_slots, ... in turn, with its own slot of FP64 rows:
 //   forward: the block recursion of k_forward_dmfma on the FP64 circulant, with the FP64
 //            W~ = exp(coef aux - m_l) of k_rescue_potentials (the FP32 tables may hold zeros
@@ -1868,6 +1871,7 @@ __global__ __launch_bounds__(kThreads, NT == 2 ? 2 : 1) void k_rescue(
     for (int i = lo + wid; i < hi; i += n_slots) {
         const DrawTask t = rsc.list[i];
         const ChainInfo& c = chains[t.chain];
+        if (phase == 2 && rsc.words[kRescueChain + 2 * rsc.n_chains + t.chain] == 2) continue;
         if (NT == 2 ? c.L > 32 : c.L != 16 * NT) {  // another launch's chain, or none's
             if (NT == 2 && !fp64_circulant(c.L) && lane == 0)
                 set_status(status, FH_ERR_NONFINITE, t.chain);
@@ -1956,20 +1960,21 @@ __global__ __launch_bounds__(kThreads, 1) void k_rescue_share_fwd4(
     double* __restrict__ blk_logz, double* __restrict__ blk_la,
     const uint64_t* __restrict__ sweep_ptr, int32_t* status, const Rescue rsc,
     const DrawTask* __restrict__ arep, int32_t* __restrict__ rep_slot, double* __restrict__ ws,
-    int64_t slot_elems, const double* __restrict__ W64, int64_t aux_elems) {
+    int64_t slot_elems, const double* __restrict__ W64, int64_t aux_elems, int n_word,
+    int slot_word) {
     static_assert(kWaves == 4, "one wavefront per 16 x 16 tile of the 32 x 32 filter");
     __shared__ f64x4 xch[2][4][64];  // the W-weighted tiles of a step, double-buffered
     __shared__ int32_t slot_sh;
     const int lane = threadIdx.x & 63;
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // this wavefront's tile
-    const int n = __builtin_amdgcn_readfirstlane(rsc.words[6]);
+    const int n = __builtin_amdgcn_readfirstlane(rsc.words[n_word]);
     const uint64_t sweep = *sweep_ptr;
     int buf = 0;
     for (int i = blockIdx.x; i < n; i += gridDim.x) {
         const DrawTask t = arep[i];
         const ChainInfo& c = chains[t.chain];
         if (c.L > 32) continue;  // the 16 x 16 tilings take it (the whole workgroup skips)
-        if (threadIdx.x == 0) slot_sh = atomicAdd(&rsc.words[4], 1);
+        if (threadIdx.x == 0) slot_sh = atomicAdd(&rsc.words[slot_word], 1);
         __syncthreads();
         const int slot_id = slot_sh;
         double* slot = ws + (int64_t)slot_id * slot_elems;
@@ -2011,21 +2016,22 @@ __global__ __launch_bounds__(kThreads, 1) void k_rescue_share_fwd(
     double* __restrict__ blk_logz, double* __restrict__ blk_la,
     const uint64_t* __restrict__ sweep_ptr, int32_t* status, const Rescue rsc,
     const DrawTask* __restrict__ arep, int32_t* __restrict__ rep_slot, double* __restrict__ ws,
-    int64_t slot_elems, const double* __restrict__ W64, int64_t aux_elems) {
+    int64_t slot_elems, const double* __restrict__ W64, int64_t aux_elems, int n_word,
+    int slot_word) {
     static_assert(NT == 3 || NT == 4, "the 16 x 16 tilings");
     constexpr int L = 16 * NT, N = L * L;
     __shared__ f64x4 xch[2][NT * NT][64];
     __shared__ int32_t slot_sh;
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = __builtin_amdgcn_readfirstlane(rsc.words[6]);
+    const int n = __builtin_amdgcn_readfirstlane(rsc.words[n_word]);
     const uint64_t sweep = *sweep_ptr;
     int buf = 0;
     for (int i = blockIdx.x; i < n; i += gridDim.x) {
         const DrawTask t = arep[i];
         const ChainInfo& c = chains[t.chain];
         if (c.L != L) continue;  // another launch's chain (the whole workgroup)
-        if (threadIdx.x == 0) slot_sh = atomicAdd(&rsc.words[4], 1);
+        if (threadIdx.x == 0) slot_sh = atomicAdd(&rsc.words[slot_word], 1);
         __syncthreads();
         const int slot_id = slot_sh;
         double* slot = ws + (int64_t)slot_id * slot_elems;
@@ -2106,15 +2112,14 @@ struct StageLists {
     int32_t* staged;   // [chain's sb_off + spin nb + block] 1 if k_backward_stage draws it
     int32_t* members;  // [chain's blk_off ..]: per (spin, block) its worldlines, sorted
     DrawTask* tasks;   // p: first member's index, pad: member count (counts in lists)
-    DrawTask* tasks_a; // the same for the held chains (phase A)
+    DrawTask* tasks_s; // the same for the re-filter's FP64 rows (its phases A and B)
     int32_t row_size;  // bytes of a stored row's value
 };
 __device__ inline void stage_members(const ChainInfo& c, const DrawTask& t, const int32_t* row,
-                                     int p0, int p1, int rowb, bool held, int32_t* scratch_lds,
-                                     int32_t* lists, const StageLists& st) {
+                                     int p0, int p1, bool rows, bool slots,
+                                     int32_t* scratch_lds, int32_t* lists, const StageLists& st) {
     __shared__ int32_t place[kDedupMaxN];  // counts, then the next free position, per site
     __shared__ int2 part[kWaves];
-    const int R = min(kStageMembers, kStageBytes / rowb);
     const int per = (c.N + kThreads - 1) / kThreads, tid = threadIdx.x, lane = tid & 63;
     for (int i = tid; i < c.N; i += kThreads) place[i] = 0;
     __syncthreads();
@@ -2148,7 +2153,7 @@ __device__ inline void stage_members(const ChainInfo& c, const DrawTask& t, cons
     for (int i = tid * per; i < min((tid + 1) * per, c.N); ++i) {
         const int n = place[i];
         if (n > 0) {
-            if (at.y % R == 0) scratch_lds[at.y / R] = at.x;  // a group's first worldline
+            scratch_lds[at.y] = at.x;  // the start site's first worldline
             ++at.y;
         }
         place[i] = at.x;
@@ -2158,16 +2163,20 @@ __device__ inline void stage_members(const ChainInfo& c, const DrawTask& t, cons
     const int64_t m0 = c.blk_off + (t.p ? (int64_t)c.n_up * c.nb : 0) + (int64_t)t.block * (p1 - p0);
     for (int q = p0 + tid; q < p1; q += kThreads)
         st.members[m0 + atomicAdd(&place[row[q]], 1)] = q;
-    const int groups = (n_occ + R - 1) / R;
-    for (int gi = tid; gi < groups; gi += kThreads) {
-        const int a = scratch_lds[gi], e = gi + 1 < groups ? scratch_lds[gi + 1] : p1 - p0;
-        const int nt = (e - a + kStageMembers - 1) / kStageMembers;
-        const int base = atomicAdd(&lists[held ? kListStageA : kListStage], nt);
-        DrawTask* out = held ? st.tasks_a : st.tasks;
-        for (int k = 0; k < nt; ++k)
-            out[base + k] = DrawTask{t.chain, (int32_t)(m0 + a + k * kStageMembers), t.block,
-                                     min(kStageMembers, e - a - k * kStageMembers)};
-    }
+    auto groups = [&](int rowb, int32_t* count, DrawTask* out) {  // of R start sites each
+        const int R = min(kStageMembers, kStageBytes / rowb);
+        for (int gi = tid; gi * R < n_occ; gi += kThreads) {
+            const int a = scratch_lds[gi * R];
+            const int e = (gi + 1) * R < n_occ ? scratch_lds[(gi + 1) * R] : p1 - p0;
+            const int nt = (e - a + kStageMembers - 1) / kStageMembers;
+            const int base = atomicAdd(count, nt);
+            for (int k = 0; k < nt; ++k)
+                out[base + k] = DrawTask{t.chain, (int32_t)(m0 + a + k * kStageMembers), t.block,
+                                         min(kStageMembers, e - a - k * kStageMembers)};
+        }
+    };
+    if (rows) groups(c.N * st.row_size, &lists[kListStage], st.tasks);
+    if (slots) groups(c.N * 8, &lists[kListStageS], st.tasks_s);
 }
 
 // Shared forward filters, before an FP32 forward pass: one workgroup per (chain, spin, block)
@@ -2234,8 +2243,6 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
         atomicAdd(&rsc.words[kRescueChain + 3 * rsc.n_chains + t.chain], n_rep);
     // worldlines that share rows enough are drawn by k_backward_stage
     {
-        const bool held = rescue_held(rsc, t.chain);
-        const int rowb = c.N * (held ? 8 : st.row_size), n_mem = p1 - p0;
         // Where the line lies: a staged workgroup reads its representatives' whole rows once per
         // slice, the windowed kernel about seven 128-byte lines per worldline and slice (more
         // than half of them misses). 16 x 32 x 32, two sweeps from the start (every worldline its own
@@ -2243,11 +2250,17 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
         // settled batches are the same at all three. Rows of odd lattices (N not a multiple of 4) are not
         // 16-byte aligned, and invalid sites are left to the kernels that report them. Below 8 x 8
         // the window is the lattice, and one wavefront per four worldlines has less to set up.
-        const bool on = c.win_on && c.L >= kStageMinL && c.N % 4 == 0 && !n_bad &&
-                        rowb <= kStageBytes &&
-                        (int64_t)n_rep * rowb <= (int64_t)n_mem * kStageCost;
-        if (threadIdx.x == 0) st.staged[c.sb_off + t.p * c.nb + t.block] = on ? 1 : 0;
-        if (on) stage_members(c, t, row, p0, p1, rowb, held, rlist, lists, st);
+        const bool held = rescue_held(rsc, t.chain), able = c.win_on && c.L >= kStageMinL &&
+                                                            c.N % 4 == 0 && !n_bad;
+        auto on = [&](int rowb) {
+            return able && rowb <= kStageBytes &&
+                   (int64_t)n_rep * rowb <= (int64_t)(p1 - p0) * kStageCost;
+        };
+        const bool rows = !held && on(c.N * st.row_size), slots = rsc.words && on(c.N * 8);
+        if (threadIdx.x == 0)
+            st.staged[c.sb_off + t.p * c.nb + t.block] =
+                (rows ? kStagedRows : 0) | (slots ? kStagedSlots : 0);
+        if (rows || slots) stage_members(c, t, row, p0, p1, rows, slots, rlist, lists, st);
         __syncthreads();  // rlist is free again
     }
     // the 32 x 32 chains' representatives go to cpairs, two to a task; the padded lattices'
@@ -2370,6 +2383,9 @@ __global__ void k_rescue_reset(const Rescue rsc, int64_t n_flags) {
         rsc.words[8] = 0;
         rsc.words[9] = 0;
         rsc.words[10] = 0;
+        rsc.words[15] = 0;
+        rsc.words[16] = 0;
+        rsc.words[17] = 0;
     }
     const int n = rsc.n_chains;
     for (int64_t k = i; k < n; k += stride) {
@@ -2476,24 +2492,55 @@ __global__ __launch_bounds__(kThreads) void k_rescue_held(const ChainInfo* __res
 // After the FP32 forward pass, one workgroup per chain: a chain with more than whole_min blocks
 // queued in this pass, or still held from an earlier such pass, has all its blocks queued for the
 // FP64 re-filter; its hold then counts down (k_rescue_reset sets its length at the next pass).
+// With arep_b (sweeps of plans with a phase B), the last workgroup to finish then admits to phase B
+// the chains queued whole that phase A does not have, in chain order, while their representatives
+// fit the slots (phase A has ended by then) and provided k_backward_stage draws every (spin,
+// block) of theirs: one FP64 recursion per start site instead of one per worldline. A 64 x 64 chain
+// that fails its retry in FP32 took k_rescue 20 ms; phase B takes @PB@ ms.
 __global__ __launch_bounds__(kThreads) void k_rescue_expand(const ChainInfo* __restrict__ chains,
-                                                            const Rescue rsc) {
-    const int ci = blockIdx.x;
+                                                            const Rescue rsc, int n_slots,
+                                                            DrawTask* __restrict__ arep_b) {
+    const int ci = blockIdx.x, n = rsc.n_chains;
     const ChainInfo& c = chains[ci];
     const int cnt = rsc.words[kRescueChain + ci];
-    const int hold = rsc.words[kRescueChain + rsc.n_chains + ci];
+    const int hold = rsc.words[kRescueChain + n + ci];
     const bool many = cnt > c.whole_min;
     const bool whole = many || hold > 0;
     if (whole)
         for (int i = threadIdx.x; i < c.np * c.nb; i += blockDim.x)
             rescue_enqueue(rsc, c, ci, i / c.nb, i % c.nb);
     __syncthreads();  // every thread read the count and the hold before they change
+    __shared__ int last;
     if (threadIdx.x == 0) {
-        rsc.words[kRescueChain + rsc.n_chains + ci] = many ? kRescueHold : max(hold - 1, 0);
+        rsc.words[kRescueChain + n + ci] = many ? kRescueHold : max(hold - 1, 0);
         if (whole) {
             atomicAdd(&rsc.words[2], 1);
             rsc.words[kRescueChain + ci] = cnt + c.np * c.nb;  // the chain has queued blocks
         }
+        __threadfence();
+        last = arep_b ? atomicAdd(&rsc.words[17], 1) == n - 1 : 0;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    int slots = 0;
+    for (int k = 0; k < n; ++k) {
+        const ChainInfo& ck = chains[k];
+        const volatile int32_t* words = rsc.words;
+        const int nrec = words[kRescueChain + 3 * n + k], blocks = ck.np * ck.nb;
+        if (ck.dedup != 1 || !fp64_circulant(ck.L) || words[kRescueChain + k] < blocks ||
+            words[kRescueChain + 2 * n + k] != 0 || slots + nrec > n_slots)
+            continue;  // uniform
+        bool all = true;
+        for (int i = threadIdx.x; i < 2 * ck.nb; i += blockDim.x)
+            all = all && ((i < ck.nb ? ck.n_up : ck.n_dn) == 0 ||
+                          (rsc.staged[ck.sb_off + i] & kStagedSlots) != 0);
+        if (!__syncthreads_and(all)) continue;
+        slots += nrec;
+        for (int i = threadIdx.x; i < blocks; i += blockDim.x)  // i = p nb + block
+            if (rsc.rep[ck.blk_off + i] == i / ck.nb)
+                arep_b[atomicAdd(&rsc.words[15], 1)] = DrawTask{k, i / ck.nb, i % ck.nb, 0};
+        if (threadIdx.x == 0) rsc.words[kRescueChain + 2 * n + k] = 2;
     }
 }
 
@@ -2507,7 +2554,7 @@ __global__ __launch_bounds__(kThreads) void k_rescue_potentials(
     int64_t total_slices, const Rescue rsc, int phase) {
     const int gs = blockIdx.x;
     const int ci = find_chain(n_chains, gs, [&](int i) { return chains[i].slice_off; });
-    const bool in_a = rsc.words[kRescueChain + 2 * n_chains + ci] != 0;
+    const bool in_a = rsc.words[kRescueChain + 2 * n_chains + ci] == 1;
     const bool queued = phase == 1 ? in_a
                                    : rsc.words[kRescueChain + ci] != 0 && !(phase == 2 && in_a);
     if (!queued) return;  // nothing of this chain is in this phase
@@ -3395,7 +3442,7 @@ hipError_t launch_backward_kernels(fh_plan p, int32_t* paths, hipStream_t s) {
                                dim3(kStageThreads), 0, s, p->d.chains, p->d.stage_tasks,
                                p->d.lists, p->d.members, p->d.tables, filt, paths, p->d.perm,
                                p->d.sweep, p->d.status, p->d.bw_state, p->bw_adapt ? 1 : 0,
-                               rescue_args(p), SlotRows{});
+                               rescue_args(p), SlotRows{}, 0);
         };
         if (p->precision == FH_FP64)
             run(k_backward_stage<double, false>, (const double*)p->d.filt);
@@ -3483,7 +3530,7 @@ hipError_t launch_dedup(fh_plan p, const int32_t* paths, hipStream_t s) {
                        fp64 ? p->n_fwdd_tasks : 0,
                        fp64 ? p->n_fwdd_tasks + p->n_fwdd4_tasks : p->n_fwd64_tasks,
                        StageLists{p->d.staged, p->d.members, p->d.stage_tasks,
-                                  p->d.stage_tasks_a, (int32_t)p->real_size});
+                                  p->d.stage_tasks_s, (int32_t)p->real_size});
     return hipGetLastError();
 }
 
@@ -3513,7 +3560,8 @@ hipError_t launch_rescue_reset(fh_plan p, hipStream_t s) {
 hipError_t launch_rescue_expand(fh_plan p, hipStream_t s) {
     if (!p->d.rescue) return hipSuccess;
     hipLaunchKernelGGL(k_rescue_expand, dim3(p->n_chains), dim3(kThreads), 0, s, p->d.chains,
-                       rescue_args(p));
+                       rescue_args(p), p->n_rescue_slots,
+                       p->phase_b && !p->share_off ? p->d.arep_b : nullptr);
     return hipGetLastError();
 }
 
@@ -3532,34 +3580,36 @@ hipError_t launch_rescue(fh_plan p, const void* aux, int32_t* paths, bool draw, 
                        p->d.chains, p->n_chains, (const float*)aux, p->d.wshift, p->d.rescue_w,
                        p->aux_elems, p->total_slices, rescue_args(p), phase);
     const unsigned blocks = (unsigned)(p->n_rescue_slots / kWaves);
-    if (draw && phase == 1) {  // representatives into their slots, then every block's draws
-        // a workgroup per representative, one launch per tiling
-        hipLaunchKernelGGL(k_rescue_share_fwd4, dim3(blocks), dim3(kThreads), 0, s, p->d.chains,
-                           p->d.cmat64, (const float*)aux, p->d.wshift, p->total_slices, paths,
-                           p->d.perm, p->d.blk_logz, p->d.blk_la, p->d.sweep, p->d.status,
-                           rescue_args(p), p->d.arep, p->d.rep_slot, p->d.rescue_ws,
-                           p->rescue_slot_elems, p->d.rescue_w, p->aux_elems);
+    // representatives into their slots (phase B: chains phase A does not have), a workgroup per
+    // representative and one launch per tiling, then their worldlines' staged draws
+    auto share = [&](bool b) {
         auto fwd = [&](auto kern) {
             hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, s, p->d.chains,
                                p->d.cmat64, (const float*)aux, p->d.wshift, p->total_slices,
                                paths, p->d.perm, p->d.blk_logz, p->d.blk_la, p->d.sweep,
-                               p->d.status, rescue_args(p), p->d.arep, p->d.rep_slot,
-                               p->d.rescue_ws, p->rescue_slot_elems, p->d.rescue_w,
-                               p->aux_elems);
+                               p->d.status, rescue_args(p), b ? p->d.arep_b : p->d.arep,
+                               p->d.rep_slot, p->d.rescue_ws, p->rescue_slot_elems,
+                               p->d.rescue_w, p->aux_elems, b ? 15 : 6, b ? 16 : 4);
         };
+        fwd(k_rescue_share_fwd4);
         if (p->rescue_l64) fwd(k_rescue_share_fwd<4>);
         if (p->rescue_l48) fwd(k_rescue_share_fwd<3>);
-        // the draws: windowed chains from the slots' FP64 rows, staged or four blocks to a
-        // wavefront, the others one block to a wavefront (they take no slot: twice the slot count of them)
-        if (p->n_stage_tasks_a > 0 && !p->share_off)
+        if (p->n_stage_tasks_s > 0 && !p->share_off)
             hipLaunchKernelGGL((k_backward_stage<double, true>),
-                               dim3((unsigned)std::min(p->n_stage_tasks_a, kStageGrid)),
-                               dim3(kStageThreads), 0, s, p->d.chains, p->d.stage_tasks_a,
+                               dim3((unsigned)std::min(p->n_stage_tasks_s, kStageGrid)),
+                               dim3(kStageThreads), 0, s, p->d.chains, p->d.stage_tasks_s,
                                p->d.lists, p->d.members, p->d.tables, (const double*)nullptr,
                                paths, p->d.perm, p->d.sweep, p->d.status, p->d.bw_state, 0,
                                rescue_args(p),
                                SlotRows{p->d.rep_slot, p->d.rescue_ws, p->rescue_slot_elems,
-                                        p->d.blk_logz, p->d.blk_la});
+                                        p->d.blk_logz, p->d.blk_la},
+                               b ? 2 : 1);
+    };
+    if (draw && phase == 2 && p->phase_b) share(true);
+    if (draw && phase == 1) {
+        share(false);
+        // the draws: windowed chains from the slots' FP64 rows, staged or four blocks to a
+        // wavefront, the others one block to a wavefront (they take no slot: twice the slot count of them)
         const unsigned wblocks = (unsigned)((p->rescuable_blocks + kThreads / kWinLanes - 1) /
                                             (kThreads / kWinLanes));
         hipLaunchKernelGGL((k_backward_win<double, true>), dim3(wblocks), dim3(kThreads), 0, s,
