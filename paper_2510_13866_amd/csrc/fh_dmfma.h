@@ -531,7 +531,7 @@ __device__ inline double dmfma_big_block_forward_end(const double (&Cb)[16], int
 // *la enters as log W_start(a) and leaves as log Z without the end weight; *lz receives log Z on
 // the wavefront that gets true. Wavefronts past NT only meet the barriers.
 // Bound: FP64 products, 2 NT^2 (NT = 4: 128) of 64 cycles a wavefront and step; a 64 x 64 step took
-// 18.6 us on one wavefront, @BIG@ us here.
+// 18.6 us on one wavefront, 4.6 us here.
 template <int NT>
 __device__ inline bool dmfma_big_wg_forward(const double (&Cb)[16], int L_tau, int start, int len,
                                             int a, int e, const double* __restrict__ Wl0,

@@ -2496,7 +2496,9 @@ __global__ __launch_bounds__(kThreads) void k_rescue_held(const ChainInfo* __res
 // the chains queued whole that phase A does not have, in chain order, while their representatives
 // fit the slots (phase A has ended by then) and provided k_backward_stage draws every (spin,
 // block) of theirs: one FP64 recursion per start site instead of one per worldline. A 64 x 64 chain
-// that fails its retry in FP32 took k_rescue 20 ms; phase B takes @PB@ ms.
+// that fails its retry in FP32 took k_rescue 20 ms and takes phase B 1 ms. Plans without 48 x 48 or 64 x 64 chains do
+// without: the settled 32 x 32 batch lost 19 us a sweep to the two launches, and its burn-in, whose
+// chains have a start site for nearly every worldline, gained nothing.
 __global__ __launch_bounds__(kThreads) void k_rescue_expand(const ChainInfo* __restrict__ chains,
                                                             const Rescue rsc, int n_slots,
                                                             DrawTask* __restrict__ arep_b) {
