@@ -762,12 +762,10 @@ static hipError_t mark(fh_plan p, int k, hipStream_t s) {
     return p->timing ? hipEventRecord(p->tev[k], s) : hipSuccess;
 }
 
-// The forward kernels of a pass, from the shared-filter map (unless the caller ran it) to the
-// whole-chain queue.
+// The forward kernels of a pass, after the shared-filter map, to the whole-chain queue.
 static hipError_t enqueue_forward_kernels(fh_plan p, const void* aux, const int32_t* paths,
-                                          hipStream_t s, bool dedup = true) {
+                                          bool sweep, hipStream_t s) {
     hipError_t e = mark(p, 0, s);
-    if (e == hipSuccess && dedup) e = launch_dedup(p, paths, s);  // shared forward filters
     if (e != hipSuccess) return e;
     if (p->precision == FH_FP32_MFMA3) {
         e = launch_forward_mfma(p, aux, paths, s);
@@ -775,16 +773,16 @@ static hipError_t enqueue_forward_kernels(fh_plan p, const void* aux, const int3
         e = launch_forward_dmfma(p, aux, paths, s);  // FP64 plans: the FP64 circulant chains
         if (e == hipSuccess && p->n_fwd_tasks > 0) e = launch_forward(p, aux, paths, s);
     }
-    if (e == hipSuccess) e = launch_member_logz(p, paths, s);
+    // (an FP64 sweep's Gibbs launch does it: nothing before reads it)
+    if (e == hipSuccess && !(sweep && p->precision == FH_FP64)) e = launch_member_logz(p, paths, s);
     if (e == hipSuccess) e = mark(p, 1, s);
-    if (e == hipSuccess) e = launch_rescue_expand(p, s);  // FP32: chains re-filtered whole
     return e;
 }
 
 static hipError_t enqueue_forward(fh_plan p, const void* aux, const int32_t* paths, hipStream_t s) {
-    hipError_t e = launch_potentials(p, aux, s);
-    if (e == hipSuccess) e = launch_rescue_reset(p, s);  // FP32 plans: empty re-filter queue
-    if (e == hipSuccess) e = enqueue_forward_kernels(p, aux, paths, s);
+    hipError_t e = launch_potentials(p, aux, true, false, s);
+    if (e == hipSuccess) e = launch_dedup(p, paths, false, s);  // shared forward filters
+    if (e == hipSuccess) e = enqueue_forward_kernels(p, aux, paths, false, s);
     return e;
 }
 
@@ -825,7 +823,7 @@ int fh_backward_sample(fh_plan p, int32_t* paths, uint64_t sweep, fh_stream stre
         return FH_ERR_STATE;
     hipStream_t s = (hipStream_t)stream;
     FH_TRY(launch_set_sweep(p, sweep, s));
-    FH_TRY(launch_backward(p, paths, s));
+    FH_TRY(launch_backward(p, paths, true, s));
     FH_TRY(launch_rescue(p, p->last_aux, paths, true, 0, s));  // blocks out of FP32's range
     return FH_OK;
 }
@@ -834,7 +832,7 @@ int fh_gibbs_aux(fh_plan p, const int32_t* paths, void* aux, uint64_t sweep, fh_
     if (!p || !paths || !aux) return FH_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     FH_TRY(launch_set_sweep(p, sweep, s));
-    FH_TRY(launch_gibbs(p, paths, aux, s));
+    FH_TRY(launch_gibbs(p, paths, aux, false, s));
     p->have_filters = false;
     return FH_OK;
 }
@@ -930,15 +928,14 @@ int fh_measure_noalloc(fh_plan p, const int32_t* paths, double* Sk, double* Cr, 
 // caller's stream once phase A has ended. The two touch disjoint chains: phase A writes the
 // held chains' sites and block log Z, which the FP32 kernels skip (held at the pass start, or
 // queued); the Gibbs draw reads every site after the join.
-static hipError_t enqueue_sweep_body(fh_plan p, void* aux, int32_t* paths, hipStream_t s) {
+static hipError_t enqueue_sweep_body(fh_plan p, void* aux, int32_t* paths, bool bump,
+                                     hipStream_t s) {
     const bool split = p->side_stream != nullptr;
-    hipError_t e = launch_potentials(p, aux, s);
-    if (e == hipSuccess) e = launch_rescue_reset(p, s);
+    hipError_t e = launch_potentials(p, aux, true, bump, s);
     // the shared-filter map first: phase A sizes by it and reads it beside the forward pass
-    if (e == hipSuccess && split) e = launch_dedup(p, paths, s);
+    if (e == hipSuccess) e = launch_dedup(p, paths, split, s);
     if (split) {
         hipStream_t side = p->side_stream;
-        if (e == hipSuccess) e = launch_rescue_held(p, s);
         if (e == hipSuccess) e = hipEventRecord(p->fork_ev, s);
         if (e == hipSuccess) e = hipStreamWaitEvent(side, p->fork_ev, 0);
         if (e == hipSuccess) e = mark(p, 5, side);
@@ -946,14 +943,14 @@ static hipError_t enqueue_sweep_body(fh_plan p, void* aux, int32_t* paths, hipSt
         if (e == hipSuccess) e = mark(p, 6, side);
         if (e == hipSuccess) e = hipEventRecord(p->join_ev, side);
     }
-    if (e == hipSuccess) e = enqueue_forward_kernels(p, aux, paths, s, !split);
+    if (e == hipSuccess) e = enqueue_forward_kernels(p, aux, paths, true, s);
     if (e == hipSuccess) e = mark(p, 2, s);
-    if (e == hipSuccess) e = launch_backward(p, paths, s);
+    if (e == hipSuccess) e = launch_backward(p, paths, false, s);
     if (e == hipSuccess) e = mark(p, 3, s);
     if (e == hipSuccess && split) e = hipStreamWaitEvent(s, p->join_ev, 0);
     if (e == hipSuccess) e = launch_rescue(p, aux, paths, true, split ? 2 : 0, s);
     if (e == hipSuccess) e = mark(p, 4, s);
-    if (e == hipSuccess) e = launch_gibbs(p, paths, aux, s);
+    if (e == hipSuccess) e = launch_gibbs(p, paths, aux, true, s);
     return e;
 }
 
@@ -961,8 +958,7 @@ static int capture_sweep(fh_plan p, void* aux, int32_t* paths) {
     drop_graph(p);
     hipStream_t cs = p->capture_stream;
     FH_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-    hipError_t e = enqueue_sweep_body(p, aux, paths, cs);
-    if (e == hipSuccess) e = launch_bump_sweep(p, cs);
+    hipError_t e = enqueue_sweep_body(p, aux, paths, true, cs);
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(cs, &g);
     if (e != hipSuccess || e2 != hipSuccess) {
@@ -995,12 +991,12 @@ int fh_sweep(fh_plan p, void* aux, int32_t* paths, uint64_t first_sweep, int32_t
             int rc = capture_sweep(p, aux, paths);
             if (rc != FH_OK) return rc;
         }
-        FH_TRY(launch_set_sweep(p, first_sweep, s));
+        FH_TRY(launch_set_sweep(p, first_sweep - 1, s));  // a replay advances the index first
         for (int32_t i = 0; i < n_sweeps; ++i) FH_TRY(hipGraphLaunch(p->graph_exec, s));
     } else {
         for (int32_t i = 0; i < n_sweeps; ++i) {
             FH_TRY(launch_set_sweep(p, first_sweep + (uint64_t)i, s));
-            FH_TRY(enqueue_sweep_body(p, aux, paths, s));
+            FH_TRY(enqueue_sweep_body(p, aux, paths, false, s));
         }
     }
     p->have_filters = false;
@@ -1010,7 +1006,7 @@ int fh_sweep(fh_plan p, void* aux, int32_t* paths, uint64_t first_sweep, int32_t
 static hipError_t enqueue_logz_grad(fh_plan p, const void* aux, const int32_t* paths,
                                     int32_t anchor_slice, double* logZ, void* grad_aux,
                                     double* grad_t, hipStream_t s) {
-    hipError_t e = launch_potentials(p, aux, s);
+    hipError_t e = launch_potentials(p, aux, false, false, s);
     if (e == hipSuccess) e = launch_grad_dedup(p, paths, anchor_slice, s);
     if (e != hipSuccess) return e;
     if (p->precision == FH_FP32_MFMA3) {

@@ -89,6 +89,8 @@ constexpr int kListFwdPad = 2;
 constexpr int kListStage = 3, kListStageS = 4;
 // Worldline groups of the adjoint that hold rings (k_grad_dedup).
 constexpr int kListGrad = 5;
+// Workgroups of k_dedup and of k_member_logz that have finished.
+constexpr int kListDone = 6, kListDoneM = 7;
 constexpr int kListWords = 16;
 constexpr int kCmatPerChain = 3 * 2 * 64 * 8;
 constexpr int kCmat64PerChain = 16 * 64;
@@ -470,25 +472,22 @@ inline Rescue rescue_args(fh_plan p) {
 
 // Kernel launchers (fh_kernels.hip / fh_mfma.hip). All enqueue on `s` and return hipError_t.
 hipError_t launch_set_sweep(fh_plan p, uint64_t sweep, hipStream_t s);
-hipError_t launch_bump_sweep(fh_plan p, hipStream_t s);
-hipError_t launch_potentials(fh_plan p, const void* aux, hipStream_t s);
+// pass: a forward pass follows (its re-filter queue is emptied); bump: the sweep index advances.
+hipError_t launch_potentials(fh_plan p, const void* aux, bool pass, bool bump, hipStream_t s);
 hipError_t launch_forward(fh_plan p, const void* aux, const int32_t* paths, hipStream_t s);
 hipError_t launch_forward_dmfma(fh_plan p, const void* aux, const int32_t* paths, hipStream_t s);
 hipError_t launch_grad_dmfma(fh_plan p, const void* aux, const int32_t* paths, int32_t anchor,
                              void* grad_aux, hipStream_t s);
 hipError_t launch_forward_mfma(fh_plan p, const void* aux, const int32_t* paths, hipStream_t s);
 hipError_t launch_logz_reduce(fh_plan p, double* logZ, hipStream_t s);
-hipError_t launch_backward(fh_plan p, int32_t* paths, hipStream_t s);
-// FP32 plans: clears the rescue queue (before a forward pass), queues whole chains (after it),
-// and re-filters (and, with draw, redraws) the queued blocks in FP64. No-ops for FP64 plans.
-// Before an FP32 forward pass: the representative map of the shared forward filters.
-hipError_t launch_dedup(fh_plan p, const int32_t* paths, hipStream_t s);
-// After it: log Z and end-weight floors of the worldlines that share a representative's rows.
+// adapt: choose the next pass's kernels too (a sweep's Gibbs launch does it otherwise).
+hipError_t launch_backward(fh_plan p, int32_t* paths, bool adapt, hipStream_t s);
+// Before a forward pass: the representative map of the shared forward filters; with phase_a (an
+// FP32 sweep) the held chains are then queued whole as phase A.
+hipError_t launch_dedup(fh_plan p, const int32_t* paths, bool phase_a, hipStream_t s);
+// After it: log Z and end-weight floors of the worldlines that share a representative's rows;
+// FP32 plans then queue whole chains.
 hipError_t launch_member_logz(fh_plan p, const int32_t* paths, hipStream_t s);
-hipError_t launch_rescue_reset(fh_plan p, hipStream_t s);
-hipError_t launch_rescue_expand(fh_plan p, hipStream_t s);  // after the FP32 forward pass
-// Before a sweep's FP32 forward pass: queues the held chains whole as phase A.
-hipError_t launch_rescue_held(fh_plan p, hipStream_t s);
 // The FP64 re-filter of the queue: phase 0 all of it, 1 phase A, 2 the rest (after phase A).
 // Phase A runs the representatives' recursions into their slots, then every block's draws from
 // its representative's slot (launch_rescue with phase 1).
@@ -498,7 +497,8 @@ hipError_t launch_rescue(fh_plan p, const void* aux, int32_t* paths, bool draw, 
 // default order unless another is faster by more than 2%); timings are appended to *log.
 hipError_t tune_radix_plan(fh_plan p, int L, const double* tw_dev, hipStream_t s,
                            RadixPlan* best, std::vector<TuneRecord>* log);
-hipError_t launch_gibbs(fh_plan p, const int32_t* paths, void* aux, hipStream_t s);
+// sweep: with what else ends a sweep (k_gibbs).
+hipError_t launch_gibbs(fh_plan p, const int32_t* paths, void* aux, bool sweep, hipStream_t s);
 hipError_t launch_local(fh_plan p, const void* aux, int32_t* paths, int n_passes, hipStream_t s);
 hipError_t launch_perm_update(fh_plan p, const int32_t* paths, int n_passes, hipStream_t s);
 // `work`: 2 aux_elems + 2 total_slices doubles of per-slice rows (the plan's, or the static scratch).

@@ -257,14 +257,53 @@ __global__ void k_set_u64(uint64_t* p, uint64_t v) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
 }
 
-__global__ void k_bump_u64(uint64_t* p) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *p = *p + 1;
-}
-
 __global__ void k_zero(uint32_t* p, int64_t words) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < words;
          i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0u;
+}
+
+// Before a forward pass (thread i of stride): an empty queue, no block flagged, no chain counted or in phase A (the
+// per-chain holds and the redrawn total stay).
+__device__ inline void rescue_reset(const Rescue& rsc, int64_t n_flags, int64_t i,
+                                    int64_t stride) {
+    if (i == 0) {
+        rsc.words[0] = 0;
+        rsc.words[2] = 0;
+        rsc.words[3] = 0;
+        rsc.words[4] = 0;
+        rsc.words[5] = 0;
+        rsc.words[6] = 0;
+        rsc.words[7] = 0;
+        rsc.words[8] = 0;
+        rsc.words[9] = 0;
+        rsc.words[10] = 0;
+        rsc.words[15] = 0;
+        rsc.words[16] = 0;
+        rsc.words[17] = 0;
+    }
+    const int n = rsc.n_chains;
+    for (int64_t k = i; k < n; k += stride) {
+        rsc.words[kRescueChain + k] = 0;
+        rsc.words[kRescueChain + 2 * n + k] = 0;
+        rsc.words[kRescueChain + 3 * n + k] = 0;
+        // the hold: a chain that entered the previous pass in FP32 and left it held failed its
+        // retry (or first met a floor): hold it for the current length, and double that for
+        // the next failure; a pass in FP32 that queued nothing resets the length
+        int hold = rsc.words[kRescueChain + n + k];
+        const int hold0 = rsc.words[kRescueChain + 4 * n + k];
+        int len = max(rsc.words[kRescueChain + 5 * n + k], kRescueHold);
+        if (hold0 == 0 && hold > 0) {
+            hold = len;
+            len = min(2 * len, kRescueHoldMax);
+        } else if (hold0 == 0) {
+            len = kRescueHold;
+        }
+        rsc.words[kRescueChain + n + k] = hold;
+        rsc.words[kRescueChain + 4 * n + k] = hold;
+        rsc.words[kRescueChain + 5 * n + k] = len;
+    }
+    for (int64_t k = i; k < n_flags; k += stride) rsc.flags[k] = 0;
 }
 
 // Site potentials of one (chain, slice) in log-domain-shifted form (eq. hirsch / eq. gaussHS):
@@ -273,16 +312,25 @@ __global__ void k_zero(uint32_t* p, int64_t words) {
 // kWScaleLog2 ln 2, so W~ <= 2^60), and m is kept in FP64 and added back to log Z. Filters are
 // normalised per step, so the shift changes nothing else.
 // W[0 .. aux_elems) holds spin up, W[aux_elems .. 2 aux_elems) spin down.
+// The first kernel of every pass, so what a pass starts with is done here and takes no launch of
+// its own (about 4 us each on the critical path of a captured sweep): the dense lists' counts are
+// zeroed, with n_flags > 0 the re-filter's queue is reset, and with bump the sweep index of a
+// captured sweep advances.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_potentials(const ChainInfo* __restrict__ chains,
                                                          int n_chains, const T* __restrict__ aux,
                                                          T* __restrict__ W, double* __restrict__ wshift,
                                                          int64_t aux_elems, int64_t total_slices,
-                                                         int32_t* status, int32_t* lists) {
+                                                         int32_t* status, int32_t* lists,
+                                                         const Rescue rsc, int64_t n_flags,
+                                                         uint64_t* bump) {
     __shared__ double red[2 * kWaves];
     const int gs = blockIdx.x;
-    // the pass's dense lists start empty (k_dedup fills them after this kernel)
-    if (lists && gs == 0 && threadIdx.x < kListWords) lists[threadIdx.x] = 0;
+    if (gs == 0 && threadIdx.x < kListWords) lists[threadIdx.x] = 0;
+    if (bump && gs == 0 && threadIdx.x == 0) *bump += 1;
+    if (n_flags > 0)
+        rescue_reset(rsc, n_flags, gs * (int64_t)kThreads + threadIdx.x,
+                     (int64_t)gridDim.x * kThreads);
     const int ci = find_chain(n_chains, gs, [&](int i) { return chains[i].slice_off; });
     const ChainInfo& c = chains[ci];
     const int64_t base = c.aux_off + (int64_t)(gs - c.slice_off) * c.N;
@@ -1945,8 +1993,8 @@ __global__ __launch_bounds__(kThreads, NT == 2 ? 2 : 1) void k_rescue(
 }
 
 // Phase A of the FP64 re-filter (the held chains, beside the FP32 passes), first kernels: the
-// forward recursion of each representative in the dense list arep (k_rescue_held; every block
-// of a chain without shared filters), into a slot of its own (k_rescue_held admitted only
+// forward recursion of each representative in the dense list arep (rescue_held_admit; every block
+// of a chain without shared filters), into a slot of its own (rescue_held_admit admitted only
 // chains whose recursions fit the slots): the rows, then the end tile C f~ C. The block's log Z
 // goes to blk_logz, log Z without the end weight to blk_la (shared-filter chains), and the slot
 // to rep_slot.
@@ -2105,6 +2153,103 @@ __global__ __launch_bounds__(kThreads, kShareDrawWaves) void k_rescue_share_draw
     }
 }
 
+// After the reset and the representative map, before a sweep's FP32 forward pass, one workgroup
+// (the last one of k_dedup, or k_rescue_held where nothing is shared): every block of each chain held on the FP64 re-filter (fp64_circulant) is queued, in chain order, as
+// phase A, and the chain is marked, while the running total of the held chains' forward
+// recursions (their representatives) fits the n_slots slots; the FP32 kernels skip held chains
+// and phase A re-filters them beside the FP32 passes (a held chain left out is queued whole after
+// the forward pass, for phase 2). The queue is empty before this kernel, so the entries are laid
+// down in place. Phase A also gets the dense list of its representatives, arep.
+__device__ void rescue_held_admit(const ChainInfo* __restrict__ chains, const Rescue& rsc,
+                                  int n_slots, int shared, DrawTask* __restrict__ arep) {
+    // one thread per chain, kThreads chains at a time: block-wide inclusive scans of the held
+    // chains' recursions (admission: the running total fits the slots) and of the admitted
+    // chains' blocks (their place in the queue)
+    __shared__ int scan_rec[kThreads], scan_blk[kThreads], adm_share[kThreads];
+    const int tid = threadIdx.x, n = rsc.n_chains;
+    int off = 0, slots = 0;
+    bool some = false;  // nothing is held in most passes of most plans
+    for (int k = tid; k < n; k += kThreads) some = some || rescue_held(rsc, k);
+    if (!__syncthreads_or(some)) return;  // words[0] and words[3] are 0 already
+    for (int c0 = 0; c0 < n; c0 += kThreads) {
+        const int ci = c0 + tid;
+        bool held = false;
+        int nblk = 0, nrec = 0;
+        bool share = false;
+        if (ci < n) {
+            const ChainInfo& c = chains[ci];
+            held = fp64_circulant(c.L) && rescue_held(rsc, ci);
+            nblk = c.np * c.nb;
+            share = shared && c.dedup;
+            nrec = held ? (share ? rsc.words[kRescueChain + 3 * n + ci] : nblk) : 0;
+        }
+        scan_rec[tid] = nrec;
+        __syncthreads();
+        for (int d = 1; d < kThreads; d <<= 1) {  // inclusive scan of the recursions
+            const int v = tid >= d ? scan_rec[tid - d] : 0;
+            __syncthreads();
+            scan_rec[tid] += v;
+            __syncthreads();
+        }
+        const bool admit = held && slots + scan_rec[tid] <= n_slots;
+        scan_blk[tid] = admit ? nblk : 0;
+        adm_share[tid] = admit ? (share ? 2 : 1) : 0;
+        __syncthreads();
+        for (int d = 1; d < kThreads; d <<= 1) {  // inclusive scan of the admitted blocks
+            const int v = tid >= d ? scan_blk[tid - d] : 0;
+            __syncthreads();
+            scan_blk[tid] += v;
+            __syncthreads();
+        }
+        if (admit) rsc.words[kRescueChain + 2 * n + ci] = 1;
+        // the admitted chains' blocks, one chain after another, by the whole workgroup
+        for (int k = 0; k < kThreads && c0 + k < n; ++k) {
+            if (!adm_share[k]) continue;
+            const int ck = c0 + k;
+            const ChainInfo& c = chains[ck];
+            const int nb_k = c.np * c.nb, base = off + scan_blk[k] - nb_k;
+            for (int i = tid; i < nb_k; i += kThreads) {  // i = p nb + block
+                rsc.flags[c.blk_off + i] = 1;
+                rsc.list[base + i] = DrawTask{ck, i / c.nb, i % c.nb, 0};
+                // the representatives, in no particular order (at most n_slots of them)
+                if (adm_share[k] == 1 || rsc.rep[c.blk_off + i] == i / c.nb)
+                    arep[atomicAdd(&rsc.words[6], 1)] = DrawTask{ck, i / c.nb, i % c.nb, 0};
+            }
+        }
+        // the chunk's admitted recursions: the admitted chains are the held ones up to the last
+        // admitted, whose inclusive scan is their total
+        __shared__ int adm_rec;
+        if (tid == 0) adm_rec = 0;
+        __syncthreads();
+        if (admit) atomicMax(&adm_rec, scan_rec[tid]);
+        __syncthreads();
+        slots += adm_rec;
+        off += scan_blk[kThreads - 1];
+        __syncthreads();  // the scans' storage and adm_rec are reused by the next chunk
+    }
+    if (tid == 0) {
+        rsc.words[0] = off;
+        rsc.words[3] = off;
+    }
+}
+__global__ __launch_bounds__(kThreads) void k_rescue_held(const ChainInfo* __restrict__ chains,
+                                                          const Rescue rsc, int n_slots,
+                                                          DrawTask* __restrict__ arep) {
+    rescue_held_admit(chains, rsc, n_slots, 0, arep);
+}
+
+// True on the workgroup of a launch of `total` that gets here last, whose threads then see what
+// the others wrote before (count: zero at the launch). One barrier.
+__device__ inline bool last_workgroup(int32_t* count, int total) {
+    __shared__ int last;
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(count, 1) == total - 1;
+    __syncthreads();
+    if (last) __threadfence();
+    return last != 0;
+}
+
 // The worldlines p0 .. p1 - 1 of one (chain, spin, block), sorted by start site, and the tasks of
 // k_backward_stage over them: groups of as many representatives as its row buffer holds, each
 // group in runs of up to kStageMembers worldlines. The whole workgroup; scratch: kDedupMaxN ints.
@@ -2193,23 +2338,11 @@ __device__ inline void stage_members(const ChainInfo& c, const DrawTask& t, cons
 // in words[8]; P = 4: from n_p2 on, count in words[9]). Lattices above 32 go to cbig, 64 x 64
 // from off64 on, the others from off48 on; FP64 plans list every representative in csingles,
 // L <= 32 from the front, the larger ones likewise (counts in lists[kListFwd..]).
-__global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict__ chains,
-                                                    const DrawTask* __restrict__ tasks,
-                                                    const int32_t* __restrict__ paths,
-                                                    const uint64_t* __restrict__ sweep_ptr,
-                                                    int32_t* __restrict__ rep, const Rescue rsc,
-                                                    PairTask* __restrict__ cpairs,
-                                                    DrawTask* __restrict__ csingles,
-                                                    DrawTask* __restrict__ cbig,
-                                                    PackTask* __restrict__ cpack, int n_p2,
-                                                    int32_t* __restrict__ prep,
-                                                    int32_t* __restrict__ lists, int off64,
-                                                    int off48, const StageLists st) {
+__device__ void dedup_task(const DrawTask& t, const ChainInfo* __restrict__ chains, const int32_t* __restrict__ paths, const uint64_t* __restrict__ sweep_ptr, int32_t* __restrict__ rep, const Rescue rsc, PairTask* __restrict__ cpairs, DrawTask* __restrict__ csingles, DrawTask* __restrict__ cbig, PackTask* __restrict__ cpack, int n_p2, int32_t* __restrict__ prep, int32_t* __restrict__ lists, int off64, int off48, const StageLists st) {
     __shared__ int32_t first[kDedupMaxN];
     __shared__ int32_t rlist[kDedupMaxN];
     __shared__ int32_t n_rep, n_bad, c_base, p_base;
-    const DrawTask t = tasks[blockIdx.x];  // t.p holds the spin
-    const ChainInfo& c = chains[t.chain];
+    const ChainInfo& c = chains[t.chain];  // t.p holds the spin
     int start, len;
     block_of(c, *sweep_ptr, t.block, &start, &len);
     const int p0 = t.p ? c.n_up : 0, p1 = t.p ? c.np : c.n_up;
@@ -2322,6 +2455,85 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
     }
 }
 
+// With arep (an FP32 sweep) the last workgroup then queues the held chains as phase A.
+__global__ __launch_bounds__(kThreads) void k_dedup(
+    const DrawTask* __restrict__ tasks, const ChainInfo* __restrict__ chains, const int32_t* __restrict__ paths, const uint64_t* __restrict__ sweep_ptr, int32_t* __restrict__ rep, const Rescue rsc, PairTask* __restrict__ cpairs, DrawTask* __restrict__ csingles, DrawTask* __restrict__ cbig, PackTask* __restrict__ cpack, int n_p2, int32_t* __restrict__ prep, int32_t* __restrict__ lists, int off64, int off48, const StageLists st, int n_slots, DrawTask* __restrict__ arep) {
+    dedup_task(tasks[blockIdx.x], chains, paths, sweep_ptr, rep, rsc, cpairs, csingles, cbig, cpack, n_p2, prep, lists, off64, off48, st);
+    if (arep && last_workgroup(&lists[kListDone], gridDim.x))
+        rescue_held_admit(chains, rsc, n_slots, 1, arep);
+}
+
+// After the FP32 forward pass, one workgroup (the last one of k_member_logz, or k_rescue_expand
+// where nothing is shared): a chain with more than whole_min blocks queued in this pass, or still
+// held from an earlier such pass, has all its blocks queued for the FP64 re-filter (those of phase A
+// are); its hold then counts down (rescue_reset sets its length at the next pass).
+// With arep_b (sweeps of plans with a phase B) it then admits to phase B the chains queued whole
+// that phase A does not have, in chain order, while their representatives fit the slots (phase A
+// has ended by then) and provided k_backward_stage draws every (spin, block) of theirs: one FP64
+// recursion per start site instead of one per worldline. A 64 x 64 chain that fails its retry in
+// FP32 took k_rescue 20 ms and takes phase B 1 ms. Plans without 48 x 48 or 64 x 64 chains do
+// without: the settled 32 x 32 batch lost 19 us a sweep to the two launches, and its burn-in, whose
+// chains have a start site for nearly every worldline, gained nothing.
+__device__ void rescue_expand(const ChainInfo* __restrict__ chains, const Rescue& rsc, int n_slots,
+                              DrawTask* __restrict__ arep_b) {
+    __shared__ uint64_t left[kWaves];  // this chunk's chains to queue
+    const int tid = threadIdx.x, n = rsc.n_chains;
+    bool any = false;
+    for (int c0 = 0; c0 < n; c0 += kThreads) {
+        const int ci = c0 + tid;
+        bool queue = false;
+        if (ci < n) {  // a thread per chain
+            const ChainInfo& c = chains[ci];
+            const int cnt = rsc.words[kRescueChain + ci];
+            const int hold = rsc.words[kRescueChain + n + ci];
+            const bool many = cnt > c.whole_min;
+            if (many || hold > 0) {
+                queue = rsc.words[kRescueChain + 2 * n + ci] != 1;
+                atomicAdd(&rsc.words[2], 1);
+                rsc.words[kRescueChain + ci] = cnt + c.np * c.nb;  // the chain has queued blocks
+            }
+            rsc.words[kRescueChain + n + ci] = many ? kRescueHold : max(hold - 1, 0);
+        }
+        const uint64_t m = __ballot(queue);
+        if ((tid & 63) == 0) left[tid >> 6] = m;
+        __syncthreads();
+        for (int w = 0; w < kWaves; ++w)
+            for (uint64_t q = left[w]; q; q &= q - 1) {  // uniform
+                const int ck = c0 + 64 * w + __ffsll((unsigned long long)q) - 1;
+                const ChainInfo& c = chains[ck];
+                for (int i = tid; i < c.np * c.nb; i += kThreads)
+                    rescue_enqueue(rsc, c, ck, i / c.nb, i % c.nb);
+                any = true;
+            }
+        __syncthreads();  // left is reused
+    }
+    if (!arep_b || !any) return;  // uniform
+    __threadfence();
+    int slots = 0;
+    for (int k = 0; k < n; ++k) {
+        const ChainInfo& ck = chains[k];
+        const volatile int32_t* words = rsc.words;
+        const int nrec = words[kRescueChain + 3 * n + k], blocks = ck.np * ck.nb;
+        if (ck.dedup != 1 || !fp64_circulant(ck.L) || words[kRescueChain + k] < blocks ||
+            words[kRescueChain + 2 * n + k] != 0 || slots + nrec > n_slots)
+            continue;  // uniform
+        bool all = true;
+        for (int i = tid; i < 2 * ck.nb; i += kThreads)
+            all = all && ((i < ck.nb ? ck.n_up : ck.n_dn) == 0 ||
+                          (rsc.staged[ck.sb_off + i] & kStagedSlots) != 0);
+        if (!__syncthreads_and(all)) continue;
+        slots += nrec;
+        for (int i = tid; i < blocks; i += kThreads)  // i = p nb + block
+            if (rsc.rep[ck.blk_off + i] == i / ck.nb)
+                arep_b[atomicAdd(&rsc.words[15], 1)] = DrawTask{k, i / ck.nb, i % ck.nb, 0};
+        if (tid == 0) rsc.words[kRescueChain + 2 * n + k] = 2;
+    }
+}
+__global__ __launch_bounds__(kThreads) void k_rescue_expand(const ChainInfo* __restrict__ chains,
+                                                            const Rescue rsc) {
+    rescue_expand(chains, rsc, 0, nullptr);
+}
+
 // After the FP32 forward pass, one thread per (chain, particle, block) of the chains with dedup:
 // a worldline that shares its representative's rows takes the representative's log Z before
 // the end weight and reads its own end weight from the representative's end tile
@@ -2330,7 +2542,7 @@ __global__ __launch_bounds__(kThreads) void k_dedup(const ChainInfo* __restrict_
 // FP64 plans and lattices above 32 keep the end tiles in the filter workspace (end_row_big); on
 // FP64 plans an end weight that is not positive latches FH_ERR_NONFINITE.
 template <typename T>
-__global__ void k_member_logz(const ChainInfo* __restrict__ chains, int n_chains,
+__device__ void member_logz(int64_t i0, int64_t stride, const ChainInfo* __restrict__ chains, int n_chains,
                               const int32_t* __restrict__ paths, const int32_t* __restrict__ perm,
                               const uint64_t* __restrict__ sweep_ptr,
                               const double* __restrict__ blk_la, const T* __restrict__ endrow,
@@ -2338,8 +2550,7 @@ __global__ void k_member_logz(const ChainInfo* __restrict__ chains, int n_chains
                               double* __restrict__ blk_logz, int64_t blk_elems, int32_t* status,
                               const Rescue rsc) {
     const uint64_t sweep = *sweep_ptr;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < blk_elems;
-         i += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t i = i0; i < blk_elems; i += stride) {
         const int ci = find_chain(n_chains, i, [&](int k) { return chains[k].blk_off; });
         const ChainInfo& c = chains[ci];
         if (c.dedup != 1 || rescue_held(rsc, ci)) continue;
@@ -2366,185 +2577,21 @@ __global__ void k_member_logz(const ChainInfo* __restrict__ chains, int n_chains
         blk_logz[i] = blk_la[ri] + log((double)hv);
     }
 }
-
-// Before a forward pass: an empty queue, no block flagged, no chain counted or in phase A (the
-// per-chain holds and the redrawn total stay).
-__global__ void k_rescue_reset(const Rescue rsc, int64_t n_flags) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    if (i == 0) {
-        rsc.words[0] = 0;
-        rsc.words[2] = 0;
-        rsc.words[3] = 0;
-        rsc.words[4] = 0;
-        rsc.words[5] = 0;
-        rsc.words[6] = 0;
-        rsc.words[7] = 0;
-        rsc.words[8] = 0;
-        rsc.words[9] = 0;
-        rsc.words[10] = 0;
-        rsc.words[15] = 0;
-        rsc.words[16] = 0;
-        rsc.words[17] = 0;
-    }
-    const int n = rsc.n_chains;
-    for (int64_t k = i; k < n; k += stride) {
-        rsc.words[kRescueChain + k] = 0;
-        rsc.words[kRescueChain + 2 * n + k] = 0;
-        rsc.words[kRescueChain + 3 * n + k] = 0;
-        // the hold: a chain that entered the previous pass in FP32 and left it held failed its
-        // retry (or first met a floor): hold it for the current length, and double that for
-        // the next failure; a pass in FP32 that queued nothing resets the length
-        int hold = rsc.words[kRescueChain + n + k];
-        const int hold0 = rsc.words[kRescueChain + 4 * n + k];
-        int len = max(rsc.words[kRescueChain + 5 * n + k], kRescueHold);
-        if (hold0 == 0 && hold > 0) {
-            hold = len;
-            len = min(2 * len, kRescueHoldMax);
-        } else if (hold0 == 0) {
-            len = kRescueHold;
-        }
-        rsc.words[kRescueChain + n + k] = hold;
-        rsc.words[kRescueChain + 4 * n + k] = hold;
-        rsc.words[kRescueChain + 5 * n + k] = len;
-    }
-    for (int64_t k = i; k < n_flags; k += stride) rsc.flags[k] = 0;
+// The last workgroup then queues whole chains (FP32 plans; expand).
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_member_logz(
+    const ChainInfo* __restrict__ chains, int n_chains, const int32_t* __restrict__ paths,
+    const int32_t* __restrict__ perm, const uint64_t* __restrict__ sweep_ptr,
+    const double* __restrict__ blk_la, const T* __restrict__ endrow, const T* __restrict__ filt,
+    double* __restrict__ blk_logz, int64_t blk_elems, int32_t* status, const Rescue rsc,
+    int32_t* __restrict__ lists, int n_slots, DrawTask* __restrict__ arep_b) {
+    member_logz(blockIdx.x * (int64_t)kThreads + threadIdx.x, (int64_t)gridDim.x * kThreads, chains,
+                n_chains, paths, perm, sweep_ptr, blk_la, endrow, filt, blk_logz, blk_elems, status,
+                rsc);
+    if (rsc.words && last_workgroup(&lists[kListDoneM], gridDim.x))
+        rescue_expand(chains, rsc, n_slots, arep_b);
 }
 
-// After k_rescue_reset and k_dedup, before a sweep's FP32 forward pass, one workgroup: every
-// block of each chain held on the FP64 re-filter (fp64_circulant) is queued, in chain order, as
-// phase A, and the chain is marked, while the running total of the held chains' forward
-// recursions (their representatives) fits the n_slots slots; the FP32 kernels skip held chains
-// and phase A re-filters them beside the FP32 passes (a held chain left out is queued whole after
-// the forward pass, for phase 2). The queue is empty before this kernel, so the entries are laid
-// down in place. Phase A also gets the dense list of its representatives, arep.
-__global__ __launch_bounds__(kThreads) void k_rescue_held(const ChainInfo* __restrict__ chains,
-                                                          const Rescue rsc, int n_slots,
-                                                          int shared, DrawTask* __restrict__ arep) {
-    // one thread per chain, kThreads chains at a time: block-wide inclusive scans of the held
-    // chains' recursions (admission: the running total fits the slots) and of the admitted
-    // chains' blocks (their place in the queue)
-    __shared__ int scan_rec[kThreads], scan_blk[kThreads], adm_share[kThreads];
-    const int tid = threadIdx.x, n = rsc.n_chains;
-    int off = 0, slots = 0;
-    for (int c0 = 0; c0 < n; c0 += kThreads) {
-        const int ci = c0 + tid;
-        bool held = false;
-        int nblk = 0, nrec = 0;
-        bool share = false;
-        if (ci < n) {
-            const ChainInfo& c = chains[ci];
-            held = fp64_circulant(c.L) && rescue_held(rsc, ci);
-            nblk = c.np * c.nb;
-            share = shared && c.dedup;
-            nrec = held ? (share ? rsc.words[kRescueChain + 3 * n + ci] : nblk) : 0;
-        }
-        scan_rec[tid] = nrec;
-        __syncthreads();
-        for (int d = 1; d < kThreads; d <<= 1) {  // inclusive scan of the recursions
-            const int v = tid >= d ? scan_rec[tid - d] : 0;
-            __syncthreads();
-            scan_rec[tid] += v;
-            __syncthreads();
-        }
-        const bool admit = held && slots + scan_rec[tid] <= n_slots;
-        scan_blk[tid] = admit ? nblk : 0;
-        adm_share[tid] = admit ? (share ? 2 : 1) : 0;
-        __syncthreads();
-        for (int d = 1; d < kThreads; d <<= 1) {  // inclusive scan of the admitted blocks
-            const int v = tid >= d ? scan_blk[tid - d] : 0;
-            __syncthreads();
-            scan_blk[tid] += v;
-            __syncthreads();
-        }
-        if (admit) rsc.words[kRescueChain + 2 * n + ci] = 1;
-        // the admitted chains' blocks, one chain after another, by the whole workgroup
-        for (int k = 0; k < kThreads && c0 + k < n; ++k) {
-            if (!adm_share[k]) continue;
-            const int ck = c0 + k;
-            const ChainInfo& c = chains[ck];
-            const int nb_k = c.np * c.nb, base = off + scan_blk[k] - nb_k;
-            for (int i = tid; i < nb_k; i += kThreads) {  // i = p nb + block
-                rsc.flags[c.blk_off + i] = 1;
-                rsc.list[base + i] = DrawTask{ck, i / c.nb, i % c.nb, 0};
-                // the representatives, in no particular order (at most n_slots of them)
-                if (adm_share[k] == 1 || rsc.rep[c.blk_off + i] == i / c.nb)
-                    arep[atomicAdd(&rsc.words[6], 1)] = DrawTask{ck, i / c.nb, i % c.nb, 0};
-            }
-        }
-        // the chunk's admitted recursions: the admitted chains are the held ones up to the last
-        // admitted, whose inclusive scan is their total
-        __shared__ int adm_rec;
-        if (tid == 0) adm_rec = 0;
-        __syncthreads();
-        if (admit) atomicMax(&adm_rec, scan_rec[tid]);
-        __syncthreads();
-        slots += adm_rec;
-        off += scan_blk[kThreads - 1];
-        __syncthreads();  // the scans' storage and adm_rec are reused by the next chunk
-    }
-    if (tid == 0) {
-        rsc.words[0] = off;
-        rsc.words[3] = off;
-    }
-}
-
-// After the FP32 forward pass, one workgroup per chain: a chain with more than whole_min blocks
-// queued in this pass, or still held from an earlier such pass, has all its blocks queued for the
-// FP64 re-filter; its hold then counts down (k_rescue_reset sets its length at the next pass).
-// With arep_b (sweeps of plans with a phase B), the last workgroup to finish then admits to phase B
-// the chains queued whole that phase A does not have, in chain order, while their representatives
-// fit the slots (phase A has ended by then) and provided k_backward_stage draws every (spin,
-// block) of theirs: one FP64 recursion per start site instead of one per worldline. A 64 x 64 chain
-// that fails its retry in FP32 took k_rescue 20 ms and takes phase B 1 ms. Plans without 48 x 48 or 64 x 64 chains do
-// without: the settled 32 x 32 batch lost 19 us a sweep to the two launches, and its burn-in, whose
-// chains have a start site for nearly every worldline, gained nothing.
-__global__ __launch_bounds__(kThreads) void k_rescue_expand(const ChainInfo* __restrict__ chains,
-                                                            const Rescue rsc, int n_slots,
-                                                            DrawTask* __restrict__ arep_b) {
-    const int ci = blockIdx.x, n = rsc.n_chains;
-    const ChainInfo& c = chains[ci];
-    const int cnt = rsc.words[kRescueChain + ci];
-    const int hold = rsc.words[kRescueChain + n + ci];
-    const bool many = cnt > c.whole_min;
-    const bool whole = many || hold > 0;
-    if (whole)
-        for (int i = threadIdx.x; i < c.np * c.nb; i += blockDim.x)
-            rescue_enqueue(rsc, c, ci, i / c.nb, i % c.nb);
-    __syncthreads();  // every thread read the count and the hold before they change
-    __shared__ int last;
-    if (threadIdx.x == 0) {
-        rsc.words[kRescueChain + n + ci] = many ? kRescueHold : max(hold - 1, 0);
-        if (whole) {
-            atomicAdd(&rsc.words[2], 1);
-            rsc.words[kRescueChain + ci] = cnt + c.np * c.nb;  // the chain has queued blocks
-        }
-        __threadfence();
-        last = arep_b ? atomicAdd(&rsc.words[17], 1) == n - 1 : 0;
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
-    int slots = 0;
-    for (int k = 0; k < n; ++k) {
-        const ChainInfo& ck = chains[k];
-        const volatile int32_t* words = rsc.words;
-        const int nrec = words[kRescueChain + 3 * n + k], blocks = ck.np * ck.nb;
-        if (ck.dedup != 1 || !fp64_circulant(ck.L) || words[kRescueChain + k] < blocks ||
-            words[kRescueChain + 2 * n + k] != 0 || slots + nrec > n_slots)
-            continue;  // uniform
-        bool all = true;
-        for (int i = threadIdx.x; i < 2 * ck.nb; i += blockDim.x)
-            all = all && ((i < ck.nb ? ck.n_up : ck.n_dn) == 0 ||
-                          (rsc.staged[ck.sb_off + i] & kStagedSlots) != 0);
-        if (!__syncthreads_and(all)) continue;
-        slots += nrec;
-        for (int i = threadIdx.x; i < blocks; i += blockDim.x)  // i = p nb + block
-            if (rsc.rep[ck.blk_off + i] == i / ck.nb)
-                arep_b[atomicAdd(&rsc.words[15], 1)] = DrawTask{k, i / ck.nb, i % ck.nb, 0};
-        if (threadIdx.x == 0) rsc.words[kRescueChain + 2 * n + k] = 2;
-    }
-}
 
 // Before the FP64 re-filter, one workgroup per (chain, slice) of the chains with blocks in the
 // phase's part of the queue (phase 0: queued; 1: in phase A; 2: queued, not in phase A):
@@ -2577,25 +2624,31 @@ __global__ __launch_bounds__(kThreads) void k_rescue_potentials(
 // next `hold` backward passes use the full-row kernels; then the window is tried again. hold
 // starts at 16 and doubles, up to 64, while the retries keep failing. The switch is plan-wide:
 // both kernels are latency-bound, so splitting the chains between them would cost the sum of
-// their times. One workgroup; the per-chain counts are summed in chain order.
-__global__ void k_bw_adapt(const ChainInfo* __restrict__ chains, int n_chains,
-                           int32_t* __restrict__ bw_state) {
-    __shared__ int64_t part[2][kThreads];
+// their times. One workgroup.
+__device__ void bw_adapt(const ChainInfo* __restrict__ chains, int n_chains,
+                         int32_t* __restrict__ bw_state) {
+    __shared__ int64_t part[2][kWaves];
     int64_t unc = 0, draws = 0;
-    for (int ci = threadIdx.x; ci < n_chains; ci += blockDim.x) {
+    for (int ci = threadIdx.x; ci < n_chains; ci += kThreads) {
         const ChainInfo& c = chains[ci];
         if (!c.win_on) continue;
         unc += bw_state[kBwCounts + ci];
         draws += (int64_t)c.np * (c.L_tau - c.nb);
         bw_state[kBwCounts + ci] = 0;
     }
-    part[0][threadIdx.x] = unc;
-    part[1][threadIdx.x] = draws;
+    for (int o = 32; o > 0; o >>= 1) {
+        unc += __shfl_xor(unc, o, 64);
+        draws += __shfl_xor(draws, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        part[0][threadIdx.x >> 6] = unc;
+        part[1][threadIdx.x >> 6] = draws;
+    }
     __syncthreads();
     if (threadIdx.x != 0) return;
-    for (int k = 1; k < (int)blockDim.x; ++k) {
-        unc += part[0][k];
-        draws += part[1][k];
+    for (int w = 1; w < kWaves; ++w) {
+        unc += part[0][w];
+        draws += part[1][w];
     }
     if (bw_state[0] > 0) {  // a full-row pass just ran
         bw_state[0] -= 1;
@@ -2605,6 +2658,11 @@ __global__ void k_bw_adapt(const ChainInfo* __restrict__ chains, int n_chains,
     } else {
         bw_state[1] = 0;
     }
+}
+__global__ __launch_bounds__(kThreads) void k_bw_adapt(const ChainInfo* __restrict__ chains,
+                                                       int n_chains,
+                                                       int32_t* __restrict__ bw_state) {
+    bw_adapt(chains, n_chains, bw_state);
 }
 
 // One wavefront per (chain, worldline, block) of the chains with L != 32, the body chosen per
@@ -2814,14 +2872,38 @@ __global__ __launch_bounds__(kThreads) void k_perm_update(
 
 // Occupation counts of one slice (LDS histogram) and the exact field draw of every site:
 // Ising: s = +1 iff u < (1 + tanh(lambda (n_up - n_dn))) / 2; Gaussian: sigma = a (n - 1/2) + z.
+// In a sweep, workgroups past the slices do what is left of it beside the draws instead of in
+// launches of their own: the backward kernels' choice (bw_adapt), and on FP64 plans, whose log Z only
+// reports errors here, member_logz (the block ends it reads are fixed within a sweep).
+struct MemberArgs {
+    const int32_t* perm;
+    const double* blk_la;
+    const void* filt;
+    double* blk_logz;
+    int64_t blk_elems;
+    Rescue rsc;
+};
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_gibbs(const ChainInfo* __restrict__ chains,
                                                     int n_chains, const int32_t* __restrict__ paths,
                                                     T* __restrict__ aux,
                                                     const uint64_t* __restrict__ sweep_ptr,
-                                                    int32_t* status, int maxN) {
+                                                    int32_t* status, int maxN,
+                                                    int64_t slices, int32_t* bw_state,
+                                                    const MemberArgs ma) {
     extern __shared__ __align__(16) unsigned char smem[];
     int32_t* cnt = (int32_t*)smem;  // [2][maxN]
+    if ((int64_t)blockIdx.x >= slices) {  // what else ends a sweep (uniform)
+        if ((int64_t)blockIdx.x == slices) {
+            if (bw_state) bw_adapt(chains, n_chains, bw_state);
+        } else if constexpr (sizeof(T) == 8) {
+            member_logz<double>((blockIdx.x - slices - 1) * (int64_t)kThreads + threadIdx.x,
+                                (gridDim.x - slices - 1) * (int64_t)kThreads, chains, n_chains,
+                                paths, ma.perm, sweep_ptr, ma.blk_la, (const double*)nullptr,
+                                (const double*)ma.filt, ma.blk_logz, ma.blk_elems, status, ma.rsc);
+        }
+        return;
+    }
     const int gs = blockIdx.x;
     const int ci = find_chain(n_chains, gs, [&](int i) { return chains[i].slice_off; });
     const ChainInfo& c = chains[ci];
@@ -3384,27 +3466,24 @@ hipError_t launch_set_sweep(fh_plan p, uint64_t sweep, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_bump_sweep(fh_plan p, hipStream_t s) {
-    hipLaunchKernelGGL(k_bump_u64, dim3(1), dim3(64), 0, s, p->d.sweep);
-    return hipGetLastError();
-}
-
 hipError_t launch_zero(void* ptr, int64_t bytes, hipStream_t s) {
     const int64_t words = bytes / 4;
     hipLaunchKernelGGL(k_zero, dim3(grid_for(words)), dim3(kThreads), 0, s, (uint32_t*)ptr, words);
     return hipGetLastError();
 }
 
-hipError_t launch_potentials(fh_plan p, const void* aux, hipStream_t s) {
-    const unsigned g = (unsigned)p->total_slices;
+hipError_t launch_potentials(fh_plan p, const void* aux, bool pass, bool bump, hipStream_t s) {
+    auto run = [&](auto kern, auto* a, auto* W) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)p->total_slices), dim3(kThreads), 0, s,
+                           p->d.chains, p->n_chains, a, W, p->d.wshift, p->aux_elems,
+                           p->total_slices, p->d.status, p->d.lists, rescue_args(p),
+                           pass && p->d.rescue ? std::max<int64_t>(p->blk_elems, 1) : 0,
+                           bump ? p->d.sweep : nullptr);
+    };
     if (p->precision == FH_FP64)
-        hipLaunchKernelGGL(k_potentials<double>, dim3(g), dim3(kThreads), 0, s, p->d.chains,
-                           p->n_chains, (const double*)aux, (double*)p->d.W, p->d.wshift,
-                           p->aux_elems, p->total_slices, p->d.status, p->d.lists);
+        run(k_potentials<double>, (const double*)aux, (double*)p->d.W);
     else
-        hipLaunchKernelGGL(k_potentials<float>, dim3(g), dim3(kThreads), 0, s, p->d.chains,
-                           p->n_chains, (const float*)aux, (float*)p->d.W, p->d.wshift,
-                           p->aux_elems, p->total_slices, p->d.status, p->d.lists);
+        run(k_potentials<float>, (const float*)aux, (float*)p->d.W);
     return hipGetLastError();
 }
 
@@ -3521,57 +3600,45 @@ hipError_t launch_scale_copy(float* dst, const float* src, int64_t n, float fact
     return hipGetLastError();
 }
 
-hipError_t launch_dedup(fh_plan p, const int32_t* paths, hipStream_t s) {
-    if (p->n_dedup_tasks == 0 || p->share_off) return hipSuccess;
+hipError_t launch_dedup(fh_plan p, const int32_t* paths, bool phase_a, hipStream_t s) {
+    phase_a = phase_a && p->d.rescue;
+    if (p->n_dedup_tasks == 0 || p->share_off) {
+        if (phase_a)
+            hipLaunchKernelGGL(k_rescue_held, dim3(1), dim3(kThreads), 0, s, p->d.chains,
+                               rescue_args(p), p->n_rescue_slots, p->d.arep);
+        return hipGetLastError();
+    }
     const bool fp64 = p->precision == FH_FP64;
     hipLaunchKernelGGL(k_dedup, dim3((unsigned)p->n_dedup_tasks), dim3(kThreads), 0, s,
-                       p->d.chains, p->d.dedup_tasks, paths, p->d.sweep, p->d.rep, rescue_args(p),
+                       p->d.dedup_tasks, p->d.chains, paths, p->d.sweep, p->d.rep, rescue_args(p),
                        p->d.fwd32c_tasks,
                        fp64 ? p->d.fwddc_tasks : p->d.fwdxc_tasks, p->d.fwd64c_tasks,
                        p->d.fwdpc_tasks, p->n_fwdp2_tasks, p->d.prep, p->d.lists,
                        fp64 ? p->n_fwdd_tasks : 0,
                        fp64 ? p->n_fwdd_tasks + p->n_fwdd4_tasks : p->n_fwd64_tasks,
                        StageLists{p->d.staged, p->d.members, p->d.stage_tasks,
-                                  p->d.stage_tasks_s, (int32_t)p->real_size});
+                                  p->d.stage_tasks_s, (int32_t)p->real_size},
+                       p->n_rescue_slots, phase_a ? p->d.arep : nullptr);
     return hipGetLastError();
 }
 
 hipError_t launch_member_logz(fh_plan p, const int32_t* paths, hipStream_t s) {
-    if (p->n_dedup_tasks == 0 || p->share_off) return hipSuccess;
+    if (p->n_dedup_tasks == 0 || p->share_off) {
+        if (p->d.rescue)
+            hipLaunchKernelGGL(k_rescue_expand, dim3(1), dim3(kThreads), 0, s, p->d.chains,
+                               rescue_args(p));
+        return hipGetLastError();
+    }
+    auto run = [&](auto kern, auto* endrow, auto* filt) {
+        hipLaunchKernelGGL(kern, dim3(grid_for(p->blk_elems)), dim3(kThreads), 0, s, p->d.chains,
+                           p->n_chains, paths, p->d.perm, p->d.sweep, p->d.blk_la, endrow, filt,
+                           p->d.blk_logz, p->blk_elems, p->d.status, rescue_args(p), p->d.lists,
+                           p->n_rescue_slots, p->phase_b ? p->d.arep_b : nullptr);
+    };
     if (p->precision == FH_FP64)
-        hipLaunchKernelGGL(k_member_logz<double>, dim3(grid_for(p->blk_elems)), dim3(kThreads), 0,
-                           s, p->d.chains, p->n_chains, paths, p->d.perm, p->d.sweep, p->d.blk_la,
-                           nullptr, (const double*)p->d.filt, p->d.blk_logz, p->blk_elems,
-                           p->d.status,
-                           rescue_args(p));
+        run(k_member_logz<double>, (const double*)nullptr, (const double*)p->d.filt);
     else
-        hipLaunchKernelGGL(k_member_logz<float>, dim3(grid_for(p->blk_elems)), dim3(kThreads), 0,
-                           s, p->d.chains, p->n_chains, paths, p->d.perm, p->d.sweep, p->d.blk_la,
-                           p->d.endrow, (const float*)p->d.filt, p->d.blk_logz, p->blk_elems,
-                           p->d.status, rescue_args(p));
-    return hipGetLastError();
-}
-
-hipError_t launch_rescue_reset(fh_plan p, hipStream_t s) {
-    if (!p->d.rescue) return hipSuccess;
-    hipLaunchKernelGGL(k_rescue_reset, dim3(grid_for(std::max<int64_t>(p->blk_elems, p->n_chains))),
-                       dim3(kThreads), 0, s, rescue_args(p), p->blk_elems);
-    return hipGetLastError();
-}
-
-hipError_t launch_rescue_expand(fh_plan p, hipStream_t s) {
-    if (!p->d.rescue) return hipSuccess;
-    hipLaunchKernelGGL(k_rescue_expand, dim3(p->n_chains), dim3(kThreads), 0, s, p->d.chains,
-                       rescue_args(p), p->n_rescue_slots,
-                       p->phase_b && !p->share_off ? p->d.arep_b : nullptr);
-    return hipGetLastError();
-}
-
-hipError_t launch_rescue_held(fh_plan p, hipStream_t s) {
-    if (!p->d.rescue) return hipSuccess;
-    hipLaunchKernelGGL(k_rescue_held, dim3(1), dim3(kThreads), 0, s, p->d.chains, rescue_args(p),
-                       p->n_rescue_slots, (int)(p->n_dedup_tasks > 0 && !p->share_off),
-                       p->d.arep);
+        run(k_member_logz<float>, (const float*)p->d.endrow, (const float*)p->d.filt);
     return hipGetLastError();
 }
 
@@ -3648,12 +3715,12 @@ hipError_t launch_rescue(fh_plan p, const void* aux, int32_t* paths, bool draw, 
     return hipGetLastError();
 }
 
-hipError_t launch_backward(fh_plan p, int32_t* paths, hipStream_t s) {
-    // windowed draws where the hopping kernel allows them; 32 x 32 chains without the window (or
-    // moved off it for this sweep by k_bw_adapt) on their own full-row kernel, the rest on the
-    // generic ones
+hipError_t launch_backward(fh_plan p, int32_t* paths, bool adapt, hipStream_t s) {
+    // staged draws where worldlines share rows; windowed draws where the hopping kernel allows
+    // them; 32 x 32 chains without the window (or moved off it for this sweep by bw_adapt) on their
+    // own full-row kernel, the rest on the generic ones
     hipError_t e = launch_backward_kernels(p, paths, s);
-    if (e != hipSuccess || !p->bw_adapt || p->n_draww_tasks == 0) return e;
+    if (e != hipSuccess || !adapt || !p->bw_adapt || p->n_draww_tasks == 0) return e;
     hipLaunchKernelGGL(k_bw_adapt, dim3(1), dim3(kThreads), 0, s, p->d.chains, p->n_chains,
                        p->d.bw_state);
     return hipGetLastError();
@@ -3773,16 +3840,22 @@ hipError_t launch_mala_accept(fh_plan p, void* aux, const void* prop, const void
     return hipGetLastError();
 }
 
-hipError_t launch_gibbs(fh_plan p, const int32_t* paths, void* aux, hipStream_t s) {
+hipError_t launch_gibbs(fh_plan p, const int32_t* paths, void* aux, bool sweep, hipStream_t s) {
     const size_t lds = sizeof(int32_t) * 2 * p->max_N;
+    const bool adapt = sweep && p->bw_adapt && p->n_draww_tasks > 0;
+    const bool members = sweep && p->precision == FH_FP64 && p->n_dedup_tasks > 0 && !p->share_off;
+    const int64_t extra = members ? 1 + (int64_t)grid_for(p->blk_elems) : adapt ? 1 : 0;
+    const MemberArgs ma{p->d.perm, p->d.blk_la, p->d.filt, p->d.blk_logz, p->blk_elems,
+                        rescue_args(p)};
+    auto run = [&](auto kern, auto* a) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)(p->total_slices + extra)), dim3(kThreads), lds, s,
+                           p->d.chains, p->n_chains, paths, a, p->d.sweep, p->d.status, p->max_N,
+                           p->total_slices, adapt ? p->d.bw_state : nullptr, ma);
+    };
     if (p->precision == FH_FP64)
-        hipLaunchKernelGGL(k_gibbs<double>, dim3((unsigned)p->total_slices), dim3(kThreads), lds,
-                           s, p->d.chains, p->n_chains, paths, (double*)aux, p->d.sweep,
-                           p->d.status, p->max_N);
+        run(k_gibbs<double>, (double*)aux);
     else
-        hipLaunchKernelGGL(k_gibbs<float>, dim3((unsigned)p->total_slices), dim3(kThreads), lds,
-                           s, p->d.chains, p->n_chains, paths, (float*)aux, p->d.sweep,
-                           p->d.status, p->max_N);
+        run(k_gibbs<float>, (float*)aux);
     return hipGetLastError();
 }
 
