@@ -2239,12 +2239,16 @@ __global__ __launch_bounds__(kThreads) void k_rescue_held(const ChainInfo* __res
 }
 
 // True on the workgroup of a launch of `total` that gets here last, whose threads then see what
-// the others wrote before (count: zero at the launch). One barrier.
+// the others wrote before (count: zero at the launch). Two barriers; after the first one the
+// workgroup's writes are in its L2, and one wavefront's fence passes them on (a fence of all four
+// writes the L2 back four times: 512 workgroups took 28 us with one, 49 with four).
 __device__ inline bool last_workgroup(int32_t* count, int total) {
     __shared__ int last;
-    __threadfence();
     __syncthreads();
-    if (threadIdx.x == 0) last = atomicAdd(count, 1) == total - 1;
+    if (threadIdx.x == 0) {
+        __threadfence();
+        last = atomicAdd(count, 1) == total - 1;
+    }
     __syncthreads();
     if (last) __threadfence();
     return last != 0;
@@ -3015,47 +3019,65 @@ __global__ __launch_bounds__(kThreads) void k_mala_accept(
         for (int64_t i = threadIdx.x; i < n; i += blockDim.x) aux[c.aux_off + i] = prop[c.aux_off + i];
 }
 
-// Equal-time observables of one slice (Sec. 4), one workgroup per (chain, slice): occupation
-// counts by an LDS histogram, S^z = (n_up - n_dn) / 2, F = 2D FFT of S^z (the Stockham stages of
-// the forward filter, FP64), S(k) = |F(k)|^2 / N and, from the unscaled inverse FFT of |F|^2,
-// C(r) = (1/N) sum_j S^z_{j+r} S^z_j = IFFT(|F|^2)(r) / N^2. Rows go to the slice's place in
-// sk / cr (packed like aux); the site sums of n_up n_dn and (n_up - n_dn)^2 to sums[slice][2].
+// Equal-time observables (Sec. 4) in three kernels. With S^z = (n_up - n_dn) / 2 and F its 2D FFT,
+//   S(k) = <|F(k)|^2> / N,   C(r) = <(1/N) sum_j S^z_{j+r} S^z_j> = IFFT(<|F|^2>)(r) / N^2
+// over the slices (IFFT unscaled). Both are linear in P = sum over slices of |F|^2, so there is
+// one inverse transform per chain, and two slices a, b go through one complex forward transform
+// Z of S_a + i S_b: |F_a(k)|^2 + |F_b(k)|^2 = (|Z(k)|^2 + |Z(-k)|^2) / 2, so P needs no unpacking
+// either: it is the symmetric part of sum |Z|^2.
+// One transform each way per slice and one thread per site walking all slices took 125 + 45 us
+// for 16 Ising 32 x 32 x 160 chains; k_measure + k_measure_sum + k_measure_out take 28 + 5 + 9 us.
+
+// Slice pairs of chain ci are numbered from here on, with room for its ceil(L_tau / 2) pairs.
+__host__ __device__ inline int64_t pair_base(int64_t slice_off, int ci) {
+    return (slice_off >> 1) + ci;
+}
+
+// Pair g (slices 2g, 2g + 1; an odd chain's last one alone), one workgroup: occupation counts of
+// both slices by an LDS histogram, the transform of S_a + i S_b (the Stockham stages of the
+// forward filter, FP64), |Z|^2 to row g of the chain's place in z2 (packed like aux) and the site
+// sums of n_up n_dn and (n_up - n_dn)^2 of both slices to sums[slice_off + g][2]. Bound by the
+// instructions of the six LDS passes of a 32 x 32 transform (a fifth workgroup per compute unit,
+// with the twiddles out of LDS, gave nothing: 27.8 us).
 __global__ __launch_bounds__(kThreads) void k_measure(const ChainInfo* __restrict__ chains,
                                                       int n_chains, const double* __restrict__ tables,
                                                       const int32_t* __restrict__ paths,
-                                                      double* __restrict__ sk, double* __restrict__ cr,
-                                                      double* __restrict__ sums, int32_t* status,
-                                                      int maxN, int maxL) {
+                                                      double* __restrict__ z2,
+                                                      double* __restrict__ sums,
+                                                      int32_t* status, int maxN, int maxL) {
     extern __shared__ __align__(16) unsigned char smem[];
     cpx<double>* A = (cpx<double>*)smem;  // [maxN]
     cpx<double>* S = A + maxN;            // [maxN] FFT scratch; the histogram lives here first
     cpx<double>* tw = S + maxN;           // [maxL]
     double* red = (double*)(tw + maxL);   // [2][kWaves]
-    int32_t* cnt = (int32_t*)S;           // [2][maxN] ints fit in S (16 bytes per element)
-    const int64_t gs = blockIdx.x;
-    const int ci = find_chain(n_chains, gs, [&](int i) { return chains[i].slice_off; });
+    int32_t* cnt = (int32_t*)S;           // [4][maxN] ints fill S (16 bytes per element)
+    const int64_t gid = blockIdx.x;
+    const int ci = find_chain(n_chains, gid, [&](int i) { return pair_base(chains[i].slice_off, i); });
     const ChainInfo& c = chains[ci];
-    const int l = (int)(gs - c.slice_off);
-    const int N = c.N, L = c.L;
-    for (int r = threadIdx.x; r < 2 * N; r += blockDim.x) cnt[r] = 0;
+    const int g = (int)(gid - pair_base(c.slice_off, ci));
+    if (2 * g >= c.L_tau) return;  // whole workgroup; no barrier reached
+    const int N = c.N, L = c.L, np = c.np, n_up = c.n_up;
+    const int n_at = 2 * g + 1 < c.L_tau ? 2 * np : np;
+    for (int r = threadIdx.x; r < 4 * N; r += blockDim.x) cnt[r] = 0;
     const double* twt = tables + tab_tw(c);
     for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = {twt[2 * m], twt[2 * m + 1]};
     __syncthreads();
-    const int32_t* pl = paths + c.path_off + (int64_t)l * c.np;
-    for (int p = threadIdx.x; p < c.np; p += blockDim.x) {
-        const int r = pl[p];
+    const int32_t* pl = paths + c.path_off + (int64_t)(2 * g) * np;
+    for (int q = threadIdx.x; q < n_at; q += blockDim.x) {
+        const int r = pl[q];
+        const int second = q >= np ? 2 : 0, p = q >= np ? q - np : q;
         if (r >= 0 && r < N)
-            atomicAdd(&cnt[(p >= c.n_up ? N : 0) + r], 1);
+            atomicAdd(&cnt[(second + (p >= n_up ? 1 : 0)) * N + r], 1);
         else
             set_status(status, FH_ERR_BAD_PATH, ci);
     }
     __syncthreads();
     double d = 0.0, m2 = 0.0;
     for (int r = threadIdx.x; r < N; r += blockDim.x) {
-        const int nu = cnt[r], nd = cnt[N + r];
-        A[r] = {0.5 * (double)(nu - nd), 0.0};
-        d += (double)nu * (double)nd;
-        m2 += (double)(nu - nd) * (double)(nu - nd);
+        const int ua = cnt[r], da = cnt[N + r], ub = cnt[2 * N + r], db = cnt[3 * N + r];
+        A[r] = {0.5 * (double)(ua - da), 0.5 * (double)(ub - db)};
+        d += (double)ua * (double)da + (double)ub * (double)db;
+        m2 += (double)(ua - da) * (double)(ua - da) + (double)(ub - db) * (double)(ub - db);
     }
     d = wave_sum(d);
     m2 = wave_sum(m2);
@@ -3071,53 +3093,81 @@ __global__ __launch_bounds__(kThreads) void k_measure(const ChainInfo* __restric
             sd += red[w];
             sm += red[kWaves + w];
         }
-        sums[2 * gs] = sd;
-        sums[2 * gs + 1] = sm;
+        sums[2 * (c.slice_off + g)] = sd;
+        sums[2 * (c.slice_off + g) + 1] = sm;
     }
     fft2d<double, false>(A, S, L, c.plan, tw);
-    double* skr = sk + c.aux_off + (int64_t)l * N;
-    for (int k = threadIdx.x; k < N; k += blockDim.x) {
-        const double p2 = A[k].re * A[k].re + A[k].im * A[k].im;
-        skr[k] = p2 / (double)N;
-        A[k] = {p2, 0.0};
-    }
-    __syncthreads();
-    fft2d<double, true>(A, S, L, c.plan, tw);
-    double* crr = cr + c.aux_off + (int64_t)l * N;
-    const double inv = 1.0 / ((double)N * (double)N);
-    for (int r = threadIdx.x; r < N; r += blockDim.x) crr[r] = A[r].re * inv;
+    double* row = z2 + c.aux_off + (int64_t)g * N;
+    for (int k = threadIdx.x; k < N; k += blockDim.x)
+        row[k] = A[k].re * A[k].re + A[k].im * A[k].im;
 }
 
-// Slice averages of k_measure's rows, summed in slice order: S(k), C(r) per site of every chain
-// (threads 0 .. total_sites-1), then D and the local moment per chain.
-__global__ __launch_bounds__(kThreads) void k_measure_reduce(
-    const ChainInfo* __restrict__ chains, int n_chains, int64_t total_sites,
-    const double* __restrict__ sk, const double* __restrict__ cr, const double* __restrict__ sums,
-    double* __restrict__ Sk, double* __restrict__ Cr, double* __restrict__ D,
-    double* __restrict__ S2) {
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t < total_sites) {
-        const int ci = find_chain(n_chains, t, [&](int i) { return chains[i].site_off; });
-        const ChainInfo& c = chains[ci];
-        const int k = (int)(t - c.site_off);
-        double a = 0.0, b = 0.0;
-        for (int l = 0; l < c.L_tau; ++l) {
-            a += sk[c.aux_off + (int64_t)l * c.N + k];
-            b += cr[c.aux_off + (int64_t)l * c.N + k];
-        }
-        if (Sk) Sk[t] = a / c.L_tau;
-        if (Cr) Cr[t] = b / c.L_tau;
-    } else if (t < total_sites + n_chains) {
-        const ChainInfo& c = chains[t - total_sites];
-        double a = 0.0, b = 0.0;
-        for (int l = 0; l < c.L_tau; ++l) {
-            a += sums[2 * (c.slice_off + l)];
-            b += sums[2 * (c.slice_off + l) + 1];
-        }
-        const double n = (double)c.L_tau * (double)c.N;
-        if (D) D[t - total_sites] = a / n;
-        if (S2) S2[t - total_sites] = 0.75 * b / n;
+// Sums of k_measure's rows: a workgroup adds the pairs of kMeasureSites sites of one chain, in
+// kThreads / kMeasureSites interleaved runs added in run order, into row 0, which only it reads.
+// (One thread per site and all slices in one run left 240 of 256 compute units idle.)
+constexpr int kMeasureSites = 32;
+__global__ __launch_bounds__(kThreads) void k_measure_sum(const ChainInfo* __restrict__ chains,
+                                                          double* __restrict__ z2, int tiles) {
+    constexpr int kRuns = kThreads / kMeasureSites;
+    __shared__ double part[kRuns][kMeasureSites];
+    const int ci = blockIdx.x / tiles, first = (blockIdx.x - ci * tiles) * kMeasureSites;
+    const ChainInfo& c = chains[ci];
+    const int N = c.N, pairs = (c.L_tau + 1) >> 1;
+    if (first >= N) return;  // whole workgroup; no barrier reached
+    const int run = threadIdx.x / kMeasureSites, at = threadIdx.x % kMeasureSites;
+    const int k = first + at;
+    double* rows = z2 + c.aux_off;
+    double a = 0.0;
+    if (k < N)
+        for (int g = run; g < pairs; g += kRuns) a += rows[(int64_t)g * N + k];
+    part[run][at] = a;
+    __syncthreads();
+    if (run == 0 && k < N) {
+        for (int q = 1; q < kRuns; ++q) a += part[q][at];
+        rows[k] = a;
     }
+}
+
+// S(k), the inverse transform C(r), D and the local moment of a chain, one workgroup each. (As the
+// last workgroup of k_measure_sum it saved a launch and cost 512 fences, one per workgroup: 28 us
+// for both against 5.1 + 8.8.)
+__global__ __launch_bounds__(kThreads) void k_measure_out(
+    const ChainInfo* __restrict__ chains, const double* __restrict__ tables,
+    const double* __restrict__ z2, const double* __restrict__ sums, double* __restrict__ Sk,
+    double* __restrict__ Cr, double* __restrict__ D, double* __restrict__ S2, int maxN, int maxL) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    cpx<double>* A = (cpx<double>*)smem;  // [maxN]
+    cpx<double>* S = A + maxN;            // [maxN]
+    cpx<double>* tw = S + maxN;           // [maxL]
+    __shared__ double red[2 * kWaves];
+    const int ci = blockIdx.x;
+    const ChainInfo& c = chains[ci];
+    const int N = c.N, L = c.L, pairs = (c.L_tau + 1) >> 1;
+    const double* P = z2 + c.aux_off;
+    const double* twt = tables + tab_tw(c);
+    for (int m = threadIdx.x; m < L; m += blockDim.x) tw[m] = {twt[2 * m], twt[2 * m + 1]};
+    const double mean = 1.0 / c.L_tau, inv = 1.0 / ((double)N * (double)N);
+    for (int q = threadIdx.x; q < N; q += blockDim.x) {
+        const int y = q / L, x = q - y * L;
+        const int neg = (y ? L - y : 0) * L + (x ? L - x : 0);
+        const double p2 = 0.5 * (P[q] + P[neg]) * mean;
+        if (Sk) Sk[c.site_off + q] = p2 / (double)N;
+        A[q] = {p2, 0.0};
+    }
+    double v[2] = {0.0, 0.0};
+    for (int g = threadIdx.x; g < pairs; g += blockDim.x) {  // whole numbers: any order is exact
+        v[0] += sums[2 * (c.slice_off + g)];
+        v[1] += sums[2 * (c.slice_off + g) + 1];
+    }
+    block_sum<2>(v, red);
+    if (threadIdx.x == 0) {
+        const double n = (double)c.L_tau * (double)N;
+        if (D) D[ci] = v[0] / n;
+        if (S2) S2[ci] = 0.75 * v[1] / n;
+    }
+    if (!Cr) return;
+    fft2d<double, true>(A, S, L, c.plan, tw);
+    for (int r = threadIdx.x; r < N; r += blockDim.x) Cr[c.site_off + r] = A[r].re * inv;
 }
 
 // The rings that worldlines share (GradShare), one workgroup per (chain, spin): an LDS hash table
@@ -3794,21 +3844,24 @@ hipError_t scratch_address(void** out) {
 
 hipError_t launch_measure(fh_plan p, const int32_t* paths, double* Sk, double* Cr, double* D,
                           double* S2, hipStream_t s, double* work) {
-    const size_t lds = sizeof(cpx<double>) * (2 * (size_t)p->max_N + p->max_L) +
-                       sizeof(double) * 2 * kWaves;
-    hipError_t e = allow_lds(k_measure, lds);
+    const size_t lds = sizeof(cpx<double>) * (2 * (size_t)p->max_N + p->max_L);
+    const size_t lds_pairs = lds + sizeof(double) * 2 * kWaves;
+    hipError_t e = allow_lds(k_measure, lds_pairs);
+    if (e == hipSuccess) e = allow_lds(k_measure_out, lds);
     if (e != hipSuccess) return e;
-    double* sk = work;  // [aux_elems] S(k) rows, [aux_elems] C(r) rows, [2 slices] site sums
-    double* cr = sk + p->aux_elems;
-    double* sums = cr + p->aux_elems;
-    hipLaunchKernelGGL(k_measure, dim3((unsigned)p->total_slices), dim3(kThreads), lds, s,
-                       p->d.chains, p->n_chains, p->d.tables, paths, sk, cr, sums, p->d.status,
+    double* z2 = work;  // [aux_elems] rows, [2 slices] site sums
+    double* sums = z2 + p->aux_elems;
+    const int64_t pairs = pair_base(p->total_slices, p->n_chains);
+    hipLaunchKernelGGL(k_measure, dim3((unsigned)pairs), dim3(kThreads), lds_pairs, s,
+                       p->d.chains, p->n_chains, p->d.tables, paths, z2, sums, p->d.status,
                        p->max_N, p->max_L);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int64_t n = p->total_sites + p->n_chains;
-    hipLaunchKernelGGL(k_measure_reduce, dim3((unsigned)((n + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, s, p->d.chains, p->n_chains, p->total_sites, sk, cr,
-                       sums, Sk, Cr, D, S2);
+    const unsigned tiles = (unsigned)((p->max_N + kMeasureSites - 1) / kMeasureSites);
+    hipLaunchKernelGGL(k_measure_sum, dim3(tiles * (unsigned)p->n_chains), dim3(kThreads), 0, s,
+                       p->d.chains, z2, (int)tiles);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_measure_out, dim3((unsigned)p->n_chains), dim3(kThreads), lds, s,
+                       p->d.chains, p->d.tables, z2, sums, Sk, Cr, D, S2, p->max_N, p->max_L);
     return hipGetLastError();
 }
 
