@@ -1984,11 +1984,11 @@ __global__ __launch_bounds__(kThreads, NT == 2 ? 2 : 1) void k_rescue(
         }
         if (!DRAW || !ok) continue;
         // the slot's rows were stored by this wavefront's lanes: make them visible to its loads
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         // the full-row rule of the FP64 plans' backward kernel, on the slot's rows
         rescue_draws<0>(t, c, tables + tab_g(c), paths, perm, sweep, status, lane, slot);
         // the next block reuses the slot: its stores must follow these loads
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     }
 }
 

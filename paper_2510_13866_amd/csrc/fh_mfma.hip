@@ -143,12 +143,27 @@ __device__ inline double block_shift_sum(const double* __restrict__ shift, int s
     return wave_sum_f64(m) - (double)(len - 1) * lsc;
 }
 
+// Raw buffer resources: word 3 of the descriptor on gfx9-family chips (32-bit data format,
+// no swizzle), and the cache-policy bit of a streaming (nontemporal) store.
+constexpr int kBufferWord3 = 0x00020000;
+constexpr int kNontemporal = 2;
+
+// Bits of a float for the b32 buffer store. The value is taken as a function argument: applied
+// directly to an element of an ext_vector_type, __builtin_bit_cast reads element 0 whatever the
+// index (seen with this compiler), so it never gets a vector element.
+__device__ inline uint32_t fbits(float f) { return __builtin_bit_cast(uint32_t, f); }
+
+// A buffer resource over the n floats at p (wavefront-uniform): a load past them returns zero, a
+// store past them is dropped, so padded positions need neither masks nor branches.
+__device__ inline __amdgpu_buffer_rsrc_t float_rsrc(const float* p, int n) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, n * 4, kBufferWord3);
+}
+constexpr uint32_t kOutside = 0x40000000u;  // a byte offset past every such buffer
 // One wavefront per (chain, worldline, block): the forward recursion of one block
 //   f~_0 = delta_a; h_j = W~_{start+j} . (C f~_{j-1} C); c_j = sum h_j; f~_j = h_j / c_j
 //   log Z = coef aux_start(a) + sum_j (log c_j + m_{start+j}) + log (C f~_{len-1} C)(e)
-// storing f~_j (j >= 1) as FP32 rows of N values, like the FFT path. LFIX = 32 compiles the
-// common full-tile case with constant offsets; LFIX = 0 handles any L <= 32 by zero padding.
-template <int LFIX>
+// storing f~_j (j >= 1) as FP32 rows of N values, like the FFT path. Any L <= 32, by zero
+// padding.
 __device__ __forceinline__ void forward_mfma_body(
     int task, const ChainInfo* __restrict__ chains, const DrawTask* __restrict__ tasks, int n_tasks,
     const uint16_t* __restrict__ cmat, const float* __restrict__ aux, const float* __restrict__ W,
@@ -168,7 +183,7 @@ __device__ __forceinline__ void forward_mfma_body(
     if (c.dedup && row_owner(rsc, c, t.p, t.block) != t.p) return;
     int start, len;
     block_of(c, *sweep_ptr, t.block, &start, &len);
-    const int L = LFIX ? LFIX : c.L, N = LFIX ? LFIX * LFIX : c.N, L_tau = c.L_tau;
+    const int L = c.L, N = c.N, L_tau = c.L_tau;
     // a chain with few representatives keeps its rows in the cache for the members that read
     // them next (as in k_forward_mfma2)
     const int n_rep = c.dedup ? rsc.words[kRescueChain + 3 * rsc.n_chains + t.chain] : 0;
@@ -199,16 +214,17 @@ __device__ __forceinline__ void forward_mfma_body(
         }
     }
     const int x = lane & 31;
-    const bool xin = LFIX ? true : x < L;
-    // element (tile_row(lane, v), x) sits at lane_off + vrow(v) * L of a row
-    const int lane_off = 4 * (lane >> 5) * L + x;
-    auto vrow = [](int v) { return 8 * (v >> 2) + (v & 3); };
-    auto inside = [&](int v) { return LFIX ? true : (xin && 4 * (lane >> 5) + vrow(v) < L); };
-    auto load_w = [&](int l, float (&dst)[16]) {
-        const float* Wl = Wsp + (int64_t)l * N;
-        // a padded position reads site 0 (in bounds) and multiplies an exact zero of C f C
+    // byte offset of element (tile_row(lane, v), x) in a row or slice of N floats (padded rows
+    // lie past its end, padded columns are put there)
+    uint32_t at[16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) dst[v] = Wl[inside(v) ? lane_off + vrow(v) * L : 0];
+    for (int v = 0; v < 16; ++v) at[v] = x < L ? (uint32_t)(tile_row(lane, v) * L + x) * 4 : kOutside;
+    auto load_w = [&](int l, float (&dst)[16]) {
+        const __amdgpu_buffer_rsrc_t ws = float_rsrc(Wsp + (int64_t)l * N, N);
+        // a padded position loads zero and multiplies an exact zero of C f C
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            dst[v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ws, at[v], 0, 0));
     };
     const int ax = a % L, ay = a / L;
     // rows hold f~ 2^row_exp (the FP32 range scaling), from f_0 = 2^row_exp delta_a on
@@ -221,13 +237,13 @@ __device__ __forceinline__ void forward_mfma_body(
     double la = coef * (double)aux[c.aux_off + (int64_t)start * N + a] - lsc;
     double prod = 1.0;
     float* rows = filt + c.filt_off + ((int64_t)t.p * L_tau + (int64_t)t.block * (c.B - 1)) * N;
-    // W of the next slice is loaded right after the stores of this one, so that its wait (one
-    // step of matrix work later) finds the stores, which may be skipped for padded lanes and so
-    // are not counted ahead of time, long retired
-    // two W buffers that swap roles every step (one buffer would make the loop's back edge copy
-    // the loaded slice into it, waiting for the load)
-    float wa[16], wb[16];
+    // W of this slice and of the next two, in three buffers that rotate every step; a slice is
+    // loaded two steps before its use and before a step's stores, as in k_forward_mfma2: loads and
+    // stores retire in order, and loaded after the stores W waited for them in every step
+    // (24 x 24: 1.55 us a step, now 1.05)
+    float wa[16], wb[16], wc[16];
     load_w((start + 1) % L_tau, wa);
+    load_w((start + 2) % L_tau, wb);
     bool low = false;  // the block left FP32's range: queued for the FP64 re-filter
     auto step = [&](int j, const float (&wn)[16], float (&wf)[16]) {
         const int l = (start + j) % L_tau;
@@ -239,6 +255,8 @@ __device__ __forceinline__ void forward_mfma_body(
             F[v] = H[v] * wn[v];
             s += F[v];
         }
+        load_w((l + 2) % L_tau, wf);  // the last two steps fetch slices they do not use
+        __builtin_amdgcn_sched_barrier(0);
         const float tot = wave_sum_f32(s);
         low |= !(tot >= step_floor) | !isfinite(tot);
         // f~_j = h_j * inv, so the normaliser actually applied is exactly 1/inv: log Z takes
@@ -251,29 +269,29 @@ __device__ __forceinline__ void forward_mfma_body(
             prod = 1.0;
         }
         const float k = inv * sc;
-        float* row = rows + (int64_t)(j - 1) * N + lane_off;
+        const __amdgpu_buffer_rsrc_t row = float_rsrc(rows + (int64_t)(j - 1) * N, N);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            F[v] *= k;
-            if (inside(v)) {
-                if (cached)
-                    row[vrow(v) * L] = F[v];
-                else
-                    __builtin_nontemporal_store(F[v], row + vrow(v) * L);
-            }
+        for (int v = 0; v < 16; ++v) F[v] *= k;
+        if (cached) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                __builtin_amdgcn_raw_buffer_store_b32(fbits(F[v]), row, at[v], 0, 0);
+        } else {
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                __builtin_amdgcn_raw_buffer_store_b32(fbits(F[v]), row, at[v], 0, kNontemporal);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        load_w((l + 1) % L_tau, wf);  // the last step fetches a slice it does not use
-        __builtin_amdgcn_sched_barrier(0);
     };
     if (len > 1) {
-        step(1, wa, wb);
+        step(1, wa, wc);
         int j = 2;
-        for (; j + 1 < len; j += 2) {
+        for (; j + 2 < len; j += 3) {
             step(j, wb, wa);
-            step(j + 1, wa, wb);
+            step(j + 1, wc, wb);
+            step(j + 2, wa, wc);
         }
         if (j < len) step(j, wb, wa);
+        if (j + 1 < len) step(j + 1, wc, wb);
     }
     la += block_shift_sum(shift, start, len, L_tau, lsc, lane);
     // end weight (C f~ C)(e)
@@ -295,15 +313,15 @@ __device__ __forceinline__ void forward_mfma_body(
     }
     if (c.dedup) {  // what the worldlines sharing these rows need: log Z so far, the end tile
         if (lane == 0) blk_la[c.blk_off + (int64_t)t.p * c.nb + t.block] = la;
-        float* end = endrow + c.end_off + ((int64_t)t.p * c.nb + t.block) * N + lane_off;
+        const __amdgpu_buffer_rsrc_t end =
+            float_rsrc(endrow + c.end_off + ((int64_t)t.p * c.nb + t.block) * N, N);
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-            if (inside(v)) end[vrow(v) * L] = H[v];
+            __builtin_amdgcn_raw_buffer_store_b32(fbits(H[v]), end, at[v], 0, 0);
     }
 }
 
-template <int LFIX>
-__global__ __launch_bounds__(kThreads, LFIX ? 4 : 2) void k_forward_mfma(
+__global__ __launch_bounds__(kThreads, 2) void k_forward_mfma(
     const ChainInfo* __restrict__ chains, const DrawTask* __restrict__ tasks, int n_tasks,
     const uint16_t* __restrict__ cmat, const float* __restrict__ aux, const float* __restrict__ W,
     const double* __restrict__ wshift, int64_t aux_elems, int64_t total_slices,
@@ -312,7 +330,7 @@ __global__ __launch_bounds__(kThreads, LFIX ? 4 : 2) void k_forward_mfma(
     const Rescue rsc, const NegPairs neg, double* __restrict__ blk_la,
     float* __restrict__ endrow, const DrawTask* __restrict__ ctasks,
     const int32_t* __restrict__ ccount) {
-    forward_mfma_body<LFIX>(
+    forward_mfma_body(
         __builtin_amdgcn_readfirstlane(blockIdx.x * kWaves + (threadIdx.x >> 6)), chains, tasks,
         n_tasks, cmat, aux, W, wshift, aux_elems, total_slices, paths, perm, filt, blk_logz,
         sweep_ptr, status, rsc, neg, blk_la, endrow, ctasks, ccount);
@@ -494,6 +512,13 @@ __global__ __launch_bounds__(kThreads, 1) void k_forward_dmfma_big(
 // stores of step j (a compiler fence keeps that order) and is waited for one step later, when
 // those loads are long done and the stores may still be in flight. Task, chain, slice and row
 // bases are wavefront-uniform (scalar registers), so a store is one lane offset plus a constant.
+// A wavefront's instructions issue in order, so the two worldlines of a pair overlap little: a step
+// of a pair takes 1.85 us alone on a SIMD, a step of a lone worldline 0.95. Dense lists of up to
+// kSplitPairs pairs (two rounds of two wavefronts on each of 1024 SIMDs) therefore run one worldline
+// to a wavefront (4 Ising 32 x 32 x 160 chains, 292 pairs: 296 -> 177 us; 19 of 40 .. 160 slices,
+// 1387 pairs: 514 -> 387); above it the rows' stores bound both, and the pair's shared W counts
+// (64 chains of 80 slices, 4672 pairs: 799 us in pairs, 878 apart).
+constexpr int kSplitPairs = 2048;
 template <int LFIX>
 __device__ __forceinline__ void forward_mfma2_body(
     int task, const ChainInfo* __restrict__ chains, const PairTask* __restrict__ tasks, int n_tasks,
@@ -505,9 +530,17 @@ __device__ __forceinline__ void forward_mfma2_body(
     float* __restrict__ endrow, const PairTask* __restrict__ ctasks,
     const int32_t* __restrict__ ccount) {
     const int lane = threadIdx.x & 63;
-    // with the dense list of representative pairs (k_dedup), wavefront i takes its entry i
-    if (task >= (ccount ? *ccount : n_tasks)) return;  // whole wavefront; no barriers here
-    const PairTask t = ccount ? ctasks[task] : tasks[task];
+    // with the dense list of representative pairs (k_dedup), wavefront i takes its entry i, or,
+    // of at most kSplitPairs pairs that the launch has wavefronts for, one worldline of entry i / 2
+    const int n_list = ccount ? *ccount : n_tasks;
+    const bool split = ccount && n_list <= kSplitPairs && 2 * n_list <= n_tasks;
+    if (task >= (split ? 2 * n_list : n_list)) return;  // whole wavefront; no barriers here
+    PairTask t = ccount ? ctasks[split ? task >> 1 : task] : tasks[task];
+    if (split) {
+        t.p_a = task & 1 ? t.p_b : t.p_a;
+        t.p_b = -1;
+        if (t.p_a < 0) return;
+    }
     if (rescue_held(rsc, t.chain)) return;  // re-filtered whole in FP64 this pass
     const ChainInfo& c = chains[t.chain];
     // shared forward filters: only representatives run the recursion (k_member_logz completes
@@ -976,15 +1009,7 @@ __global__ __launch_bounds__(kThreads) void k_forward_mfma64(
     }
 }
 
-// Raw buffer resources: word 3 of the descriptor on gfx9-family chips (32-bit data format,
-// no swizzle), and the cache-policy bit of a streaming (nontemporal) store.
-constexpr int kBufferWord3 = 0x00020000;
-constexpr int kNontemporal = 2;
 
-// Bits of a float for the b32 buffer store. The value is taken as a function argument: applied
-// directly to an element of an ext_vector_type, __builtin_bit_cast reads element 0 whatever the
-// index (seen with this compiler), so it never gets a vector element.
-__device__ inline uint32_t fbits(float f) { return __builtin_bit_cast(uint32_t, f); }
 
 // Segmented sum over the lanes that share a column block of BS lanes (BS = 16: the DPP rows
 // J and J + 2; BS = 8: the half rows J and J + 4): every lane gets its block's sum. The two
@@ -1049,8 +1074,6 @@ __device__ __forceinline__ void forward_pack_body(
     const double* shift = wshift + spin * total_slices + c.slice_off;
     const double coef = spin ? c.coef_dn : c.coef_up;
     const int32_t* pc = paths + c.path_off;
-    // a full task (every slot its own worldline, L filling the blocks) stores unmasked
-    const bool full = t.n == NT * PP && L == BS;
 
     Split3 C;
     {
@@ -1067,15 +1090,16 @@ __device__ __forceinline__ void forward_pack_body(
     // register v holds tile row 8 (v / 4) + 4 hl + v % 4: block row I(v) = v / RPB, local row
     // 4 hl + cv(v)
     auto cv = [](int v) { return 8 * (v >> 2) + (v & 3) - BS * (v / RPB); };
+    auto inside = [&](int v) { return lx < L && 4 * hl + cv(v) < L; };
     const int64_t rowoff = (int64_t)t.block * (c.B - 1);
-    // per (tile, block row): this lane's slot, its byte offset in the chain's filter region
-    // (element (4 hl + cv(v), lx) of the block at off + 4 cv(v) L) and whether it is stored.
-    // The region is addressed through a buffer resource (32-bit offsets; the plan packs only
-    // chains whose filter region is under 2 GiB).
+    // per (tile, register): the byte offset of the lane's element in the chain's filter region,
+    // past its end where the slot is empty or the position padded (the store is dropped). The
+    // region is addressed through a buffer resource (32-bit offsets; the plan packs only chains
+    // whose filter region is under 2 GiB).
     const __amdgpu_buffer_rsrc_t frs = __builtin_amdgcn_make_buffer_rsrc(
         filt + c.filt_off, (short)0, 0x7fffffff, kBufferWord3);
-    uint32_t off[NT][P];
-    bool ok[NT][P];
+    constexpr uint32_t kNowhere = 0x80000000u;
+    uint32_t off[NT][16];
     // rows hold f~ 2^row_exp (the FP32 range scaling), from f_0 = 2^row_exp delta_a on
     const float sc = ldexpf(1.0f, c.row_exp);
     const double lsc = c.row_exp * 0.69314718055994530942;
@@ -1093,8 +1117,12 @@ __device__ __forceinline__ void forward_pack_body(
 #pragma unroll
             for (int v = I * RPB; v < (I + 1) * RPB; ++v)
                 F[T][v] = (lx == ax && 4 * hl + cv(v) == ay) ? sc : 0.0f;
-            off[T][I] = (uint32_t)((((int64_t)pw * L_tau + rowoff) * N + 4 * hl * L + lx) * 4);
-            ok[T][I] = s < t.n && lx < L;
+#pragma unroll
+            for (int v = I * RPB; v < (I + 1) * RPB; ++v)
+                off[T][v] = s < t.n && inside(v)
+                                ? (uint32_t)((((int64_t)pw * L_tau + rowoff) * N +
+                                              (4 * hl + cv(v)) * L + lx) * 4)
+                                : kNowhere;
         }
     // owner lane: slot (T, I, J) with T P + I = lx, first half
     const int oti = lx;
@@ -1117,19 +1145,26 @@ __device__ __forceinline__ void forward_pack_body(
             la = coef * (double)aux[c.aux_off + (int64_t)start * N + a] - lsc;
         }
     }
-    auto inside = [&](int v) { return lx < L && 4 * hl + cv(v) < L; };
-    auto load_w = [&](int l, float (&dst)[16]) {
-        const float* Wl = Wsp + (int64_t)l * N + 4 * hl * L + lx;
-        // a padded position reads the slice's first site and multiplies an exact zero of C f C
+    // W of the block rows' positions, the same for every block row (RPB registers); a padded
+    // position loads zero and multiplies an exact zero of C f C
+    uint32_t at[RPB];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) dst[v] = inside(v) ? Wl[cv(v) * L] : Wsp[(int64_t)l * N];
+    for (int v = 0; v < RPB; ++v)
+        at[v] = lx < L ? (uint32_t)((4 * hl + cv(v)) * L + lx) * 4 : kOutside;
+    auto load_w = [&](int l, float (&dst)[RPB]) {
+        const __amdgpu_buffer_rsrc_t ws = float_rsrc(Wsp + (int64_t)l * N, N);
+#pragma unroll
+        for (int v = 0; v < RPB; ++v)
+            dst[v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ws, at[v], 0, 0));
     };
     bool low = false;  // the owner's worldline left FP32's range: FP64 re-filter
-    // two W buffers that swap roles every step (one buffer would make the loop's back edge copy
-    // the loaded slice into it, waiting for the load)
-    float wa[16], wb[16];
+    // W of this slice and of the next two, in three buffers that rotate every step: a load takes
+    // about as long as a step, so it is issued two steps ahead (one step ahead, behind per-position
+    // masks, a step took 1.8 us on 16 x 16 and 1.7 on 8 x 8; it takes 1.0)
+    float wa[RPB], wb[RPB], wc[RPB];
     load_w((start + 1) % L_tau, wa);
-    auto step = [&](int j, const float (&wn)[16], float (&wf)[16]) {
+    load_w((start + 2) % L_tau, wb);
+    auto step = [&](int j, const float (&wn)[RPB], float (&wf)[RPB]) {
         const int l = (start + j) % L_tau;
         f32x16 H[NT];
 #pragma unroll
@@ -1145,10 +1180,10 @@ __device__ __forceinline__ void forward_pack_body(
         for (int v = 0; v < 16; ++v)
 #pragma unroll
             for (int T = 0; T < NT; ++T) {
-                F[T][v] = H[T][v] * wn[v];
+                F[T][v] = H[T][v] * wn[v % RPB];
                 sm[T][v / RPB] += F[T][v];
             }
-        load_w((l + 1) % L_tau, wf);  // the last step fetches a slice it does not use
+        load_w((l + 2) % L_tau, wf);  // the last two steps fetch slices they do not use
         __builtin_amdgcn_sched_barrier(0);
         float inv[NT][P], mine = 1.0f, mtot = 1.0f;
 #pragma unroll
@@ -1167,39 +1202,28 @@ __device__ __forceinline__ void forward_pack_body(
         int e;
         mant = frexp(mant, &e);
         ex2 += e;
-        // byte offsets: lane part in a VGPR, row and register part in an SGPR
-        const int rowj = (j - 1) * N;
+        const int rowj = (j - 1) * N * 4;  // the scalar part of the byte offsets
 #pragma unroll
         for (int v = 0; v < 16; ++v)
 #pragma unroll
             for (int T = 0; T < NT; ++T) F[T][v] *= inv[T][v / RPB] * sc;
-        if (full) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
+        for (int v = 0; v < 16; ++v)
 #pragma unroll
-                for (int T = 0; T < NT; ++T)
-                    __builtin_amdgcn_raw_buffer_store_b32(fbits(F[T][v]), frs, off[T][v / RPB],
-                                                          (rowj + cv(v) * L) * 4, kNontemporal);
-        } else {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const bool in = 4 * hl + cv(v) < L;
-#pragma unroll
-                for (int T = 0; T < NT; ++T)
-                    if (in && ok[T][v / RPB])
-                        __builtin_amdgcn_raw_buffer_store_b32(fbits(F[T][v]), frs, off[T][v / RPB],
-                                                              (rowj + cv(v) * L) * 4, kNontemporal);
-            }
-        }
+            for (int T = 0; T < NT; ++T)
+                __builtin_amdgcn_raw_buffer_store_b32(fbits(F[T][v]), frs, off[T][v], rowj,
+                                                      kNontemporal);
     };
     if (len > 1) {
-        step(1, wa, wb);
+        step(1, wa, wc);
         int j = 2;
-        for (; j + 1 < len; j += 2) {
+        for (; j + 2 < len; j += 3) {
             step(j, wb, wa);
-            step(j + 1, wa, wb);
+            step(j + 1, wc, wb);
+            step(j + 2, wa, wc);
         }
         if (j < len) step(j, wb, wa);
+        if (j + 1 < len) step(j + 1, wc, wb);
     }
     la += block_shift_sum(shift, start, len, L_tau, lsc, lane);
     // end weights (C f~ C)(e) of every slot: the owner reads its block's element at e
@@ -1229,7 +1253,7 @@ __device__ __forceinline__ void forward_pack_body(
 #pragma unroll
             for (int I = 0; I < P; ++I) {
                 const int s = T * PP + I * P + J;
-                if (!ok[T][I]) continue;
+                if (s >= t.n || lx >= L) continue;
                 float* end = endrow + c.end_off + ((int64_t)wl(s) * c.nb + t.block) * N +
                              4 * hl * L + lx;
 #pragma unroll
@@ -1240,7 +1264,7 @@ __device__ __forceinline__ void forward_pack_body(
 }
 
 template <int P, int NT>
-__global__ __launch_bounds__(kThreads, NT == 1 ? 4 : 2) void k_forward_pack(
+__global__ __launch_bounds__(kThreads, NT == 1 ? 3 : 2) void k_forward_pack(
     const ChainInfo* __restrict__ chains, const PackTask* __restrict__ tasks, int n_tasks,
     const uint16_t* __restrict__ cmatp, const float* __restrict__ aux, const float* __restrict__ W,
     const double* __restrict__ wshift, int64_t aux_elems, int64_t total_slices,
@@ -2019,9 +2043,9 @@ __global__ __launch_bounds__(kThreads) void k_grad_reduce(
 
 // The forward kernel classes of a split-bf16 plan whose chains take several of them (32 x 32
 // pairs, padded tiles, packed 2 x 2 and 4 x 4 tiles) in one launch: workgroups [0, b1) run the
-// pair kernel's tasks, [b1, b2) the padded tiles', [b2, b3) the 2 x 2 packed tiles', the rest
-// the 4 x 4 ones', each class with the arithmetic of its own kernel. Once the chains cluster,
-// each class is a few recursions of up to L_tau - 1 dependent steps; side by side, the pass
+// 2 x 2 packed tiles' tasks, [b1, b2) the 4 x 4 ones', [b2, b3) the padded tiles', the rest the
+// pair kernel's (256 mixed chains: 610 us, pairs first 636), each class with the arithmetic of its
+// own kernel. Once the chains cluster, each class is a few recursions of up to L_tau - 1 dependent steps; side by side, the pass
 // takes the longest of them instead of their sum.
 struct FwdClasses {
     const PairTask* pairs;
@@ -2051,23 +2075,23 @@ __global__ __launch_bounds__(kThreads, 2) void k_forward_classes(
     const int b = blockIdx.x, w = threadIdx.x >> 6;
     auto task = [&](int b0) { return __builtin_amdgcn_readfirstlane((b - b0) * kWaves + w); };
     if (b < fc.b1)
-        forward_mfma2_body<32>(task(0), chains, fc.pairs, fc.n_pairs, cmat, aux, W, wshift,
-                               aux_elems, total_slices, paths, perm, filt, blk_logz, sweep_ptr,
-                               status, rsc, neg, blk_la, endrow, fc.cpairs, fc.n_cpairs);
-    else if (b < fc.b2)
-        forward_mfma_body<0>(task(fc.b1), chains, fc.singles, fc.n_singles, cmat, aux, W, wshift,
-                             aux_elems, total_slices, paths, perm, filt, blk_logz, sweep_ptr,
-                             status, rsc, neg, blk_la, endrow, fc.csingles, fc.n_csingles);
-    else if (b < fc.b3)
-        forward_pack_body<2, kPackTiles>(task(fc.b2), chains, fc.pack2, fc.n_pack2, cmatp, aux, W,
+        forward_pack_body<2, kPackTiles>(task(0), chains, fc.pack2, fc.n_pack2, cmatp, aux, W,
                                          wshift, aux_elems, total_slices, paths, perm, filt,
                                          blk_logz, sweep_ptr, status, rsc, neg, blk_la, endrow,
                                          fc.cpack2, fc.n_cpack2, prep);
-    else
-        forward_pack_body<4, kPackTiles>(task(fc.b3), chains, fc.pack4, fc.n_pack4, cmatp, aux, W,
+    else if (b < fc.b2)
+        forward_pack_body<4, kPackTiles>(task(fc.b1), chains, fc.pack4, fc.n_pack4, cmatp, aux, W,
                                          wshift, aux_elems, total_slices, paths, perm, filt,
                                          blk_logz, sweep_ptr, status, rsc, neg, blk_la, endrow,
                                          fc.cpack4, fc.n_cpack4, prep);
+    else if (b < fc.b3)
+        forward_mfma_body(task(fc.b2), chains, fc.singles, fc.n_singles, cmat, aux, W, wshift,
+                          aux_elems, total_slices, paths, perm, filt, blk_logz, sweep_ptr, status,
+                          rsc, neg, blk_la, endrow, fc.csingles, fc.n_csingles);
+    else
+        forward_mfma2_body<32>(task(fc.b3), chains, fc.pairs, fc.n_pairs, cmat, aux, W, wshift,
+                               aux_elems, total_slices, paths, perm, filt, blk_logz, sweep_ptr,
+                               status, rsc, neg, blk_la, endrow, fc.cpairs, fc.n_cpairs);
 }
 
 }  // namespace
@@ -2119,10 +2143,10 @@ hipError_t launch_forward_mfma(fh_plan p, const void* aux, const int32_t* paths,
         fc.n_singles = p->n_fwdx_tasks;
         fc.n_pack2 = p->n_fwdp2_tasks;
         fc.n_pack4 = p->n_fwdp4_tasks;
-        fc.b1 = blocks_for(p->n_fwd32_tasks);
-        fc.b2 = fc.b1 + blocks_for(p->n_fwdx_tasks);
-        fc.b3 = fc.b2 + blocks_for(p->n_fwdp2_tasks);
-        const int32_t blocks = fc.b3 + blocks_for(p->n_fwdp4_tasks);
+        fc.b1 = blocks_for(p->n_fwdp2_tasks);
+        fc.b2 = fc.b1 + blocks_for(p->n_fwdp4_tasks);
+        fc.b3 = fc.b2 + blocks_for(p->n_fwdx_tasks);
+        const int32_t blocks = fc.b3 + blocks_for(p->n_fwd32_tasks);
         hipLaunchKernelGGL(k_forward_classes, dim3((unsigned)blocks), dim3(kThreads), 0, s,
                            p->d.chains, p->d.cmat, p->d.cmatp, (const float*)aux,
                            (const float*)p->d.W, p->d.wshift, p->aux_elems, p->total_slices,
@@ -2149,7 +2173,7 @@ hipError_t launch_forward_mfma(fh_plan p, const void* aux, const int32_t* paths,
     }
     if (classes == 1 && p->n_fwdx_tasks > 0) {
         const unsigned blocks = (unsigned)((p->n_fwdx_tasks + kWaves - 1) / kWaves);
-        hipLaunchKernelGGL(k_forward_mfma<0>, dim3(blocks), dim3(kThreads), 0, s, p->d.chains,
+        hipLaunchKernelGGL(k_forward_mfma, dim3(blocks), dim3(kThreads), 0, s, p->d.chains,
                            p->d.fwdx_tasks, p->n_fwdx_tasks, p->d.cmat, (const float*)aux,
                            (const float*)p->d.W, p->d.wshift, p->aux_elems, p->total_slices,
                            paths, p->d.perm, (float*)p->d.filt, p->d.blk_logz, p->d.sweep, p->d.status,
