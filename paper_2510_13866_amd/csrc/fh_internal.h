@@ -71,11 +71,14 @@ inline int64_t tab_size(int L) { return 2 * (int64_t)L * L + L + 2 * L; }
 constexpr int kBwCounts = 4;  // offset of the per-chain counts in Device::bw_state
 // k_backward_stage: worldlines per workgroup, bytes of rows per slice in LDS (two slices are held),
 // workgroups per launch, and the row bytes per worldline up to which k_dedup stages a (chain,
-// spin, block).
+// spin, block): below it a row's copy serves enough draws. Backward passes in us, staged / by
+// k_backward_win, at bytes per worldline: 25 chains of 16 x 16 in blocks of 20 slices, 62 / 106 at
+// 256, 100 / 108 at 512, 144 / 111 at 1024; 16 of 24 x 24 x 80, 101 / 135 at 288, 135 / 144 at 576,
+// 201 / 162 at 1152; 8 of 32 x 32 x 80, 107 / 110 at 256, 137 / 117 at 512, 180 / 143 at 1024.
 constexpr int kStageMembers = 64;
 constexpr int kStageBytes = 32768;
 constexpr int kStageGrid = 1024;
-constexpr int kStageCost = 2048;
+constexpr int kStageCost = 384;
 constexpr int kStageMinL = 8;
 // What k_backward_stage draws of a (chain, spin, block): its draws from the plan's rows, and from the
 // FP64 re-filter's slots.

@@ -2744,14 +2744,18 @@ __device__ inline int local_move(const ChainInfo& c, const double* g, const T* a
 // its own slice L_tau-2 and to slice 0 of q. So the thread of p takes both ends of the link: it
 // moves slice 0 of q = perm[p], then slice L_tau-1 of p, which sees the site just taken; no other
 // thread reads or writes either. Two-slice chains, whose slice 1 is both, move it in a launch of
-// its own (PHASE 3). Interior phases take k0 plus the grid's y index as the group k of kLocalSlices
-// slices (from 2 kLocalSlices k + 1 or + 2 on); threads past a chain's last slice of the phase
-// leave. A thread's slices share its chain lookup, and the sites between them are read once. Bound:
+// its own (PHASE 3). Interior phases take k0 plus the grid's y index as the group k of SLICES
+// slices (from 2 SLICES k + 1 or + 2 on); threads past a chain's last slice of the phase
+// leave. A thread's slices share its chain lookup, and the sites between them are read once. A
+// phase too small to fill the chip with four slices to a thread (kLocalFill proposals: two
+// wavefronts on each of 1024 SIMDs) takes one, whose latency is half (17 chains of 18 x 18 x 27:
+// 4.7 us a phase against 8.7; 1.3e6 proposals: 23 against 17.5). Bound:
 // the generator's 64-bit multiplications and the FP64 ratio of each proposal. A pass over 16
 // chains of 512 + 512 worldlines, L_tau = 160, 2.6e6 proposals: 55 us as four launches of one
 // proposal per thread, 39 us as three.
 constexpr int kLocalSlices = 4;
-template <typename T, int PHASE>
+constexpr int64_t kLocalFill = (int64_t)2 * 1024 * 64 * kLocalSlices;
+template <typename T, int PHASE, int SLICES>
 __global__ __launch_bounds__(kThreads) void k_local(const ChainInfo* __restrict__ chains,
                                                     int n_chains, int64_t particles,
                                                     const double* __restrict__ tables,
@@ -2783,15 +2787,15 @@ __global__ __launch_bounds__(kThreads) void k_local(const ChainInfo* __restrict_
         return taken;
     };
     if (PHASE < 2) {
-        // kLocalSlices slices of the phase: the 2 kLocalSlices + 1 sites first, all in flight
-        const int l0 = 2 * kLocalSlices * (k0 + (int)blockIdx.y) + 1 + PHASE;
+        // SLICES slices of the phase: the 2 SLICES + 1 sites first, all in flight
+        const int l0 = 2 * SLICES * (k0 + (int)blockIdx.y) + 1 + PHASE;
         if (l0 > L_tau - 2) return;
-        int site[2 * kLocalSlices + 1];
+        int site[2 * SLICES + 1];
 #pragma unroll
-        for (int i = 0; i <= 2 * kLocalSlices; ++i)
+        for (int i = 0; i <= 2 * SLICES; ++i)
             site[i] = col[(int64_t)min(l0 - 1 + i, L_tau - 1) * np + p];
 #pragma unroll
-        for (int i = 0; i < kLocalSlices; ++i)
+        for (int i = 0; i < SLICES; ++i)
             if (l0 + 2 * i <= L_tau - 2)
                 move(l0 + 2 * i, p, site[2 * i], site[2 * i + 2], site[2 * i + 1]);
     } else {
@@ -3786,7 +3790,10 @@ hipError_t launch_local_t(fh_plan p, const T* aux, int32_t* paths, int n_passes,
         two_slices = two_slices || c.L_tau == 2;
     }
     // slice groups of the interior phases
-    const int pairs = std::max(1, ((max_tau - 1) / 2 + kLocalSlices - 1) / kLocalSlices);
+    const int odd = (max_tau - 1) / 2;
+    const bool wide = p->particles * odd >= kLocalFill;
+    const int per = wide ? kLocalSlices : 1;
+    const int pairs = std::max(1, (odd + per - 1) / per);
     constexpr int kMaxGridY = 65535;
     for (int ps = 0; ps < n_passes; ++ps) {
         auto run = [&](auto kern, dim3 grid, int k0) {
@@ -3794,12 +3801,19 @@ hipError_t launch_local_t(fh_plan p, const T* aux, int32_t* paths, int n_passes,
                                p->particles, p->d.tables, aux, paths, p->d.perm, p->d.sweep, ps,
                                k0, p->d.status);
         };
-        for (int k0 = 0; k0 < pairs; k0 += kMaxGridY)
-            run(k_local<T, 0>, dim3(blocks, (unsigned)std::min(kMaxGridY, pairs - k0)), k0);
-        for (int k0 = 0; k0 < pairs; k0 += kMaxGridY)
-            run(k_local<T, 1>, dim3(blocks, (unsigned)std::min(kMaxGridY, pairs - k0)), k0);
-        run(k_local<T, 2>, dim3(blocks), 0);
-        if (two_slices) run(k_local<T, 3>, dim3(blocks), 0);
+        auto interior = [&](auto kern) {
+            for (int k0 = 0; k0 < pairs; k0 += kMaxGridY)
+                run(kern, dim3(blocks, (unsigned)std::min(kMaxGridY, pairs - k0)), k0);
+        };
+        if (wide) {
+            interior(k_local<T, 0, kLocalSlices>);
+            interior(k_local<T, 1, kLocalSlices>);
+        } else {
+            interior(k_local<T, 0, 1>);
+            interior(k_local<T, 1, 1>);
+        }
+        run(k_local<T, 2, 1>, dim3(blocks), 0);
+        if (two_slices) run(k_local<T, 3, 1>, dim3(blocks), 0);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

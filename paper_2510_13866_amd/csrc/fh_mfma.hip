@@ -98,6 +98,23 @@ __device__ inline f32x16 mfma(const bf16x8& a, const bf16x8& b, const f32x16& c)
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// The pair e of chunk q of split3_chunk, with the residuals on the vector unit (shift or mask, then an
+// exact subtraction): v_dot2 holds up the matrix core, these instructions run beside its products.
+// (No contraction: fused with the product a row value comes from, a residual would not be exact.)
+__device__ inline void split3_pair(const f32x16& x, int q, int e, u32x4& uh, u32x4& um, u32x4& ul) {
+#pragma clang fp contract(off)
+    auto lo = [](uint32_t p, float a) { return a - __builtin_bit_cast(float, p << 16); };
+    auto hi = [](uint32_t p, float b) { return b - __builtin_bit_cast(float, p & 0xFFFF0000u); };
+    const float a = x[8 * q + 2 * e], b = x[8 * q + 2 * e + 1];
+    const uint32_t ph = pk_bf16(a, b);
+    const float ra = lo(ph, a), rb = hi(ph, b);
+    const uint32_t pm = pk_bf16(ra, rb);
+    const float sa = lo(pm, ra), sb = hi(pm, rb);
+    uh[e] = ph;
+    um[e] = pm;
+    ul[e] = pk_bf16(sa, sb);
+}
+
 // X (accumulator layout) -> X^T C: six split products per K chunk, smaller terms first.
 __device__ inline f32x16 circ_step(const f32x16& x, const Split3& C, const NegPairs& n) {
     f32x16 acc = {};
@@ -112,6 +129,46 @@ __device__ inline f32x16 circ_step(const f32x16& x, const Split3& C, const NegPa
         acc = mfma(h, C.m[q], acc);
         acc = mfma(h, C.h[q], acc);
     }
+    return acc;
+}
+
+// circ_step for the forward recursions, whose passes often have few wavefronts. The twelve
+// products are one chain of accumulations, 34 cycles each, and a wavefront issues in order, so the
+// second chunk is split between the first chunk's products (eleven vector instructions take about
+// 60 cycles, six fit beside a product; with v_dot2 residuals six take 40 cycles on top of it). The
+// scheduling barriers, which scalar and memory instructions may cross, keep them there: a step of a
+// lone 16 x 16 recursion takes 0.85 us, 0.95 with both chunks split ahead of their products.
+__device__ inline f32x16 circ_step_lone(const f32x16& x, const Split3& C, const NegPairs& n) {
+    constexpr int kAddrMem = 0x4 | 0x10;
+    f32x16 acc = {};
+    bf16x8 h, m, l;
+    u32x4 uh, um, ul;
+    split3_chunk(x, 0, h, m, l, n);
+    __builtin_amdgcn_sched_barrier(kAddrMem);
+    acc = mfma(l, C.h[0], acc);
+    split3_pair(x, 1, 0, uh, um, ul);
+    __builtin_amdgcn_sched_barrier(kAddrMem);
+    acc = mfma(m, C.m[0], acc);
+    split3_pair(x, 1, 1, uh, um, ul);
+    __builtin_amdgcn_sched_barrier(kAddrMem);
+    acc = mfma(m, C.h[0], acc);
+    split3_pair(x, 1, 2, uh, um, ul);
+    __builtin_amdgcn_sched_barrier(kAddrMem);
+    acc = mfma(h, C.l[0], acc);
+    __builtin_amdgcn_sched_barrier(kAddrMem);
+    acc = mfma(h, C.m[0], acc);
+    split3_pair(x, 1, 3, uh, um, ul);
+    __builtin_amdgcn_sched_barrier(kAddrMem);
+    acc = mfma(h, C.h[0], acc);
+    h = __builtin_bit_cast(bf16x8, uh);
+    m = __builtin_bit_cast(bf16x8, um);
+    l = __builtin_bit_cast(bf16x8, ul);
+    acc = mfma(l, C.h[1], acc);
+    acc = mfma(m, C.m[1], acc);
+    acc = mfma(m, C.h[1], acc);
+    acc = mfma(h, C.l[1], acc);
+    acc = mfma(h, C.m[1], acc);
+    acc = mfma(h, C.h[1], acc);
     return acc;
 }
 
@@ -242,20 +299,24 @@ __device__ __forceinline__ void forward_mfma_body(
     // stores retire in order, and loaded after the stores W waited for them in every step
     // (24 x 24: 1.55 us a step, now 1.05)
     float wa[16], wb[16], wc[16];
-    load_w((start + 1) % L_tau, wa);
-    load_w((start + 2) % L_tau, wb);
+    int lw = (start + 1) % L_tau;  // the slice of the next load (a running index: no division)
+    auto next_w = [&](float (&dst)[16]) {
+        load_w(lw, dst);
+        lw = lw + 1 == L_tau ? 0 : lw + 1;
+    };
+    next_w(wa);
+    next_w(wb);
     bool low = false;  // the block left FP32's range: queued for the FP64 re-filter
     auto step = [&](int j, const float (&wn)[16], float (&wf)[16]) {
-        const int l = (start + j) % L_tau;
-        const f32x16 X = circ_step(F, C, neg);
-        const f32x16 H = circ_step(X, C, neg);
+        const f32x16 X = circ_step_lone(F, C, neg);
+        const f32x16 H = circ_step_lone(X, C, neg);
         float s = 0.0f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             F[v] = H[v] * wn[v];
             s += F[v];
         }
-        load_w((l + 2) % L_tau, wf);  // the last two steps fetch slices they do not use
+        next_w(wf);  // the last two steps fetch slices they do not use
         __builtin_amdgcn_sched_barrier(0);
         const float tot = wave_sum_f32(s);
         low |= !(tot >= step_floor) | !isfinite(tot);
@@ -295,8 +356,8 @@ __device__ __forceinline__ void forward_mfma_body(
     }
     la += block_shift_sum(shift, start, len, L_tau, lsc, lane);
     // end weight (C f~ C)(e)
-    const f32x16 X = circ_step(F, C, neg);
-    const f32x16 H = circ_step(X, C, neg);
+    const f32x16 X = circ_step_lone(F, C, neg);
+    const f32x16 H = circ_step_lone(X, C, neg);
     const int ex = e % L, ey = e / L;
     const int ve = (ey >> 3) * 4 + (ey & 3);
     const int le = ex + 32 * ((ey >> 2) & 1);
@@ -627,20 +688,24 @@ __device__ __forceinline__ void forward_mfma2_body(
         // is hidden; with a single buffer the loop's back edge would copy the freshly loaded
         // slice into it and wait for the load in every step
         float wa[16], wb[16], wc[16];
-        load_w((start + 1) % L_tau, wa);
-        load_w((start + 2) % L_tau, wb);
+        int lw = (start + 1) % L_tau;  // the slice of the next load (a running index: no division)
+        auto next_w = [&](float (&dst)[16]) {
+            load_w(lw, dst);
+            lw = lw + 1 == L_tau ? 0 : lw + 1;
+        };
+        next_w(wa);
+        next_w(wb);
         bool low0 = false, low1 = false;  // a worldline left FP32's range: FP64 re-filter
         // One step: uses wn (this slice's W) and loads the W of the slice after next into wf
         // before the stores, so that the wait before a W multiply leaves the stores in flight.
         auto step = [&](int j, const float (&wn)[16], float (&wf)[16]) {
-            const int l = (start + j) % L_tau;
             f32x16 H0, H1;
             {
-                const f32x16 X0 = circ_step(F0, C, neg);
+                const f32x16 X0 = circ_step_lone(F0, C, neg);
                 f32x16 X1;
-                if constexpr (PAIR) X1 = circ_step(F1, C, neg);
-                H0 = circ_step(X0, C, neg);
-                if constexpr (PAIR) H1 = circ_step(X1, C, neg);
+                if constexpr (PAIR) X1 = circ_step_lone(F1, C, neg);
+                H0 = circ_step_lone(X0, C, neg);
+                if constexpr (PAIR) H1 = circ_step_lone(X1, C, neg);
             }
             float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
@@ -654,7 +719,7 @@ __device__ __forceinline__ void forward_mfma2_body(
             }
             // the W of the slice after next (the last two steps fetch slices they do not use;
             // always in bounds)
-            load_w((l + 2) % L_tau, wf);
+            next_w(wf);
             __builtin_amdgcn_sched_barrier(0);
             const float tot0 = wave_sum_f32(s0), tot1 = PAIR ? wave_sum_f32(s1) : 1.0f;
             low0 |= !(tot0 >= step_floor) | !isfinite(tot0);
@@ -711,11 +776,11 @@ __device__ __forceinline__ void forward_mfma2_body(
         // end weights (C f~ C)(e)
         f32x16 H0, H1;
         {
-            const f32x16 X0 = circ_step(F0, C, neg);
+            const f32x16 X0 = circ_step_lone(F0, C, neg);
             f32x16 X1;
-            if constexpr (PAIR) X1 = circ_step(F1, C, neg);
-            H0 = circ_step(X0, C, neg);
-            if constexpr (PAIR) H1 = circ_step(X1, C, neg);
+            if constexpr (PAIR) X1 = circ_step_lone(F1, C, neg);
+            H0 = circ_step_lone(X0, C, neg);
+            if constexpr (PAIR) H1 = circ_step_lone(X1, C, neg);
         }
         float hv0 = 0.0f, hv1 = 0.0f;
         {
@@ -1162,15 +1227,19 @@ __device__ __forceinline__ void forward_pack_body(
     // about as long as a step, so it is issued two steps ahead (one step ahead, behind per-position
     // masks, a step took 1.8 us on 16 x 16 and 1.7 on 8 x 8; it takes 1.0)
     float wa[RPB], wb[RPB], wc[RPB];
-    load_w((start + 1) % L_tau, wa);
-    load_w((start + 2) % L_tau, wb);
+    int lw = (start + 1) % L_tau;  // the slice of the next load (a running index: no division)
+    auto next_w = [&](float (&dst)[RPB]) {
+        load_w(lw, dst);
+        lw = lw + 1 == L_tau ? 0 : lw + 1;
+    };
+    next_w(wa);
+    next_w(wb);
     auto step = [&](int j, const float (&wn)[RPB], float (&wf)[RPB]) {
-        const int l = (start + j) % L_tau;
         f32x16 H[NT];
 #pragma unroll
-        for (int T = 0; T < NT; ++T) H[T] = circ_step(F[T], C, neg);
+        for (int T = 0; T < NT; ++T) H[T] = circ_step_lone(F[T], C, neg);
 #pragma unroll
-        for (int T = 0; T < NT; ++T) H[T] = circ_step(H[T], C, neg);
+        for (int T = 0; T < NT; ++T) H[T] = circ_step_lone(H[T], C, neg);
         float sm[NT][P];
 #pragma unroll
         for (int T = 0; T < NT; ++T)
@@ -1183,7 +1252,7 @@ __device__ __forceinline__ void forward_pack_body(
                 F[T][v] = H[T][v] * wn[v % RPB];
                 sm[T][v / RPB] += F[T][v];
             }
-        load_w((l + 2) % L_tau, wf);  // the last two steps fetch slices they do not use
+        next_w(wf);  // the last two steps fetch slices they do not use
         __builtin_amdgcn_sched_barrier(0);
         float inv[NT][P], mine = 1.0f, mtot = 1.0f;
 #pragma unroll
@@ -1229,7 +1298,7 @@ __device__ __forceinline__ void forward_pack_body(
     // end weights (C f~ C)(e) of every slot: the owner reads its block's element at e
     f32x16 H[NT];
 #pragma unroll
-    for (int T = 0; T < NT; ++T) H[T] = circ_step(circ_step(F[T], C, neg), C, neg);
+    for (int T = 0; T < NT; ++T) H[T] = circ_step_lone(circ_step_lone(F[T], C, neg), C, neg);
     const int row = BS * oI + oe / L, col = BS * J + oe % L;
     const int src = col + 32 * ((row >> 2) & 1), ve = 4 * (row >> 3) + (row & 3);
     float hv = 0.0f;
