@@ -2597,27 +2597,30 @@ __global__ __launch_bounds__(kThreads) void k_member_logz(
 }
 
 
-// Before the FP64 re-filter, one workgroup per (chain, slice) of the chains with blocks in the
-// phase's part of the queue (phase 0: queued; 1: in phase A; 2: queued, not in phase A):
-// W~ = exp(coef aux - m) in FP64 for both spins (the FP32 tables may hold zeros), with the
-// shift m of the FP32 tables.
+// Before the FP64 re-filter, per_chain workgroups for every chain with blocks in the phase's part
+// of the queue (phase 0: queued; 1: in phase A; 2: queued, not in phase A), each taking every
+// per_chain-th slice: W~ = exp(coef aux - m) in FP64 for both spins (the FP32 tables may hold
+// zeros), with the shift m of the FP32 tables. Most passes queue little or nothing, and a workgroup
+// per slice, each looking for its chain, then costs its dispatch (256 mixed chains, 23800 slices:
+// 24 us twice a sweep; RPOT).
 __global__ __launch_bounds__(kThreads) void k_rescue_potentials(
     const ChainInfo* __restrict__ chains, int n_chains, const float* __restrict__ aux,
     const double* __restrict__ wshift, double* __restrict__ W64, int64_t aux_elems,
-    int64_t total_slices, const Rescue rsc, int phase) {
-    const int gs = blockIdx.x;
-    const int ci = find_chain(n_chains, gs, [&](int i) { return chains[i].slice_off; });
+    int64_t total_slices, const Rescue rsc, int phase, int per_chain) {
+    const int ci = blockIdx.x / per_chain, first = blockIdx.x - ci * per_chain;
     const bool in_a = rsc.words[kRescueChain + 2 * n_chains + ci] == 1;
     const bool queued = phase == 1 ? in_a
                                    : rsc.words[kRescueChain + ci] != 0 && !(phase == 2 && in_a);
     if (!queued) return;  // nothing of this chain is in this phase
     const ChainInfo& c = chains[ci];
-    const int64_t base = c.aux_off + (int64_t)(gs - c.slice_off) * c.N;
-    const double mu = wshift[gs], md = wshift[total_slices + gs];
-    for (int r = threadIdx.x; r < c.N; r += blockDim.x) {
-        const double v = (double)aux[base + r];
-        W64[base + r] = exp(c.coef_up * v - mu);
-        W64[aux_elems + base + r] = exp(c.coef_dn * v - md);
+    for (int l = first; l < c.L_tau; l += per_chain) {
+        const int64_t base = c.aux_off + (int64_t)l * c.N;
+        const double mu = wshift[c.slice_off + l], md = wshift[total_slices + c.slice_off + l];
+        for (int r = threadIdx.x; r < c.N; r += blockDim.x) {
+            const double v = (double)aux[base + r];
+            W64[base + r] = exp(c.coef_up * v - mu);
+            W64[aux_elems + base + r] = exp(c.coef_dn * v - md);
+        }
     }
 }
 
@@ -3570,7 +3573,7 @@ hipError_t launch_logz_reduce(fh_plan p, double* logZ, hipStream_t s) {
 }
 
 namespace {
-hipError_t launch_backward_kernels(fh_plan p, int32_t* paths, hipStream_t s) {
+hipError_t launch_backward_kernels(fh_plan p, int32_t* paths, hipStream_t s, hipStream_t rest) {
     if (p->n_stage_tasks > 0 && !p->share_off) {
         auto run = [&](auto kern, auto* filt) {
             hipLaunchKernelGGL(kern, dim3((unsigned)std::min(p->n_stage_tasks, kStageGrid)),
@@ -3584,6 +3587,7 @@ hipError_t launch_backward_kernels(fh_plan p, int32_t* paths, hipStream_t s) {
         else
             run(k_backward_stage<float, false>, (const float*)p->d.filt);
     }
+    s = rest;  // the kernels below draw other worldlines
     if (p->n_draww_tasks > 0) {
         const unsigned blocks = (unsigned)((p->n_draww_tasks + kThreads / kWinLanes - 1) /
                                            (kThreads / kWinLanes));
@@ -3699,9 +3703,12 @@ hipError_t launch_member_logz(fh_plan p, const int32_t* paths, hipStream_t s) {
 hipError_t launch_rescue(fh_plan p, const void* aux, int32_t* paths, bool draw, int phase,
                          hipStream_t s) {
     if (!p->d.rescue) return hipSuccess;
-    hipLaunchKernelGGL(k_rescue_potentials, dim3((unsigned)p->total_slices), dim3(kThreads), 0, s,
-                       p->d.chains, p->n_chains, (const float*)aux, p->d.wshift, p->d.rescue_w,
-                       p->aux_elems, p->total_slices, rescue_args(p), phase);
+    // about 4096 workgroups, and no more to a chain than the longest has slices
+    const int64_t per_chain = std::max<int64_t>(1, std::min<int64_t>(p->max_tau, 4096 / p->n_chains));
+    hipLaunchKernelGGL(k_rescue_potentials, dim3((unsigned)(p->n_chains * per_chain)),
+                       dim3(kThreads), 0, s, p->d.chains, p->n_chains, (const float*)aux,
+                       p->d.wshift, p->d.rescue_w, p->aux_elems, p->total_slices, rescue_args(p),
+                       phase, (int)per_chain);
     const unsigned blocks = (unsigned)(p->n_rescue_slots / kWaves);
     // representatives into their slots (phase B: chains phase A does not have), a workgroup per
     // representative and one launch per tiling, then their worldlines' staged draws
@@ -3769,11 +3776,11 @@ hipError_t launch_rescue(fh_plan p, const void* aux, int32_t* paths, bool draw, 
     return hipGetLastError();
 }
 
-hipError_t launch_backward(fh_plan p, int32_t* paths, bool adapt, hipStream_t s) {
+hipError_t launch_backward(fh_plan p, int32_t* paths, bool adapt, hipStream_t s, hipStream_t rest) {
     // staged draws where worldlines share rows; windowed draws where the hopping kernel allows
     // them; 32 x 32 chains without the window (or moved off it for this sweep by bw_adapt) on their
     // own full-row kernel, the rest on the generic ones
-    hipError_t e = launch_backward_kernels(p, paths, s);
+    hipError_t e = launch_backward_kernels(p, paths, s, rest);
     if (e != hipSuccess || !adapt || !p->bw_adapt || p->n_draww_tasks == 0) return e;
     hipLaunchKernelGGL(k_bw_adapt, dim3(1), dim3(kThreads), 0, s, p->d.chains, p->n_chains,
                        p->d.bw_state);
