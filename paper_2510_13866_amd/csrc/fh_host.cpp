@@ -327,6 +327,7 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
         p->max_L = std::max(p->max_L, ci.L);
         p->max_np = std::max(p->max_np, ci.np);
         p->max_tau = std::max(p->max_tau, ci.L_tau);
+        p->mixed_sides = p->mixed_sides || (!p->chains.empty() && ci.L != p->chains[0].L);
         p->chains.push_back(ci);
     }
     p->aux_elems = aux;
@@ -952,9 +953,15 @@ static hipError_t enqueue_sweep_body(fh_plan p, void* aux, int32_t* paths, bool 
     }
     if (e == hipSuccess) e = enqueue_forward_kernels(p, aux, paths, true, s);
     if (e == hipSuccess) e = mark(p, 2, s);
-    // the draws that are not staged run beside those that are: they write other worldlines' sites,
-    // and one kernel after another a sweep waited for the slowest worldlines of each
-    const bool apart = split && p->n_stage_tasks > 0 && !p->share_off;
+    // The draws that are not staged run beside those that are: they write other worldlines' sites,
+    // and one kernel after another a sweep waited for the slowest worldlines of each (256 mixed
+    // chains 1553 -> 1495 us, 64 Ising 16 x 16 252 -> 244, 16 x 32 x 32 414 -> 407). Not so in plans
+    // of one lattice side with more than kApartDraws worldline blocks: their unstaged kernels mostly
+    // find nothing to draw, and their empty workgroups take the places of the staged draws' second
+    // round (4 x 32 x 32 x 1024 in 16 blocks, 65536 of them: 377 us one after another, 396 beside).
+    constexpr int kApartDraws = 32768;
+    const bool apart = split && p->n_stage_tasks > 0 && !p->share_off &&
+                       (p->mixed_sides || p->n_draww_tasks <= kApartDraws);
     hipStream_t rest = apart ? p->draw_stream : s;
     if (e == hipSuccess && apart) e = hipEventRecord(p->draw_fork_ev, s);
     if (e == hipSuccess && apart) e = hipStreamWaitEvent(rest, p->draw_fork_ev, 0);

@@ -428,6 +428,7 @@ struct fh_plan_s {
     int64_t rescue_slot_elems = 0;  // doubles per slot: (B - 1) N of the largest L <= 32 chain
     int64_t total_sites = 0;  // sum of N over the chains
     int32_t max_N = 0, max_L = 0, max_np = 0, max_tau = 0;
+    bool mixed_sides = false;  // chains of more than one lattice side
     size_t real_size = 8;
     std::vector<fh::TuneRecord> tune_log;  // FH_FLAG_AUTOTUNE timings, in the order taken
     fh::Device d;

@@ -1119,6 +1119,9 @@ __global__ __launch_bounds__(kThreads) void k_backward_win(
     // chain is windowed)
     const bool active = listed && (SLOT ? c.win_on != 0 : !rescue_queued(rsc, c, t.p, t.block)) &&
                         !staged(rsc, c, t.p, t.block, SLOT ? kStagedSlots : kStagedRows);
+    // most workgroups have nothing to draw where k_backward_stage draws: they leave at once, as they
+    // hold its workgroups up (4 x 32 x 32 x 1024 in 16 blocks: 408 -> 396 us a sweep)
+    if (!__syncthreads_or(active)) return;
     // an inactive group draws nothing; on a one-site lattice its table fill and loads stay minimal
     const int L = active ? c.L : 1, N = active ? c.N : 1, L_tau = c.L_tau, w = c.win_w;
     double* g = gsh[grp] + kWinMaxL;  // g[d] = g(d mod L) for -L < d < L
@@ -1127,7 +1130,7 @@ __global__ __launch_bounds__(kThreads) void k_backward_win(
         g[d] = gd;
         g[d - L] = gd;
     }
-    __syncthreads();  // the only barrier; every wave reaches it
+    __syncthreads();  // every wave of a workgroup that draws reaches it
     const uint64_t sweep = *sweep_ptr;
     int start = 0, len = 1;
     if (active) block_of(c, sweep, t.block, &start, &len);
@@ -2602,7 +2605,7 @@ __global__ __launch_bounds__(kThreads) void k_member_logz(
 // per_chain-th slice: W~ = exp(coef aux - m) in FP64 for both spins (the FP32 tables may hold
 // zeros), with the shift m of the FP32 tables. Most passes queue little or nothing, and a workgroup
 // per slice, each looking for its chain, then costs its dispatch (256 mixed chains, 23800 slices:
-// 24 us twice a sweep; RPOT).
+// 24 us twice a sweep, 6 this way).
 __global__ __launch_bounds__(kThreads) void k_rescue_potentials(
     const ChainInfo* __restrict__ chains, int n_chains, const float* __restrict__ aux,
     const double* __restrict__ wshift, double* __restrict__ W64, int64_t aux_elems,
