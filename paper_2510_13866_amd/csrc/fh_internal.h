@@ -429,6 +429,10 @@ struct fh_plan_s {
     int64_t total_sites = 0;  // sum of N over the chains
     int32_t max_N = 0, max_L = 0, max_np = 0, max_tau = 0;
     bool mixed_sides = false;  // chains of more than one lattice side
+    // what d.sweep holds once the work queued so far has run; unknown after a failed call, and for
+    // good once a caller's graph writes it
+    bool sweep_known = false, sweep_captured = false;
+    uint64_t sweep_word = 0;
     size_t real_size = 8;
     std::vector<fh::TuneRecord> tune_log;  // FH_FLAG_AUTOTUNE timings, in the order taken
     fh::Device d;

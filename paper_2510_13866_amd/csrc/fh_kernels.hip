@@ -3522,8 +3522,20 @@ size_t grad_lds_bytes(fh_plan p) {
 }
 
 hipError_t launch_set_sweep(fh_plan p, uint64_t sweep, hipStream_t s) {
+    // recorded into a caller's graph, the kernel runs whenever that graph does: from then on the
+    // word's value is not known here
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const hipError_t ce = hipStreamIsCapturing(s, &cap);
+    if (ce != hipSuccess) (void)hipGetLastError();
+    p->sweep_captured = p->sweep_captured || ce != hipSuccess || cap != hipStreamCaptureStatusNone;
+    p->sweep_known = false;
     hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, s, p->d.sweep, sweep);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e == hipSuccess && !p->sweep_captured) {
+        p->sweep_known = true;
+        p->sweep_word = sweep;
+    }
+    return e;
 }
 
 hipError_t launch_zero(void* ptr, int64_t bytes, hipStream_t s) {
