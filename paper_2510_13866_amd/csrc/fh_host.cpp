@@ -255,9 +255,6 @@ static void destroy_streams(fh_plan p) {
     if (p->side_stream) (void)hipStreamDestroy(p->side_stream);
     if (p->fork_ev) (void)hipEventDestroy(p->fork_ev);
     if (p->join_ev) (void)hipEventDestroy(p->join_ev);
-    if (p->draw_stream) (void)hipStreamDestroy(p->draw_stream);
-    if (p->draw_fork_ev) (void)hipEventDestroy(p->draw_fork_ev);
-    if (p->draw_join_ev) (void)hipEventDestroy(p->draw_join_ev);
 }
 
 int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t precision,
@@ -327,7 +324,6 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
         p->max_L = std::max(p->max_L, ci.L);
         p->max_np = std::max(p->max_np, ci.np);
         p->max_tau = std::max(p->max_tau, ci.L_tau);
-        p->mixed_sides = p->mixed_sides || (!p->chains.empty() && ci.L != p->chains[0].L);
         p->chains.push_back(ci);
     }
     p->aux_elems = aux;
@@ -652,9 +648,6 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
         e = hipStreamCreateWithFlags(&p->side_stream, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&p->fork_ev, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&p->join_ev, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipStreamCreateWithFlags(&p->draw_stream, hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&p->draw_fork_ev, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&p->draw_join_ev, hipEventDisableTiming);
     }
     // the static scratch of fh_measure_noalloc on this device: an address that cannot be taken
     // only disables that entry point
@@ -831,7 +824,7 @@ int fh_backward_sample(fh_plan p, int32_t* paths, uint64_t sweep, fh_stream stre
         return FH_ERR_STATE;
     hipStream_t s = (hipStream_t)stream;
     FH_TRY(launch_set_sweep(p, sweep, s));
-    FH_TRY(launch_backward(p, paths, true, s, s));
+    FH_TRY(launch_backward(p, paths, true, s));
     FH_TRY(launch_rescue(p, p->last_aux, paths, true, 0, s));  // blocks out of FP32's range
     return FH_OK;
 }
@@ -953,21 +946,7 @@ static hipError_t enqueue_sweep_body(fh_plan p, void* aux, int32_t* paths, bool 
     }
     if (e == hipSuccess) e = enqueue_forward_kernels(p, aux, paths, true, s);
     if (e == hipSuccess) e = mark(p, 2, s);
-    // The draws that are not staged run beside those that are: they write other worldlines' sites,
-    // and one kernel after another a sweep waited for the slowest worldlines of each (256 mixed
-    // chains 1553 -> 1495 us, 64 Ising 16 x 16 252 -> 244, 16 x 32 x 32 414 -> 407). Not so in plans
-    // of one lattice side with more than kApartDraws worldline blocks: their unstaged kernels mostly
-    // find nothing to draw, and their empty workgroups take the places of the staged draws' second
-    // round (4 x 32 x 32 x 1024 in 16 blocks, 65536 of them: 377 us one after another, 396 beside).
-    constexpr int kApartDraws = 32768;
-    const bool apart = split && p->n_stage_tasks > 0 && !p->share_off &&
-                       (p->mixed_sides || p->n_draww_tasks <= kApartDraws);
-    hipStream_t rest = apart ? p->draw_stream : s;
-    if (e == hipSuccess && apart) e = hipEventRecord(p->draw_fork_ev, s);
-    if (e == hipSuccess && apart) e = hipStreamWaitEvent(rest, p->draw_fork_ev, 0);
-    if (e == hipSuccess) e = launch_backward(p, paths, false, s, rest);
-    if (e == hipSuccess && apart) e = hipEventRecord(p->draw_join_ev, rest);
-    if (e == hipSuccess && apart) e = hipStreamWaitEvent(s, p->draw_join_ev, 0);
+    if (e == hipSuccess) e = launch_backward(p, paths, false, s);
     if (e == hipSuccess) e = mark(p, 3, s);
     if (e == hipSuccess && split) e = hipStreamWaitEvent(s, p->join_ev, 0);
     if (e == hipSuccess) e = launch_rescue(p, aux, paths, true, split ? 2 : 0, s);

@@ -428,7 +428,6 @@ struct fh_plan_s {
     int64_t rescue_slot_elems = 0;  // doubles per slot: (B - 1) N of the largest L <= 32 chain
     int64_t total_sites = 0;  // sum of N over the chains
     int32_t max_N = 0, max_L = 0, max_np = 0, max_tau = 0;
-    bool mixed_sides = false;  // chains of more than one lattice side
     // what d.sweep holds once the work queued so far has run; unknown after a failed call, and for
     // good once a caller's graph writes it
     bool sweep_known = false, sweep_captured = false;
@@ -451,8 +450,6 @@ struct fh_plan_s {
     // FP32 forward and backward passes of the other chains on the caller's stream
     hipStream_t side_stream = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
-    hipStream_t draw_stream = nullptr;  // the unstaged draws of a sweep, beside the staged ones
-    hipEvent_t draw_fork_ev = nullptr, draw_join_ev = nullptr;
     // graph cache for fh_sweep
     hipStream_t capture_stream = nullptr;
     hipGraphExec_t graph_exec = nullptr;
@@ -491,7 +488,7 @@ hipError_t launch_grad_dmfma(fh_plan p, const void* aux, const int32_t* paths, i
 hipError_t launch_forward_mfma(fh_plan p, const void* aux, const int32_t* paths, hipStream_t s);
 hipError_t launch_logz_reduce(fh_plan p, double* logZ, hipStream_t s);
 // adapt: choose the next pass's kernels too (a sweep's Gibbs launch does it otherwise).
-hipError_t launch_backward(fh_plan p, int32_t* paths, bool adapt, hipStream_t s, hipStream_t rest);
+hipError_t launch_backward(fh_plan p, int32_t* paths, bool adapt, hipStream_t s);
 // Before a forward pass: the representative map of the shared forward filters; with phase_a (an
 // FP32 sweep) the held chains are then queued whole as phase A.
 hipError_t launch_dedup(fh_plan p, const int32_t* paths, bool phase_a, hipStream_t s);

@@ -1119,8 +1119,8 @@ __global__ __launch_bounds__(kThreads) void k_backward_win(
     // chain is windowed)
     const bool active = listed && (SLOT ? c.win_on != 0 : !rescue_queued(rsc, c, t.p, t.block)) &&
                         !staged(rsc, c, t.p, t.block, SLOT ? kStagedSlots : kStagedRows);
-    // most workgroups have nothing to draw where k_backward_stage draws: they leave at once, as they
-    // hold its workgroups up (4 x 32 x 32 x 1024 in 16 blocks: 408 -> 396 us a sweep)
+    // most workgroups have nothing to draw where k_backward_stage draws: they leave at once
+    // (4 x 32 x 32 x 1024 in 16 blocks, 4096 workgroups: 381 -> 377 us a sweep)
     if (!__syncthreads_or(active)) return;
     // an inactive group draws nothing; on a one-site lattice its table fill and loads stay minimal
     const int L = active ? c.L : 1, N = active ? c.N : 1, L_tau = c.L_tau, w = c.win_w;
@@ -3588,7 +3588,7 @@ hipError_t launch_logz_reduce(fh_plan p, double* logZ, hipStream_t s) {
 }
 
 namespace {
-hipError_t launch_backward_kernels(fh_plan p, int32_t* paths, hipStream_t s, hipStream_t rest) {
+hipError_t launch_backward_kernels(fh_plan p, int32_t* paths, hipStream_t s) {
     if (p->n_stage_tasks > 0 && !p->share_off) {
         auto run = [&](auto kern, auto* filt) {
             hipLaunchKernelGGL(kern, dim3((unsigned)std::min(p->n_stage_tasks, kStageGrid)),
@@ -3602,7 +3602,6 @@ hipError_t launch_backward_kernels(fh_plan p, int32_t* paths, hipStream_t s, hip
         else
             run(k_backward_stage<float, false>, (const float*)p->d.filt);
     }
-    s = rest;  // the kernels below draw other worldlines
     if (p->n_draww_tasks > 0) {
         const unsigned blocks = (unsigned)((p->n_draww_tasks + kThreads / kWinLanes - 1) /
                                            (kThreads / kWinLanes));
@@ -3791,11 +3790,11 @@ hipError_t launch_rescue(fh_plan p, const void* aux, int32_t* paths, bool draw, 
     return hipGetLastError();
 }
 
-hipError_t launch_backward(fh_plan p, int32_t* paths, bool adapt, hipStream_t s, hipStream_t rest) {
+hipError_t launch_backward(fh_plan p, int32_t* paths, bool adapt, hipStream_t s) {
     // staged draws where worldlines share rows; windowed draws where the hopping kernel allows
     // them; 32 x 32 chains without the window (or moved off it for this sweep by bw_adapt) on their
     // own full-row kernel, the rest on the generic ones
-    hipError_t e = launch_backward_kernels(p, paths, s, rest);
+    hipError_t e = launch_backward_kernels(p, paths, s);
     if (e != hipSuccess || !adapt || !p->bw_adapt || p->n_draww_tasks == 0) return e;
     hipLaunchKernelGGL(k_bw_adapt, dim3(1), dim3(kThreads), 0, s, p->d.chains, p->n_chains,
                        p->d.bw_state);
