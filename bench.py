@@ -547,9 +547,9 @@ def main():
                                                                                  "k_forward_fft")
     names = {"forward": "forward filter (%s)" % fwd_kernel,
              "backward": "backward sampler (%s)" % ("k_backward_l32" if args.full_row_draw
-                                                    else "k_backward_win, full-row kernels")}
+                                                    else "k_backward_stage, k_backward_win")}
     knames = {"forward": fwd_kernel,
-              "backward": "k_backward_l32" if args.full_row_draw else "k_backward_win"}
+              "backward": "k_backward_l32" if args.full_row_draw else "k_backward_stage"}
     roofs = {}
     for k in ("forward", "backward"):
         gbs = algo[k] / (times[k] / 1e3) / 1e9

@@ -79,8 +79,9 @@ int fh_debug_backward_adapt(fh_plan plan, int32_t enable, int32_t* full_row_pass
 
 /* FP32 plans queue the blocks whose filters leave FP32's range (see the range note of fh.h),
  * and every block of a chain that had such a block in this or one of the four preceding forward
- * passes, for an FP64 re-filter and redraw (the FP32 forward kernels skip the chains held so). fh_debug_rescue synchronises the device and reports
- * the queue of the last forward pass (with what its backward pass added): last_count
+ * passes, for an FP64 re-filter and redraw (the FP32 forward kernels skip the chains held so).
+ * fh_debug_rescue synchronises the device and reports the queue of the last forward pass (with
+ * what its backward pass added): last_count
  * (nullable) receives its length, whole_chains (nullable) the chains queued whole, total
  * (nullable) the blocks redrawn by every backward pass since the previous call (then reset to
  * 0), and list (caller-owned host memory, cap triples, may be null when cap = 0) the first
@@ -92,7 +93,7 @@ int fh_debug_rescue(fh_plan plan, int32_t* last_count, int32_t* whole_chains, in
  * backward weights are all zero. Needs stored filters (FH_ERR_STATE otherwise). Synchronous. */
 int fh_debug_fill_filter_row(fh_plan plan, int32_t chain, int32_t particle, int32_t row,
                              double value);
-/* Shared forward filters (FP32 matrix-core plans, 32 x 32 chains): the worldlines of one
+/* Shared forward filters (the matrix-core plans of both precisions): the worldlines of one
  * (chain, spin, block) with the same start site share the stored rows of the lowest of them,
  * their representative. Synchronises the device and copies the representative map of the last
  * forward pass, one chain-local particle index per (chain, particle, block) at

@@ -159,7 +159,7 @@ struct GroupTask {
 // underflows in one slice can move log Z by 16 nats), while the blocks of a settled chain meet a
 // floor all together or not at all. When its hold has run out, a chain runs FP32 again to see
 // whether it still needs FP64; each such retry that fails doubles the next hold, up to
-// kRescueHoldMax passes, and a pass that needs no FP64 resets it to kRescueHold (k_rescue_reset).
+// kRescueHoldMax passes, and a pass that needs no FP64 resets it to kRescueHold (rescue_reset).
 constexpr int kWScaleLog2 = 100;
 constexpr int kRowExp = 20;
 constexpr float kRangeFloor = 0x1p-90f;
@@ -250,7 +250,7 @@ __device__ inline bool rescue_enqueue(const Rescue& r, const ChainInfo& c, int c
 }
 // A kernel found block (chain, p, block) out of FP32's range: queue it, count it for its chain
 // and hold the chain on the FP64 re-filter for the next kRescueHold forward passes, or longer
-// after failed retries (k_rescue_reset; a backward pass queues after the chain's blocks were
+// after failed retries (rescue_reset; a backward pass queues after the chain's blocks were
 // expanded for this one).
 __device__ inline void rescue_push(const Rescue& r, const ChainInfo& c, int chain, int p,
                                    int block, int cause) {

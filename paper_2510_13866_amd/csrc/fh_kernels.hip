@@ -263,8 +263,8 @@ __global__ void k_zero(uint32_t* p, int64_t words) {
         p[i] = 0u;
 }
 
-// Before a forward pass (thread i of stride): an empty queue, no block flagged, no chain counted or in phase A (the
-// per-chain holds and the redrawn total stay).
+// Before a forward pass (thread i of stride): an empty queue, no block flagged, no chain counted
+// or in phase A (the per-chain holds and the redrawn total stay).
 __device__ inline void rescue_reset(const Rescue& rsc, int64_t n_flags, int64_t i,
                                     int64_t stride) {
     if (i == 0) {
@@ -1889,8 +1889,8 @@ __device__ __attribute__((noinline)) void rescue_draws(const DrawTask& t, const 
 // FP32's range (kRangeFloor). The FP32 pass's rows for such a block hold values at FP32's floor
 // that decide its draws and log Z; FP64 holds them to ~2^-1022. Phase 0 takes the whole queue,
 // phase 1 its phase A [0, words[3]) (a sweep's held chains, beside the FP32 passes), phase 2 the
-// rest (after phase 1 has ended) but for the chains of phase B (k_rescue_expand). One wavefront takes queued blocks i = lo + wid,
-// lo + wid + n_slots, ... in turn, with its own slot of FP64 rows:
+// rest (after phase 1 has ended) but for the chains of phase B (rescue_expand). One wavefront takes
+// queued blocks i = lo + wid, lo + wid + n_slots, ... in turn, with its own slot of FP64 rows:
 //   forward: the block recursion of k_forward_dmfma on the FP64 circulant, with the FP64
 //            W~ = exp(coef aux - m_l) of k_rescue_potentials (the FP32 tables may hold zeros
 //            there); log Z to blk_logz; rows to the slot (DRAW), or else, rounded and scaled,
@@ -1986,7 +1986,10 @@ __global__ __launch_bounds__(kThreads, NT == 2 ? 2 : 1) void k_rescue(
             blk_logz[c.blk_off + (int64_t)t.p * c.nb + t.block] = lz;
         }
         if (!DRAW || !ok) continue;
-        // the slot's rows were stored by this wavefront's lanes: make them visible to its loads
+        // The slot's rows were stored by this wavefront's lanes: make them visible to its loads,
+        // within its own compute unit (a fence for the whole device writes the L2 back twice for
+        // each of some 7000 blocks: two sweeps from the start of 16 x 32 x 32, 5.0 against 4.5 ms
+        // in this kernel each).
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         // the full-row rule of the FP64 plans' backward kernel, on the slot's rows
         rescue_draws<0>(t, c, tables + tab_g(c), paths, perm, sweep, status, lane, slot);
@@ -2157,8 +2160,9 @@ __global__ __launch_bounds__(kThreads, kShareDrawWaves) void k_rescue_share_draw
 }
 
 // After the reset and the representative map, before a sweep's FP32 forward pass, one workgroup
-// (the last one of k_dedup, or k_rescue_held where nothing is shared): every block of each chain held on the FP64 re-filter (fp64_circulant) is queued, in chain order, as
-// phase A, and the chain is marked, while the running total of the held chains' forward
+// (the last one of k_dedup, or k_rescue_held where nothing is shared): every block of each chain
+// held on the FP64 re-filter (fp64_circulant) is queued, in chain order, as phase A, and the chain
+// is marked, while the running total of the held chains' forward
 // recursions (their representatives) fits the n_slots slots; the FP32 kernels skip held chains
 // and phase A re-filters them beside the FP32 passes (a held chain left out is queued whole after
 // the forward pass, for phase 2). The queue is empty before this kernel, so the entries are laid
@@ -2345,7 +2349,14 @@ __device__ inline void stage_members(const ChainInfo& c, const DrawTask& t, cons
 // in words[8]; P = 4: from n_p2 on, count in words[9]). Lattices above 32 go to cbig, 64 x 64
 // from off64 on, the others from off48 on; FP64 plans list every representative in csingles,
 // L <= 32 from the front, the larger ones likewise (counts in lists[kListFwd..]).
-__device__ void dedup_task(const DrawTask& t, const ChainInfo* __restrict__ chains, const int32_t* __restrict__ paths, const uint64_t* __restrict__ sweep_ptr, int32_t* __restrict__ rep, const Rescue rsc, PairTask* __restrict__ cpairs, DrawTask* __restrict__ csingles, DrawTask* __restrict__ cbig, PackTask* __restrict__ cpack, int n_p2, int32_t* __restrict__ prep, int32_t* __restrict__ lists, int off64, int off48, const StageLists st) {
+__device__ void dedup_task(const DrawTask& t, const ChainInfo* __restrict__ chains,
+                           const int32_t* __restrict__ paths,
+                           const uint64_t* __restrict__ sweep_ptr, int32_t* __restrict__ rep,
+                           const Rescue rsc, PairTask* __restrict__ cpairs,
+                           DrawTask* __restrict__ csingles, DrawTask* __restrict__ cbig,
+                           PackTask* __restrict__ cpack, int n_p2, int32_t* __restrict__ prep,
+                           int32_t* __restrict__ lists, int off64, int off48,
+                           const StageLists st) {
     __shared__ int32_t first[kDedupMaxN];
     __shared__ int32_t rlist[kDedupMaxN];
     __shared__ int32_t n_rep, n_bad, c_base, p_base;
@@ -2385,11 +2396,10 @@ __device__ void dedup_task(const DrawTask& t, const ChainInfo* __restrict__ chai
     {
         // Where the line lies: a staged workgroup reads its representatives' whole rows once per
         // slice, the windowed kernel about seven 128-byte lines per worldline and slice (more
-        // than half of them misses). 16 x 32 x 32, two sweeps from the start (every worldline its own
-        // row), took 17.4 ms with the line at 1 KB or 2 KB a worldline and 21.4 ms at 4 KB; the
-        // settled batches are the same at all three. Rows of odd lattices (N not a multiple of 4) are not
-        // 16-byte aligned, and invalid sites are left to the kernels that report them. Below 8 x 8
-        // the window is the lattice, and one wavefront per four worldlines has less to set up.
+        // than half of them misses); kStageCost has both sides. Rows of odd lattices (N not a
+        // multiple of 4) are not 16-byte aligned, and invalid sites are left to the kernels that
+        // report them. Below 8 x 8 the window is the lattice, and one wavefront per four
+        // worldlines has less to set up.
         const bool held = rescue_held(rsc, t.chain), able = c.win_on && c.L >= kStageMinL &&
                                                             c.N % 4 == 0 && !n_bad;
         auto on = [&](int rowb) {
@@ -2464,8 +2474,14 @@ __device__ void dedup_task(const DrawTask& t, const ChainInfo* __restrict__ chai
 
 // With arep (an FP32 sweep) the last workgroup then queues the held chains as phase A.
 __global__ __launch_bounds__(kThreads) void k_dedup(
-    const DrawTask* __restrict__ tasks, const ChainInfo* __restrict__ chains, const int32_t* __restrict__ paths, const uint64_t* __restrict__ sweep_ptr, int32_t* __restrict__ rep, const Rescue rsc, PairTask* __restrict__ cpairs, DrawTask* __restrict__ csingles, DrawTask* __restrict__ cbig, PackTask* __restrict__ cpack, int n_p2, int32_t* __restrict__ prep, int32_t* __restrict__ lists, int off64, int off48, const StageLists st, int n_slots, DrawTask* __restrict__ arep) {
-    dedup_task(tasks[blockIdx.x], chains, paths, sweep_ptr, rep, rsc, cpairs, csingles, cbig, cpack, n_p2, prep, lists, off64, off48, st);
+    const DrawTask* __restrict__ tasks, const ChainInfo* __restrict__ chains,
+    const int32_t* __restrict__ paths, const uint64_t* __restrict__ sweep_ptr,
+    int32_t* __restrict__ rep, const Rescue rsc, PairTask* __restrict__ cpairs,
+    DrawTask* __restrict__ csingles, DrawTask* __restrict__ cbig, PackTask* __restrict__ cpack,
+    int n_p2, int32_t* __restrict__ prep, int32_t* __restrict__ lists, int off64, int off48,
+    const StageLists st, int n_slots, DrawTask* __restrict__ arep) {
+    dedup_task(tasks[blockIdx.x], chains, paths, sweep_ptr, rep, rsc, cpairs, csingles, cbig, cpack,
+               n_p2, prep, lists, off64, off48, st);
     if (arep && last_workgroup(&lists[kListDone], gridDim.x))
         rescue_held_admit(chains, rsc, n_slots, 1, arep);
 }
