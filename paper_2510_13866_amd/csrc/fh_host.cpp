@@ -202,7 +202,7 @@ hipError_t dalloc(T** p, size_t bytes) {
 }
 
 void free_device(fh::Device& d) {
-    void* ptrs[] = {d.chains, d.tables, d.cmat, d.cmat64, d.fwdd_tasks, d.W, d.wshift, d.filt, d.blk_logz, d.dt, d.fwd_tasks,
+    void* ptrs[] = {d.chains, d.slice_chain, d.tables, d.cmat, d.cmat64, d.fwdd_tasks, d.W, d.wshift, d.filt, d.blk_logz, d.dt, d.fwd_tasks,
                     d.draw_tasks, d.group_tasks, d.gpart, d.ckpt, d.rep, d.blk_la, d.endrow, d.dedup_tasks, d.lists, d.staged, d.members, d.stage_tasks, d.stage_tasks_s, d.grad.list, d.grad.count, d.grad.n, d.grad.of, d.grad.per, d.grad.groups, d.fwddc_tasks, d.fwd64c_tasks, d.fwd32_tasks, d.fwd32c_tasks, d.fwdxc_tasks, d.fwdpc_tasks, d.prep, d.fwdx_tasks, d.fwdp_tasks, d.cmatp, d.cmatb, d.fwd64_tasks, d.draw32_tasks, d.draww_tasks, d.drawx_tasks, d.meas, d.mala, d.perm, d.perm_inv, d.sign, d.bw_state,
                     d.rescue, d.rescue_list, d.rep_slot, d.arep, d.arep_b, d.rescue_ws, d.rescue_w, d.status, d.sweep};
     for (void* p : ptrs)
@@ -546,6 +546,13 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
     fh::Device& dv = p->d;
     const size_t rs = p->real_size;
     if (e == hipSuccess) e = dalloc(&dv.chains, sizeof(ChainInfo) * n_chains);
+    if (e == hipSuccess) e = dalloc(&dv.slice_chain, sizeof(int32_t) * (size_t)p->total_slices);
+    if (e == hipSuccess) {
+        std::vector<int32_t> of((size_t)p->total_slices);
+        for (int c = 0; c < n_chains; ++c)
+            std::fill_n(of.begin() + p->chains[c].slice_off, p->chains[c].L_tau, c);
+        e = hipMemcpy(dv.slice_chain, of.data(), sizeof(int32_t) * of.size(), hipMemcpyHostToDevice);
+    }
     if (e == hipSuccess) e = dalloc(&dv.tables, sizeof(double) * p->tables.size());
     if (e == hipSuccess) e = dalloc(&dv.cmat, sizeof(uint16_t) * p->cmat.size());
     if (e == hipSuccess) e = dalloc(&dv.W, rs * 2 * (size_t)aux);

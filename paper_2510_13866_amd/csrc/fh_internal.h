@@ -314,6 +314,7 @@ constexpr int kGradAlone = 512;
 
 struct Device {
     ChainInfo* chains = nullptr;
+    int32_t* slice_chain = nullptr;  // [global slice] its chain
     double* tables = nullptr;
     uint16_t* cmat = nullptr;  // per chain: split-bf16 circulant operand [3][2][64][8]
     uint16_t* cmatp = nullptr; // per chain with L <= kPackMaxL: the block-diagonal operand, same layout

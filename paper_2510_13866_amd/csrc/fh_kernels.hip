@@ -315,10 +315,13 @@ __device__ inline void rescue_reset(const Rescue& rsc, int64_t n_flags, int64_t 
 // The first kernel of every pass, so what a pass starts with is done here and takes no launch of
 // its own (about 4 us each on the critical path of a captured sweep): the dense lists' counts are
 // zeroed, with n_flags > 0 the re-filter's queue is reset, and with bump the sweep index of a
-// captured sweep advances.
+// captured sweep advances. A workgroup finds its chain in a table: a binary search, eight dependent
+// loads at 256 chains, was most of a small slice's time (23800 slices of 350 sites on average:
+// 59 us, 51 now; the field draw 139 and 125).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_potentials(const ChainInfo* __restrict__ chains,
-                                                         int n_chains, const T* __restrict__ aux,
+                                                         const int32_t* __restrict__ slice_chain,
+                                                         const T* __restrict__ aux,
                                                          T* __restrict__ W, double* __restrict__ wshift,
                                                          int64_t aux_elems, int64_t total_slices,
                                                          int32_t* status, int32_t* lists,
@@ -331,7 +334,7 @@ __global__ __launch_bounds__(kThreads) void k_potentials(const ChainInfo* __rest
     if (n_flags > 0)
         rescue_reset(rsc, n_flags, gs * (int64_t)kThreads + threadIdx.x,
                      (int64_t)gridDim.x * kThreads);
-    const int ci = find_chain(n_chains, gs, [&](int i) { return chains[i].slice_off; });
+    const int ci = slice_chain[gs];
     const ChainInfo& c = chains[ci];
     const int64_t base = c.aux_off + (int64_t)(gs - c.slice_off) * c.N;
     double mu = -INFINITY, md = -INFINITY;
@@ -2919,8 +2922,9 @@ __global__ __launch_bounds__(kThreads) void k_gibbs(const ChainInfo* __restrict_
                                                     T* __restrict__ aux,
                                                     const uint64_t* __restrict__ sweep_ptr,
                                                     int32_t* status, int maxN,
-                                                    int64_t slices, int32_t* bw_state,
-                                                    const MemberArgs ma) {
+                                                    int64_t slices,
+                                                    const int32_t* __restrict__ slice_chain,
+                                                    int32_t* bw_state, const MemberArgs ma) {
     extern __shared__ __align__(16) unsigned char smem[];
     int32_t* cnt = (int32_t*)smem;  // [2][maxN]
     if ((int64_t)blockIdx.x >= slices) {  // what else ends a sweep (uniform)
@@ -2935,11 +2939,11 @@ __global__ __launch_bounds__(kThreads) void k_gibbs(const ChainInfo* __restrict_
         return;
     }
     const int gs = blockIdx.x;
-    const int ci = find_chain(n_chains, gs, [&](int i) { return chains[i].slice_off; });
+    const int ci = slice_chain[gs];
     const ChainInfo& c = chains[ci];
     const int l = (int)(gs - c.slice_off);
     const uint64_t sweep = *sweep_ptr;
-    for (int r = threadIdx.x; r < 2 * c.N; r += blockDim.x) cnt[(r / c.N) * maxN + r % c.N] = 0;
+    for (int r = threadIdx.x; r < c.N; r += blockDim.x) cnt[r] = cnt[maxN + r] = 0;
     __syncthreads();
     const int32_t* pl = paths + c.path_off + (int64_t)l * c.np;
     for (int p = threadIdx.x; p < c.np; p += blockDim.x) {
@@ -3563,7 +3567,7 @@ hipError_t launch_zero(void* ptr, int64_t bytes, hipStream_t s) {
 hipError_t launch_potentials(fh_plan p, const void* aux, bool pass, bool bump, hipStream_t s) {
     auto run = [&](auto kern, auto* a, auto* W) {
         hipLaunchKernelGGL(kern, dim3((unsigned)p->total_slices), dim3(kThreads), 0, s,
-                           p->d.chains, p->n_chains, a, W, p->d.wshift, p->aux_elems,
+                           p->d.chains, p->d.slice_chain, a, W, p->d.wshift, p->aux_elems,
                            p->total_slices, p->d.status, p->d.lists, rescue_args(p),
                            pass && p->d.rescue ? std::max<int64_t>(p->blk_elems, 1) : 0,
                            bump ? p->d.sweep : nullptr);
@@ -3954,7 +3958,7 @@ hipError_t launch_gibbs(fh_plan p, const int32_t* paths, void* aux, bool sweep, 
     auto run = [&](auto kern, auto* a) {
         hipLaunchKernelGGL(kern, dim3((unsigned)(p->total_slices + extra)), dim3(kThreads), lds, s,
                            p->d.chains, p->n_chains, paths, a, p->d.sweep, p->d.status, p->max_N,
-                           p->total_slices, adapt ? p->d.bw_state : nullptr, ma);
+                           p->total_slices, p->d.slice_chain, adapt ? p->d.bw_state : nullptr, ma);
     };
     if (p->precision == FH_FP64)
         run(k_gibbs<double>, (double*)aux);
