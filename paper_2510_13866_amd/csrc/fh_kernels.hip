@@ -369,10 +369,12 @@ __global__ __launch_bounds__(kThreads) void k_potentials(const ChainInfo* __rest
         mu -= kWScaleLog2 * 0.69314718055994530942;
         md -= kWScaleLog2 * 0.69314718055994530942;
     }
+    const bool same = c.coef_up == c.coef_dn;  // Gaussian fields: one exponential serves both spins
     for (int r = threadIdx.x; r < c.N; r += blockDim.x) {
         const double v = (double)aux[base + r];
-        W[base + r] = (T)exp(c.coef_up * v - mu);
-        W[aux_elems + base + r] = (T)exp(c.coef_dn * v - md);
+        const T up = (T)exp(c.coef_up * v - mu);
+        W[base + r] = up;
+        W[aux_elems + base + r] = same ? up : (T)exp(c.coef_dn * v - md);
     }
     if (threadIdx.x == 0) {
         wshift[gs] = mu;
@@ -2638,10 +2640,12 @@ __global__ __launch_bounds__(kThreads) void k_rescue_potentials(
     for (int l = first; l < c.L_tau; l += per_chain) {
         const int64_t base = c.aux_off + (int64_t)l * c.N;
         const double mu = wshift[c.slice_off + l], md = wshift[total_slices + c.slice_off + l];
+        const bool same = c.coef_up == c.coef_dn && mu == md;  // Gaussian fields
         for (int r = threadIdx.x; r < c.N; r += blockDim.x) {
             const double v = (double)aux[base + r];
-            W64[base + r] = exp(c.coef_up * v - mu);
-            W64[aux_elems + base + r] = exp(c.coef_dn * v - md);
+            const double up = exp(c.coef_up * v - mu);
+            W64[base + r] = up;
+            W64[aux_elems + base + r] = same ? up : exp(c.coef_dn * v - md);
         }
     }
 }
