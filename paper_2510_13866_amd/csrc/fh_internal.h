@@ -269,6 +269,11 @@ __device__ inline bool rescue_queued(const Rescue& r, const ChainInfo& c, int p,
 __device__ inline bool rescue_held(const Rescue& r, int chain) {
     return r.words && r.words[kRescueChain + r.n_chains + chain] > 0;
 }
+// The same of a chain the FP64 re-filter takes. The others (36 x 36, 54 x 54) keep their FP32
+// pass while they are held: nothing else gives them this pass's rows and log Z.
+__device__ inline bool refiltered(const Rescue& r, const ChainInfo& c, int chain) {
+    return fp64_circulant(c.L) && rescue_held(r, chain);
+}
 
 // One autotuner timing: the radix order `plan` of lattice size L took `ms` per timing launch.
 struct TuneRecord {

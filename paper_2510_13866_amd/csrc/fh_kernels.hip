@@ -395,7 +395,7 @@ __global__ __launch_bounds__(kThreads) void k_forward_fft(
     const PairTask t = tasks[blockIdx.x];
     const ChainInfo& c = chains[t.chain];
     // re-filtered whole in FP64 this pass (the whole workgroup leaves: no barrier is skipped)
-    if (fp64_circulant(c.L) && rescue_held(rsc, t.chain)) return;
+    if (refiltered(rsc, c, t.chain)) return;
     int start, len;
     block_of(c, *sweep_ptr, t.block, &start, &len);
     const bool has_b = t.p_b >= 0;
@@ -2190,7 +2190,7 @@ __device__ void rescue_held_admit(const ChainInfo* __restrict__ chains, const Re
         bool share = false;
         if (ci < n) {
             const ChainInfo& c = chains[ci];
-            held = fp64_circulant(c.L) && rescue_held(rsc, ci);
+            held = refiltered(rsc, c, ci);
             nblk = c.np * c.nb;
             share = shared && c.dedup;
             nrec = held ? (share ? rsc.words[kRescueChain + 3 * n + ci] : nblk) : 0;
@@ -2345,7 +2345,7 @@ __device__ inline void stage_members(const ChainInfo& c, const DrawTask& t, cons
 // slices and its start site, so every worldline of the (spin, block) is mapped to the lowest
 // worldline with the same start site (its representative; itself if it is the lowest); the
 // forward kernel runs the representatives only and the backward kernels read their rows.
-// For dedup = 1 chains not held this pass it also appends the (spin, block)'s representatives,
+// For dedup = 1 chains not re-filtered in this pass it also appends the (spin, block)'s representatives,
 // in worldline order and two to a task, to the dense list cpairs (count in words[5]), which the
 // split-bf16 forward then takes from the front: its active wavefronts are the first ones
 // dispatched, spread over the XCDs, instead of sitting at fixed grid positions that map a whole
@@ -2405,7 +2405,7 @@ __device__ void dedup_task(const DrawTask& t, const ChainInfo* __restrict__ chai
         // multiple of 4) are not 16-byte aligned, and invalid sites are left to the kernels that
         // report them. Below 8 x 8 the window is the lattice, and one wavefront per four
         // worldlines has less to set up.
-        const bool held = rescue_held(rsc, t.chain), able = c.win_on && c.L >= kStageMinL &&
+        const bool held = refiltered(rsc, c, t.chain), able = c.win_on && c.L >= kStageMinL &&
                                                             c.N % 4 == 0 && !n_bad;
         auto on = [&](int rowb) {
             return able && rowb <= kStageBytes &&
@@ -2427,7 +2427,7 @@ __device__ void dedup_task(const DrawTask& t, const ChainInfo* __restrict__ chai
     const int PP = c.pack * c.pack;  // worldlines per packed tile
     DrawTask* singles = fp64 || !big ? csingles : cbig;
     if (c.dedup != 1 || (pairs ? !cpairs : c.pack ? !cpack : !singles) ||
-        rescue_held(rsc, t.chain))
+        refiltered(rsc, c, t.chain))
         return;
     // the representatives in worldline order (first wavefront), then their pairs
     if (threadIdx.x < 64) {
@@ -2581,7 +2581,7 @@ __device__ void member_logz(int64_t i0, int64_t stride, const ChainInfo* __restr
     for (int64_t i = i0; i < blk_elems; i += stride) {
         const int ci = find_chain(n_chains, i, [&](int k) { return chains[k].blk_off; });
         const ChainInfo& c = chains[ci];
-        if (c.dedup != 1 || rescue_held(rsc, ci)) continue;
+        if (c.dedup != 1 || refiltered(rsc, c, ci)) continue;
         const int64_t local = i - c.blk_off;
         const int p = (int)(local / c.nb), b = (int)(local % c.nb);
         const int rp = rsc.rep[i];

@@ -920,7 +920,7 @@ __global__ __launch_bounds__(kThreads) void k_forward_mfma64(
     const bool cached = ccount && (int64_t)rsc.words[kRescueChain + 3 * rsc.n_chains + t.chain] *
                                           (c.B - 1) * c.N * 4 <= kCachedRowBytes;
     // re-filtered whole in FP64 this pass (lattices with the FP64 circulant)
-    if ((!PAD || fp64_circulant(c.L)) && rescue_held(rsc, t.chain)) return;
+    if (refiltered(rsc, c, t.chain)) return;
     const int L = PAD ? c.L : 64, N = PAD ? c.N : 4096;
     int start, len;
     block_of(c, *sweep_ptr, t.block, &start, &len);
