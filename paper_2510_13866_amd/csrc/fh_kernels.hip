@@ -3741,6 +3741,8 @@ hipError_t launch_member_logz(fh_plan p, const int32_t* paths, hipStream_t s) {
 hipError_t launch_rescue(fh_plan p, const void* aux, int32_t* paths, bool draw, int phase,
                          hipStream_t s) {
     if (!p->d.rescue) return hipSuccess;
+    // phase A takes only chains with the FP64 circulant (a plan of 36 x 36 or 54 x 54 has none)
+    if (phase == 1 && p->rescuable_blocks == 0) return hipSuccess;
     // about 4096 workgroups, and no more to a chain than the longest has slices
     const int64_t per_chain = std::max<int64_t>(1, std::min<int64_t>(p->max_tau, 4096 / p->n_chains));
     hipLaunchKernelGGL(k_rescue_potentials, dim3((unsigned)(p->n_chains * per_chain)),
