@@ -58,6 +58,13 @@ int fh_debug_window_select(const double* g, int32_t L, int32_t* w, double* g_out
 int fh_debug_window_draw(int32_t L, int32_t w, const double* g, double g_out, const double* f,
                          int32_t s_site, double u, int32_t* site, int32_t* certified);
 
+/* Where the staged backward draws read 16-byte unit `unit` of a row buffer that holds n_rows (1..64)
+ * filter rows of N values (a multiple of 4) of value_size (4 or 8) bytes one after the other, row r
+ * starting at element first[r] of the chain's filters: *place, in 16-byte units from there.
+ * FH_ERR_INVALID_ARG on bad input. */
+int fh_debug_stage_place(const int64_t* first, int32_t n_rows, int32_t value_size, int32_t N,
+                         int32_t unit, int64_t* place);
+
 /* Device-plan test hooks (they synchronise the device):
  *   fh_debug_inflate_window_bound multiplies every chain's outside bound by factor >= 1 (an
  *   infinite factor sends every windowed draw through the full-row scan; a larger bound only

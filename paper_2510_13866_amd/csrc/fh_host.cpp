@@ -1356,6 +1356,19 @@ int fh_debug_window_draw(int32_t L, int32_t w, const double* g, double g_out, co
     return FH_OK;
 }
 
+int fh_debug_stage_place(const int64_t* first, int32_t n_rows, int32_t value_size, int32_t N,
+                         int32_t unit, int64_t* place) {
+    if (!first || !place || n_rows < 1 || n_rows > kStageMembers ||
+        (value_size != 4 && value_size != 8) || N < 4 || N % 4 != 0)
+        return FH_ERR_INVALID_ARG;
+    const int upr = N * value_size / 16;
+    if (unit < 0 || unit >= n_rows * upr) return FH_ERR_INVALID_ARG;
+    int64_t rows[kStageMembers];
+    for (int r = 0; r < n_rows; ++r) rows[r] = stage_place(first[r], value_size);
+    *place = stage_unit(rows, unit, upr);
+    return FH_OK;
+}
+
 int fh_debug_inflate_window_bound(fh_plan p, double factor) {
     if (!p || !(factor >= 1.0)) return FH_ERR_INVALID_ARG;
     FH_TRY(hipDeviceSynchronize());

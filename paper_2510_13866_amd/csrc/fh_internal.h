@@ -80,6 +80,12 @@ constexpr int kStageBytes = 32768;
 constexpr int kStageGrid = 1024;
 constexpr int kStageCost = 384;
 constexpr int kStageMinL = 8;
+// Where k_backward_stage reads, in 16-byte units from a chain's filters or from the re-filter's slots
+// and in 64 bits: a half-filled 64 x 64 chain in FP64 passes 2^32 units (64 GiB) at 512 slices. A row
+// from its first element's index (a multiple of 16 bytes: N is a multiple of 4), and unit u of the
+// rows of upr units each that lie one after the other in the row buffer.
+FH_HD inline int64_t stage_place(int64_t first, int value_size) { return first / (16 / value_size); }
+FH_HD inline int64_t stage_unit(const int64_t* rows, int u, int upr) { return rows[u / upr] + u % upr; }
 // What k_backward_stage draws of a (chain, spin, block): its draws from the plan's rows, and from the
 // FP64 re-filter's slots.
 constexpr int kStagedRows = 1, kStagedSlots = 2;

@@ -1538,7 +1538,7 @@ __global__ __launch_bounds__(kStageThreads, 4) void k_backward_stage(
     __shared__ double gsh[2 * kWinMaxL];
     __shared__ double ubuf[2][4 * kStageMembers];
     __shared__ int32_t sites[2][kStageMembers];
-    __shared__ int32_t src_sh[kStageMembers];  // per slot: its row of j = 1, in 16-B units from src
+    __shared__ int64_t src_sh[kStageMembers];  // per slot: its row of j = 1 (stage_place) from src
     __shared__ double sum_sh[4][128];  // per consumer wavefront: the fallbacks' lane sums
     __shared__ int32_t mem_sh[kStageMembers], slot_sh[kStageMembers], act_sh[kStageMembers];
     __shared__ int32_t nslot_sh;
@@ -1570,7 +1570,7 @@ __global__ __launch_bounds__(kStageThreads, 4) void k_backward_stage(
                 const int64_t ri = c.blk_off + (int64_t)ro * c.nb + t.block;
                 const int64_t row1 = SLOT ? (int64_t)sr.rep_slot[ri] * sr.slot_elems
                                           : ((int64_t)ro * L_tau + (int64_t)t.block * (c.B - 1)) * N;
-                src_sh[slot] = (int32_t)(row1 / (16 / (int)sizeof(T)));
+                src_sh[slot] = stage_place(row1, (int)sizeof(T));
             }
             mem_sh[lane] = p;
             slot_sh[lane] = slot;
@@ -1589,12 +1589,10 @@ __global__ __launch_bounds__(kStageThreads, 4) void k_backward_stage(
             const int upr = N * (int)sizeof(T) / 16;  // 16-B units per row
             const int units = nslot_sh * upr;
             const int nl = __builtin_amdgcn_readfirstlane((units + 255) / 256);
-            uint32_t base[kStageLoads];  // past the last unit: the first one again
+            int64_t base[kStageLoads];  // past the last unit: the first one again
 #pragma unroll
-            for (int i = 0; i < kStageLoads; ++i) {
-                const int u = pt + 256 * i < units ? pt + 256 * i : 0;
-                base[i] = (uint32_t)src_sh[u / upr] + (uint32_t)(u % upr);
-            }
+            for (int i = 0; i < kStageLoads; ++i)
+                base[i] = stage_unit(src_sh, pt + 256 * i < units ? pt + 256 * i : 0, upr);
             u32x4 ra[kStageLoads];
             auto fetch = [&](int s, u32x4 (&r)[kStageLoads]) __attribute__((always_inline)) {  // the rows of draw s (row nd - s)
                 const u32x4* o = (const u32x4*)src + (int64_t)max(nd - s - 1, 0) * upr;
@@ -1810,7 +1808,7 @@ __global__ __launch_bounds__(kStageThreads, 4) void k_backward_stage(
                     const int qe = start + len >= L_tau ? perm[c.part_off + p] : p;
                     const int e = checked_site(pc[(int64_t)((start + len) % L_tau) * np + qe], N,
                                                status, t.chain);
-                    const double hv = (double)src[(int64_t)src_sh[slot_sh[lane]] * 2 +
+                    const double hv = (double)src[src_sh[slot_sh[lane]] * 2 +
                                                   (int64_t)(c.B - 1) * N + e];
                     if (!(hv > 0.0)) set_status(status, FH_ERR_NONFINITE, t.chain);
                     sr.blk_logz[bi] = sr.blk_la[c.blk_off + (int64_t)ro * c.nb + t.block] + log(hv);
