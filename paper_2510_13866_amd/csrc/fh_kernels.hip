@@ -2361,8 +2361,8 @@ __device__ void dedup_task(const DrawTask& t, const ChainInfo* __restrict__ chai
                            int32_t* __restrict__ lists, int off64, int off48,
                            const StageLists st) {
     __shared__ int32_t first[kDedupMaxN];
-    __shared__ int32_t rlist[kDedupMaxN];
-    __shared__ int32_t n_rep, n_bad, c_base, p_base;
+    __shared__ int32_t scratch[kDedupMaxN];
+    __shared__ int32_t n_rep, n_bad;
     const ChainInfo& c = chains[t.chain];  // t.p holds the spin
     int start, len;
     block_of(c, *sweep_ptr, t.block, &start, &len);
@@ -2413,8 +2413,7 @@ __device__ void dedup_task(const DrawTask& t, const ChainInfo* __restrict__ chai
         if (threadIdx.x == 0)
             st.staged[c.sb_off + t.p * c.nb + t.block] =
                 (rows ? kStagedRows : 0) | (slots ? kStagedSlots : 0);
-        if (rows || slots) stage_members(c, t, row, p0, p1, rows, slots, rlist, lists, st);
-        __syncthreads();  // rlist is free again
+        if (rows || slots) stage_members(c, t, row, p0, p1, rows, slots, scratch, lists, st);
     }
     // the 32 x 32 chains' representatives go to cpairs, two to a task; the padded lattices'
     // (16 < L < 32, one worldline to a wavefront) to csingles (count in words[7]); the packed
@@ -2427,52 +2426,61 @@ __device__ void dedup_task(const DrawTask& t, const ChainInfo* __restrict__ chai
     if (c.dedup != 1 || (pairs ? !cpairs : c.pack ? !cpack : !singles) ||
         refiltered(rsc, c, t.chain))
         return;
-    // the representatives in worldline order (first wavefront), then their pairs
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        int cnt = 0;
-        for (int q0 = p0; q0 < p1; q0 += 64) {
-            const int q = q0 + lane;
-            bool is_rep = false;
-            if (q < p1) {
-                const int a = row[q];
-                is_rep = !(a >= 0 && a < c.N) || first[a] == q;
-            }
-            const uint64_t m = __ballot(is_rep);
-            if (is_rep) rlist[cnt + __popcll(m & ((1ull << lane) - 1))] = q;
-            cnt += __popcll(m);
+    // The first wavefront lists the representatives in worldline order, straight into the space it
+    // takes for them: a worldline with an invalid site is its own representative, so they may be
+    // more than the lattice has sites.
+    if (threadIdx.x >= 64) return;
+    const int lane = threadIdx.x;
+    int c_base = 0, p_base = 0;
+    if (lane == 0) {
+        if (pairs) {
+            c_base = atomicAdd(&rsc.words[5], (n_rep + 1) / 2);
+        } else if (c.pack) {
+            p_base = atomicAdd(&rsc.words[10], n_rep);
+            c_base = atomicAdd(&rsc.words[c.pack == 2 ? 8 : 9], (n_rep + PP - 1) / PP) +
+                     (c.pack == 2 ? 0 : n_p2);
+        } else if (fp64 || big) {
+            static_assert(kListFwd48 == kListFwdPad, "the third list of either plan");
+            c_base = c.L <= 32 ? atomicAdd(&lists[kListFwd], n_rep)
+                     : c.L == 64 ? off64 + atomicAdd(&lists[kListFwd64], n_rep)
+                                 : off48 + atomicAdd(&lists[kListFwd48], n_rep);
+        } else {
+            c_base = atomicAdd(&rsc.words[7], n_rep);
         }
-        if (lane == 0) {
-            if (pairs) {
-                c_base = atomicAdd(&rsc.words[5], (cnt + 1) / 2);
-            } else if (c.pack) {
-                p_base = atomicAdd(&rsc.words[10], cnt);
-                c_base = atomicAdd(&rsc.words[c.pack == 2 ? 8 : 9], (cnt + PP - 1) / PP) +
-                         (c.pack == 2 ? 0 : n_p2);
-            } else if (fp64 || big) {
-                static_assert(kListFwd48 == kListFwdPad, "the third list of either plan");
-                c_base = c.L <= 32 ? atomicAdd(&lists[kListFwd], cnt)
-                         : c.L == 64 ? off64 + atomicAdd(&lists[kListFwd64], cnt)
-                                     : off48 + atomicAdd(&lists[kListFwd48], cnt);
+    }
+    c_base = __builtin_amdgcn_readfirstlane(c_base);
+    p_base = __builtin_amdgcn_readfirstlane(p_base);
+    int cnt = 0;
+    for (int q0 = p0; q0 < p1; q0 += 64) {
+        const int q = q0 + lane;
+        bool is_rep = false;
+        if (q < p1) {
+            const int a = row[q];
+            is_rep = !(a >= 0 && a < c.N) || first[a] == q;
+        }
+        const uint64_t m = __ballot(is_rep);
+        const int k = cnt + __popcll(m & ((1ull << lane) - 1));
+        cnt += __popcll(m);
+        if (!is_rep) continue;
+        if (c.pack) {
+            prep[p_base + k] = q;
+        } else if (pairs) {
+            PairTask& pt = cpairs[c_base + k / 2];
+            if (k & 1) {
+                pt.p_b = q;
             } else {
-                c_base = atomicAdd(&rsc.words[7], cnt);
+                pt.chain = t.chain;
+                pt.p_a = q;
+                pt.block = t.block;
+                if (k + 1 == n_rep) pt.p_b = -1;
             }
+        } else {
+            singles[c_base + k] = DrawTask{t.chain, q, t.block, 0};
         }
     }
-    __syncthreads();
-    if (c.pack) {
-        for (int i = threadIdx.x; i < n_rep; i += blockDim.x) prep[p_base + i] = rlist[i];
-        for (int k = threadIdx.x; k * PP < n_rep; k += blockDim.x)
+    if (c.pack)
+        for (int k = lane; k * PP < n_rep; k += 64)
             cpack[c_base + k] = PackTask{t.chain, p_base + k * PP, min(PP, n_rep - k * PP), t.block};
-    } else if (pairs) {
-        const int npairs = (n_rep + 1) / 2;
-        for (int i = threadIdx.x; i < npairs; i += blockDim.x)
-            cpairs[c_base + i] = PairTask{t.chain, rlist[2 * i],
-                                          2 * i + 1 < n_rep ? rlist[2 * i + 1] : -1, t.block};
-    } else {
-        for (int i = threadIdx.x; i < n_rep; i += blockDim.x)
-            singles[c_base + i] = DrawTask{t.chain, rlist[i], t.block, 0};
-    }
 }
 
 // With arep (an FP32 sweep) the last workgroup then queues the held chains as phase A.
