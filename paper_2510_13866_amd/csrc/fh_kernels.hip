@@ -2249,11 +2249,14 @@ __global__ __launch_bounds__(kThreads) void k_rescue_held(const ChainInfo* __res
 }
 
 // True on the workgroup of a launch of `total` that gets here last, whose threads then see what
-// the others wrote before (count: zero at the launch). Two barriers; after the first one the
-// workgroup's writes are in its L2, and one wavefront's fence passes them on (a fence of all four
-// writes the L2 back four times: 512 workgroups took 28 us with one, 49 with four).
+// the others wrote before (count: zero at the launch). Two barriers. Every wavefront waits for its
+// own stores and atomics before the first one, which does not (a workgroup's wavefronts see one
+// another's stores through their L1 without it): only then are all of the workgroup's in its L2, and
+// one wavefront's fence passes them on (a fence of all four writes the L2 back four times: 512
+// workgroups took 28 us with one, 49 with four).
 __device__ inline bool last_workgroup(int32_t* count, int total) {
     __shared__ int last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();
