@@ -1600,6 +1600,10 @@ __global__ __launch_bounds__(kThreads, LFIX || !CK ? 3 : 2) void k_grad_mfma(
                     if (LFIX || (xx < L && yy < L)) srow[yy * L + xx] = (m0[i] + m1[i]) + (m2[i] + m3[i]);
                 }
             }
+        } else {  // no barrier: the next slice's beta must still follow these reads of this one's
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
         if (j > 0) {
             float s = 0.0f;
@@ -2016,6 +2020,10 @@ __global__ __launch_bounds__(kThreads) void k_grad_dmfma(
                     if (xx < L && yy < L) srow[yy * L + xx] = (m0[i] + m1[i]) + (m2[i] + m3[i]);
                 }
             }
+        } else {  // no barrier: the next slice's beta must still follow these reads of this one's
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
         if (j > 0) {
             double sum = 0.0;
