@@ -97,7 +97,9 @@ int fh_debug_rescue(fh_plan plan, int32_t* last_count, int32_t* whole_chains, in
                     int32_t* list, int32_t cap);
 /* Overwrites every value of stored filter row `row` (numbered as fh_get_filters returns them) of
  * (chain, particle) with `value`, in the plan's precision; the host's way to force a row whose
- * backward weights are all zero. Needs stored filters (FH_ERR_STATE otherwise). Synchronous. */
+ * backward weights are all zero. Worldlines that share the row (fh_debug_representatives; after an
+ * adjoint, worldlines on the same ring) see it too. Needs stored filters (FH_ERR_STATE otherwise).
+ * Synchronous. */
 int fh_debug_fill_filter_row(fh_plan plan, int32_t chain, int32_t particle, int32_t row,
                              double value);
 /* Shared forward filters (the matrix-core plans of both precisions): the worldlines of one

@@ -1148,6 +1148,20 @@ int fh_get_status(fh_plan p, int32_t* code, int32_t* first_chain) {
     return FH_OK;
 }
 
+// The worldline whose stored rows hold those of each block of `particle`: its representative's with
+// shared forward filters, the worldline whose ring it shares after an adjoint (one entry counts).
+// The device has finished the pass that wrote them.
+static hipError_t row_owners(fh_plan p, const ChainInfo& c, int32_t particle,
+                             std::vector<int32_t>* owner) {
+    owner->assign((size_t)c.nb, particle);
+    if (p->filters_are_ring)
+        return hipMemcpy(owner->data(), p->d.grad.of + c.part_off + particle, sizeof(int32_t),
+                         hipMemcpyDeviceToHost);
+    if (!c.dedup || !p->d.rep) return hipSuccess;
+    return hipMemcpy(owner->data(), p->d.rep + c.blk_off + (int64_t)particle * c.nb,
+                     sizeof(int32_t) * c.nb, hipMemcpyDeviceToHost);
+}
+
 int fh_get_filters(fh_plan p, int32_t chain, int32_t particle, void* dst, int64_t capacity,
                    int64_t* n_rows, fh_stream stream) {
     if (!p || chain < 0 || chain >= p->n_chains) return FH_ERR_INVALID_ARG;
@@ -1159,19 +1173,9 @@ int fh_get_filters(fh_plan p, int32_t chain, int32_t particle, void* dst, int64_
     if (!dst) return FH_OK;
     if (capacity < rows * c.N) return FH_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    // sweep rows of a chain with shared forward filters: block b's rows are its
-    // representative's
-    std::vector<int32_t> owner((size_t)c.nb, particle);
-    if (!p->filters_are_ring && c.dedup && p->d.rep) {
-        FH_TRY(hipStreamSynchronize(s));
-        FH_TRY(hipMemcpy(owner.data(), p->d.rep + c.blk_off + (int64_t)particle * c.nb,
-                         sizeof(int32_t) * c.nb, hipMemcpyDeviceToHost));
-    }
-    if (p->filters_are_ring) {  // the worldline whose ring it shares
-        FH_TRY(hipStreamSynchronize(s));
-        FH_TRY(hipMemcpy(owner.data(), p->d.grad.of + c.part_off + particle, sizeof(int32_t),
-                         hipMemcpyDeviceToHost));
-    }
+    FH_TRY(hipStreamSynchronize(s));
+    std::vector<int32_t> owner;
+    FH_TRY(row_owners(p, c, particle, &owner));
     // ring rows: one block of L_tau rows; sweep rows: B - 1 (the last block: its length - 1)
     const int nseg = p->filters_are_ring ? 1 : c.nb;
     int64_t done = 0;
@@ -1441,7 +1445,10 @@ int fh_debug_fill_filter_row(fh_plan p, int32_t chain, int32_t particle, int32_t
     const int64_t rows = p->filters_are_ring ? c.L_tau : c.L_tau - c.nb;
     if (row < 0 || row >= rows) return FH_ERR_INVALID_ARG;
     FH_TRY(hipDeviceSynchronize());
-    const size_t off = (size_t)(c.filt_off + ((int64_t)particle * c.L_tau + row) * c.N);
+    std::vector<int32_t> owner;
+    FH_TRY(row_owners(p, c, particle, &owner));
+    const size_t b = p->filters_are_ring ? 0 : (size_t)std::min(row / (c.B - 1), c.nb - 1);
+    const size_t off = (size_t)(c.filt_off + ((int64_t)owner[b] * c.L_tau + row) * c.N);
     if (p->real_size == 8) {
         std::vector<double> v((size_t)c.N, value);
         FH_TRY(hipMemcpy((double*)p->d.filt + off, v.data(), sizeof(double) * c.N,
