@@ -3214,64 +3214,77 @@ __global__ __launch_bounds__(kThreads) void k_measure_out(
 }
 
 // The rings that worldlines share (GradShare), one workgroup per (chain, spin): an LDS hash table
-// over (anchor site, closing site) keeps the lowest worldline and the number of each pair, and a
-// scan in worldline order lists the lowest ones, so the list is the same on every call. A spin
-// with more than kGradKeys different pairs shares nothing; an invalid site keeps its own ring (the
+// over (anchor site, closing site), at most half full, keeps the lowest worldline and the number of
+// each pair, and a scan in worldline order lists the lowest ones, so the list is the same on every
+// call. A spin with more than kGradKeys different pairs shares nothing, and leaves the table when it
+// meets the first pair too many (a table that fills up is searched from end to end for every further
+// worldline: a gradient of 60000 worldlines of 16 x 16 x 2 on some 39000 pairs took 73 ms; it takes
+// 1.0, and 1.3 with every ring its own and no table). An invalid site keeps its own ring (the
 // adjoint reports it). Settled Gaussian chains have one ring per spin. The groups with rings are
 // listed densely: left at their places in the grid (every 128th one of a settled batch), the
-// dispatcher put them on a few compute units, one after another (64 settled 32 x 32 chains in
-// FP64, 128 of 16384 groups: 17.1 ms, sixteen groups deep).
+// dispatcher put them on a few compute units, one after another (64 settled 32 x 32 chains in FP64,
+// 128 of 16384 groups: 17.1 ms, sixteen groups deep).
 constexpr int kGradKeys = 4096;
+constexpr int kGradSlots = 2 * kGradKeys;
 __global__ __launch_bounds__(kThreads) void k_grad_dedup(const ChainInfo* __restrict__ chains,
                                                          const int32_t* __restrict__ paths,
                                                          const int32_t* __restrict__ perm,
                                                          int anchor, int gsize, int alone,
                                                          const GradShare gs) {
-    __shared__ int32_t keys[kGradKeys], low[kGradKeys], cnt[kGradKeys];
-    __shared__ int32_t full, part[kWaves];
+    __shared__ int32_t keys[kGradSlots], low[kGradSlots], cnt[kGradSlots];
+    __shared__ int32_t n_keys, part[kWaves];
     const int ci = blockIdx.x >> 1, spin = blockIdx.x & 1, tid = threadIdx.x, lane = tid & 63;
     const ChainInfo& c = chains[ci];
     const int p0 = spin ? c.n_up : 0, p1 = spin ? c.np : c.n_up;
-    for (int i = tid; i < kGradKeys; i += kThreads) {
+    // the table in use: twice the pairs there can be, or the half of it, which is cleared sooner
+    const int slots = 2 * (p1 - p0) <= kGradSlots / 2 ? kGradSlots / 2 : kGradSlots;
+    const int shift = slots == kGradSlots ? 19 : 20;
+    static_assert(kGradSlots == 1 << 13, "the hash keeps the top 13 or 12 bits");
+    for (int i = tid; i < slots; i += kThreads) {
         keys[i] = -1;
         low[i] = 0x7fffffff;
         cnt[i] = 0;
     }
-    if (tid == 0) full = 0;
+    if (tid == 0) n_keys = 0;
     __syncthreads();
     const int32_t* row = paths + c.path_off + (int64_t)anchor * c.np;
     auto key_of = [&](int p) {
         const int a = row[p], e = row[perm[c.part_off + p]];
         return (a < 0 || a >= c.N || e < 0 || e >= c.N) ? -1 : a * c.N + e;
     };
-    auto first = [&](int key) { return (int)(((uint32_t)key * 2654435761u) >> 20); };
-    static_assert(kGradKeys == 1 << 12, "the hash keeps the top 12 bits");
-    for (int p = p0 + tid; p < p1; p += kThreads) {
-        const int key = key_of(p);
-        if (key < 0) continue;
-        int h = first(key), probes = 0;
-        for (; probes < kGradKeys; ++probes, h = (h + 1) & (kGradKeys - 1)) {
-            const int was = atomicCAS(&keys[h], -1, key);
-            if (was == -1 || was == key) break;
-        }
-        if (probes == kGradKeys) {
-            full = 1;
-        } else {
+    auto first = [&](int key) { return (int)(((uint32_t)key * 2654435761u) >> shift); };
+    for (int q = p0 + tid - lane; q < p1; q += kThreads) {  // a wavefront's worldlines
+        if (*(volatile int32_t*)&n_keys > kGradKeys) break;  // 256 at most are on their way
+        const int p = q + lane, key = p < p1 ? key_of(p) : -1;
+        bool fresh = false;
+        if (key >= 0) {
+            int h = first(key), was;
+            while ((was = atomicCAS(&keys[h], -1, key)) != -1 && was != key) h = (h + 1) & (slots - 1);
+            fresh = was == -1;
             atomicMin(&low[h], p);
             atomicAdd(&cnt[h], 1);
         }
+        const uint64_t m = __ballot(fresh);
+        if (lane == 0) atomicAdd(&n_keys, __popcll(m));
     }
     __syncthreads();
-    const bool own = full != 0;
+    const bool own = n_keys > kGradKeys;
     int at = 0;  // listed so far
-    for (int q = p0; q < p1; q += kThreads) {
+    if (own) {
+        for (int p = p0 + tid; p < p1; p += kThreads) {
+            gs.of[c.part_off + p] = gs.list[c.part_off + p] = p;
+            gs.count[c.part_off + p] = 1;
+        }
+        at = p1 - p0;
+    }
+    for (int q = p0; q < p1 && !own; q += kThreads) {
         const int p = q + tid;
         int rep = p, times = 1;
-        if (p < p1 && !own) {
+        if (p < p1) {
             const int key = key_of(p);
             if (key >= 0) {
                 int h = first(key);
-                while (keys[h] != key) h = (h + 1) & (kGradKeys - 1);  // it is in the table
+                while (keys[h] != key) h = (h + 1) & (slots - 1);  // it is in the table
                 rep = low[h];
                 times = cnt[h];
             }
