@@ -2163,7 +2163,7 @@ __global__ __launch_bounds__(kThreads, kShareDrawWaves) void k_rescue_share_draw
 }
 
 // After the reset and the representative map, before a sweep's FP32 forward pass, one workgroup
-// (the last one of k_dedup, or k_rescue_held where nothing is shared): every block of each chain
+// (the last one of k_dedup, or k_rescue_held): every block of each chain
 // held on the FP64 re-filter (fp64_circulant) is queued, in chain order, as phase A, and the chain
 // is marked, while the running total of the held chains' forward
 // recursions (their representatives) fits the n_slots slots; the FP32 kernels skip held chains
@@ -2244,10 +2244,17 @@ __device__ void rescue_held_admit(const ChainInfo* __restrict__ chains, const Re
 }
 __global__ __launch_bounds__(kThreads) void k_rescue_held(const ChainInfo* __restrict__ chains,
                                                           const Rescue rsc, int n_slots,
+                                                          int shared,
                                                           DrawTask* __restrict__ arep) {
-    rescue_held_admit(chains, rsc, n_slots, 0, arep);
+    rescue_held_admit(chains, rsc, n_slots, shared, arep);
 }
 
+// Launches of more workgroups leave what the last one would do to a kernel of its own: a fence per
+// workgroup then costs more than a launch. Sweeps in us, last workgroup / kernel of its own, with the
+// workgroups of k_dedup and k_member_logz: 64 Ising 16 x 16, 128 and 64: 227 / 231; 8 in 10 blocks,
+// 160 and 80: 151 / 154; 16 in 10 blocks, 320 and 160: 213 / 210; 4 of 32 x 32 in 16 blocks, 128 and
+// 256: 369 / 366; 8 of 16 x 16 in 50 blocks, 800 and 400: 205 / 184.
+constexpr int kLastGrid = 192;
 // True on the workgroup of a launch of `total` that gets here last, whose threads then see what
 // the others wrote before (count: zero at the launch). Two barriers. Every wavefront waits for its
 // own stores and atomics before the first one, which does not (a workgroup's wavefronts see one
@@ -2486,7 +2493,8 @@ __device__ void dedup_task(const DrawTask& t, const ChainInfo* __restrict__ chai
             cpack[c_base + k] = PackTask{t.chain, p_base + k * PP, min(PP, n_rep - k * PP), t.block};
 }
 
-// With arep (an FP32 sweep) the last workgroup then queues the held chains as phase A.
+// With arep (an FP32 sweep, up to kLastGrid workgroups) the last one then queues the held chains as
+// phase A.
 __global__ __launch_bounds__(kThreads) void k_dedup(
     const DrawTask* __restrict__ tasks, const ChainInfo* __restrict__ chains,
     const int32_t* __restrict__ paths, const uint64_t* __restrict__ sweep_ptr,
@@ -2500,8 +2508,7 @@ __global__ __launch_bounds__(kThreads) void k_dedup(
         rescue_held_admit(chains, rsc, n_slots, 1, arep);
 }
 
-// After the FP32 forward pass, one workgroup (the last one of k_member_logz, or k_rescue_expand
-// where nothing is shared): a chain with more than whole_min blocks queued in this pass, or still
+// After the FP32 forward pass, one workgroup (the last one of k_member_logz, or k_rescue_expand): a chain with more than whole_min blocks queued in this pass, or still
 // held from an earlier such pass, has all its blocks queued for the FP64 re-filter (those of phase A
 // are); its hold then counts down (rescue_reset sets its length at the next pass).
 // With arep_b (sweeps of plans with a phase B) it then admits to phase B the chains queued whole
@@ -2567,8 +2574,9 @@ __device__ void rescue_expand(const ChainInfo* __restrict__ chains, const Rescue
     }
 }
 __global__ __launch_bounds__(kThreads) void k_rescue_expand(const ChainInfo* __restrict__ chains,
-                                                            const Rescue rsc) {
-    rescue_expand(chains, rsc, 0, nullptr);
+                                                            const Rescue rsc, int n_slots,
+                                                            DrawTask* __restrict__ arep_b) {
+    rescue_expand(chains, rsc, n_slots, arep_b);
 }
 
 // After the FP32 forward pass, one thread per (chain, particle, block) of the chains with dedup:
@@ -2614,18 +2622,18 @@ __device__ void member_logz(int64_t i0, int64_t stride, const ChainInfo* __restr
         blk_logz[i] = blk_la[ri] + log((double)hv);
     }
 }
-// The last workgroup then queues whole chains (FP32 plans; expand).
+// With expand (FP32 plans, up to kLastGrid workgroups) the last one then queues whole chains.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_member_logz(
     const ChainInfo* __restrict__ chains, int n_chains, const int32_t* __restrict__ paths,
     const int32_t* __restrict__ perm, const uint64_t* __restrict__ sweep_ptr,
     const double* __restrict__ blk_la, const T* __restrict__ endrow, const T* __restrict__ filt,
     double* __restrict__ blk_logz, int64_t blk_elems, int32_t* status, const Rescue rsc,
-    int32_t* __restrict__ lists, int n_slots, DrawTask* __restrict__ arep_b) {
+    int32_t* __restrict__ lists, int expand, int n_slots, DrawTask* __restrict__ arep_b) {
     member_logz(blockIdx.x * (int64_t)kThreads + threadIdx.x, (int64_t)gridDim.x * kThreads, chains,
                 n_chains, paths, perm, sweep_ptr, blk_la, endrow, filt, blk_logz, blk_elems, status,
                 rsc);
-    if (rsc.words && last_workgroup(&lists[kListDoneM], gridDim.x))
+    if (expand && last_workgroup(&lists[kListDoneM], gridDim.x))
         rescue_expand(chains, rsc, n_slots, arep_b);
 }
 
@@ -3719,44 +3727,52 @@ hipError_t launch_scale_copy(float* dst, const float* src, int64_t n, float fact
 }
 
 hipError_t launch_dedup(fh_plan p, const int32_t* paths, bool phase_a, hipStream_t s) {
+    const bool shared = p->n_dedup_tasks > 0 && !p->share_off;
     phase_a = phase_a && p->d.rescue;
-    if (p->n_dedup_tasks == 0 || p->share_off) {
-        if (phase_a)
-            hipLaunchKernelGGL(k_rescue_held, dim3(1), dim3(kThreads), 0, s, p->d.chains,
-                               rescue_args(p), p->n_rescue_slots, p->d.arep);
-        return hipGetLastError();
+    const bool inside = phase_a && shared && p->n_dedup_tasks <= kLastGrid;
+    if (shared) {
+        const bool fp64 = p->precision == FH_FP64;
+        hipLaunchKernelGGL(k_dedup, dim3((unsigned)p->n_dedup_tasks), dim3(kThreads), 0, s,
+                           p->d.dedup_tasks, p->d.chains, paths, p->d.sweep, p->d.rep,
+                           rescue_args(p), p->d.fwd32c_tasks,
+                           fp64 ? p->d.fwddc_tasks : p->d.fwdxc_tasks, p->d.fwd64c_tasks,
+                           p->d.fwdpc_tasks, p->n_fwdp2_tasks, p->d.prep, p->d.lists,
+                           fp64 ? p->n_fwdd_tasks : 0,
+                           fp64 ? p->n_fwdd_tasks + p->n_fwdd4_tasks : p->n_fwd64_tasks,
+                           StageLists{p->d.staged, p->d.members, p->d.stage_tasks,
+                                      p->d.stage_tasks_s, (int32_t)p->real_size},
+                           p->n_rescue_slots, inside ? p->d.arep : nullptr);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    const bool fp64 = p->precision == FH_FP64;
-    hipLaunchKernelGGL(k_dedup, dim3((unsigned)p->n_dedup_tasks), dim3(kThreads), 0, s,
-                       p->d.dedup_tasks, p->d.chains, paths, p->d.sweep, p->d.rep, rescue_args(p),
-                       p->d.fwd32c_tasks,
-                       fp64 ? p->d.fwddc_tasks : p->d.fwdxc_tasks, p->d.fwd64c_tasks,
-                       p->d.fwdpc_tasks, p->n_fwdp2_tasks, p->d.prep, p->d.lists,
-                       fp64 ? p->n_fwdd_tasks : 0,
-                       fp64 ? p->n_fwdd_tasks + p->n_fwdd4_tasks : p->n_fwd64_tasks,
-                       StageLists{p->d.staged, p->d.members, p->d.stage_tasks,
-                                  p->d.stage_tasks_s, (int32_t)p->real_size},
-                       p->n_rescue_slots, phase_a ? p->d.arep : nullptr);
+    if (phase_a && !inside)
+        hipLaunchKernelGGL(k_rescue_held, dim3(1), dim3(kThreads), 0, s, p->d.chains,
+                           rescue_args(p), p->n_rescue_slots, (int)shared, p->d.arep);
     return hipGetLastError();
 }
 
 hipError_t launch_member_logz(fh_plan p, const int32_t* paths, hipStream_t s) {
-    if (p->n_dedup_tasks == 0 || p->share_off) {
-        if (p->d.rescue)
-            hipLaunchKernelGGL(k_rescue_expand, dim3(1), dim3(kThreads), 0, s, p->d.chains,
-                               rescue_args(p));
-        return hipGetLastError();
+    const bool shared = p->n_dedup_tasks > 0 && !p->share_off;
+    DrawTask* arep_b = shared && p->phase_b ? p->d.arep_b : nullptr;
+    const unsigned blocks = grid_for(p->blk_elems);
+    const bool inside = p->d.rescue && shared && blocks <= (unsigned)kLastGrid;
+    if (shared) {
+        auto run = [&](auto kern, auto* endrow, auto* filt) {
+            hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, s, p->d.chains, p->n_chains,
+                               paths, p->d.perm, p->d.sweep, p->d.blk_la, endrow, filt,
+                               p->d.blk_logz, p->blk_elems, p->d.status, rescue_args(p),
+                               p->d.lists, (int)inside, p->n_rescue_slots, arep_b);
+        };
+        if (p->precision == FH_FP64)
+            run(k_member_logz<double>, (const double*)nullptr, (const double*)p->d.filt);
+        else
+            run(k_member_logz<float>, (const float*)p->d.endrow, (const float*)p->d.filt);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    auto run = [&](auto kern, auto* endrow, auto* filt) {
-        hipLaunchKernelGGL(kern, dim3(grid_for(p->blk_elems)), dim3(kThreads), 0, s, p->d.chains,
-                           p->n_chains, paths, p->d.perm, p->d.sweep, p->d.blk_la, endrow, filt,
-                           p->d.blk_logz, p->blk_elems, p->d.status, rescue_args(p), p->d.lists,
-                           p->n_rescue_slots, p->phase_b ? p->d.arep_b : nullptr);
-    };
-    if (p->precision == FH_FP64)
-        run(k_member_logz<double>, (const double*)nullptr, (const double*)p->d.filt);
-    else
-        run(k_member_logz<float>, (const float*)p->d.endrow, (const float*)p->d.filt);
+    if (p->d.rescue && !inside)
+        hipLaunchKernelGGL(k_rescue_expand, dim3(1), dim3(kThreads), 0, s, p->d.chains,
+                           rescue_args(p), p->n_rescue_slots, arep_b);
     return hipGetLastError();
 }
 
