@@ -322,6 +322,7 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
         blk += (int64_t)ci.np * ci.nb;
         p->max_N = std::max(p->max_N, ci.N);
         p->max_L = std::max(p->max_L, ci.L);
+        p->min_L = std::min(p->min_L, ci.L);
         p->max_np = std::max(p->max_np, ci.np);
         p->max_tau = std::max(p->max_tau, ci.L_tau);
         p->chains.push_back(ci);

@@ -439,7 +439,7 @@ struct fh_plan_s {
     int64_t end_elems = 0;          // end tiles of the chains with dedup (f32 elements)
     int64_t rescue_slot_elems = 0;  // doubles per slot: (B - 1) N of the largest L <= 32 chain
     int64_t total_sites = 0;  // sum of N over the chains
-    int32_t max_N = 0, max_L = 0, max_np = 0, max_tau = 0;
+    int32_t max_N = 0, max_L = 0, min_L = INT32_MAX, max_np = 0, max_tau = 0;
     // what d.sweep holds once the work queued so far has run; unknown after a failed call, and for
     // good once a caller's graph writes it
     bool sweep_known = false, sweep_captured = false;

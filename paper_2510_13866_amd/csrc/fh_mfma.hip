@@ -1783,8 +1783,11 @@ __device__ inline bool grad_wg64(const double* __restrict__ cm, int L, int L_tau
 // The adjoint of k_grad_mfma on the FP64 matrix cores (FP64 plans, every chain L <= 32): the
 // same ring, recursion, marginals and d/dt stencil, every product and sum in FP64 with the
 // circulant of k_forward_dmfma; ring rows stored as FP64 rows, group partial slabs in FP64;
-// the checkpoints of FH_FLAG_GRAD_CHECKPOINT as in k_grad_mfma.
-template <bool CK>
+// the checkpoints of FH_FLAG_GRAD_CHECKPOINT as in k_grad_mfma. TILES: 1 where every chain has
+// L <= 16 (one tile), 4 where none has, else 0 (each ring as its L asks; the same bits either way): the
+// choice inside the slice loop cost 3.5% (4 chains of 32 x 32 x 128 with checkpoints, 5.84 / 6.04 ms),
+// without one tile 8 chains of 16 x 16 x 64 take 1.32 instead of 0.79 ms.
+template <bool CK, int TILES>
 __global__ __launch_bounds__(kThreads) void k_grad_dmfma(
     const ChainInfo* __restrict__ chains, const GroupTask* __restrict__ groups,
     const double* __restrict__ cmat64, const double* __restrict__ aux,
@@ -1839,7 +1842,7 @@ __global__ __launch_bounds__(kThreads) void k_grad_dmfma(
     for (int q = 0; q < 16; ++q) Cb[q] = cmat64[((int64_t)g.chain * 16 + q) * 64 + lane];
     const double C4[4] = {Cb[0], Cb[2], Cb[4], Cb[6]};
     auto conv = [&](const Tile64& X) {  // C X C; a lattice with L <= 16 has one tile
-        if (L > 16) return circ64(circ64(X, Cb), Cb);
+        if (TILES == 4 || (TILES == 0 && L > 16)) return circ64(circ64(X, Cb), Cb);
         Tile64 Y = {};
         Y.t[0] = circ16(X.t[0], C4, L);
         return Y;
@@ -2346,13 +2349,19 @@ hipError_t launch_grad_reduce(fh_plan p, void* grad_aux, double* logZ, double* g
 
 hipError_t launch_grad_dmfma(fh_plan p, const void* aux, const int32_t* paths, int32_t anchor,
                              void* grad_aux, hipStream_t s) {
-    hipLaunchKernelGGL(p->d.ckpt ? k_grad_dmfma<true> : k_grad_dmfma<false>, dim3(p->n_groups),
-                       dim3(kThreads), 0, s, p->d.chains,
-                       p->d.group_tasks, p->d.cmat64, (const double*)aux, (const double*)p->d.W,
-                       p->d.wshift, p->aux_elems, p->total_slices, paths, (double*)p->d.filt,
-                       grad_aux ? (double*)p->d.gpart : nullptr, p->d.blk_logz, p->d.dt, anchor,
-                       p->d.perm,
-                       p->d.status, (double*)p->d.ckpt, p->d.grad);
+    auto run = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(p->n_groups), dim3(kThreads), 0, s, p->d.chains,
+                           p->d.group_tasks, p->d.cmat64, (const double*)aux, (const double*)p->d.W,
+                           p->d.wshift, p->aux_elems, p->total_slices, paths, (double*)p->d.filt,
+                           grad_aux ? (double*)p->d.gpart : nullptr, p->d.blk_logz, p->d.dt,
+                           anchor, p->d.perm, p->d.status, (double*)p->d.ckpt, p->d.grad);
+    };
+    if (p->max_L <= 16)
+        run(p->d.ckpt ? k_grad_dmfma<true, 1> : k_grad_dmfma<false, 1>);
+    else if (p->min_L > 16)
+        run(p->d.ckpt ? k_grad_dmfma<true, 4> : k_grad_dmfma<false, 4>);
+    else
+        run(p->d.ckpt ? k_grad_dmfma<true, 0> : k_grad_dmfma<false, 0>);
     return hipGetLastError();
 }
 
