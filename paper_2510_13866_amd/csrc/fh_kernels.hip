@@ -3157,6 +3157,11 @@ __global__ __launch_bounds__(kThreads) void k_measure(const ChainInfo* __restric
 // kThreads / kMeasureSites interleaved runs added in run order, into row 0, which only it reads.
 // (One thread per site and all slices in one run left 240 of 256 compute units idle.)
 constexpr int kMeasureSites = 32;
+// Plans whose chains all have at most so many rows, on at most so many sites, leave out the launch:
+// k_measure_out adds the rows, in the same order. A call in us, with k_measure_sum / without: one 4 x 4
+// chain of 16 slices 17.1 / 14.4 (one launch fewer), 64 of 16 x 16 x 16 16.7 / 16.0, 16 of 32 x 32 x 16
+// 23.6 / 27.3, one 16 x 16 chain of 64 slices 15.5 / 20.4 (one workgroup then walks the rows).
+constexpr int kMeasureRows = kThreads / kMeasureSites, kMeasureRowSites = 256;
 __global__ __launch_bounds__(kThreads) void k_measure_sum(const ChainInfo* __restrict__ chains,
                                                           double* __restrict__ z2, int tiles) {
     constexpr int kRuns = kThreads / kMeasureSites;
@@ -3179,13 +3184,15 @@ __global__ __launch_bounds__(kThreads) void k_measure_sum(const ChainInfo* __res
     }
 }
 
-// S(k), the inverse transform C(r), D and the local moment of a chain, one workgroup each. (As the
+// S(k), the inverse transform C(r), D and the local moment of a chain, one workgroup each, from the
+// summed rows in row 0, or with sum_rows from all rows. (As the
 // last workgroup of k_measure_sum it saved a launch and cost 512 fences, one per workgroup: 28 us
 // for both against 5.1 + 8.8.)
 __global__ __launch_bounds__(kThreads) void k_measure_out(
     const ChainInfo* __restrict__ chains, const double* __restrict__ tables,
     const double* __restrict__ z2, const double* __restrict__ sums, double* __restrict__ Sk,
-    double* __restrict__ Cr, double* __restrict__ D, double* __restrict__ S2, int maxN, int maxL) {
+    double* __restrict__ Cr, double* __restrict__ D, double* __restrict__ S2, int maxN, int maxL,
+    int sum_rows) {
     extern __shared__ __align__(16) unsigned char smem[];
     cpx<double>* A = (cpx<double>*)smem;  // [maxN]
     cpx<double>* S = A + maxN;            // [maxN]
@@ -3201,7 +3208,12 @@ __global__ __launch_bounds__(kThreads) void k_measure_out(
     for (int q = threadIdx.x; q < N; q += blockDim.x) {
         const int y = q / L, x = q - y * L;
         const int neg = (y ? L - y : 0) * L + (x ? L - x : 0);
-        const double p2 = 0.5 * (P[q] + P[neg]) * mean;
+        double a = P[q], b = P[neg];
+        for (int g = 1; g < pairs && sum_rows; ++g) {  // k_measure_sum's order: one row a run
+            a += P[(int64_t)g * N + q];
+            b += P[(int64_t)g * N + neg];
+        }
+        const double p2 = 0.5 * (a + b) * mean;
         if (Sk) Sk[c.site_off + q] = p2 / (double)N;
         A[q] = {p2, 0.0};
     }
@@ -3955,12 +3967,15 @@ hipError_t launch_measure(fh_plan p, const int32_t* paths, double* Sk, double* C
                        p->d.chains, p->n_chains, p->d.tables, paths, z2, sums, p->d.status,
                        p->max_N, p->max_L);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const unsigned tiles = (unsigned)((p->max_N + kMeasureSites - 1) / kMeasureSites);
-    hipLaunchKernelGGL(k_measure_sum, dim3(tiles * (unsigned)p->n_chains), dim3(kThreads), 0, s,
-                       p->d.chains, z2, (int)tiles);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const bool few = p->max_tau <= 2 * kMeasureRows && p->max_N <= kMeasureRowSites;
+    if (!few) {
+        const unsigned tiles = (unsigned)((p->max_N + kMeasureSites - 1) / kMeasureSites);
+        hipLaunchKernelGGL(k_measure_sum, dim3(tiles * (unsigned)p->n_chains), dim3(kThreads), 0, s,
+                           p->d.chains, z2, (int)tiles);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_measure_out, dim3((unsigned)p->n_chains), dim3(kThreads), lds, s,
-                       p->d.chains, p->d.tables, z2, sums, Sk, Cr, D, S2, p->max_N, p->max_L);
+                       p->d.chains, p->d.tables, z2, sums, Sk, Cr, D, S2, p->max_N, p->max_L, (int)few);
     return hipGetLastError();
 }
 
