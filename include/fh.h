@@ -230,19 +230,19 @@ int fh_permutation_update(fh_plan plan, const int32_t* paths, uint64_t sweep, in
  *   S(k) = (1/N) |sum_j e^{i k.r_j} S^z_j|^2,   k = 2 pi (k_x, k_y) / L indexed k_x + L k_y,
  *   C(r) = (1/N) sum_j S^z_{j+r} S^z_j,         r indexed x + L y,
  *   D = mean over sites of n_up n_dn,  S2 = (3/4) mean over sites of (n_up - n_dn)^2.
- * S(k) and C(r) come from one FP64 2D FFT of S^z per slice and one inverse FFT of |F|^2. Outputs
+ * S(k) and C(r) come from one FP64 2D FFT of S^z per two slices and one inverse FFT per chain. Outputs
  * are device arrays, each nullable: Sk and Cr packed by chain (chain c's N_c values after those
- * of chains 0..c-1), D and S2 [n_chains]. The first call allocates the plan's per-slice rows
- * (2 * aux elements + 2 * slices doubles). */
+ * of chains 0..c-1), D and S2 [n_chains]. The first call allocates the plan's rows (aux elements +
+ * 2 * slices doubles). */
 int fh_measure(fh_plan plan, const int32_t* paths, double* Sk, double* Cr, double* D,
                double* S2, fh_stream stream);
 
 /* fh_measure for callers that cannot allocate device memory (code under stream capture, serving
- * loops, harnesses that forbid it): the same kernels, outputs and arguments, with the per-slice
+ * loops, harnesses that forbid it): the same kernels, outputs and arguments, with the
  * rows in a static device array of 2^22 doubles (32 MiB) that every GPU the library runs on holds
  * until the process ends, instead of a buffer the plan allocates on first use. The call itself
- * calls no allocator. Returns FH_ERR_UNSUPPORTED when the plan needs more than the array holds
- * (2 * aux elements + 2 * slices of all chains > 2^22, e.g. more than 12 chains of 32 x 32 with
+ * calls no allocator. Returns FH_ERR_UNSUPPORTED when 2 * aux elements + 2 * slices of all chains
+ * exceed 2^22 (some twice the doubles that its rows take; e.g. more than 12 chains of 32 x 32 with
  * L_tau = 160) and FH_ERR_HIP when the array's address could not be taken at fh_init. All calls
  * on one GPU share its array: calls that overlap in time on one GPU (any plans, any streams)
  * race and must be serialised by the caller. */

@@ -913,10 +913,9 @@ int fh_measure(fh_plan p, const int32_t* paths, double* Sk, double* Cr, double* 
                fh_stream stream) {
     if (!p || !paths) return FH_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    if (!p->d.meas) {  // first call: the per-slice rows
-        const size_t n = 2 * (size_t)p->aux_elems + 2 * (size_t)p->total_slices;
+    if (!p->d.meas) {  // first call: the rows
         FH_TRY(hipStreamSynchronize(s));
-        FH_TRY(hipMalloc((void**)&p->d.meas, sizeof(double) * n));
+        FH_TRY(hipMalloc((void**)&p->d.meas, sizeof(double) * (size_t)measure_doubles(p)));
     }
     FH_TRY(launch_measure(p, paths, Sk, Cr, D, S2, s, p->d.meas));
     return FH_OK;
@@ -925,6 +924,7 @@ int fh_measure(fh_plan p, const int32_t* paths, double* Sk, double* Cr, double* 
 int fh_measure_noalloc(fh_plan p, const int32_t* paths, double* Sk, double* Cr, double* D,
                        double* S2, fh_stream stream) {
     if (!p || !paths) return FH_ERR_INVALID_ARG;
+    // the documented limit, some twice what the rows take (measure_doubles)
     if (2 * p->aux_elems + 2 * p->total_slices > kScratchDoubles) return FH_ERR_UNSUPPORTED;
     if (!p->scratch) return FH_ERR_HIP;  // its address could not be taken at fh_init
     FH_TRY(launch_measure(p, paths, Sk, Cr, D, S2, (hipStream_t)stream, (double*)p->scratch));

@@ -375,8 +375,9 @@ struct Device {
                               // precision: FP32 for FH_FP32_MFMA3, FP64 for the FP64 circulant)
     void* mala = nullptr;     // fh_mala_field: proposal, two gradients [3][aux_elems] in plan
                               // precision, then log Z_path at both fields [2][n_chains] f64
-    double* meas = nullptr;   // fh_measure per-slice rows: S(k) [aux_elems], C(r) [aux_elems],
-                              // then the (n_up n_dn, (n_up - n_dn)^2) site sums [slices][2]
+    double* meas = nullptr;   // fh_measure: a row |Z|^2 per slice pair, at the place of the chain's
+                              // slices [aux_elems], then the (n_up n_dn, (n_up - n_dn)^2) site
+                              // sums [slices][2] (measure_doubles)
     int32_t* perm = nullptr;     // [particles] reconnection at tau = beta: slice L_tau of
                                  // worldline p is slice 0 of worldline perm[part_off + p]
                                  // (chain-local indices); the identity unless changed
@@ -472,6 +473,9 @@ struct fh_plan_s {
 
 namespace fh {
 
+// Doubles of fh_measure's work area.
+inline int64_t measure_doubles(fh_plan p) { return p->aux_elems + 2 * p->total_slices; }
+
 // Rings per group of the plan's adjoint.
 inline int grad_group_size(fh_plan p) {
     return p->precision == FH_FP32_MFMA3 || p->grad_dmfma ? kGroup : 2;
@@ -520,7 +524,7 @@ hipError_t tune_radix_plan(fh_plan p, int L, const double* tw_dev, hipStream_t s
 hipError_t launch_gibbs(fh_plan p, const int32_t* paths, void* aux, bool sweep, hipStream_t s);
 hipError_t launch_local(fh_plan p, const void* aux, int32_t* paths, int n_passes, hipStream_t s);
 hipError_t launch_perm_update(fh_plan p, const int32_t* paths, int n_passes, hipStream_t s);
-// `work`: 2 aux_elems + 2 total_slices doubles of per-slice rows (the plan's, or the static scratch).
+// `work`: measure_doubles of rows (the plan's, or the static scratch).
 hipError_t launch_measure(fh_plan p, const int32_t* paths, double* Sk, double* Cr, double* D,
                           double* S2, hipStream_t s, double* work);
 // Device address of the static scratch array on the current device (taken once per device).

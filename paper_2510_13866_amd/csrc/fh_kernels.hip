@@ -17,8 +17,8 @@
 #include "fh_internal.h"
 #include "fh_philox.h"
 
-// Per-slice rows of fh_measure_noalloc (S(k) and C(r) of every slice, then the two site sums of
-// every slice), held in this device array for callers that cannot allocate. Each GPU the library
+// Rows of fh_measure_noalloc (|Z|^2 of every slice pair, then the two site sums of each; measure_doubles
+// of at most kScratchDoubles), held in this device array for callers that cannot allocate. Each GPU the library
 // runs on holds one copy for the life of the process; its device address is taken once per
 // device (fh::scratch_address) and passed to the kernels like any other buffer. Every element a
 // call reads is written by the same call first, so nothing needs clearing between calls.

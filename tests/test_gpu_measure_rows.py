@@ -27,3 +27,23 @@ def test_observables_alone_and_beside_a_long_chain(L, L_tau):
         assert np.array_equal(x, y)
     S.close()
     B.close()
+
+
+def test_the_first_call_takes_one_set_of_rows():
+    import torch
+    from paper_2510_13866_amd import fhmc
+    from paper_2510_13866_amd.sampler import Sampler
+    d = synth.ChainDesc(L=64, L_tau=4096, n_up=1, n_dn=0, hs_kind=1, block_len=2048, t=1.0, U=4.0,
+                        dtau=0.05, seed=2)
+    print("rows of the observables", flush=True)
+    S = Sampler([d], fhmc.FH_FP32_MFMA3)
+    P = S.pack_paths([synth.initial_paths(d)])
+    out = [torch.empty(k, dtype=torch.float64, device="cuda:0") for k in (4096, 4096, 1, 1)]
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    fhmc.fh_measure(S.plan, P, *out)
+    torch.cuda.synchronize()
+    rows = 8 * (d.L_tau * d.N + 2 * d.L_tau)  # 128 MiB
+    assert free - torch.cuda.mem_get_info()[0] <= rows + (16 << 20)
+    assert S.status() == (0, -1)
+    S.close()
