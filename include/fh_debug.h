@@ -114,6 +114,13 @@ int fh_debug_representatives(fh_plan plan, int32_t* rep, int64_t cap, int64_t* n
  * identity), the reference for tests that the shared filters change no result; 1 (the
  * default): shared. Synchronous; drops the captured sweep and invalidates stored filters. */
 int fh_debug_share_filters(fh_plan plan, int32_t enable);
+/* How the last forward pass left the plan to its draws (synchronises the device): counts[0] the
+ * (spin, block)s whose draws are staged from the plan's rows, counts[1] those staged from the FP64
+ * re-filter's slots where their chain is in one of its phases, counts[2] and counts[3] the tasks of
+ * these (up to 64 worldlines each), counts[4] the chains in phase A of a sweep (held when it began),
+ * counts[5] those in phase B (queued whole in it), counts[6] the recursions phase B has run. counts
+ * holds 7 int32 written by the call (caller-owned host memory; zeros where no chain shares). */
+int fh_debug_staged(fh_plan plan, int32_t* counts);
 /* Synchronises the device and writes to holds (caller-owned host memory, [n_chains]) the forward
  * passes each chain stays on the FP64 re-filter: a chain with L <= 32 and holds[c] > 0 is
  * skipped by the next forward pass's FP32 kernels and re-filtered whole. FP64 plans write 0. */

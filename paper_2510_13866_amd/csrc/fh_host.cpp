@@ -1490,6 +1490,34 @@ int fh_debug_representatives(fh_plan p, int32_t* rep, int64_t cap, int64_t* n) {
     return FH_OK;
 }
 
+int fh_debug_staged(fh_plan p, int32_t* counts) {
+    if (!p || !counts) return FH_ERR_INVALID_ARG;
+    std::fill(counts, counts + 7, 0);
+    if (!p->d.rep || p->share_off) return FH_OK;
+    FH_TRY(hipDeviceSynchronize());
+    const ChainInfo& last = p->chains.back();
+    std::vector<int32_t> staged((size_t)last.sb_off + 2 * (size_t)last.nb);
+    FH_TRY(hipMemcpy(staged.data(), p->d.staged, sizeof(int32_t) * staged.size(),
+                     hipMemcpyDeviceToHost));
+    for (int32_t v : staged) {
+        counts[0] += (v & kStagedRows) != 0;
+        counts[1] += (v & kStagedSlots) != 0;
+    }
+    int32_t lists[kListWords];
+    FH_TRY(hipMemcpy(lists, p->d.lists, sizeof(lists), hipMemcpyDeviceToHost));
+    counts[2] = lists[kListStage];
+    counts[3] = lists[kListStageS];
+    if (!p->d.rescue) return FH_OK;
+    std::vector<int32_t> w((size_t)(kRescueChain + 3 * p->n_chains));
+    FH_TRY(hipMemcpy(w.data(), p->d.rescue, sizeof(int32_t) * w.size(), hipMemcpyDeviceToHost));
+    for (int c = 0; c < p->n_chains; ++c) {
+        counts[4] += w[(size_t)(kRescueChain + 2 * p->n_chains + c)] == 1;
+        counts[5] += w[(size_t)(kRescueChain + 2 * p->n_chains + c)] == 2;
+    }
+    counts[6] = w[16];
+    return FH_OK;
+}
+
 int fh_debug_rescue_holds(fh_plan p, int32_t* holds) {
     if (!p || !holds) return FH_ERR_INVALID_ARG;
     std::fill(holds, holds + p->n_chains, 0);

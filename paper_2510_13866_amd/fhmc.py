@@ -111,6 +111,7 @@ _sig("fh_debug_backward_kernels", c_int32, c_void_p, POINTER(c_int32), POINTER(c
 _sig("fh_debug_forward_kernels", c_int32, c_void_p, POINTER(c_int32))
 _sig("fh_debug_backward_adapt", c_int32, c_void_p, c_int32, POINTER(c_int32))
 _sig("fh_debug_rescue_holds", c_int32, c_void_p, POINTER(c_int32))
+_sig("fh_debug_staged", c_int32, c_void_p, POINTER(c_int32))
 _sig("fh_debug_rescue_causes", c_int32, c_void_p, POINTER(c_int32))
 _sig("fh_debug_fill_filter_row", c_int32, c_void_p, c_int32, c_int32, c_int32, c_double)
 _sig("fh_debug_representatives", c_int32, c_void_p, POINTER(c_int32), c_int64, POINTER(c_int64))
@@ -312,6 +313,13 @@ def fh_debug_rescue_holds(plan, n_chains):
     _check(lib.fh_debug_rescue_holds(plan, buf.ctypes.data_as(POINTER(c_int32))),
            "fh_debug_rescue_holds")
     return buf
+
+
+def fh_debug_staged(plan):
+    """The 7 counts of fh_debug_staged."""
+    buf = (c_int32 * 7)()
+    _check(lib.fh_debug_staged(plan, buf), "fh_debug_staged")
+    return list(buf)
 
 
 def fh_debug_representatives(plan):
