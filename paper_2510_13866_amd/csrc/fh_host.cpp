@@ -530,6 +530,7 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
         int64_t rescuable = 0;
         for (const ChainInfo& ci : p->chains)
             if (fp64_circulant(ci.L)) {
+                p->rescue_l32 = p->rescue_l32 || ci.L <= 32;
                 p->rescue_l48 = p->rescue_l48 || ci.L == 48;
                 p->rescue_l64 = p->rescue_l64 || ci.L == 64;
                 // the block's rows and the end tile (phase A)

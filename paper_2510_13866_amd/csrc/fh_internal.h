@@ -425,7 +425,8 @@ struct fh_plan_s {
     // after them in fwdd_tasks: the tasks of the 64 x 64, then of the 48 x 48 chains
     int32_t n_fwdd4_tasks = 0, n_fwdd3_tasks = 0;
     bool phase_b = false;  // a sweep re-filters chains that just left FP32's range in phase B
-    bool rescue_l48 = false, rescue_l64 = false;  // FP32 plans: chains the big FP64 re-filter takes
+    // FP32 plans: the chains the FP64 re-filter takes (L <= 32, L = 48, L = 64)
+    bool rescue_l32 = false, rescue_l48 = false, rescue_l64 = false;
     bool grad_dmfma = false;   // FP64 plan whose chains all have L <= 32: adjoint on the matrix cores
     double win_bound_scale = 1.0;  // test hook: >= 1 inflates every window bound
     bool bw_adapt = true;          // switch clustered chains to the full-row kernels

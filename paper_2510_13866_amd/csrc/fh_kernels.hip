@@ -3821,7 +3821,7 @@ hipError_t launch_rescue(fh_plan p, const void* aux, int32_t* paths, bool draw, 
                                p->d.rep_slot, p->d.rescue_ws, p->rescue_slot_elems,
                                p->d.rescue_w, p->aux_elems, b ? 15 : 6, b ? 16 : 4);
         };
-        fwd(k_rescue_share_fwd4);
+        if (p->rescue_l32) fwd(k_rescue_share_fwd4);
         if (p->rescue_l64) fwd(k_rescue_share_fwd<4>);
         if (p->rescue_l48) fwd(k_rescue_share_fwd<3>);
         if (p->n_stage_tasks_s > 0 && !p->share_off)
