@@ -7,6 +7,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <map>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -250,9 +252,45 @@ const char* fh_strerror(int code) {
     }
 }
 
+// Side streams of destroyed plans, by device, for the next plans: they are kept until the process
+// ends. The runtime writes into a destroyed stream's memory when it lets go of the commands that
+// other streams waited for (a count and a flag, some milliseconds after hipDeviceSynchronize and
+// hipStreamDestroy have returned), and the plan's side stream is waited for by the caller's in every
+// sweep: half of the plans destroyed after eager sweeps had 12 bytes of whatever took that memory
+// overwritten. There are as many as plans were alive at once.
+namespace {
+struct SideStreams {
+    std::mutex lock;
+    std::map<int, std::vector<hipStream_t>> idle;
+};
+SideStreams& side_streams() {
+    static SideStreams* s = new SideStreams();  // not destroyed: plans may outlive static objects
+    return *s;
+}
+hipError_t take_side_stream(fh_plan p) {
+    hipError_t e = hipGetDevice(&p->device);
+    if (e != hipSuccess) return e;
+    {
+        std::lock_guard<std::mutex> g(side_streams().lock);
+        std::vector<hipStream_t>& idle = side_streams().idle[p->device];
+        if (!idle.empty()) {
+            p->side_stream = idle.back();
+            idle.pop_back();
+            return hipSuccess;
+        }
+    }
+    return hipStreamCreateWithFlags(&p->side_stream, hipStreamNonBlocking);
+}
+void give_side_stream(fh_plan p) {
+    std::lock_guard<std::mutex> g(side_streams().lock);
+    side_streams().idle[p->device].push_back(p->side_stream);
+    p->side_stream = nullptr;
+}
+}  // namespace
+
 static void destroy_streams(fh_plan p) {
     if (p->capture_stream) (void)hipStreamDestroy(p->capture_stream);
-    if (p->side_stream) (void)hipStreamDestroy(p->side_stream);
+    if (p->side_stream) give_side_stream(p);
     if (p->fork_ev) (void)hipEventDestroy(p->fork_ev);
     if (p->join_ev) (void)hipEventDestroy(p->join_ev);
 }
@@ -654,7 +692,7 @@ int fh_init(fh_plan* out, const fh_chain_desc* descs, int32_t n_chains, int32_t 
     if (e == hipSuccess) e = hipMemcpy(dv.tables, p->tables.data(), sizeof(double) * p->tables.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&p->capture_stream, hipStreamNonBlocking);
     if (e == hipSuccess && dv.rescue) {  // FP32 plans: phase A of the re-filter beside the sweep
-        e = hipStreamCreateWithFlags(&p->side_stream, hipStreamNonBlocking);
+        e = take_side_stream(p);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&p->fork_ev, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&p->join_ev, hipEventDisableTiming);
     }

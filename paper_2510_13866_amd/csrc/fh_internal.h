@@ -461,8 +461,10 @@ struct fh_plan_s {
     bool timing = false;
     hipEvent_t tev[8] = {};
     // FP32 plans: a sweep re-filters the chains held on FP64 (phase A) on this stream, beside the
-    // FP32 forward and backward passes of the other chains on the caller's stream
+    // FP32 forward and backward passes of the other chains on the caller's stream. It comes from, and
+    // goes back to, the streams kept for `device`.
     hipStream_t side_stream = nullptr;
+    int device = 0;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
     // graph cache for fh_sweep
     hipStream_t capture_stream = nullptr;
