@@ -223,6 +223,7 @@ void drop_graph(fh_plan p) {
 
 int hip_status(hipError_t e) {
     if (e == hipSuccess) return FH_OK;
+    (void)hipGetLastError();  // reported here: the caller's next HIP call must not report it again
     if (e == hipErrorOutOfMemory) return FH_ERR_OOM;
     return FH_ERR_HIP;
 }

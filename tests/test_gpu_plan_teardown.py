@@ -57,3 +57,22 @@ def test_side_streams_of_several_plans_alive_at_once():
             want = P if want is None else want
             assert torch.equal(P, want)
             S.close()
+
+
+def test_a_refused_launch_leaves_no_error_behind():
+    """The FP64 FFT adjoint of 64 x 64 takes more LDS than a workgroup has: the call says so, and the
+    process's next HIP calls are not blamed for it."""
+    from paper_2510_13866_amd import fhmc
+    from paper_2510_13866_amd.sampler import Sampler
+    d = [synth.ChainDesc(L=64, L_tau=3, n_up=2, n_dn=1, hs_kind=0, block_len=0, t=1.0, U=4.0,
+                         dtau=0.05, seed=6)]
+    print("refused launch", flush=True)
+    S = Sampler(d, fhmc.FH_FP64)
+    A, P = S.pack_aux([synth.initial_aux(d[0])]), S.pack_paths([synth.initial_paths(d[0])])
+    with pytest.raises(fhmc.FhError):
+        S.logz_grad(A, P, 0)
+    torch.cuda.current_stream().synchronize()
+    assert float((A.clone() + 1).sum() - A.sum()) == pytest.approx(A.numel(), rel=1e-9)
+    S.sweep(A, P, 0, 1)
+    assert S.status() == (0, -1)
+    S.close()
