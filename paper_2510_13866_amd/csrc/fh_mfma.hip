@@ -1404,13 +1404,33 @@ __device__ __forceinline__ void ring_store(float* row, const f32x16& F, int lane
     }
 }
 
+// The FP32 adjoint's backward products take C 2^10 on either side, so that the factor (worldlines on
+// the ring, 2^20 at most) coef / <f, beta> stays in range wherever one worldline's would with C itself.
+// Every other result is a ratio in which the power of two cancels. (In FP64 <f, beta> is at least the
+// smallest hop, 1e-81 at 32 x 32 and t dtau = 0.02: the factor cannot leave the range.)
+constexpr float kBetaScale = 0x1p10f;
+__device__ inline uint32_t scaled_pair(uint32_t v) {  // two bf16 values, exactly
+    const float lo = __builtin_bit_cast(float, v << 16) * kBetaScale;
+    const float hi = __builtin_bit_cast(float, v & 0xFFFF0000u) * kBetaScale;
+    return (fbits(lo) >> 16) | (fbits(hi) & 0xFFFF0000u);
+}
+__device__ inline bf16x8 scaled_terms(const bf16x8& c) {
+    u32x4 u = __builtin_bit_cast(u32x4, c);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t v = u[i];
+        u[i] = scaled_pair(v);
+    }
+    return __builtin_bit_cast(bf16x8, u);
+}
+
 // Adjoint of the forward filter over the ring anchored at `anchor` (one block of length L_tau,
 // closing on the anchor site e of the reconnected worldline, e = a without reconnection), on
 // the matrix cores. A workgroup takes up to kGroup of the rings that the worldlines of one (chain,
 // spin) share (GradShare; each counts as often as it is shared), one per wavefront, in lockstep
 // over the slices:
 //   forward:  f~_j as in k_forward_mfma, every row j = 0..L_tau-1 stored (row 0 = delta_a)
-//   backward: u_{L_tau} = delta_e; beta_j = C u_{j+1} C; u_j = W~_j . beta_j / sum
+//   backward: u_{L_tau} = delta_e; beta_j = C u_{j+1} C 2^20 (kBetaScale); u_j = W~_j . beta_j / sum
 //   d log Z / d log W_j(r) = f~_j(r) beta_j(r) / <f~_j, beta_j>   (the smoothing marginal)
 //   d log Z / d t += dtau <A beta_j, f~_j> / <beta_j, f~_j>, A the nearest-neighbour hopping
 //                    matrix: G = exp(t dtau A), so dG/dt = dtau A G and <u, (dG/dt) f> =
@@ -1522,6 +1542,12 @@ __global__ __launch_bounds__(kThreads, LFIX || !CK ? 3 : 2) void k_grad_mfma(
     }
     __syncthreads();  // every row of the group is stored before any wavefront reads one back
     // ---- backward messages
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        C.h[q] = scaled_terms(C.h[q]);
+        C.m[q] = scaled_terms(C.m[q]);
+        C.l[q] = scaled_terms(C.l[q]);
+    }
     f32x16 U;
 #pragma unroll
     for (int v = 0; v < 16; ++v) U[v] = (x == ex && tile_row(lane, v) == ey) ? 1.0f : 0.0f;
