@@ -485,7 +485,7 @@ def main():
     assert fhmc.lib.fh_debug_sweep_timing(St.plan, 1) == 0
     run_chain(St, At, Pt, 0, args.warmup, stream)
     seg = [0.0, 0.0, 0.0, 0.0]
-    fwd_chains, fwd_reps, bwd_chains = [], [], []
+    fwd_chains, fwd_reps, bwd_chains, bwd_rows = [], [], [], []
     d0 = descs[0]                                                  # every chain has this shape
     own = np.repeat(np.arange(d0.n_particles), 1)                  # one block per worldline
     with torch.cuda.stream(stream):
@@ -495,7 +495,8 @@ def main():
             St.sweep(At, Pt, args.warmup + i, 1, stream)
             for k, v in enumerate(fhmc.fh_debug_sweep_times(St.plan)):
                 seg[k] += v
-            whole = fhmc.fh_debug_rescue(St.plan)[3]
+            _, _, queue, whole = fhmc.fh_debug_rescue(St.plan, cap=1 << 20)
+            queued = np.bincount([q[0] for q in queue], minlength=len(descs))
             # worldlines whose forward recursion ran: the representatives of the shared forward
             # filters (every worldline on plans that share none), in the chains not held
             rep = fhmc.fh_debug_representatives(St.plan)
@@ -505,6 +506,16 @@ def main():
                 if held[c] == 0:
                     n_rep += (d0.n_particles if len(rep) == 0 else
                               int(np.sum(rep[c * d0.n_particles:(c + 1) * d0.n_particles] == own)))
+            # rows the backward kernels cannot do without: of each (chain, spin) that they draw, the
+            # representatives' whole rows once, or a window of 49 sites per draw if that is less
+            n_rows = 0.0
+            for c in range(len(descs)):
+                if queued[c] >= d0.n_particles:
+                    continue  # re-filtered whole
+                r = rep[c * d0.n_particles:(c + 1) * d0.n_particles] if shared else own
+                for lo, hi in ((0, d0.n_up), (d0.n_up, d0.n_particles)):
+                    n_rows += min(float(np.sum(r[lo:hi] == own[lo:hi])), (hi - lo) * 49.0 / d0.N)
+            bwd_rows.append(n_rows)
             fwd_chains.append(int(np.sum(held == 0)))
             fwd_reps.append(n_rep)
             bwd_chains.append(len(descs) - whole)
@@ -525,9 +536,6 @@ def main():
     rows = d0.n_particles * (d0.L_tau - 1)                         # per chain: one block each
     N = d0.N
     w_bytes = 2 * d0.L_tau * N * rsz                               # site potentials, both spins
-    # backward: the full-row kernel reads every filter row; the windowed one reads the 7 x 7
-    # window around the next slice's site (half-width 3 at dtau = 0.05), fallbacks aside
-    read_per_row = N * rsz if args.full_row_draw else 49 * rsz
     # per launch, averaged over the timed sweeps: the chains each launch worked on, and the
     # worldlines whose recursion the forward ran (rows written: L_tau - 1 per worldline plus the
     # end tile of the shared filters)
@@ -536,7 +544,9 @@ def main():
     bwd_avg = sum(bwd_chains) / args.steps
     rows_per_rep = (d0.L_tau - 1) + (1 if shared else 0)
     algo = {"forward": round(rep_avg * rows_per_rep * N * rsz + fwd_avg * w_bytes),
-            "backward": round(bwd_avg * rows * (read_per_row + 4))}  # + the drawn site (int32)
+            # the rows (see above) and the drawn sites (int32)
+            "backward": round(sum(bwd_rows) / args.steps * (d0.L_tau - 1) * N * rsz +
+                              bwd_avg * rows * 4)}
     extra["fp32_kernel_chains_per_launch"] = {
         "forward": fwd_avg, "forward_worldlines": rep_avg, "backward": bwd_avg,
         "of": len(descs), "worldlines_per_chain": d0.n_particles,
