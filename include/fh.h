@@ -79,7 +79,7 @@ enum fh_precision {
  * rows scaled high in FP32's range, queue every block whose forward step loses nearly all its
  * mass to the weights (below 2^-196 of it), whose end weight falls below 2^-110 of the row mass
  * or whose backward draw picks a site with a filter value below that, queue every block of a
- * chain that has a queued block (in that pass and the next two), and redo the
+ * chain that has a queued block (in that pass and at least the next four), and redo the
  * queued blocks in FP64: the forward recursion on the FP64 circulant with W computed in FP64 from
  * the field (its log Z replaces the FP32 one, its rows rounded to FP32 replace the stored rows),
  * and, in fh_backward_sample and fh_sweep, the block's draws from the FP64 rows with the same

@@ -122,8 +122,9 @@ int fh_debug_share_filters(fh_plan plan, int32_t enable);
  * holds 7 int32 written by the call (caller-owned host memory; zeros where no chain shares). */
 int fh_debug_staged(fh_plan plan, int32_t* counts);
 /* Synchronises the device and writes to holds (caller-owned host memory, [n_chains]) the forward
- * passes each chain stays on the FP64 re-filter: a chain with L <= 32 and holds[c] > 0 is
- * skipped by the next forward pass's FP32 kernels and re-filtered whole. FP64 plans write 0. */
+ * passes each chain stays on the FP64 re-filter: a chain that it takes (L <= 32, 48 or 64) and
+ * whose holds[c] > 0 is skipped by the next forward pass's FP32 kernels and re-filtered whole.
+ * FP64 plans write 0. */
 int fh_debug_rescue_holds(fh_plan plan, int32_t* holds);
 
 /* FP32 plans: why the kernels queued blocks for the FP64 re-filter, counted since fh_init (a

@@ -216,7 +216,7 @@ constexpr int64_t kCachedRowBytes = 16ll << 20;
 // Per-pass state of the FP32 plans as the kernels see it: the rescue words above, the per-block
 // flags, the queue, and the representative map of the shared forward filters (rep, per
 // (chain, particle, block) at blk_off + p nb + b: the worldline whose stored rows the block's
-// draws read; null where no chain shares, and on FP64 plans).
+// draws read; null where no chain shares).
 // Phase A's FP64 rows as the windowed backward kernel reads them when it draws the held chains'
 // blocks (k_backward_win with SLOT): the slot of each representative's block, the slots, and the
 // log Z pieces of the worldlines that share a representative's rows.
@@ -350,8 +350,8 @@ struct Device {
     DrawTask* stage_tasks = nullptr;
     DrawTask* stage_tasks_s = nullptr;
     GradShare grad = {};              // shared adjoints
-    DrawTask* fwd64c_tasks = nullptr;  // split-bf16: the same, as fwd64_tasks
     DrawTask* fwddc_tasks = nullptr;  // FP64 plans: the representatives k_dedup lists, as fwdd_tasks
+    DrawTask* fwd64c_tasks = nullptr;  // split-bf16: the same, as fwd64_tasks
     double* dt = nullptr;     // per particle d log Z / d t
     PairTask* fwd_tasks = nullptr;
     DrawTask* draw_tasks = nullptr;
@@ -360,12 +360,13 @@ struct Device {
     PairTask* fwd32c_tasks = nullptr;   // the dense representative pairs k_dedup lists (as many)
     DrawTask* fwdxc_tasks = nullptr;    // the same for the padded lattices' single worldlines
     DrawTask* fwdx_tasks = nullptr;     // MFMA forward: single worldlines of 16 < L < 32 chains
-    PackTask* fwdp_tasks = nullptr;
+    PackTask* fwdp_tasks = nullptr;     // MFMA forward, packed: P = 2 tasks, then P = 4 tasks
     // the packed tiles of representatives k_dedup lists (P = 2 from the front, P = 4 from
     // n_fwdp2_tasks on; PackTask.p0 indexes prep) and the representatives they hold
     PackTask* fwdpc_tasks = nullptr;
     int32_t* prep = nullptr;
-    DrawTask* fwd64_tasks = nullptr;    // MFMA forward: single worldlines of L = 64 chains     // MFMA forward, packed: P = 2 tasks, then P = 4 tasks
+    DrawTask* fwd64_tasks = nullptr;    // MFMA forward: single worldlines of L = 64 chains, then of
+                                        // 32 < L < 64
     DrawTask* draw32_tasks = nullptr;   // backward: worldline blocks of L = 32 chains
     DrawTask* draww_tasks = nullptr;    // backward, windowed draws (k_backward_win)
     DrawTask* drawx_tasks = nullptr;    // backward: the remaining chains (any L)

@@ -2808,7 +2808,7 @@ __device__ inline int local_move(const ChainInfo& c, const double* g, const T* a
 // 4.7 us a phase against 8.7; 1.3e6 proposals: 23 against 17.5). Bound:
 // the generator's 64-bit multiplications and the FP64 ratio of each proposal. A pass over 16
 // chains of 512 + 512 worldlines, L_tau = 160, 2.6e6 proposals: 55 us as four launches of one
-// proposal per thread, 39 us as three.
+// proposal per thread, 39 us as three (17.5, 17 and 4.8).
 constexpr int kLocalSlices = 4;
 constexpr int64_t kLocalFill = (int64_t)2 * 1024 * 64 * kLocalSlices;
 template <typename T, int PHASE, int SLICES>

@@ -992,7 +992,7 @@ __global__ __launch_bounds__(kThreads) void k_forward_mfma64(
     // operand blocks take the registers of that prefetch, loads it between the two products
     float wn[2][2][16];
     if constexpr (!PAD) load_w((start + 1) % L_tau, wn);
-    bool low = false;  // the block left FP32's range (the FP64 re-filter takes L <= 32 only)
+    bool low = false;  // the block left FP32's range: queued for the FP64 re-filter (L = 48, 64)
     for (int j = 1; j < len; ++j) {
         const int l = (start + j) % L_tau;
         f32x16 X[2][2], H[2][2];
