@@ -17,11 +17,12 @@
 #include "fh_internal.h"
 #include "fh_philox.h"
 
-// Rows of fh_measure_noalloc (|Z|^2 of every slice pair, then the two site sums of each; measure_doubles
-// of at most kScratchDoubles), held in this device array for callers that cannot allocate. Each GPU the library
-// runs on holds one copy for the life of the process; its device address is taken once per
-// device (fh::scratch_address) and passed to the kernels like any other buffer. Every element a
-// call reads is written by the same call first, so nothing needs clearing between calls.
+// Rows of fh_measure_noalloc (|Z|^2 of every slice pair, then the two site sums of each;
+// measure_doubles of at most kScratchDoubles), held in this device array for callers that cannot
+// allocate. Each GPU the library runs on holds one copy for the life of the process; its device
+// address is taken once per device (fh::scratch_address) and passed to the kernels like any other
+// buffer. Every element a call reads is written by the same call first, so nothing needs clearing
+// between calls.
 static __device__ __align__(256) double scratch[fh::kScratchDoubles];
 
 namespace fh {
@@ -2353,9 +2354,9 @@ __device__ inline void stage_members(const ChainInfo& c, const DrawTask& t, cons
 // slices and its start site, so every worldline of the (spin, block) is mapped to the lowest
 // worldline with the same start site (its representative; itself if it is the lowest); the
 // forward kernel runs the representatives only and the backward kernels read their rows.
-// For dedup = 1 chains not re-filtered in this pass it also appends the (spin, block)'s representatives,
-// in worldline order and two to a task, to the dense list cpairs (count in words[5]), which the
-// split-bf16 forward then takes from the front: its active wavefronts are the first ones
+// For dedup = 1 chains not re-filtered in this pass it also appends the (spin, block)'s
+// representatives, in worldline order and two to a task, to the dense list cpairs (count in words[5]),
+// which the split-bf16 forward then takes from the front: its active wavefronts are the first ones
 // dispatched, spread over the XCDs, instead of sitting at fixed grid positions that map a whole
 // settled batch onto a few compute units. Packed lattices (pack = P) list their representatives
 // in prep (count in words[10]) and P^2 of them to a tile in cpack (P = 2: from the front, count
@@ -2518,9 +2519,10 @@ __global__ __launch_bounds__(kThreads) void k_dedup(
         rescue_held_admit(chains, rsc, n_slots, 1, arep);
 }
 
-// After the FP32 forward pass, one workgroup (the last one of k_member_logz, or k_rescue_expand): a chain with more than whole_min blocks queued in this pass, or still
-// held from an earlier such pass, has all its blocks queued for the FP64 re-filter (those of phase A
-// are); its hold then counts down (rescue_reset sets its length at the next pass).
+// After the FP32 forward pass, one workgroup (the last one of k_member_logz, or k_rescue_expand): a
+// chain with more than whole_min blocks queued in this pass, or still held from an earlier such pass,
+// has all its blocks queued for the FP64 re-filter (those of phase A are); its hold then counts down
+// (rescue_reset sets its length at the next pass).
 // With arep_b (sweeps of plans with a phase B) it then admits to phase B the chains queued whole
 // that phase A does not have, in chain order, while their representatives fit the slots (phase A
 // has ended by then) and provided k_backward_stage draws every (spin, block) of theirs: one FP64
